@@ -78,6 +78,11 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
         delete c;
         return BSIM_E_NOMEM;
     }
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->stage_host), sizeof(StageHost), hipHostMallocDefault) !=
+        hipSuccess) {
+        bsim_ctx_free(c);
+        return BSIM_E_NOMEM;
+    }
     if (hipHostMalloc(reinterpret_cast<void**>(&c->count_host), kStripes * sizeof(uint32_t),
                       hipHostMallocDefault) != hipSuccess) {
         bsim_ctx_free(c);
@@ -111,6 +116,7 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     ctx_release_work(ctx);
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->status_host) (void)hipHostFree(ctx->status_host);
+    if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
     if (ctx->count_host) (void)hipHostFree(ctx->count_host);
     for (hipEvent_t e : ctx->loop_ev)
         if (e) (void)hipEventDestroy(e);

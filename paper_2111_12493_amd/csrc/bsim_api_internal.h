@@ -13,6 +13,7 @@ struct bsim_ctx {
     hipStream_t stream = nullptr;
     std::string err;
     bsim::RunStatus* status_host = nullptr;  // pinned, 4 entries
+    bsim::StageHost* stage_host = nullptr;   // pinned: what staging copies back
     hipEvent_t loop_ev[2] = {nullptr, nullptr};  // status-copy events of the refinement loop
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;

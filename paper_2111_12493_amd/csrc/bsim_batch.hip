@@ -312,14 +312,14 @@ void batch_summarize(bsim_ctx* ctx, const bsim_graph* graphs, uint32_t G, const 
     RunStatus* ustat = arena.alloc<RunStatus>(1);
     build_union(graphs, G, u, gid, ustat, &ctx->status_host[3], arena, s);
     u.hub_table_slots = ctx->hub_table_slots;
-    stage_graph(u, ustat, &ctx->status_host[3], arena, s);
+    stage_graph(u, ctx->stage_host, arena, s);
     // direction parameterization: the view of a disjoint union is the
     // disjoint union of the graphs' views
     const bool view = (p.flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS)) != 0;
     DirectedView dv;
     if (view) {
         direction_view(u, p.flags, nullptr, dv, arena, s);
-        stage_graph(dv.h, ustat, &ctx->status_host[3], arena, s);
+        stage_graph(dv.h, ctx->stage_host, arena, s);
     }
     const Staged& ur = view ? dv.h : u;
     const Staged& uf = view ? dv.f : u;

@@ -217,9 +217,8 @@ bsim_update* diff_snapshots(bsim_ctx* ctx, const bsim_graph& b, const bsim_graph
     Staged g0, g1;
     upload_graph(b, g0, arena, s);
     upload_graph(a, g1, arena, s);
-    RunStatus* st = arena.alloc<RunStatus>(1);
-    stage_graph(g0, st, &ctx->status_host[3], arena, s);  // validates
-    stage_graph(g1, st, &ctx->status_host[3], arena, s);
+    stage_graph(g0, ctx->stage_host, arena, s);  // validates
+    stage_graph(g1, ctx->stage_host, arena, s);
     const uint32_t n0 = g0.n, n1 = g1.n;
     const EdgeSet e0 = edge_set(g0, arena, s);
     const EdgeSet e1 = edge_set(g1, arena, s);

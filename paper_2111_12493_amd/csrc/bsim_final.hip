@@ -95,9 +95,7 @@ template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_edge_keys(
     const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt,
     const LabT* __restrict__ lab, const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst,
-    const uint32_t* __restrict__ tile_i0, const uint32_t* __restrict__ tile_i1,
-    const uint32_t* __restrict__ tile_e0, const uint32_t* __restrict__ tile_e1,
-    const uint32_t* __restrict__ act, uint32_t n_tiles,
+    const uint4* __restrict__ tiles, const uint32_t* __restrict__ act, uint32_t n_tiles,
     const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int lb, int bb,
     uint64_t* __restrict__ keys) {
     __shared__ KeyShared S;
@@ -111,9 +109,10 @@ __global__ void __launch_bounds__(kBlock) k_edge_keys(
     }
     const uint32_t tile = blockIdx.x - n_hubs;
     if (tile >= n_tiles) return;
-    const uint32_t i0 = tile_i0[tile], nv = tile_i1[tile] - i0;
-    const uint32_t ebase = tile_e0[tile];
-    const uint32_t ne = tile_e1[tile] - ebase;
+    const uint4 td = tiles[tile];
+    const uint32_t i0 = td.x, nv = td.y - i0;
+    const uint32_t ebase = td.z;
+    const uint32_t ne = td.w - ebase;
     for (uint32_t i = tid; i < nv; i += kBlock) S.off[i] = row_off[act[i0 + i]] - ebase;
     if (tid == 0) S.off[nv] = ne;
     __syncthreads();
@@ -389,13 +388,13 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
     } else if (g.label_bytes == 2)
         k_edge_keys<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
                                                       static_cast<const uint16_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tile_i0, g.tile_i1, g.tile_e0, g.tile_e1, g.act,
+                                                      g.tiles, g.act,
                                                       g.n_tiles, g.hub_v, g.n_hubs,
                                                       lb, bb, ka);
     else
         k_edge_keys<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
                                                       static_cast<const uint32_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tile_i0, g.tile_i1, g.tile_e0, g.tile_e1, g.act,
+                                                      g.tiles, g.act,
                                                       g.n_tiles, g.hub_v, g.n_hubs,
                                                       lb, bb, ka);
     hip_check(hipGetLastError(), "edge key launch");

@@ -1225,8 +1225,7 @@ void full_levels(bsim_state* st, uint32_t j0, Arena& arena) {
     g.hub_table_slots = st->ctx->hub_table_slots;
     g.max_label = st->max_label;
     g.trusted = true;
-    RunStatus* sd = arena.alloc<RunStatus>(1);
-    stage_graph(g, sd, &st->ctx->status_host[3], arena, s);
+    stage_graph(g, st->ctx->stage_host, arena, s);
     HashScratch hs;
     alloc_hash_scratch(g, hs, arena, s);
     for (uint32_t j = j0; j <= st->K; j++) {
@@ -1573,8 +1572,7 @@ bsim_result* create_state(bsim_ctx* ctx, const bsim_graph& graph, const bsim_par
     Staged g;
     upload_graph(graph, g, arena, s);
     g.hub_table_slots = ctx->hub_table_slots;
-    RunStatus* stage_status = arena.alloc<RunStatus>(1);
-    stage_graph(g, stage_status, &ctx->status_host[3], arena, s);
+    stage_graph(g, ctx->stage_host, arena, s);
     st->ctx = ctx;
     st->s = s;
     hip_check(hipStreamCreateWithFlags(&st->s2, hipStreamNonBlocking), "class stream");

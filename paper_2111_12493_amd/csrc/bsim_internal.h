@@ -156,10 +156,7 @@ struct IterArgs {
     uint64_t* h_next;       // h^k
     const uint8_t* alive;   // nullable
     uint32_t* rep;
-    const uint32_t* tile_i0;    // tile = positions [i0, i1) of the tile-vertex list
-    const uint32_t* tile_i1;
-    const uint32_t* tile_e0;    // and its edges [e0, e1)
-    const uint32_t* tile_e1;
+    const uint4* tiles;         // positions [x, y) of the tile-vertex list, edges [z, w)
     const uint32_t* act;        // tile vertices (out-degree 1..kHubMinDegree-1), ascending
     const uint32_t* iso;        // vertices without out-edges, ascending
     const uint32_t* hc_hub;     // hub chunk block -> hub index
@@ -358,10 +355,7 @@ struct Staged {
     uint32_t in_label_base = 0;
     uint64_t* salt = nullptr;
     uint32_t n_tiles = 0;
-    uint32_t* tile_i0 = nullptr;     // tile: positions [i0, i1) of `act`, edges [e0, e1)
-    uint32_t* tile_i1 = nullptr;
-    uint32_t* tile_e0 = nullptr;
-    uint32_t* tile_e1 = nullptr;
+    uint4* tiles = nullptr;          // tile: positions [x, y) of `act`, edges [z, w)
     uint32_t n_act = 0;
     uint32_t* act = nullptr;         // vertices of out-degree 1..kHubMinDegree-1
     uint32_t n_iso = 0;
@@ -386,10 +380,21 @@ struct Staged {
     std::vector<uint32_t> host_hub_deg;
 };
 
+// What staging copies back, in pinned memory: the validation status, the
+// counts (hubs, tile vertices, vertices without out-edges, tiles) and the
+// first hubs as (vertex, degree, first edge).  The ids of 4,096 hubs are
+// 48 KiB, a copy that costs hardly more than the counts alone; a graph needs
+// 6.3 million edges to have more.
+constexpr uint32_t kStageHubs = 4096;
+struct StageHost {
+    RunStatus st;
+    uint32_t counts[8];
+    uint32_t hubs[3 * kStageHubs];
+};
+
 // Validate the CSR and build the tile / hub schedule (a1).  Throws
 // DeviceError with BSIM_E_INVALID / BSIM_E_RANGE on malformed input.
-void stage_graph(Staged& g, RunStatus* status_dev, RunStatus* status_host, Arena& arena,
-                 hipStream_t s);
+void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s);
 
 // The graphs of the direction and label parameterizations (Sec. 2.4), built
 // on the device from a staged graph g: f = the edges whose label is in

@@ -286,13 +286,14 @@ __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint
     const uint32_t tid = threadIdx.x, k = a.k;
     const bool test = run_test(a);
     const bool hash = run_hash(a);
-    const uint32_t i0 = a.tile_i0[tile], nv = a.tile_i1[tile] - i0;
-    const uint32_t ebase = a.tile_e0[tile];
+    const uint4 td = a.tiles[tile];
+    const uint32_t i0 = td.x, nv = td.y - i0;
+    const uint32_t ebase = td.z;
     // A launch queued after the stop finds the sticky done flag set; every
     // block of it then takes the same stop decision, so its waves may skip
     // their loads at once (the exit itself still follows stop_decision).
     const bool skip = early_done(a);
-    const uint32_t ne = skip ? 0u : a.tile_e1[tile] - ebase;
+    const uint32_t ne = skip ? 0u : td.w - ebase;
     const bool mine = !skip && tid < nv;
     const uint32_t v = mine ? a.act[i0 + tid] : 0u;
     uint32_t ro0 = 0, rv = v, gi = 0;
@@ -945,10 +946,7 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.h_next = rb.h[k & 1];
     a.alive = g.alive;
     a.rep = rb.rep;
-    a.tile_i0 = g.tile_i0;
-    a.tile_i1 = g.tile_i1;
-    a.tile_e0 = g.tile_e0;
-    a.tile_e1 = g.tile_e1;
+    a.tiles = g.tiles;
     a.act = g.act;
     a.iso = g.iso;
     a.n_iso = g.n_iso;
@@ -1033,10 +1031,7 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     a.h_prev = h_prev;
     a.h_next = h_next;
     a.alive = g.alive;
-    a.tile_i0 = g.tile_i0;
-    a.tile_i1 = g.tile_i1;
-    a.tile_e0 = g.tile_e0;
-    a.tile_e1 = g.tile_e1;
+    a.tiles = g.tiles;
     a.act = g.act;
     a.iso = g.iso;
     a.n_iso = g.n_iso;

@@ -98,8 +98,7 @@ void run(bsim_ctx* ctx, const bsim_graph& graph, const bsim_params& p, bsim_noal
     Staged g;
     upload_graph(graph, g, arena, s);  // device pointers, nothing copied
     g.hub_table_slots = ctx->hub_table_slots;
-    RunStatus* stage_status = arena.alloc<RunStatus>(1);
-    stage_graph(g, stage_status, &ctx->status_host[3], arena, s);
+    stage_graph(g, ctx->stage_host, arena, s);
     RunBuffers rb;
     alloc_run_buffers(g, p.k_max, (p.flags & BSIM_STOP_AT_FIXPOINT) != 0, rb, arena, s);
     LoopResult lr = run_refinement(ctx, g, p, rb, nullptr, arena, nullptr, false);

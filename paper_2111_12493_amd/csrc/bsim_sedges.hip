@@ -371,8 +371,7 @@ template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_seg_fill(
     const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt, const LabT* __restrict__ lab,
     const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst, const uint32_t* __restrict__ estart,
-    const uint32_t* __restrict__ voff, const uint32_t* __restrict__ tile_i0, const uint32_t* __restrict__ tile_i1,
-    const uint32_t* __restrict__ tile_e0, const uint32_t* __restrict__ tile_e1, const uint32_t* __restrict__ act,
+    const uint32_t* __restrict__ voff, const uint4* __restrict__ tiles, const uint32_t* __restrict__ act,
     uint32_t n_tiles, const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int bb, uint64_t* __restrict__ vals) {
     __shared__ FillShared S;
     const uint32_t tid = threadIdx.x;
@@ -386,9 +385,10 @@ __global__ void __launch_bounds__(kBlock) k_seg_fill(
     }
     const uint32_t tile = blockIdx.x - n_hubs;
     if (tile >= n_tiles) return;
-    const uint32_t i0 = tile_i0[tile], nv = tile_i1[tile] - i0;
-    const uint32_t ebase = tile_e0[tile];
-    const uint32_t ne = tile_e1[tile] - ebase;
+    const uint4 td = tiles[tile];
+    const uint32_t i0 = td.x, nv = td.y - i0;
+    const uint32_t ebase = td.z;
+    const uint32_t ne = td.w - ebase;
     for (uint32_t i = tid; i < nv; i += kBlock) {
         const uint32_t v = act[i0 + i];
         const uint32_t o = row_off[v] - ebase;
@@ -565,12 +565,10 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
     const uint32_t grid = g.n_hubs + g.n_tiles;
     if (g.label_bytes == 2)
         k_seg_fill<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint16_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tile_i0, g.tile_i1, g.tile_e0,
-                                                     g.tile_e1, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
+                                                     dst_ids, estart, voff, g.tiles, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
     else
         k_seg_fill<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint32_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tile_i0, g.tile_i1, g.tile_e0,
-                                                     g.tile_e1, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
+                                                     dst_ids, estart, voff, g.tiles, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
     // 3. size classes
     uint32_t* uniq = arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1);
     auto list_cap = [&](uint32_t above) { return std::min<uint64_t>(nb, m / (above + 1ull) + 1); };

@@ -6,10 +6,10 @@
 // label salts, and cuts the vertex range into tiles and hub buckets:
 //   * a vertex with kHubMinDegree or more out-edges (too many for one tile)
 //     is a hub;
-//   * every other vertex belongs to exactly one tile, a run of consecutive
-//     non-hub vertices packed greedily (within windows of kPackWindow
-//     vertices, one thread per window) up to kTileMaxEdges - 1 edges and
-//     kTileMaxVerts vertices; a non-hub vertex always fits an empty tile;
+//   * every other vertex with out-edges belongs to exactly one tile, a run of
+//     consecutive such vertices packed greedily (within kStageVerts vertices)
+//     up to kTileMaxEdges - 1 edges and kTileMaxVerts vertices; a non-hub
+//     vertex always fits an empty tile;
 //   * a hub of degree d is cut into chunks of kTileMaxEdges edges that write
 //     its mixed pair keys to d scratch slots, and into 2^b hash buckets that
 //     each fit the LDS table of the hub-bucket launch.
@@ -137,172 +137,288 @@ void scan_exclusive(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tot
 
 namespace {
 
-__global__ void __launch_bounds__(kBlock) k_stage_vertices(
-    const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ type_off,
-    const uint8_t* __restrict__ alive, uint32_t n, uint64_t m, uint32_t* __restrict__ hubf,
-    uint32_t* __restrict__ actf, uint32_t* __restrict__ isof, RunStatus* status) {
-    uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    const bool in = v < n;
-    if (!in) v = n - 1;  // inactive lanes mirror the last vertex and store nothing
-    uint32_t a = row_off[v], b = row_off[v + 1];
-    uint32_t err = 0;
-    if (b < a) err |= kErrInvalid;
-    if (type_off[v + 1] < type_off[v]) err |= kErrInvalid;
-    if (v == 0 && (a != 0 || type_off[0] != 0)) err |= kErrInvalid;
-    if (v == n - 1 && static_cast<uint64_t>(b) != m) err |= kErrInvalid;
-    uint32_t d = b - a;
-    if (alive && !alive[v] && (d != 0)) err |= kErrInvalid;
-    uint32_t nt = type_off[v + 1] - type_off[v];
-    // one atomic per block: same-address atomics from every wave would serialize
-    __shared__ uint32_t s_max[kBlock / 64];
-    uint32_t wmax = in ? nt : 0;
-    for (int dd = 32; dd >= 1; dd >>= 1)
-        wmax = max(wmax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(wmax), dd, 64)));
-    if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = wmax;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < kBlock / 64; i++) wmax = max(wmax, s_max[i]);
-        // the maximum only grows: a block that cannot raise it (nearly all
-        // of them once a few have run) issues no atomic at all
-        if (wmax && wmax > __hip_atomic_load(&status->max_types, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(&status->max_types, wmax);
+// Staging is two passes over the row offsets with a one-block scan between
+// them, and one pass over the edges beside the first.  A workgroup owns
+// kStageVerts consecutive vertices: it classifies them (hub, tile vertex, no
+// out-edges), compacts the tile vertices' edge ranges in LDS and packs them
+// into tiles, so a tile never leaves its workgroup's vertices.  The first
+// pass counts (hubs, tile vertices, vertices without out-edges, tiles), the
+// scan places the counts, the second pass repeats the work and writes the
+// lists.  Repeating it costs 4 bytes per vertex; carrying flags, positions
+// and three separate scans and compactions between passes cost 72.
+//
+// Packing is greedy.  Row ends grow with the vertex, so the vertices that
+// still fit a tile starting at edge a are a prefix (row end - a below
+// kTileMaxEdges; a hub between two tile vertices exceeds that by itself):
+// one wave tests 64 candidates per ballot, at most four ballots a tile.  A
+// single lane walking its window vertex by vertex took 106-185 us whatever
+// the graph's size, twice per call.
+//
+// Bound: the row and type offsets once and the row offsets again, the lists
+// written, and the edges once.  On 10,000 vertices and 50,000 edges the three
+// kernels take 26 us where 19 launches took 410 us; on 2^27 vertices and
+// 2^30 edges of 16-bit labels 2.9 ms (counting 2.06, scan 0.08, writing 0.78)
+// where they took 7.1 ms.
+constexpr uint32_t kStageVerts = 2048;
+constexpr uint32_t kStageRounds = kStageVerts / kBlock;
+constexpr uint32_t kStageGroups = kStageVerts / 64;  // 64-vertex groups: (round, wave)
+static_assert(kStageGroups <= 64, "one wave scans the group counts");
+static_assert(kTileMaxVerts % 64 == 0, "packing tests whole ballots");
+
+struct StageShared {
+    uint32_t off[kStageVerts + 1];
+    uint32_t a[kStageVerts];        // edge ranges of the tile vertices
+    uint32_t b[kStageVerts];
+    uint32_t act[kStageGroups];     // tile vertices and hubs per group
+    uint32_t hub[kStageGroups];
+    uint32_t red[kBlock / 64];
+    uint32_t n_act;
+};
+
+struct StageArgs {
+    const uint32_t* row_off;
+    const uint32_t* type_off;
+    const uint8_t* alive;
+    uint32_t n;
+    uint64_t m;
+    const uint32_t* tgt;
+    const void* lab;
+    uint32_t n_vblk;     // vertex blocks (the grid's first)
+    uint4* cnt;          // per vertex block: hubs, tile vertices, no out-edges, tiles
+    uint32_t wide;       // tgt and lab are aligned for four edges per load
+    uint32_t* act;
+    uint32_t* iso;
+    uint32_t* hubs;      // (vertex, degree, first edge) each
+    uint4* tiles;
+    uint32_t hub_cap, tile_cap;
+    RunStatus* status;
+};
+
+// Greedy packing of the na compacted edge ranges by one wave; returns the
+// tile count.  out (nullable) receives positions base + i.
+__device__ uint32_t pack_tiles(const StageShared& S, uint32_t na, uint32_t base, uint4* out, uint32_t room) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t made = 0;
+    for (uint32_t start = 0; start < na; made++) {
+        const uint32_t a0 = S.a[start];
+        uint32_t end = start;
+        for (uint32_t q = 0; q < kTileMaxVerts / 64; q++) {
+            const uint32_t j = start + q * 64 + lane;
+            const bool fits = j < na && S.b[j] - a0 < static_cast<uint32_t>(kTileMaxEdges);
+            const uint32_t c = static_cast<uint32_t>(__popcll(__ballot(fits)));
+            end += c;
+            if (c < 64) break;
+        }
+        if (end == start) end = start + 1;  // offsets that are not monotone: the call fails later
+        if (out && lane == 0 && made < room) out[made] = make_uint4(base + start, base + end, a0, S.b[end - 1]);
+        start = end;
     }
-    bool hub = (b >= a) && d >= kHubMinDegree;
-    if (in) {
-        hubf[v] = hub ? 1u : 0u;
-        actf[v] = (b > a && !hub) ? 1u : 0u;
-        isof[v] = (b <= a) ? 1u : 0u;
-        if (err) atomicOr(&status->error, err);
+    return made;
+}
+
+template <bool kEmit>
+__device__ void stage_vertices(const StageArgs& a, StageShared& S) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint32_t base = blockIdx.x * kStageVerts;
+    const uint32_t cnt = min(kStageVerts, a.n - base);
+    for (uint32_t i = tid; i <= cnt; i += kBlock) S.off[i] = a.row_off[base + i];
+    __syncthreads();
+    uint32_t err = 0, types = 0, is_act = 0, is_hub = 0;  // bit r: round r's vertex
+#pragma unroll
+    for (uint32_t r = 0; r < kStageRounds; r++) {
+        const uint32_t i = r * kBlock + tid, v = base + i;
+        const bool in = i < cnt;
+        uint32_t x = 0, y = 0;
+        if (in) {
+            x = S.off[i];
+            y = S.off[i + 1];
+            if (!kEmit) {
+                const uint32_t t0 = a.type_off[v], t1 = a.type_off[v + 1];
+                if (y < x || t1 < t0) err |= kErrInvalid;
+                if (v == 0 && (x != 0 || t0 != 0)) err |= kErrInvalid;
+                if (v == a.n - 1 && static_cast<uint64_t>(y) != a.m) err |= kErrInvalid;
+                if (a.alive && y != x && !a.alive[v]) err |= kErrInvalid;
+                types = max(types, t1 - t0);
+            }
+        }
+        const bool edges = in && y > x;
+        const bool hub = edges && y - x >= kHubMinDegree;
+        if (hub) is_hub |= 1u << r;
+        if (edges && !hub) is_act |= 1u << r;
+        const uint64_t ba = __ballot(edges && !hub), bh = __ballot(hub);
+        if (lane == 0) {
+            S.act[r * (kBlock / 64) + wv] = static_cast<uint32_t>(__popcll(ba));
+            S.hub[r * (kBlock / 64) + wv] = static_cast<uint32_t>(__popcll(bh));
+        }
+    }
+    __syncthreads();
+    // exclusive prefixes of the group counts, one group per lane
+    const uint32_t ca = lane < kStageGroups ? S.act[lane] : 0, ch = lane < kStageGroups ? S.hub[lane] : 0;
+    const uint32_t ia = wave_incl_scan(ca), ih = wave_incl_scan(ch);
+    const uint32_t na = static_cast<uint32_t>(__shfl(static_cast<int>(ia), 63, 64));
+    const uint32_t nh = static_cast<uint32_t>(__shfl(static_cast<int>(ih), 63, 64));
+    uint4 at = make_uint4(0, 0, 0, 0);
+    if (kEmit) at = a.cnt[blockIdx.x];
+#pragma unroll
+    for (uint32_t r = 0; r < kStageRounds; r++) {
+        const uint32_t i = r * kBlock + tid, v = base + i;
+        const uint32_t grp = r * (kBlock / 64) + wv;
+        const uint32_t ga = static_cast<uint32_t>(__shfl(static_cast<int>(ia - ca), static_cast<int>(grp), 64));
+        const uint32_t gh = static_cast<uint32_t>(__shfl(static_cast<int>(ih - ch), static_cast<int>(grp), 64));
+        const bool act = (is_act >> r) & 1, hub = (is_hub >> r) & 1;
+        const uint64_t lt = (1ull << lane) - 1;
+        const uint32_t pa = ga + static_cast<uint32_t>(__popcll(__ballot(act) & lt));
+        const uint32_t ph = gh + static_cast<uint32_t>(__popcll(__ballot(hub) & lt));
+        if (act) {
+            S.a[pa] = S.off[i];
+            S.b[pa] = S.off[i + 1];
+        }
+        if (kEmit && i < cnt) {
+            if (act) {
+                a.act[at.y + pa] = v;
+            } else if (hub) {
+                if (at.x + ph < a.hub_cap) {
+                    uint32_t* h = a.hubs + 3ull * (at.x + ph);
+                    h[0] = v;
+                    h[1] = S.off[i + 1] - S.off[i];
+                    h[2] = S.off[i];
+                }
+            } else {
+                a.iso[at.z + (i - pa - ph)] = v;
+            }
+        }
+    }
+    if (!kEmit) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            types = max(types, static_cast<uint32_t>(__shfl_xor(static_cast<int>(types), d, 64)));
+            err |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(err), d, 64));
+        }
+        // the maximum only grows: a wave that cannot raise it (nearly all of
+        // them once a few have run) issues no atomic; same-address atomics
+        // serialize across the chip
+        if (lane == 0) {
+            if (types > __hip_atomic_load(&a.status->max_types, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&a.status->max_types, types);
+            if (err) atomicOr(&a.status->error, err);
+        }
+    }
+    __syncthreads();
+    if (wv == 0) {
+        uint4* out = kEmit && at.w < a.tile_cap ? a.tiles + at.w : nullptr;
+        const uint32_t made = pack_tiles(S, na, at.y, out, kEmit ? a.tile_cap - at.w : 0u);
+        if (!kEmit && lane == 0) a.cnt[blockIdx.x] = make_uint4(nh, na, cnt - na - nh, made);
     }
 }
 
+// Target range, deadness and the largest label over the edges of one block.
 template <typename LabT>
-__global__ void __launch_bounds__(kBlock) k_stage_edges(const uint32_t* __restrict__ tgt,
-                                                        const LabT* __restrict__ lab,
-                                                        const uint8_t* __restrict__ alive,
-                                                        uint32_t n, uint64_t m, RunStatus* status) {
+__device__ void stage_edges(const StageArgs& a, uint32_t* s_red) {
+    const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
+    const uint64_t tid0 = static_cast<uint64_t>(blockIdx.x - a.n_vblk) * kBlock + threadIdx.x;
+    const uint64_t step = static_cast<uint64_t>(gridDim.x - a.n_vblk) * kBlock;
     uint32_t err = 0, mx = 0;
-    for (uint64_t e = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; e < m;
-         e += static_cast<uint64_t>(gridDim.x) * kBlock) {
-        uint32_t w = tgt[e];
-        if (w >= n) err |= kErrRange;
-        else if (alive && !alive[w]) err |= kErrInvalid;
-        mx = max(mx, static_cast<uint32_t>(lab[e]));
+    auto edge = [&](uint32_t w, uint32_t l) {
+        if (w >= a.n)
+            err |= kErrRange;
+        else if (a.alive && !a.alive[w])
+            err |= kErrInvalid;
+        mx = max(mx, l);
+    };
+    uint64_t done = 0;
+    if (a.wide) {
+        // four edges per load where both arrays allow it: the counting pass
+        // over 2^27 vertices and 2^30 edges moves its 7.5 GB at 3.6 TB/s
+        // (2.06 ms; with one edge per load, in two launches, 2.77 ms)
+        struct alignas(4 * sizeof(LabT)) Lab4 {
+            LabT x[4];
+        };
+        const uint4* t4 = reinterpret_cast<const uint4*>(a.tgt);
+        const Lab4* l4 = reinterpret_cast<const Lab4*>(lab);
+        for (uint64_t q = tid0; q < a.m / 4; q += step) {
+            const uint4 w = t4[q];
+            const Lab4 l = l4[q];
+            edge(w.x, l.x[0]);
+            edge(w.y, l.x[1]);
+            edge(w.z, l.x[2]);
+            edge(w.w, l.x[3]);
+        }
+        done = a.m / 4 * 4;
     }
+    for (uint64_t e = done + tid0; e < a.m; e += step) edge(a.tgt[e], static_cast<uint32_t>(lab[e]));
     // reduce over the block before touching global memory
-    __shared__ uint32_t s_mx[kBlock / 64], s_err[kBlock / 64];
+#pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), d, 64)));
         err |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(err), d, 64));
     }
-    if ((threadIdx.x & 63) == 0) {
-        s_mx[threadIdx.x >> 6] = mx;
-        s_err[threadIdx.x >> 6] = err;
-    }
+    if (err && (threadIdx.x & 63) == 0) atomicOr(&a.status->error, err);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kBlock / 64; i++) {
-            mx = max(mx, s_mx[i]);
-            err |= s_err[i];
-        }
-        if (mx && mx > __hip_atomic_load(&status->max_label, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(&status->max_label, mx);
-        if (err) atomicOr(&status->error, err);
+        for (int i = 1; i < kBlock / 64; i++) mx = max(mx, s_red[i]);
+        if (mx && mx > __hip_atomic_load(&a.status->max_label, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&a.status->max_label, mx);
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_compact_flags(const uint32_t* __restrict__ flag,
-                                                          const uint32_t* __restrict__ pos,
-                                                          uint32_t n, uint32_t* __restrict__ out) {
-    uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v < n && flag[v]) out[pos[v]] = v;
+template <typename LabT>
+__global__ void __launch_bounds__(kBlock) k_stage_count(StageArgs a) {
+    __shared__ StageShared S;
+    if (blockIdx.x < a.n_vblk)
+        stage_vertices<false>(a, S);
+    else
+        stage_edges<LabT>(a, S.red);
 }
 
-// Greedy tile packing within windows of kPackWindow consecutive entries of
-// the tile-vertex list (one wave per window): a tile grows until the next
-// vertex would bring it to kTileMaxEdges edges or kTileMaxVerts vertices, or
-// its edges would not follow the tile's (a hub lies between).  The wave
-// loads the window's edge ranges together into LDS, then one lane runs the
-// greedy scan over them.  With emit == false only the tile count per window
-// is written (to cnt[w]); with emit == true tiles are written from pos[w] on.
-constexpr uint32_t kPackWindow = 1024;
-constexpr uint32_t kPackWaves = kBlock / 64;
-
-__global__ void __launch_bounds__(kBlock) k_pack_tiles(const uint32_t* __restrict__ row_off,
-                                                       const uint32_t* __restrict__ act, uint32_t n_act,
-                                                       bool emit, uint32_t* __restrict__ cnt,
-                                                       const uint32_t* __restrict__ pos,
-                                                       uint32_t* __restrict__ i0, uint32_t* __restrict__ i1,
-                                                       uint32_t* __restrict__ e0, uint32_t* __restrict__ e1) {
-    __shared__ uint32_t s_a[kPackWaves][kPackWindow];
-    __shared__ uint32_t s_b[kPackWaves][kPackWindow];
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t w = blockIdx.x * kPackWaves + wv;
-    const uint64_t ib64 = static_cast<uint64_t>(w) * kPackWindow;
-    if (ib64 >= n_act) return;  // whole waves only: no block barrier below
-    const uint32_t ib = static_cast<uint32_t>(ib64);
-    const uint32_t ie = static_cast<uint32_t>(min<uint64_t>(n_act, ib64 + kPackWindow));
-    for (uint32_t i = ib + lane; i < ie; i += 64) {
-        const uint32_t v = act[i];
-        s_a[wv][i - ib] = row_off[v];
-        s_b[wv][i - ib] = row_off[v + 1];
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane != 0) return;
-    const uint32_t* A = s_a[wv];
-    const uint32_t* B = s_b[wv];
-    uint32_t out = emit ? pos[w] : 0, made = 0;
-    uint32_t start = ib, edges = 0, verts = 0, ebeg = 0, eend = 0;
-    for (uint32_t i = ib; i < ie; i++) {
-        const uint32_t a = A[i - ib], b = B[i - ib];
-        const uint32_t d = b - a;
-        if (verts && (a != eend || verts == static_cast<uint32_t>(kTileMaxVerts) ||
-                      edges + d >= static_cast<uint32_t>(kTileMaxEdges))) {
-            if (emit) {
-                i0[out] = start;
-                i1[out] = i;
-                e0[out] = ebeg;
-                e1[out] = eend;
-                out++;
-            }
-            made++;
-            verts = edges = 0;
-        }
-        if (!verts) {
-            start = i;
-            ebeg = a;
-        }
-        edges += d;
-        verts++;
-        eend = b;
-    }
-    if (verts) {
-        if (emit) {
-            i0[out] = start;
-            i1[out] = ie;
-            e0[out] = ebeg;
-            e1[out] = eend;
-            out++;
-        }
-        made++;
-    }
-    if (!emit) cnt[w] = made;
+__global__ void __launch_bounds__(kBlock) k_stage_emit(StageArgs a) {
+    __shared__ StageShared S;
+    // malformed offsets: the counts mean nothing, and the call fails
+    if (a.status->error & kErrInvalid) return;
+    stage_vertices<true>(a, S);
 }
 
-__global__ void __launch_bounds__(kBlock) k_hub_degrees(const uint32_t* __restrict__ row_off,
-                                                         const uint32_t* __restrict__ hubs,
-                                                         uint32_t nh, uint32_t* __restrict__ deg) {
-    uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < nh) deg[i] = row_off[hubs[i] + 1] - row_off[hubs[i]];
-}
+// Exclusive scan of the per-block counts in place; totals to total[0..3].
+constexpr uint32_t kSpineItems = 4;
 
-__global__ void __launch_bounds__(kBlock) k_hub_starts(const uint32_t* __restrict__ row_off,
-                                                        const uint32_t* __restrict__ hubs,
-                                                        uint32_t nh, uint32_t* __restrict__ start) {
-    uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < nh) start[i] = row_off[hubs[i]];
+__global__ void __launch_bounds__(1024) k_stage_spine(uint4* cnt, uint32_t nb, uint32_t* total) {
+    __shared__ uint4 s_w[16];
+    const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint4 carry = make_uint4(0, 0, 0, 0);
+    auto add = [](uint4 x, uint4 y) { return make_uint4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w); };
+    for (uint64_t b0 = 0; b0 < nb; b0 += 1024 * kSpineItems) {
+        const uint64_t j0 = b0 + static_cast<uint64_t>(threadIdx.x) * kSpineItems;
+        uint4 v[kSpineItems], sum = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (uint32_t i = 0; i < kSpineItems; i++) {
+            v[i] = j0 + i < nb ? cnt[j0 + i] : make_uint4(0, 0, 0, 0);
+            sum = add(sum, v[i]);
+        }
+        const uint4 inc = make_uint4(wave_incl_scan(sum.x), wave_incl_scan(sum.y), wave_incl_scan(sum.z),
+                                     wave_incl_scan(sum.w));
+        if (lane == 63) s_w[wid] = inc;
+        __syncthreads();
+        uint4 run = carry;
+        for (uint32_t i = 0; i < 16; i++) {
+            const uint4 t = s_w[i];
+            if (i < wid) run = add(run, t);
+            carry = add(carry, t);
+        }
+        run = make_uint4(run.x + inc.x - sum.x, run.y + inc.y - sum.y, run.z + inc.z - sum.z,
+                         run.w + inc.w - sum.w);
+#pragma unroll
+        for (uint32_t i = 0; i < kSpineItems; i++) {
+            if (j0 + i < nb) cnt[j0 + i] = run;
+            run = add(run, v[i]);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        total[0] = carry.x;
+        total[1] = carry.y;
+        total[2] = carry.z;
+        total[3] = carry.w;
+    }
 }
 
 // salt(l) = M(C_L + l); at and past in_base (when nonzero) the salts of
@@ -314,181 +430,167 @@ __global__ void __launch_bounds__(kBlock) k_salt(uint64_t* salt, uint32_t count,
     salt[l] = mix64(kCL + x);
 }
 
+// The hub schedule, on the host (a graph of 2^30 edges has some 10^5 hubs):
+// hubs by degree, largest first, so that long buckets start early.  info
+// holds (vertex, degree, first edge) per hub in vertex order.
+void schedule_hubs(Staged& g, const uint32_t* info, Arena& arena, hipStream_t s) {
+    const uint32_t nh = g.n_hubs;
+    // ties in hub order: a stable radix sort on the complemented degree (a
+    // comparison sort takes milliseconds here)
+    std::vector<uint32_t> order(nh);
+    {
+        std::vector<uint64_t> key(nh), k2;
+        std::vector<uint32_t> v2;
+        for (uint32_t i = 0; i < nh; i++) {
+            key[i] = 0xFFFFFFFFull - info[3ull * i + 1];
+            order[i] = i;
+        }
+        host_radix_sort(key, order, 32, k2, v2);
+    }
+    // a hub of degree d > kSoloMaxEdges: ceil(d / kTileMaxEdges) chunk
+    // blocks, and 2^b bucket blocks so that a bucket expects at most 3/4
+    // of the LDS slots; the others are solo blocks (no chunks, no buckets)
+    const uint64_t per_bucket = std::max<uint64_t>(1, uint64_t(g.hub_table_slots) * 3 / 4);
+    uint32_t n_big = 0, n_chunks = 0, n_blocks = 0;
+    std::vector<uint32_t> logb(nh, 0);
+    for (uint32_t i = 0; i < nh; i++) {
+        const uint32_t d = info[3ull * order[i] + 1];
+        if (d <= kSoloMaxEdges) break;  // by degree: the solo hubs follow
+        n_big = i + 1;
+        const uint64_t want = (d + per_bucket - 1) / per_bucket;
+        logb[i] = std::min<uint32_t>(static_cast<uint32_t>(bit_width(next_pow2(want)) - 1), kMaxHubLogB);
+        n_chunks += ceil_div(d, kTileMaxEdges);
+        n_blocks += 1u << logb[i];
+    }
+    // every array of the schedule in one upload
+    std::vector<uint32_t> up(2ull * nh + 5ull * nh + 2ull * n_chunks + 2ull * n_blocks);
+    uint64_t* key_off = reinterpret_cast<uint64_t*>(up.data());  // first: 8-byte entries
+    uint32_t* hv = up.data() + 2ull * nh;
+    uint32_t *hd = hv + nh, *hl = hd + nh, *hc0 = hl + nh, *hnc = hc0 + nh;
+    uint32_t *ch = hnc + nh, *ce = ch + n_chunks, *bh = ce + n_chunks, *bb = bh + n_blocks;
+    uint64_t keys = 0;
+    uint32_t nc = 0, nb = 0;
+    for (uint32_t i = 0; i < nh; i++) {
+        const uint32_t* h = info + 3ull * order[i];
+        hv[i] = h[0];
+        hd[i] = h[1];
+        hl[i] = logb[i];
+        key_off[i] = keys;
+        hc0[i] = nc;
+        hnc[i] = i < n_big ? ceil_div(h[1], kTileMaxEdges) : 0;
+        if (i >= n_big) continue;
+        keys += h[1];
+        for (uint32_t c = 0; c < hnc[i]; c++) {
+            ch[nc] = i;
+            ce[nc++] = h[2] + c * kTileMaxEdges;
+        }
+        for (uint32_t b = 0; b < (1u << logb[i]); b++) {
+            bh[nb] = i;
+            bb[nb++] = b;
+        }
+    }
+    uint32_t* d = arena.alloc<uint32_t>(up.size());
+    // (pageable memory: the call returns once the source has been read)
+    hip_check(hipMemcpyAsync(d, up.data(), up.size() * 4, hipMemcpyHostToDevice, s), "hub schedule");
+    auto dev = [&](const uint32_t* host) { return d + (host - up.data()); };
+    g.host_hub_v.assign(hv, hv + nh);
+    g.host_hub_deg.assign(hd, hd + nh);
+    g.n_solo = nh - n_big;
+    g.n_hub_chunks = n_chunks;
+    g.n_hub_blocks = n_blocks;
+    g.hub_keys_total = keys;
+    g.hub_key_off = reinterpret_cast<uint64_t*>(d);
+    g.hub_v = dev(hv);
+    g.hub_deg = dev(hd);
+    g.hub_logb = dev(hl);
+    g.hub_chunk0 = dev(hc0);
+    g.hub_nchunks = dev(hnc);
+    g.hc_hub = dev(ch);
+    g.hc_e0 = dev(ce);
+    g.hb_hub = dev(bh);
+    g.hb_bucket = dev(bb);
+}
+
 }  // namespace
 
-void stage_graph(Staged& g, RunStatus* status_dev, RunStatus* status_host, Arena& arena,
-                 hipStream_t s) {
+void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     const uint32_t n = g.n;
-    hip_check(hipMemsetAsync(status_dev, 0, sizeof(RunStatus), s), "stage status");
-    uint32_t* hubf = arena.alloc<uint32_t>(n + 1);
-    uint32_t* actf = arena.alloc<uint32_t>(n + 1);
-    uint32_t* isof = arena.alloc<uint32_t>(n + 1);
-    uint32_t* counts = arena.alloc<uint32_t>(8);
-    hip_check(hipMemsetAsync(counts, 0, 8 * 4, s), "stage counts");
+    // status, counts and hub list lie together, as in StageHost
+    const uint32_t hub_cap = static_cast<uint32_t>(g.m / kHubMinDegree) + 1;
+    const size_t head = sizeof(RunStatus) + sizeof(host->counts);
+    uint8_t* dev = arena.alloc<uint8_t>(head + 12ull * hub_cap);
+    RunStatus* status = reinterpret_cast<RunStatus*>(dev);
+    uint32_t* counts = reinterpret_cast<uint32_t*>(dev + sizeof(RunStatus));
+    uint32_t* hubs = reinterpret_cast<uint32_t*>(dev + head);
+    hip_check(hipMemsetAsync(dev, 0, head, s), "stage status");
+    // tiles: one that its edges end is followed by a vertex with which it
+    // would reach kTileMaxEdges (two neighbours share that sum, and the
+    // first vertex of a tile counts for itself and its predecessor), one
+    // that its vertices end holds kTileMaxVerts, one that a hub ends
+    // precedes that hub, and every workgroup's last tile may be short
+    const uint32_t n_vblk = ceil_div(n, kStageVerts);
+    const uint64_t tile_cap = 2 * g.m / kTileMaxEdges + n / kTileMaxVerts + hub_cap + n_vblk + 1;
+    StageArgs a{};
+    a.row_off = g.row_off;
+    a.type_off = g.type_off;
+    a.alive = g.alive;
+    a.n = n;
+    a.m = g.m;
+    a.tgt = g.tgt;
+    a.lab = g.lab;
+    a.n_vblk = n_vblk;
+    a.cnt = arena.alloc<uint4>(n_vblk + 1ull);
+    a.wide = (reinterpret_cast<uintptr_t>(g.tgt) % 16 == 0 &&
+              reinterpret_cast<uintptr_t>(g.lab) % (4 * g.label_bytes) == 0)
+                 ? 1u
+                 : 0u;
+    a.act = g.act = arena.alloc<uint32_t>(n + 1ull);
+    a.iso = g.iso = arena.alloc<uint32_t>(n + 1ull);
+    a.hubs = hubs;
+    a.tiles = g.tiles = arena.alloc<uint4>(tile_cap);
+    a.hub_cap = hub_cap;
+    a.tile_cap = static_cast<uint32_t>(tile_cap);
+    a.status = status;
     if (n > 0) {
-        k_stage_vertices<<<ceil_div(n, kBlock), kBlock, 0, s>>>(g.row_off, g.type_off, g.alive, n,
-                                                                g.m, hubf, actf, isof, status_dev);
-        if (g.m > 0 && !g.trusted) {
-            uint32_t nbk = std::min<uint64_t>(ceil_div(g.m, kBlock), 2048);
-            if (g.label_bytes == 2)
-                k_stage_edges<uint16_t><<<nbk, kBlock, 0, s>>>(
-                    g.tgt, static_cast<const uint16_t*>(g.lab), g.alive, n, g.m, status_dev);
-            else
-                k_stage_edges<uint32_t><<<nbk, kBlock, 0, s>>>(
-                    g.tgt, static_cast<const uint32_t*>(g.lab), g.alive, n, g.m, status_dev);
-        }
+        const uint32_t n_eblk = g.m && !g.trusted ? std::min<uint32_t>(ceil_div(g.m, 4 * kBlock), 2048) : 0u;
+        if (g.label_bytes == 2)
+            k_stage_count<uint16_t><<<n_vblk + n_eblk, kBlock, 0, s>>>(a);
+        else
+            k_stage_count<uint32_t><<<n_vblk + n_eblk, kBlock, 0, s>>>(a);
+        k_stage_spine<<<1, 1024, 0, s>>>(a.cnt, n_vblk, counts);
+        k_stage_emit<<<n_vblk, kBlock, 0, s>>>(a);
         hip_check(hipGetLastError(), "stage launch");
     }
-    // hubs -> hub list
-    uint32_t* hpos = arena.alloc<uint32_t>(n + 1);
-    scan_exclusive(hubf, hpos, n, counts + 1, arena, s);
-    uint32_t* hubs = arena.alloc<uint32_t>(n + 1);
-    if (n) k_compact_flags<<<ceil_div(n, kBlock), kBlock, 0, s>>>(hubf, hpos, n, hubs);
-    // tile vertices and vertices without out-edges -> lists
-    uint32_t* apos = arena.alloc<uint32_t>(n + 1);
-    uint32_t* ipos = arena.alloc<uint32_t>(n + 1);
-    scan_exclusive(actf, apos, n, counts + 4, arena, s);
-    scan_exclusive(isof, ipos, n, counts + 5, arena, s);
-    g.act = arena.alloc<uint32_t>(n + 1);
-    g.iso = arena.alloc<uint32_t>(n + 1);
-    if (n) {
-        k_compact_flags<<<ceil_div(n, kBlock), kBlock, 0, s>>>(actf, apos, n, g.act);
-        k_compact_flags<<<ceil_div(n, kBlock), kBlock, 0, s>>>(isof, ipos, n, g.iso);
-    }
-    hip_check(hipMemcpyAsync(status_host, status_dev, sizeof(RunStatus), hipMemcpyDeviceToHost, s),
-              "stage status");
-    uint32_t hc[8];
-    hip_check(hipMemcpyAsync(hc, counts, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "stage counts");
+    // one copy brings the counts and, for most graphs, every hub
+    const uint32_t with = std::min(hub_cap, kStageHubs);
+    hip_check(hipMemcpyAsync(host, dev, head + 12ull * with, hipMemcpyDeviceToHost, s), "stage counts");
     hip_check(hipStreamSynchronize(s), "stage sync");
-    if (status_host->error & kErrRange)
+    if (host->st.error & kErrRange)
         throw DeviceError{BSIM_E_RANGE, "edge target out of range"};
-    if (status_host->error & kErrInvalid)
+    if (host->st.error & kErrInvalid)
         throw DeviceError{BSIM_E_INVALID, "malformed CSR or an edge touching a dead vertex"};
-    if (status_host->max_types > 4096)
+    if (host->st.max_types > 4096)
         throw DeviceError{BSIM_E_UNSUPPORTED, "more than 4096 type ids on one vertex"};
-    if (status_host->max_label >= (1u << 24))
+    if (host->st.max_label >= (1u << 24))
         throw DeviceError{BSIM_E_UNSUPPORTED, "edge labels must be < 2^24"};
-    if (!g.trusted) g.max_label = status_host->max_label;
-    g.n_hubs = hc[1];
-    g.n_act = hc[4];
-    g.n_iso = hc[5];
-
-    // tiles: greedy packing per window of the tile-vertex list
-    const uint32_t nwin = ceil_div(g.n_act, kPackWindow);
-    uint32_t* wcnt = arena.alloc<uint32_t>(nwin + 1);
-    uint32_t* wpos = arena.alloc<uint32_t>(nwin + 1);
-    if (nwin) k_pack_tiles<<<ceil_div(nwin, kPackWaves), kBlock, 0, s>>>(g.row_off, g.act, g.n_act, false, wcnt,
-                                                                      nullptr, nullptr, nullptr, nullptr,
-                                                                      nullptr);
-    scan_exclusive(wcnt, wpos, nwin, counts + 2, arena, s);
-    uint32_t ntiles = 0;
-    hip_check(hipMemcpyAsync(&ntiles, counts + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "tiles");
-    hip_check(hipStreamSynchronize(s), "tiles sync");
-    g.n_tiles = ntiles;
-    g.tile_i0 = arena.alloc<uint32_t>(ntiles + 1);
-    g.tile_i1 = arena.alloc<uint32_t>(ntiles + 1);
-    g.tile_e0 = arena.alloc<uint32_t>(ntiles + 1);
-    g.tile_e1 = arena.alloc<uint32_t>(ntiles + 1);
-    if (nwin) k_pack_tiles<<<ceil_div(nwin, kPackWaves), kBlock, 0, s>>>(g.row_off, g.act, g.n_act, true, nullptr,
-                                                                      wpos, g.tile_i0, g.tile_i1, g.tile_e0,
-                                                                      g.tile_e1);
-    hip_check(hipGetLastError(), "tile packing");
-
-    // hubs: schedule on the host (few), largest first so long buckets start early
-    g.host_hub_v.assign(g.n_hubs, 0);
-    g.host_hub_deg.assign(g.n_hubs, 0);
-    if (g.n_hubs) {
-        uint32_t* hdeg = arena.alloc<uint32_t>(g.n_hubs);
-        k_hub_degrees<<<ceil_div(g.n_hubs, kBlock), kBlock, 0, s>>>(g.row_off, hubs, g.n_hubs, hdeg);
-        hip_check(hipMemcpyAsync(g.host_hub_v.data(), hubs, g.n_hubs * sizeof(uint32_t),
-                                 hipMemcpyDeviceToHost, s), "hubs");
-        hip_check(hipMemcpyAsync(g.host_hub_deg.data(), hdeg, g.n_hubs * sizeof(uint32_t),
-                                 hipMemcpyDeviceToHost, s), "hub degrees");
+    if (!g.trusted) g.max_label = host->st.max_label;
+    g.n_hubs = host->counts[0];
+    g.n_act = host->counts[1];
+    g.n_iso = host->counts[2];
+    g.n_tiles = host->counts[3];
+    if (g.n_hubs > hub_cap || g.n_tiles > tile_cap)
+        throw DeviceError{BSIM_E_DEVICE, "internal: a staging list outgrew its bound"};
+    g.host_hub_v.clear();
+    g.host_hub_deg.clear();
+    g.n_solo = g.n_hub_chunks = g.n_hub_blocks = 0;
+    g.hub_keys_total = 0;
+    if (g.n_hubs > with) {
+        std::vector<uint32_t> all(3ull * g.n_hubs);
+        hip_check(hipMemcpyAsync(all.data(), hubs, all.size() * 4, hipMemcpyDeviceToHost, s), "hubs");
         hip_check(hipStreamSynchronize(s), "hubs sync");
-        // by degree, largest first, ties in hub order: a stable radix sort
-        // on the complemented degree (a graph of 2^30 edges has some 10^5
-        // hubs, which a comparison sort orders in milliseconds)
-        std::vector<uint32_t> order(g.n_hubs);
-        {
-            std::vector<uint64_t> key(g.n_hubs), k2;
-            std::vector<uint32_t> v2;
-            for (uint32_t i = 0; i < g.n_hubs; i++) {
-                key[i] = 0xFFFFFFFFull - g.host_hub_deg[i];
-                order[i] = i;
-            }
-            host_radix_sort(key, order, 32, k2, v2);
-        }
-        // a hub of degree d > kSoloMaxEdges: ceil(d / kTileMaxEdges) chunk
-        // blocks, and 2^b bucket blocks so that a bucket expects at most 3/4
-        // of the LDS slots; the others are solo blocks (no chunks, no buckets)
-        const uint64_t per_bucket = std::max<uint64_t>(1, uint64_t(g.hub_table_slots) * 3 / 4);
-        std::vector<uint32_t> hv(g.n_hubs), hd(g.n_hubs), hl(g.n_hubs);
-        std::vector<uint64_t> ho(g.n_hubs);
-        std::vector<uint32_t> ch, ce, bh, bb;
-        std::vector<uint32_t> hstart(g.n_hubs);
-        uint64_t keys = 0;
-        uint32_t n_big = 0;
-        for (uint32_t i = 0; i < g.n_hubs; i++) {
-            hv[i] = g.host_hub_v[order[i]];
-            hd[i] = g.host_hub_deg[order[i]];
-            ho[i] = keys;
-            hl[i] = 0;
-            if (hd[i] <= kSoloMaxEdges) continue;
-            n_big = i + 1;
-            keys += hd[i];
-            const uint64_t want = (hd[i] + per_bucket - 1) / per_bucket;
-            hl[i] = std::min<uint32_t>(static_cast<uint32_t>(bit_width(next_pow2(want)) - 1), kMaxHubLogB);
-            for (uint32_t b = 0; b < (1u << hl[i]); b++) {
-                bh.push_back(i);
-                bb.push_back(b);
-            }
-        }
-        g.n_solo = g.n_hubs - n_big;
-        uint32_t* hv_dev = arena.alloc<uint32_t>(g.n_hubs);
-        uint32_t* hs_dev = arena.alloc<uint32_t>(g.n_hubs);
-        hip_check(hipMemcpyAsync(hv_dev, hv.data(), hv.size() * 4, hipMemcpyHostToDevice, s), "hub v");
-        k_hub_starts<<<ceil_div(g.n_hubs, kBlock), kBlock, 0, s>>>(g.row_off, hv_dev, g.n_hubs, hs_dev);
-        hip_check(hipMemcpyAsync(hstart.data(), hs_dev, g.n_hubs * 4, hipMemcpyDeviceToHost, s), "hub starts");
-        hip_check(hipStreamSynchronize(s), "hub starts sync");
-        std::vector<uint32_t> hc0(g.n_hubs), hnc(g.n_hubs);
-        for (uint32_t i = 0; i < g.n_hubs; i++) {
-            hc0[i] = static_cast<uint32_t>(ch.size());
-            hnc[i] = i < n_big ? ceil_div(hd[i], kTileMaxEdges) : 0;
-            for (uint32_t c = 0; c < hnc[i]; c++) {
-                ch.push_back(i);
-                ce.push_back(hstart[i] + c * kTileMaxEdges);
-            }
-        }
-        g.host_hub_v = hv;
-        g.host_hub_deg = hd;
-        g.n_hub_chunks = static_cast<uint32_t>(ch.size());
-        g.n_hub_blocks = static_cast<uint32_t>(bh.size());
-        g.hub_keys_total = keys;
-        g.hub_v = hv_dev;
-        g.hub_deg = arena.alloc<uint32_t>(g.n_hubs);
-        g.hub_logb = arena.alloc<uint32_t>(g.n_hubs);
-        g.hub_key_off = arena.alloc<uint64_t>(g.n_hubs);
-        g.hub_chunk0 = arena.alloc<uint32_t>(g.n_hubs);
-        g.hub_nchunks = arena.alloc<uint32_t>(g.n_hubs);
-        hip_check(hipMemcpyAsync(g.hub_chunk0, hc0.data(), hc0.size() * 4, hipMemcpyHostToDevice, s), "hub c0");
-        hip_check(hipMemcpyAsync(g.hub_nchunks, hnc.data(), hnc.size() * 4, hipMemcpyHostToDevice, s), "hub nc");
-        g.hc_hub = arena.alloc<uint32_t>(g.n_hub_chunks);
-        g.hc_e0 = arena.alloc<uint32_t>(g.n_hub_chunks);
-        g.hb_hub = arena.alloc<uint32_t>(g.n_hub_blocks);
-        g.hb_bucket = arena.alloc<uint32_t>(g.n_hub_blocks);
-        hip_check(hipMemcpyAsync(g.hub_deg, hd.data(), hd.size() * 4, hipMemcpyHostToDevice, s), "hub deg");
-        hip_check(hipMemcpyAsync(g.hub_logb, hl.data(), hl.size() * 4, hipMemcpyHostToDevice, s), "hub logb");
-        hip_check(hipMemcpyAsync(g.hub_key_off, ho.data(), ho.size() * 8, hipMemcpyHostToDevice, s), "hub off");
-        hip_check(hipMemcpyAsync(g.hc_hub, ch.data(), ch.size() * 4, hipMemcpyHostToDevice, s), "hub chunks");
-        hip_check(hipMemcpyAsync(g.hc_e0, ce.data(), ce.size() * 4, hipMemcpyHostToDevice, s), "hub chunk e0");
-        hip_check(hipMemcpyAsync(g.hb_hub, bh.data(), bh.size() * 4, hipMemcpyHostToDevice, s), "hub blocks");
-        hip_check(hipMemcpyAsync(g.hb_bucket, bb.data(), bb.size() * 4, hipMemcpyHostToDevice, s), "hub buckets");
-        hip_check(hipStreamSynchronize(s), "hub schedule sync");
-    } else {
-        g.n_hub_chunks = 0;
-        g.n_hub_blocks = 0;
-        g.n_solo = 0;
-        g.hub_keys_total = 0;
+        schedule_hubs(g, all.data(), arena, s);
+    } else if (g.n_hubs) {
+        schedule_hubs(g, host->hubs, arena, s);
     }
 
     // label salts

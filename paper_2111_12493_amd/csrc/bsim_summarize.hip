@@ -382,15 +382,14 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     Staged g;
     upload_graph(graph, g, arena, s);
     g.hub_table_slots = ctx->hub_table_slots;
-    RunStatus* stage_status = arena.alloc<RunStatus>(1);
-    stage_graph(g, stage_status, &ctx->status_host[3], arena, s);
+    stage_graph(g, ctx->stage_host, arena, s);
     // direction / label parameterizations: refine the view h, take the
     // summary edges from the kept edges f
     const bool view = labels || (p.flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS));
     DirectedView dv;
     if (view) {
         direction_view(g, p.flags, labels, dv, arena, s);
-        stage_graph(dv.h, stage_status, &ctx->status_host[3], arena, s);
+        stage_graph(dv.h, ctx->stage_host, arena, s);
     }
     const Staged& gr = view ? dv.h : g;
     const Staged& gf = view ? dv.f : g;
