@@ -166,12 +166,13 @@ typedef struct {
     float ms_iter_kernels; /* when the ctx option "time_launches" is N > 0: summed
                               durations of every N-th refinement-kernel launch
                               among those that hashed a level (launches
-                              1..k_done+1, less launch k_done+1 when it ran
-                              split; later ones return at once), else 0 */
+                              1..k_done, and k_done+1 with tail_split_ppm 0),
+                              with the class test of that level, else 0 */
     float ms_hub_kernels;  /* the same for the hub-vertex launches */
     uint32_t n_timed_launches; /* launches those sums cover */
-    uint32_t n_split_launches; /* refinement launches run as a split half and a
-                                  hash half (ctx option "tail_split_ppm") */
+    uint32_t n_split_launches; /* refinement launches that ran after the class
+                                  test of the level before them was complete
+                                  (ctx option "tail_split_ppm") */
     float ms_resolve;      /* bsim_apply_updates: host time of the batch's op
                               resolution (validation and net changes), before
                               any device work; 0 for the other calls */
@@ -208,7 +209,8 @@ void bsim_ctx_free(bsim_ctx* ctx);
 const char* bsim_last_error(const bsim_ctx* ctx);
 const char* bsim_status_string(int status);
 /* Run-time options (see bsim_option_names()): "chunk_max" = refinement
- * launches queued per stop-flag check (1..4096); "time_launches" = N > 0
+ * launches queued past the last one that the device has reported (1..4096;
+ * at most 4 are, and with 1 the host waits for every stop test); "time_launches" = N > 0
  * to bracket every N-th refinement and hub launch (0..1 << 20) with HIP
  * events and report the summed kernel times in bsim_result.ms_iter_kernels /
  * ms_hub_kernels (events on every launch add gaps between launches, so
@@ -219,12 +221,10 @@ const char* bsim_status_string(int status);
  * which an update level is recomputed for all vertices (0: always, the
  * plain form); "frontier_edge_pct" (1..100, default 15) = the same for the
  * share of the out-edges that a level's frontier reads;
- * "tail_split_ppm" (0..1000000, default 100) = when the refinement launches
- * run one per stop check (graphs whose launch takes milliseconds, or
- * chunk_max = 1), a level that founds at most this many classes per
- * million vertices has the next level's split test run as a launch of its
- * own before that level's hashes, so a run that reaches its fixpoint there
- * hashes no further level (0: off);
+ * "tail_split_ppm" (0..1000000, default 100) = above 0, a refinement
+ * launch's stop test knows the classes of the level just hashed, so a run
+ * hashes no level past its last one; 0 = the test looks one level further
+ * back, and level k_done + 1 is hashed and dropped;
  * "autotune" (0/1, default 1) = batched calls pick their schedule per size
  * class by timing the candidates on the first call of the class;
  * "batch_small_edges" (N >= 0) = a fixed batched schedule instead: graphs

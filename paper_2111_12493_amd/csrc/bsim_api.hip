@@ -88,11 +88,10 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
         bsim_ctx_free(c);
         return BSIM_E_NOMEM;
     }
-    for (hipEvent_t& e : c->loop_ev) {
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            bsim_ctx_free(c);
-            return BSIM_E_DEVICE;
-        }
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->report_host), kReportRing * sizeof(uint64_t),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        bsim_ctx_free(c);
+        return BSIM_E_NOMEM;
     }
     // the allocation-free entry point's scratch on this device (once per device)
     const int rc = noalloc_scratch_init(device, &c->err);
@@ -118,23 +117,23 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     if (ctx->status_host) (void)hipHostFree(ctx->status_host);
     if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
     if (ctx->count_host) (void)hipHostFree(ctx->count_host);
-    for (hipEvent_t e : ctx->loop_ev)
-        if (e) (void)hipEventDestroy(e);
+    if (ctx->report_host) (void)hipHostFree(ctx->report_host);
     delete ctx;
 }
 
 const char* bsim_last_error(const bsim_ctx* ctx) { return ctx ? ctx->err.c_str() : ""; }
 
 const char* bsim_option_names(void) {
-    return "chunk_max (refinement launches queued per stop-flag check, 1..4096); "
+    return "chunk_max (refinement launches queued past the last one the device has reported, 1..4096; "
+           "at most 4 are); "
            "time_launches (N, 0..1048576: time every N-th refinement launch with HIP events, 0 = off); "
            "hub_table_slots (LDS slots of a hub-bucket block: power of two, 64..device limit); "
            "frontier_limit_pct (0..100: an update level whose frontier exceeds this share of the vertices is "
            "recomputed for all vertices; 0 = always, the plain full recomputation; default 10); "
            "frontier_edge_pct (1..100: the same for a frontier's share of the out-edges; default 15); "
-           "tail_split_ppm (0..1000000: when refinement launches run one per stop check, a level that founds "
-           "at most this many classes per million vertices has the next level's split run as a launch of its "
-           "own, so a run that stops there computes no further hashes; 0 = off, default 100); "
+           "tail_split_ppm (0..1000000: above 0, the default is 100, a launch's stop test knows the classes of "
+           "the level just hashed, and a run hashes no level past its last; 0 = the test looks one level "
+           "further back and one more level is hashed); "
            "autotune (0/1: batched calls pick their schedule per size class by timing the candidates on the "
            "first call of the class; 1 = default); "
            "batch_small_edges (N >= 0: a fixed batched schedule, graphs of at most N edges that fit one "

@@ -14,16 +14,16 @@ struct bsim_ctx {
     std::string err;
     bsim::RunStatus* status_host = nullptr;  // pinned, 4 entries
     bsim::StageHost* stage_host = nullptr;   // pinned: what staging copies back
-    hipEvent_t loop_ev[2] = {nullptr, nullptr};  // status-copy events of the refinement loop
+    uint64_t* report_host = nullptr;         // pinned: kReportRing words, written by refinement launches
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;
     uint32_t hub_table_slots = 8192;  // LDS slots per hub-bucket block on this device
     uint32_t frontier_limit_pct = 10;  // incremental: larger frontiers recompute the level for all vertices
     uint32_t frontier_edge_pct = 15;   // ... and so do frontiers with more than this share of the edges
-    // one launch per stop check: once a level founds at most this many
-    // classes per million vertices, the next level's split runs on its own
+    // 0: the stop test looks two levels back, so that one level past the last
+    // is hashed; else it knows the level just hashed
     uint32_t tail_split_ppm = 100;
-    uint32_t* count_host = nullptr;   // pinned: a level's founded counts (kStripes entries)
+    uint32_t* count_host = nullptr;   // pinned scratch for counts (kStripes entries)
     // batched calls: schedules picked by the autotuner, per size class
     uint32_t autotune = 1;
     struct BatchTune {

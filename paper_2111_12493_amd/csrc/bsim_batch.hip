@@ -325,7 +325,7 @@ void batch_summarize(bsim_ctx* ctx, const bsim_graph* graphs, uint32_t G, const 
     const Staged& uf = view ? dv.f : u;
     const bool stop = (p.flags & BSIM_STOP_AT_FIXPOINT) != 0;
     RunBuffers rb;
-    alloc_run_buffers(ur, p.k_max, stop, rb, arena, s);
+    alloc_run_buffers(ur, rb, arena, s);
     rb.bc.gid = gid;
     rb.bc.n_graphs = G;
     rb.bc.virt_base = u.n;

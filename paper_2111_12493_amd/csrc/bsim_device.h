@@ -142,10 +142,6 @@ __device__ __forceinline__ uint32_t lds_insert_bounded(uint64_t* tab, uint32_t s
     return 2u;
 }
 
-__device__ __forceinline__ void add_block_count(uint32_t* stripes, uint32_t k, uint32_t c) {
-    if (c) atomicAdd(&stripes[(k & (kStripeRing - 1)) * kStripes + (blockIdx.x & (kStripes - 1))], c);
-}
-
 // Tile layout in LDS: s_off[i] = first edge of local vertex i relative to
 // the tile's first edge (i = 0..nv), s_seg[j] = local vertex owning edge j.
 // Requires nv <= kTileMaxVerts and ne = s_off[nv] < kTileMaxEdges.

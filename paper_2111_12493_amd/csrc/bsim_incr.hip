@@ -1650,7 +1650,7 @@ bsim_result* create_state(bsim_ctx* ctx, const bsim_graph& graph, const bsim_par
     } else {
         // every level h^0..h^K by the batch refinement (no early stop)
         RunBuffers rb;
-        alloc_run_buffers(g, p.k_max, false, rb, arena, s);
+        alloc_run_buffers(g, rb, arena, s);
         LevelSink sink;
         for (auto& l : st->levels) sink.levels.push_back(l.p);
         bsim_params bp{p.k_max, p.flags & ~BSIM_STOP_AT_FIXPOINT};

@@ -75,21 +75,17 @@ constexpr int kHubBlock = 512;           // threads per hub-bucket block
 constexpr int kMaxHubLogB = 8;           // at most 256 hash buckets per hub
 constexpr uint32_t kHubTableDefault = 4096;  // LDS slots per hub-bucket block (32 KiB)
 constexpr int kHubOffStride = (1 << kMaxHubLogB) + 1;  // bucket offsets per hub chunk
-constexpr int kStripes = 64;             // striped per-level claim counters
+// Striped per-level claim counters, each on a cache line of its own: atomics
+// on one line are served one after the other, and every wave that founds
+// classes adds to a stripe.  With the 64 stripes packed in two lines level 0
+// of 2^27 vertices took 10.7 ms, on lines of their own 2.4 ms.
+constexpr int kStripes = 64;
+constexpr int kStripePitch = 32;         // words between counters
 constexpr int kStripeRing = 4;
 constexpr int kListPerStripe = 4096;     // claimed split-table slots remembered per stripe
 constexpr uint32_t kNoRep = 0xFFFFFFFEu; // virtual class of every vertex before level 0
 
 // Device-side status of a refinement run.
-// Launch k normally tests level k-2, splits level k-1 and hashes level k
-// (kPhaseFused).  Near a fixpoint it can run as two launches: kPhaseSplit
-// (stop test of level k-2, split of level k-1, no hashes), then kPhaseHash
-// (stop test of level k-1, which the split launch completed, then h^k), so
-// a run that stops at level k-1 computes no h^k.
-constexpr uint32_t kPhaseFused = 0;
-constexpr uint32_t kPhaseSplit = 1;
-constexpr uint32_t kPhaseHash = 2;
-
 struct RunStatus {
     uint32_t done;      // sticky: set by the first launch that sees the stop condition
     uint32_t k_done;
@@ -113,6 +109,15 @@ struct SplitTable {
     uint32_t* list;       // kStripes * kListPerStripe claimed slot indices
     uint32_t mask;        // cap - 1
 };
+
+// What launch k of the refinement tells the host: word k mod kReportRing of a
+// pinned array holds tag(k) and flags in its high half and the class count of
+// the level it tested in its low half.
+constexpr uint32_t kReportRing = 64;
+constexpr uint32_t kReportDone = 1u;
+constexpr uint32_t kReportFixpoint = 2u;
+constexpr uint32_t kReportError = 4u;
+__host__ __device__ constexpr uint32_t report_tag(uint32_t k) { return k << 3; }
 
 // Per-graph control of a batched run: many independent graphs refined as one
 // disjoint union.  Level-0 classes are keyed by a virtual class per graph, so
@@ -145,7 +150,7 @@ struct SmallPlan {
     uint32_t grid = 0;                // persistent workgroups
 };
 
-// Arguments of one refinement launch k: split test of level k-1, h^k.
+// Arguments of one refinement launch k: stop test of level k - lag, h^k.
 struct IterArgs {
     const uint32_t* row_off;
     const uint32_t* tgt;
@@ -155,7 +160,6 @@ struct IterArgs {
     const uint64_t* h_prev; // h^{k-1}
     uint64_t* h_next;       // h^k
     const uint8_t* alive;   // nullable
-    uint32_t* rep;
     const uint4* tiles;         // positions [x, y) of the tile-vertex list, edges [z, w)
     const uint32_t* act;        // tile vertices (out-degree 1..kHubMinDegree-1), ascending
     const uint32_t* iso;        // vertices without out-edges, ascending
@@ -166,24 +170,38 @@ struct IterArgs {
     const uint64_t* hub_key_off;  // first scratch key of the hub
     uint64_t* hub_keys;
     uint32_t* hub_boff;           // per hub chunk: kHubOffStride bucket offsets
-    SplitTable test_tab;    // receives the split-offs of level k-1
-    SplitTable clr_tab;     // filled at level k-2, cleared here
-    uint32_t* lcnt;         // [kStripeRing][kStripes] claims per level
-    uint32_t* totals;       // totals[j] = n_j
+    const uint32_t* lcnt;   // [kStripeRing][kStripes] claims per level, kStripePitch apart
+    uint32_t* totals;       // totals[j mod kStripeRing] = n_j
     RunStatus* status;
+    uint64_t* report;       // pinned host words (nullable)
     const uint32_t* solo_v;     // solo hub vertices
     uint32_t n_tiles;
     uint32_t n_hub_chunks;
     uint32_t n_solo;
     uint32_t n_iso;
     uint32_t n_iso_blocks;
-    uint32_t all_levels;    // every level has its own hash array (else two alternate)
     uint32_t k;
+    uint32_t lag;           // the stop test is that of level k - lag
     uint32_t k_max;
     uint32_t stop;
-    uint32_t hash_only;     // h^k only: no stop test, split test or recycling
-    uint32_t phase;         // kPhaseFused, or one half of a split launch (kPhaseSplit, kPhaseHash)
-    uint32_t stop_only;     // one workgroup that records the stop the host already knows of
+    uint32_t hash_only;     // h^k only: no stop test
+    uint32_t stop_only;     // one workgroup: the stop test only
+    BatchCtl bc;
+};
+
+// Arguments of the split launch of level k.
+struct SplitArgs {
+    const uint64_t* h;      // h^k
+    uint32_t* rep;
+    const uint32_t* act;    // tile vertices, then hubs: the vertices tested from level 2 on
+    const uint32_t* hub_v;
+    uint32_t n_act;
+    uint32_t count;         // vertices tested at this level
+    SplitTable test_tab;    // receives the split-offs
+    SplitTable clr_tab;     // filled at level k-1, cleared here
+    uint32_t* lcnt;
+    const RunStatus* status;
+    uint32_t k;
     BatchCtl bc;
 };
 
@@ -415,9 +433,8 @@ struct RunBuffers {
     uint64_t* h[2] = {nullptr, nullptr};
     uint32_t* rep = nullptr;
     SplitTable tab[2];
-    uint32_t* lcnt = nullptr;      // [kStripeRing * kStripes]
-    uint32_t* totals = nullptr;    // [k_cap]
-    uint32_t k_cap = 0;
+    uint32_t* lcnt = nullptr;      // [kStripeRing * kStripes * kStripePitch]
+    uint32_t* totals = nullptr;    // [kStripeRing]
     uint64_t* hub_keys = nullptr;
     uint32_t* hub_boff = nullptr;
     uint64_t* hub_acc = nullptr;
@@ -426,20 +443,21 @@ struct RunBuffers {
     SmallPlan small;               // batched runs only
 };
 
-void alloc_run_buffers(const Staged& g, uint32_t k_max, bool stop, RunBuffers& rb, Arena& arena,
-                       hipStream_t s);
+void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_t s);
 
 // Level 0: type hashes, h^0 = t, the type classes (rep) and n_0.
 void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_t s);
 
-// Launch k: stop test, split test of level k-1, h^k (tiles and hub chunks),
-// or one half of it (phase; see kPhaseFused).  stop_only: the hash half of a
-// launch whose split half ended the run (the host has read the founded
-// count): a single workgroup takes the stop decision and records it, where
-// the whole grid would only dispatch and exit.
-void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t k_max,
-                      bool stop, bool all_levels, hipStream_t s, uint32_t phase = kPhaseFused,
-                      bool stop_only = false);
+// Launch k: stop test of level k - lag, h^k (tiles and hub chunks).
+// stop_only: one workgroup that takes the stop decision and reports it to
+// the host, where a whole grid would only dispatch and exit.
+void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop,
+                      bool all_levels, uint64_t* report, bool stop_only, hipStream_t s);
+// Workgroups of a full launch k.
+uint32_t iteration_grid(const Staged& g, uint32_t k, bool all_levels);
+
+// The classes of level k from h^k.
+void launch_split(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t s);
 
 // Hub buckets of iteration k (only when the graph has hubs and k <= k_max).
 void launch_hubs(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t s);
@@ -457,8 +475,8 @@ void alloc_hash_scratch(const Staged& g, HashScratch& hs, Arena& arena, hipStrea
 void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_prev, uint64_t* h_next,
                        const HashScratch& hs, uint32_t level, hipStream_t s);
 
-// Batched runs: per-graph stop test of level k-2, before launch k.
-void launch_graph_stop(const RunBuffers& rb, uint32_t k, uint32_t k_max, bool stop, hipStream_t s);
+// Batched runs: per-graph stop test of level k - lag, before launch k.
+void launch_graph_stop(const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop, hipStream_t s);
 
 // Batched runs: LDS bytes of a small-graph workgroup with the given
 // capacities (and its hash-table slots), and the launch that refines the

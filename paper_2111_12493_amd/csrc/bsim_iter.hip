@@ -2,31 +2,26 @@
 //
 // Level 0 (k_init) hashes every vertex's type set (Algorithm 4's
 // initialization: the ID of the local schema) and groups vertices by it.
-// Launch k >= 1 (k_iterate) runs three phases in every block:
-//   0. stop test on the class count of level k-2, which is complete once
-//      launch k-1 has finished; recycling of counters and of the split table
-//      that level k-2 used;
-//   1. split test of level k-1 for the block's own vertices: a vertex whose
-//      h^{k-1} differs from its representative's joins (or founds) the class
-//      (rep, h^{k-1}) in the split table; the number of founded classes is
-//      n_{k-1} - n_{k-2};
-//   2. h^k: a tile block gathers h^{k-1} of its out-edge targets
-//      (SignalMessages), de-duplicates the (label, hash) pair keys of each
-//      vertex in a per-vertex open-addressing region of an LDS table
-//      (MergeMessages' hash table), sums the mixed distinct keys
-//      (the order-independent Hash) and writes h^k; a hub chunk block writes
-//      its mixed keys to the hub's scratch area instead.
-// Then k_hub de-duplicates each hub's scratch keys bucket by bucket in LDS
-// and adds each bucket's distinct sum to the hub's accumulator;
-// k_hub_finish turns the sums into h^k.
-//
-// The stop test lags the hashes by two launches, so once the block count
-// stops growing at level j, launch j+1 has computed h^{j+1} that is never
-// used and launch j+2 sets the sticky done flag; every later launch returns
-// at once, so the host can queue launches ahead.  A launch can also run as
-// two (kPhaseSplit, then kPhaseHash): the host reads the classes that the
-// split half founded before it decides on the hash half, which lets a run
-// that reaches its fixpoint there hash no further level.
+// Level k >= 1 is then
+//   k_iterate  stop test of level k-1 (every block takes the same decision
+//              from the level's founded counts; block 0 records it), then
+//              h^k: a tile block gathers h^{k-1} of its out-edge targets
+//              (SignalMessages), de-duplicates the (label, hash) pair keys of
+//              each vertex in a per-vertex open-addressing region of an LDS
+//              table (MergeMessages' hash table), sums the mixed distinct
+//              keys (the order-independent Hash) and writes h^k; a hub chunk
+//              block writes its mixed keys to the hub's scratch area instead;
+//   k_hub      de-duplicates each hub's scratch keys bucket by bucket in LDS
+//              and adds each bucket's distinct sum to the hub's accumulator;
+//              k_hub_finish turns the sums into h^k;
+//   k_split    the classes of level k: a vertex whose h^k differs from its
+//              representative's joins (or founds) the class (rep, h^k) in the
+//              split table; the number of founded classes is n_k - n_{k-1}.
+//              It also empties the table that level k-1 filled.
+// A run that stops at level j hashes no level past it: launch j+1 of
+// k_iterate finds the stop.  The done flag is sticky and later launches
+// return at once, so the host can queue launches ahead; block 0 of every
+// launch tells the host the class count through a word in host memory.
 #include "bsim_device.h"
 
 namespace bsim {
@@ -71,24 +66,29 @@ __device__ uint64_t split_join(const SplitTable& T, const uint64_t* __restrict__
     }
 }
 
-// split_join for the participating lanes of a wave, one call per distinct
-// (r, key): lanes are grouped by ballots first, so a key shared by many
-// vertices (every vertex without out-edges of one type set joins one class)
-// reaches the table once per wave.  All lanes of the wave must call it.
-// Returns the owner word for participating lanes; *founded / *slot as
-// split_join for the group's leader, 0 / 0xFFFFFFFF for the others.
+// split_join for the participating lanes of a wave, with the lanes of one
+// (r, key) grouped by ballots first, so that a key shared by many vertices
+// (every vertex without out-edges of one type set joins one class) reaches
+// the table about once per wave.  The keys of the first kJoinRounds pending
+// lanes are grouped; a key held by a large share of the vertices is almost
+// surely among them, and the rest go to the table by themselves.  All lanes
+// of the wave must call it.  Returns the owner word for participating lanes;
+// *founded / *slot as split_join for a group's leader, 0 / 0xFFFFFFFF for
+// the others.
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t x, uint32_t src) {
     const int lo = __shfl(static_cast<int>(static_cast<uint32_t>(x)), static_cast<int>(src), 64);
     const int hi = __shfl(static_cast<int>(static_cast<uint32_t>(x >> 32)), static_cast<int>(src), 64);
     return (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
 }
 
+constexpr int kJoinRounds = 8;
+
 __device__ uint64_t wave_split_join(const SplitTable& T, const uint64_t* __restrict__ keys, bool participant,
                                     uint32_t r, uint64_t key, uint32_t v, uint32_t* founded, uint32_t* slot_out) {
     const uint32_t lane = lane_id();
     uint32_t leader_of = lane;
     bool pending = participant;
-    for (;;) {
+    for (int round = 0; round < kJoinRounds; round++) {
         const uint64_t ball = __ballot(pending);
         if (!ball) break;
         const uint32_t leader = static_cast<uint32_t>(__ffsll(static_cast<long long>(ball)) - 1);
@@ -123,31 +123,41 @@ __device__ void wave_count_by_key(bool take, uint32_t key, uint32_t* base) {
     }
 }
 
-// Count the classes founded by this block at `level` (stripe counter) and
-// remember their slots so the table can be cleared selectively.
-__device__ void record_founders(const SplitTable& T, uint32_t* lcnt, uint32_t level,
-                                uint32_t founded, uint32_t slot, uint32_t* s_red, uint32_t* s_base) {
-    const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
-    const uint64_t ball = __ballot(founded != 0);
-    const uint32_t wcount = static_cast<uint32_t>(__popcll(ball));
-    const uint32_t wrank = static_cast<uint32_t>(__popcll(ball & ((1ull << lane) - 1)));
-    if (lane == 0) s_red[wid] = wcount;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (int w = 0; w < kBlock / 64; w++) {
-        if (w < static_cast<int>(wid)) off += s_red[w];
-        tot += s_red[w];
+// The claim counter of one stripe at `level`.
+__device__ __forceinline__ uint32_t* stripe_of(uint32_t* lcnt, uint32_t level, uint32_t stripe) {
+    return lcnt + ((level & (kStripeRing - 1)) * kStripes + stripe) * kStripePitch;
+}
+__device__ __forceinline__ uint32_t stripe_count(const uint32_t* lcnt, uint32_t level, uint32_t stripe) {
+    return lcnt[((level & (kStripeRing - 1)) * kStripes + stripe) * kStripePitch];
+}
+
+// Count the classes this wave founded at `level` (up to N per lane, one
+// atomic per wave that founded any) and remember their slots so the table
+// can be cleared selectively.  All lanes of the wave call it.
+template <int N>
+__device__ __forceinline__ void record_founders(const SplitTable& T, uint32_t* lcnt, uint32_t level,
+                                                const uint32_t (&founded)[N], const uint32_t (&slot)[N]) {
+    const uint32_t lane = lane_id();
+    uint64_t ball[N];
+    uint32_t total = 0;
+#pragma unroll
+    for (int q = 0; q < N; q++) {
+        ball[q] = __ballot(founded[q] != 0);
+        total += static_cast<uint32_t>(__popcll(ball[q]));
     }
-    const uint32_t stripe = blockIdx.x & (kStripes - 1);
-    if (threadIdx.x == 0)
-        *s_base = tot ? atomicAdd(&lcnt[(level & (kStripeRing - 1)) * kStripes + stripe], tot) : 0;
-    __syncthreads();
-    if (founded) {
+    if (!total) return;
+    const uint32_t stripe = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kStripes - 1);
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(stripe_of(lcnt, level, stripe), total);
+    base = static_cast<uint32_t>(__shfl(static_cast<int>(base), 0, 64));
+#pragma unroll
+    for (int q = 0; q < N; q++) {
         // every counted position is written
-        const uint32_t pos = *s_base + off + wrank;
-        if (pos < static_cast<uint32_t>(kListPerStripe)) T.list[stripe * kListPerStripe + pos] = slot;
+        const uint32_t pos = base + static_cast<uint32_t>(__popcll(ball[q] & ((1ull << lane) - 1)));
+        if (founded[q] && pos < static_cast<uint32_t>(kListPerStripe))
+            T.list[stripe * kListPerStripe + pos] = slot[q];
+        base += static_cast<uint32_t>(__popcll(ball[q]));
     }
-    __syncthreads();
 }
 
 // ------------------------------------------------------------ level 0
@@ -181,24 +191,31 @@ __global__ void __launch_bounds__(kBlock) k_types(const uint32_t* __restrict__ t
 // Level-0 classes by t (written by k_types, the launch before): many
 // vertices share a type set, so each wave's lanes are grouped by key before
 // they touch the table.
+constexpr int kSplitPerThread = 4;
+
 __global__ void __launch_bounds__(kBlock) k_init(const uint64_t* __restrict__ t, const uint8_t* __restrict__ alive,
                                                  uint32_t n, uint32_t* __restrict__ rep, SplitTable T,
                                                  uint32_t* lcnt, BatchCtl bc) {
-    __shared__ uint32_t s_red[kBlock / 64];
-    __shared__ uint32_t s_base;
-    const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    uint32_t founded = 0, slot = 0xFFFFFFFFu;
-    uint32_t r = 0xFFFFFFFFu;
-    const bool part = v < n && (!alive || alive[v]);
-    const uint32_t gi = (part && bc.gid) ? bc.gid[v] : 0u;
-    const uint32_t vr = bc.gid ? bc.virt_base + gi : kNoRep;
-    uint64_t key = 0;
-    if (part) key = t[v];
-    const uint64_t o = wave_split_join(T, t, part, vr, key, v, &founded, &slot);
-    if (part) r = static_cast<uint32_t>(o);
-    if (bc.gid) wave_count_by_key(founded != 0, gi, bc.hist);
-    if (v < n) rep[v] = r;
-    record_founders(T, lcnt, 0, founded, slot, s_red, &s_base);
+    const uint32_t first = blockIdx.x * (kBlock * kSplitPerThread) + threadIdx.x;
+    uint32_t founded[kSplitPerThread], slot[kSplitPerThread];
+    uint64_t key[kSplitPerThread];
+    bool part[kSplitPerThread];
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        const uint32_t v = first + q * kBlock;
+        part[q] = v < n && (!alive || alive[v]);
+        key[q] = part[q] ? t[v] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        const uint32_t v = first + q * kBlock;
+        const uint32_t gi = (part[q] && bc.gid) ? bc.gid[v] : 0u;
+        const uint32_t vr = bc.gid ? bc.virt_base + gi : kNoRep;
+        const uint64_t o = wave_split_join(T, t, part[q], vr, key[q], v, &founded[q], &slot[q]);
+        if (bc.gid) wave_count_by_key(founded[q] != 0, gi, bc.hist);
+        if (v < n) rep[v] = part[q] ? static_cast<uint32_t>(o) : 0xFFFFFFFFu;
+    }
+    record_founders(T, lcnt, 0, founded, slot);
 }
 
 // ------------------------------------------------------------ launch k
@@ -216,75 +233,60 @@ static_assert(offsetof(IterShared, red) >= kSoloSlots * sizeof(uint64_t),
               "a solo block's table must end before the block's control words");
 static_assert(kTileMaxEdges >= (kBlock / 64) * 8, "a solo block's wave sums live in seg");
 
-// Split test of level k-1 for one owned vertex (h_prev holds h^{k-1}).
-__device__ __forceinline__ void split_test(const IterArgs& a, uint32_t v, uint32_t* founded,
-                                           uint32_t* slot) {
-    *founded = 0;
-    *slot = 0xFFFFFFFFu;
-    if (a.alive && !a.alive[v]) return;
-    if (a.bc.gid && a.k - 1 > a.bc.done_level[a.bc.gid[v]]) return;
-    const uint32_t r = a.rep[v];
-    if (r == v) return;
-    const uint64_t hv = a.h_prev[v];
-    if (hv == a.h_prev[r]) return;
-    a.rep[v] = static_cast<uint32_t>(split_join(a.test_tab, a.h_prev, r, hv, v, founded, slot));
-    if (a.bc.gid && *founded)
-        atomicAdd(&a.bc.hist[static_cast<size_t>(a.k - 1) * a.bc.n_graphs + a.bc.gid[v]], 1u);
-}
-
-// What launch k does: the split test of level k-1, the hashes h^k, and the
-// stop test of level k - stop_lag (its split is complete by then).
-__device__ __forceinline__ bool run_test(const IterArgs& a) {
-    return !a.hash_only && a.phase != kPhaseHash && a.k >= 2 && a.k - 1 <= a.k_max;
-}
-__device__ __forceinline__ bool run_hash(const IterArgs& a) { return a.phase != kPhaseSplit && a.k <= a.k_max; }
-__device__ __forceinline__ uint32_t stop_lag(const IterArgs& a) { return a.phase == kPhaseHash ? 1u : 2u; }
+__device__ __forceinline__ bool run_hash(const IterArgs& a) { return a.k <= a.k_max; }
 
 // The sticky done flag as this wave sees it (only to skip loads; see tile_block).
 __device__ __forceinline__ bool early_done(const IterArgs& a) {
     return !a.hash_only && __hip_atomic_load(&a.status->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
 
-// Stop test of level k - stop_lag (wave 0), from the values loaded at block start:
-// S.ctl[0] = 1 when the run is done; block 0 also records n_{k-2} and, on
-// stopping, the final status.  Visible to the block after its next barrier.
+// Stop test of level k - lag (wave 0), from the values loaded at block start:
+// S.ctl[0] = 1 when the run is done.  Block 0 also keeps the class count,
+// records the final status when the run stops, and reports to the host.
+// Visible to the block after its next barrier.
 __device__ __forceinline__ void stop_decision(const IterArgs& a, IterShared& S, uint32_t p_done,
                                               uint32_t p_cnt, uint32_t p_tot) {
     const uint32_t tid = threadIdx.x, k = a.k;
     if (tid >= 64) return;
-    uint32_t ex = p_done;
+    uint32_t ex = p_done, fix = 0, nl = 0;
     // batched runs: the per-graph stop launch before this one sets done
-    const uint32_t lag = stop_lag(a);
-    if (!ex && k >= lag && !a.bc.gid && !a.hash_only) {
-        const uint32_t lv = k - lag;
+    if (!ex && k >= a.lag && !a.bc.gid && !a.hash_only) {
+        const uint32_t lv = k - a.lag;
         const uint32_t c = wave_sum_u32(p_cnt);
-        const uint32_t nl = lv == 0 ? c : p_tot + c;
-        if (tid == 0) {
-            if (blockIdx.x == 0) a.totals[lv] = nl;
-            const uint32_t fix = (lv >= 1 && c == 0) ? 1u : 0u;
-            if ((a.stop && fix) || lv >= a.k_max) {
-                ex = 1;
-                if (blockIdx.x == 0) {
-                    a.status->k_done = lv;
-                    a.status->fixpoint = fix;
-                    a.status->done = 1;
-                }
+        nl = lv == 0 ? c : p_tot + c;
+        fix = (lv >= 1 && c == 0) ? 1u : 0u;
+        if ((a.stop && fix) || lv >= a.k_max) ex = 1;
+        if (tid == 0 && blockIdx.x == 0) {
+            a.totals[lv & (kStripeRing - 1)] = nl;
+            if (ex) {
+                a.status->k_done = lv;
+                a.status->fixpoint = fix;
+                a.status->done = 1;
             }
         }
     }
-    if (tid == 0) S.ctl[0] = ex;
+    if (tid == 0) {
+        S.ctl[0] = ex;
+        if (blockIdx.x == 0 && a.report) {
+            const uint32_t flags = (ex ? kReportDone : 0u) | (fix ? kReportFixpoint : 0u) |
+                                   (a.status->error ? kReportError : 0u);
+            // one word: the host needs no ordering between the parts
+            __hip_atomic_store(&a.report[k & (kReportRing - 1)],
+                               (static_cast<uint64_t>(report_tag(k) | flags) << 32) | nl, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
 
 // A tile block.  Its latency is a chain of dependent memory round trips, so
-// every load is issued before the first barrier: tile bounds -> offsets and
-// per-vertex state -> edge targets / labels and the representative's hash
-// -> neighbour hashes.  Nothing is written before the stop decision.
+// every load is issued before the first barrier: tile bounds -> offsets,
+// edge targets and labels -> neighbour hashes.  Nothing is written before
+// the stop decision.
 // Returns false when the run is done.
 template <typename LabT>
 __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint32_t p_done, uint32_t p_cnt,
                            uint32_t p_tot) {
     const uint32_t tid = threadIdx.x, k = a.k;
-    const bool test = run_test(a);
     const bool hash = run_hash(a);
     const uint4 td = a.tiles[tile];
     const uint32_t i0 = td.x, nv = td.y - i0;
@@ -296,24 +298,15 @@ __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint
     const uint32_t ne = skip ? 0u : td.w - ebase;
     const bool mine = !skip && tid < nv;
     const uint32_t v = mine ? a.act[i0 + tid] : 0u;
-    uint32_t ro0 = 0, rv = v, gi = 0;
-    uint64_t hv_own = 0, tv = 0;
-    bool live = false;
+    uint32_t ro0 = 0;
+    uint64_t tv = 0;
     // batched runs: a graph that stopped at level L keeps its level-L state
-    bool act_test = true, act_hash = true;
+    bool act_hash = true;
     if (mine) {
         ro0 = a.row_off[v];
-        live = !a.alive || a.alive[v];
         if (a.bc.gid) {
-            gi = a.bc.gid[v];
-            const uint32_t dl = a.bc.done_level[gi];
-            const bool ext = a.bc.ext && a.bc.ext[gi];
-            act_test = !ext && k - 1 <= dl;
-            act_hash = !ext && k <= dl;
-        }
-        if (test) {
-            rv = a.rep[v];
-            hv_own = a.h_prev[v];
+            const uint32_t gi = a.bc.gid[v];
+            act_hash = !(a.bc.ext && a.bc.ext[gi]) && k <= a.bc.done_level[gi];
         }
         if (hash) tv = a.t[v];
     }
@@ -333,10 +326,6 @@ __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint
             l[r] = static_cast<uint32_t>(__builtin_nontemporal_load(&lab[ebase + j]));
         }
     }
-    // split test of level k-1: the representative's hash
-    const bool probe = test && mine && live && act_test && rv != v;
-    uint64_t hv_rep = 0;
-    if (probe) hv_rep = a.h_prev[rv];
 #pragma unroll
     for (int r = 0; r < kEdgesPerThread; r++) {
         const uint32_t j = tid + r * kBlock;
@@ -352,14 +341,6 @@ __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint
     }
     __syncthreads();
     if (S.ctl[0]) return false;
-    if (test) {
-        // leave the class of rep[v] if h^{k-1} differs
-        uint32_t founded = 0, slot = 0xFFFFFFFFu;
-        if (probe && hv_own != hv_rep)
-            a.rep[v] = static_cast<uint32_t>(split_join(a.test_tab, a.h_prev, rv, hv_own, v, &founded, &slot));
-        if (a.bc.gid) wave_count_by_key(founded != 0, gi, a.bc.hist + static_cast<size_t>(k - 1) * a.bc.n_graphs);
-        record_founders(a.test_tab, a.lcnt, k - 1, founded, slot, S.red, &S.ctl[1]);
-    }
     if (!hash) return true;
     for (uint32_t j = tid; j < 2 * ne; j += kBlock) S.tab[j] = 0;
     tile_segments(nv, S.off, S.seg, S.red);
@@ -401,17 +382,17 @@ __device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint
             atomicAdd(reinterpret_cast<unsigned long long*>(&S.acc[seg[r]]), static_cast<unsigned long long>(f[r]));
     }
     __syncthreads();
-    if (mine && act_hash) a.h_next[v] = live ? mix64(tv ^ mix64(kCS + S.acc[tid])) : 0;
+    // (a tile vertex has edges, so it is alive)
+    if (mine && act_hash) a.h_next[v] = mix64(tv ^ mix64(kCS + S.acc[tid]));
     return true;
 }
 
 // A hub chunk block: kTileMaxEdges edges of one hub.  Loads first, as in
-// tile_block; the hub's first chunk block owns the hub vertex's split test.
+// tile_block.
 template <typename LabT>
 __device__ bool hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, uint32_t p_done, uint32_t p_cnt,
                                 uint32_t p_tot) {
-    const uint32_t tid = threadIdx.x, k = a.k;
-    const bool test = run_test(a);
+    const uint32_t tid = threadIdx.x;
     const bool hash = run_hash(a);
     const uint32_t hi = a.hc_hub[blk];
     const uint32_t e0 = a.hc_e0[blk];
@@ -442,11 +423,6 @@ __device__ bool hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, 
     stop_decision(a, S, p_done, p_cnt, p_tot);
     __syncthreads();
     if (S.ctl[0]) return false;
-    if (test) {
-        uint32_t founded = 0, slot = 0xFFFFFFFFu;
-        if (tid == 0 && e0 == vbeg) split_test(a, v, &founded, &slot);
-        record_founders(a.test_tab, a.lcnt, k - 1, founded, slot, S.red, &S.ctl[1]);
-    }
     if (!hash) return true;
     uint64_t* __restrict__ out = a.hub_keys + koff + (e0 - vbeg);
     // group the chunk's nonzero keys by hash bucket (top logb bits) so each
@@ -496,7 +472,6 @@ template <typename LabT>
 __device__ bool solo_block(const IterArgs& a, uint32_t v, IterShared& S, uint32_t p_done, uint32_t p_cnt,
                            uint32_t p_tot) {
     const uint32_t tid = threadIdx.x, k = a.k;
-    const bool test = run_test(a);
     const bool hash = run_hash(a);
     const uint32_t e0 = a.row_off[v];
     const uint32_t ne = early_done(a) ? 0u : a.row_off[v + 1] - e0;
@@ -528,11 +503,6 @@ __device__ bool solo_block(const IterArgs& a, uint32_t v, IterShared& S, uint32_
     for (uint32_t j = tid; j < kSoloSlots; j += kBlock) tab[j] = 0;
     __syncthreads();
     if (S.ctl[0]) return false;
-    if (test) {
-        uint32_t founded = 0, slot = 0xFFFFFFFFu;
-        if (tid == 0) split_test(a, v, &founded, &slot);
-        record_founders(a.test_tab, a.lcnt, k - 1, founded, slot, S.red, &S.ctl[1]);
-    }
     if (!hash) return true;
     // home-slot attempts first, all in flight together (see tile_block)
     uint64_t acc = 0;
@@ -575,105 +545,42 @@ __device__ bool solo_block(const IterArgs& a, uint32_t v, IterShared& S, uint32_
     return true;
 }
 
-// kIsoPerBlock vertices without out-edges: split test, and h^k = M(t ^
-// M(C_S)) where the hash buffer still needs it.
+// kIsoPerBlock vertices without out-edges: h^k = M(t ^ M(C_S)) for every
+// k >= 1, written where the hash buffer does not hold it yet.
 __device__ bool iso_block(const IterArgs& a, uint32_t blk, IterShared& S, uint32_t p_done, uint32_t p_cnt,
                           uint32_t p_tot) {
     const uint32_t tid = threadIdx.x, k = a.k;
-    const bool test = run_test(a);
-    const bool hash = run_hash(a) && (k <= 2 || a.all_levels);
-    uint32_t v[kIsoPerThread], rv[kIsoPerThread], gi[kIsoPerThread];
-    uint64_t hv_own[kIsoPerThread], hv_rep[kIsoPerThread], tv[kIsoPerThread];
-    bool mine[kIsoPerThread], live[kIsoPerThread], probe[kIsoPerThread], act_hash[kIsoPerThread];
+    uint32_t v[kIsoPerThread];
+    uint64_t tv[kIsoPerThread];
+    bool mine[kIsoPerThread], live[kIsoPerThread];
 #pragma unroll
     for (int r = 0; r < kIsoPerThread; r++) {
         const uint32_t i = blk * kIsoPerBlock + r * kBlock + tid;
         mine[r] = i < a.n_iso;
         v[r] = mine[r] ? a.iso[i] : 0u;
-        rv[r] = v[r];
-        gi[r] = 0;
-        hv_own[r] = tv[r] = hv_rep[r] = 0;
+        tv[r] = 0;
         live[r] = false;
-        act_hash[r] = true;
-        bool act_test = true;
         if (mine[r]) {
             live[r] = !a.alive || a.alive[v[r]];
             if (a.bc.gid) {
-                gi[r] = a.bc.gid[v[r]];
-                const uint32_t dl = a.bc.done_level[gi[r]];
-                const bool ext = a.bc.ext && a.bc.ext[gi[r]];
-                act_test = !ext && k - 1 <= dl;
-                act_hash[r] = !ext && k <= dl;
+                const uint32_t gi = a.bc.gid[v[r]];
+                mine[r] = !(a.bc.ext && a.bc.ext[gi]) && k <= a.bc.done_level[gi];
             }
-            if (test) {
-                rv[r] = a.rep[v[r]];
-                hv_own[r] = a.h_prev[v[r]];
-            }
-            if (hash) tv[r] = a.t[v[r]];
+            tv[r] = a.t[v[r]];
         }
-        probe[r] = test && mine[r] && live[r] && act_test && rv[r] != v[r];
     }
-#pragma unroll
-    for (int r = 0; r < kIsoPerThread; r++)
-        if (probe[r]) hv_rep[r] = a.h_prev[rv[r]];
     stop_decision(a, S, p_done, p_cnt, p_tot);
     __syncthreads();
     if (S.ctl[0]) return false;
-    if (test) {
-        for (int r = 0; r < kIsoPerThread; r++) {
-            // vertices without out-edges of one type set and one class all
-            // carry the same key: group them per wave before the table
-            uint32_t founded = 0, slot = 0xFFFFFFFFu;
-            const bool part = probe[r] && hv_own[r] != hv_rep[r];
-            const uint64_t o = wave_split_join(a.test_tab, a.h_prev, part, rv[r], hv_own[r], v[r], &founded, &slot);
-            if (part) a.rep[v[r]] = static_cast<uint32_t>(o);
-            if (a.bc.gid)
-                wave_count_by_key(founded != 0, gi[r], a.bc.hist + static_cast<size_t>(k - 1) * a.bc.n_graphs);
-            record_founders(a.test_tab, a.lcnt, k - 1, founded, slot, S.red, &S.ctl[1]);
-        }
-    }
-    if (hash) {
 #pragma unroll
-        for (int r = 0; r < kIsoPerThread; r++)
-            if (mine[r] && act_hash[r]) a.h_next[v[r]] = live[r] ? mix64(tv[r] ^ mix64(kCS)) : 0;
-    }
+    for (int r = 0; r < kIsoPerThread; r++)
+        if (mine[r]) a.h_next[v[r]] = live[r] ? mix64(tv[r] ^ mix64(kCS)) : 0;
     return true;
 }
 
 // A block with no tile (an empty graph still needs its stop test).
-__device__ bool null_block(const IterArgs& a, IterShared& S, uint32_t p_done, uint32_t p_cnt, uint32_t p_tot) {
+__device__ void null_block(const IterArgs& a, IterShared& S, uint32_t p_done, uint32_t p_cnt, uint32_t p_tot) {
     stop_decision(a, S, p_done, p_cnt, p_tot);
-    __syncthreads();
-    return S.ctl[0] == 0;
-}
-
-// Recycling, after the block's own work: counters of level k-3 and the
-// split table that level k-2 filled (launch k+1 tests level k in it).
-__device__ void recycle(const IterArgs& a) {
-    const uint32_t tid = threadIdx.x, k = a.k;
-    if (blockIdx.x == 0 && tid < kStripes && k >= 3)
-        a.lcnt[((k - 3) & (kStripeRing - 1)) * kStripes + tid] = 0;
-    if (k < 2) return;
-    const uint32_t* cnt = a.lcnt + ((k - 2) & (kStripeRing - 1)) * kStripes;
-    bool overflow = false;
-    for (int st = 0; st < kStripes; st++) overflow |= cnt[st] > static_cast<uint32_t>(kListPerStripe);
-    if (overflow) {
-        const uint64_t cap = static_cast<uint64_t>(a.clr_tab.mask) + 1;
-        const uint64_t per = (cap + gridDim.x - 1) / gridDim.x;
-        const uint64_t lo = per * blockIdx.x, hi = min(cap, lo + per);
-        for (uint64_t j = lo + tid; j < hi; j += kBlock) a.clr_tab.slots[j] = 0;
-    } else {
-        const uint64_t items = static_cast<uint64_t>(kStripes) * kListPerStripe;
-        for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + tid; i < items;
-             i += static_cast<uint64_t>(gridDim.x) * kBlock) {
-            const uint32_t st = static_cast<uint32_t>(i / kListPerStripe);
-            const uint32_t e = static_cast<uint32_t>(i % kListPerStripe);
-            if (e < cnt[st]) {
-                const uint32_t idx = a.clr_tab.list[i];
-                if (idx <= a.clr_tab.mask) a.clr_tab.slots[idx] = 0;
-            }
-        }
-    }
 }
 
 template <typename LabT>
@@ -681,33 +588,119 @@ __global__ void __launch_bounds__(kBlock) k_iterate(IterArgs a) {
     __shared__ IterShared S;
     const uint32_t tid = threadIdx.x;
     const uint32_t k = a.k;
-    // stop-test inputs (level k - stop_lag), loaded together with everything else
+    // stop-test inputs (level k - lag), loaded together with everything else
     uint32_t p_done = 0, p_cnt = 0, p_tot = 0;
     if (tid < 64) {
         p_done = __hip_atomic_load(&a.status->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t lag = stop_lag(a);
-        if (k >= lag && !a.bc.gid && !a.hash_only) {
-            const uint32_t lv = k - lag;
-            p_cnt = a.lcnt[(lv & (kStripeRing - 1)) * kStripes + tid];
-            p_tot = lv ? a.totals[lv - 1] : 0u;
+        if (k >= a.lag && !a.bc.gid && !a.hash_only) {
+            const uint32_t lv = k - a.lag;
+            p_cnt = stripe_count(a.lcnt, lv, tid);
+            p_tot = lv ? a.totals[(lv - 1) & (kStripeRing - 1)] : 0u;
         }
     }
-    bool go;
     const uint32_t b = blockIdx.x;
     if (a.stop_only)
-        go = null_block(a, S, p_done, p_cnt, p_tot);
+        null_block(a, S, p_done, p_cnt, p_tot);
     else if (b < a.n_hub_chunks)
-        go = hub_chunk_block<LabT>(a, b, S, p_done, p_cnt, p_tot);
+        hub_chunk_block<LabT>(a, b, S, p_done, p_cnt, p_tot);
     else if (b - a.n_hub_chunks < a.n_solo)
-        go = solo_block<LabT>(a, a.solo_v[b - a.n_hub_chunks], S, p_done, p_cnt, p_tot);
+        solo_block<LabT>(a, a.solo_v[b - a.n_hub_chunks], S, p_done, p_cnt, p_tot);
     else if (b - a.n_hub_chunks - a.n_solo < a.n_iso_blocks)
-        go = iso_block(a, b - a.n_hub_chunks - a.n_solo, S, p_done, p_cnt, p_tot);
+        iso_block(a, b - a.n_hub_chunks - a.n_solo, S, p_done, p_cnt, p_tot);
     else if (b - a.n_hub_chunks - a.n_solo - a.n_iso_blocks < a.n_tiles)
-        go = tile_block<LabT>(a, b - a.n_hub_chunks - a.n_solo - a.n_iso_blocks, S, p_done, p_cnt, p_tot);
+        tile_block<LabT>(a, b - a.n_hub_chunks - a.n_solo - a.n_iso_blocks, S, p_done, p_cnt, p_tot);
     else
-        go = null_block(a, S, p_done, p_cnt, p_tot);
-    // the hash half of a split launch recycles nothing: its split half did
-    if (go && !a.hash_only && a.phase != kPhaseHash) recycle(a);
+        null_block(a, S, p_done, p_cnt, p_tot);
+}
+
+// ------------------------------------------------------------ classes of level k
+
+// Empty the table that level k-1 filled, from the list of its claimed slots
+// (one stripe after the other per block), or whole when a list overflowed;
+// and the counters that level k+1 will use.
+__device__ void recycle(const SplitArgs& a) {
+    const uint32_t tid = threadIdx.x, k = a.k;
+    if (blockIdx.x == 0 && tid < kStripes) *stripe_of(a.lcnt, k + 1, tid) = 0;
+    const uint32_t mine = stripe_count(a.lcnt, k - 1, tid & (kStripes - 1));
+    if (__ballot(mine > static_cast<uint32_t>(kListPerStripe))) {
+        const uint64_t cap = static_cast<uint64_t>(a.clr_tab.mask) + 1;
+        const uint64_t per = (cap + gridDim.x - 1) / gridDim.x;
+        const uint64_t lo = per * blockIdx.x, hi = min(cap, lo + per);
+        for (uint64_t j = lo + tid; j < hi; j += kBlock) a.clr_tab.slots[j] = 0;
+        return;
+    }
+    for (uint32_t st = blockIdx.x; st < static_cast<uint32_t>(kStripes); st += gridDim.x) {
+        const uint32_t c = stripe_count(a.lcnt, k - 1, st);
+        for (uint32_t e = tid; e < c; e += kBlock) {
+            const uint32_t idx = a.clr_tab.list[st * kListPerStripe + e];
+            if (idx <= a.clr_tab.mask) a.clr_tab.slots[idx] = 0;
+        }
+    }
+}
+
+// Split test of level k.  At level 1 every vertex takes it; from level 2 on
+// a vertex without out-edges cannot leave its class (its hash is the same
+// function of t at every level >= 1), so the tile vertices and the hubs do.
+// A vertex that is its class's representative, as nearly all are once a
+// graph has mostly classes of one, costs the 4 bytes of rep alone.
+//
+// Bound: rep streamed, h of the non-representatives gathered, and at level 1
+// the claims (a random 8-byte line each).  It runs as a launch of its own
+// because the next launch then knows the level's class count before it
+// hashes: with the test inside the next level's hashing launch, every run
+// hashed one level that the fixpoint test discarded, and each tile block
+// carried the test's four dependent loads and its barriers.  On 2^24 vertices
+// and 2^27 edges of a uniform graph a level of both took 3.1 ms and the
+// discarded level as much; hashing alone takes 2.65 ms, the split 0.93 ms at
+// level 1 and 0.04-0.08 ms from there on.
+__global__ void __launch_bounds__(kBlock) k_split(SplitArgs a) {
+    if (a.status->done) return;
+    const uint32_t first = blockIdx.x * (kBlock * kSplitPerThread) + threadIdx.x;
+    const uint32_t k = a.k;
+    uint32_t v[kSplitPerThread], r[kSplitPerThread], gi[kSplitPerThread];
+    uint64_t hv[kSplitPerThread], hr[kSplitPerThread];
+    bool probe[kSplitPerThread];
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        const uint32_t i = first + q * kBlock;
+        probe[q] = i < a.count;
+        v[q] = 0;
+        if (probe[q]) v[q] = k == 1 ? i : i < a.n_act ? a.act[i] : a.hub_v[i - a.n_act];
+    }
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        r[q] = probe[q] ? a.rep[v[q]] : 0u;
+        gi[q] = 0;
+        if (probe[q] && a.bc.gid) {
+            gi[q] = a.bc.gid[v[q]];
+            probe[q] = !(a.bc.ext && a.bc.ext[gi[q]]) && k <= a.bc.done_level[gi[q]];
+        }
+        probe[q] = probe[q] && r[q] != v[q] && r[q] != 0xFFFFFFFFu;  // (a dead vertex has no class)
+    }
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        hv[q] = hr[q] = 0;
+        if (probe[q]) {
+            hv[q] = a.h[v[q]];
+            hr[q] = a.h[r[q]];
+        }
+    }
+    uint32_t founded[kSplitPerThread], slot[kSplitPerThread];
+#pragma unroll
+    for (int q = 0; q < kSplitPerThread; q++) {
+        const bool part = probe[q] && hv[q] != hr[q];
+        founded[q] = 0;
+        slot[q] = 0xFFFFFFFFu;
+        uint64_t o = 0;
+        if (k == 1)
+            o = wave_split_join(a.test_tab, a.h, part, r[q], hv[q], v[q], &founded[q], &slot[q]);
+        else if (part)
+            o = split_join(a.test_tab, a.h, r[q], hv[q], v[q], &founded[q], &slot[q]);
+        if (part) a.rep[v[q]] = static_cast<uint32_t>(o);
+        if (a.bc.gid) wave_count_by_key(founded[q] != 0, gi[q], a.bc.hist + static_cast<size_t>(k) * a.bc.n_graphs);
+    }
+    record_founders(a.test_tab, a.lcnt, k, founded, slot);
+    recycle(a);
 }
 
 // ------------------------------------------------------------ hub buckets
@@ -845,13 +838,13 @@ __global__ void __launch_bounds__(kBlock) k_hub_finish(const uint64_t* t, const 
 
 // ------------------------------------------------------------ batched stop
 
-// Launch k of a batched run begins with this: graph g stops at level k-2
-// when its class count did not grow there (fixpoint) or k-2 reaches k_max.
-__global__ void __launch_bounds__(kBlock) k_graph_stop(BatchCtl bc, uint32_t k, uint32_t k_max, uint32_t stop,
-                                                       RunStatus* status) {
+// Launch k of a batched run begins with this: graph g stops at level k-lag
+// when its class count did not grow there (fixpoint) or k-lag reaches k_max.
+__global__ void __launch_bounds__(kBlock) k_graph_stop(BatchCtl bc, uint32_t k, uint32_t lag, uint32_t k_max,
+                                                       uint32_t stop, RunStatus* status) {
     const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
-    if (g >= bc.n_graphs || k < 2 || bc.done_level[g] != 0xFFFFFFFFu) return;
-    const uint32_t lv = k - 2;
+    if (g >= bc.n_graphs || k < lag || bc.done_level[g] != 0xFFFFFFFFu) return;
+    const uint32_t lv = k - lag;
     const uint32_t c = bc.hist[static_cast<size_t>(lv) * bc.n_graphs + g];
     const uint32_t fx = (lv >= 1 && c == 0) ? 1u : 0u;
     if ((stop && fx) || lv >= k_max) {
@@ -895,48 +888,73 @@ static SplitTable make_table(Arena& arena, uint64_t cap) {
     return T;
 }
 
-void alloc_run_buffers(const Staged& g, uint32_t k_max, bool stop, RunBuffers& rb, Arena& arena,
-                       hipStream_t s) {
+// Clear up to kClearRanges ranges in one launch (a level-0 setup clears six,
+// and a launch apiece costs more than the small ones' bytes).
+constexpr int kClearRanges = 8;
+struct ClearArgs {
+    uint4* p[kClearRanges];
+    uint64_t n[kClearRanges];  // 16-byte words (allocations are 256-byte multiples)
+};
+
+__global__ void __launch_bounds__(kBlock) k_clear(ClearArgs a) {
+    const uint64_t first = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const uint64_t step = static_cast<uint64_t>(gridDim.x) * kBlock;
+#pragma unroll
+    for (int i = 0; i < kClearRanges; i++)
+        for (uint64_t j = first; j < a.n[i]; j += step) a.p[i][j] = make_uint4(0, 0, 0, 0);
+}
+
+void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_t s) {
     const uint32_t n = g.n;
     rb.t = arena.alloc<uint64_t>(n);
     rb.h[0] = arena.alloc<uint64_t>(n);
     rb.h[1] = arena.alloc<uint64_t>(n);
     rb.rep = arena.alloc<uint32_t>(n);
     const uint64_t cap = split_table_slots(n);
+    ClearArgs c{};
+    int nc = 0;
+    uint64_t words = 0;
+    auto clear = [&](void* p, uint64_t bytes) {
+        c.p[nc] = static_cast<uint4*>(p);
+        c.n[nc] = (bytes + 15) / 16;
+        words = std::max(words, c.n[nc++]);
+    };
     for (int i = 0; i < 2; i++) {
         rb.tab[i] = make_table(arena, cap);
-        hip_check(hipMemsetAsync(rb.tab[i].slots, 0, static_cast<size_t>(cap) * sizeof(uint64_t), s),
-                  "clear split table");
+        clear(rb.tab[i].slots, cap * sizeof(uint64_t));
     }
-    rb.lcnt = arena.alloc<uint32_t>(kStripeRing * kStripes);
-    // level j's count is written by launch j+2 <= k_done+2; k_done <= max(n, 1)
-    // when stopping at the fixpoint, else k_max
-    const uint64_t kc = stop ? std::min<uint64_t>(k_max, static_cast<uint64_t>(n) + 1) : k_max;
-    rb.k_cap = static_cast<uint32_t>(kc) + 3;
-    rb.totals = arena.alloc<uint32_t>(rb.k_cap);
+    rb.lcnt = arena.alloc<uint32_t>(kStripeRing * kStripes * kStripePitch);
+    rb.totals = arena.alloc<uint32_t>(kStripeRing);
     rb.hub_keys = arena.alloc<uint64_t>(g.hub_keys_total + 1);
     rb.hub_boff = arena.alloc<uint32_t>((static_cast<size_t>(g.n_hub_chunks) + 1) * kHubOffStride);
     rb.hub_acc = arena.alloc<uint64_t>(g.n_hubs + 1);
     rb.status = arena.alloc<RunStatus>(1);
-    hip_check(hipMemsetAsync(rb.lcnt, 0, kStripeRing * kStripes * 4, s), "clear counters");
-    hip_check(hipMemsetAsync(rb.totals, 0, rb.k_cap * 4, s), "clear totals");
-    hip_check(hipMemsetAsync(rb.hub_acc, 0, (g.n_hubs + 1) * 8, s), "clear hub acc");
-    hip_check(hipMemsetAsync(rb.status, 0, sizeof(RunStatus), s), "clear status");
+    clear(rb.lcnt, kStripeRing * kStripes * kStripePitch * 4);
+    clear(rb.hub_acc, (g.n_hubs + 1) * 8ull);
+    clear(rb.status, sizeof(RunStatus));
+    k_clear<<<std::min<uint32_t>(ceil_div(words, kBlock), 8192), kBlock, 0, s>>>(c);
+    hip_check(hipGetLastError(), "clear run buffers");
 }
 
 void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_t s) {
     const uint32_t n = g.n;
     const uint32_t grid = std::max<uint32_t>(ceil_div(n, kBlock), 1);
     k_types<<<grid, kBlock, 0, s>>>(g.type_off, g.type_ids, g.alive, n, untyped ? 1 : 0, rb.t, rb.h[0]);
-    k_init<<<grid, kBlock, 0, s>>>(rb.t, g.alive, n, rb.rep, rb.tab[0], rb.lcnt, rb.bc);
+    k_init<<<std::max<uint32_t>(ceil_div(n, kBlock * kSplitPerThread), 1), kBlock, 0, s>>>(rb.t, g.alive, n, rb.rep, rb.tab[0], rb.lcnt, rb.bc);
     hip_check(hipGetLastError(), "init launch");
 }
 
-void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t k_max,
-                      bool stop, bool all_levels, hipStream_t s, uint32_t phase, bool stop_only) {
+uint32_t iteration_grid(const Staged& g, uint32_t k, bool all_levels) {
+    const uint32_t iso = k <= 2 || all_levels ? ceil_div(g.n_iso, kIsoPerBlock) : 0u;
+    return std::max<uint32_t>(g.n_hub_chunks + g.n_solo + iso + g.n_tiles, 1);
+}
+
+void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop,
+                      bool all_levels, uint64_t* report, bool stop_only, hipStream_t s) {
     IterArgs a{};
-    a.phase = phase;
     a.stop_only = stop_only ? 1u : 0u;
+    a.report = report;
+    a.lag = lag;
     a.row_off = g.row_off;
     a.tgt = g.tgt;
     a.lab = g.lab;
@@ -945,12 +963,11 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.h_prev = rb.h[(k - 1) & 1];
     a.h_next = rb.h[k & 1];
     a.alive = g.alive;
-    a.rep = rb.rep;
     a.tiles = g.tiles;
     a.act = g.act;
     a.iso = g.iso;
     a.n_iso = g.n_iso;
-    a.n_iso_blocks = ceil_div(g.n_iso, kIsoPerBlock);
+    a.n_iso_blocks = k <= 2 || all_levels ? ceil_div(g.n_iso, kIsoPerBlock) : 0u;
     a.hc_hub = g.hc_hub;
     a.hc_e0 = g.hc_e0;
     a.hub_v = g.hub_v;
@@ -958,8 +975,6 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.hub_key_off = g.hub_key_off;
     a.hub_keys = rb.hub_keys;
     a.hub_boff = rb.hub_boff;
-    a.test_tab = rb.tab[(k - 1) & 1];
-    a.clr_tab = rb.tab[k & 1];
     a.lcnt = rb.lcnt;
     a.totals = rb.totals;
     a.status = rb.status;
@@ -970,15 +985,32 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.k = k;
     a.k_max = k_max;
     a.stop = stop ? 1u : 0u;
-    a.all_levels = all_levels ? 1u : 0u;
     a.bc = rb.bc;
-    const uint32_t grid =
-        stop_only ? 1u : std::max<uint32_t>(g.n_hub_chunks + g.n_solo + a.n_iso_blocks + g.n_tiles, 1);
+    const uint32_t grid = stop_only ? 1u : iteration_grid(g, k, all_levels);
     if (g.label_bytes == 2)
         k_iterate<uint16_t><<<grid, kBlock, 0, s>>>(a);
     else
         k_iterate<uint32_t><<<grid, kBlock, 0, s>>>(a);
     hip_check(hipGetLastError(), "iteration launch");
+}
+
+void launch_split(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t s) {
+    SplitArgs a{};
+    a.h = rb.h[k & 1];
+    a.rep = rb.rep;
+    a.act = g.act;
+    a.hub_v = g.hub_v;
+    a.n_act = g.n_act;
+    a.count = k == 1 ? g.n : g.n_act + g.n_hubs;
+    a.test_tab = rb.tab[k & 1];
+    a.clr_tab = rb.tab[(k - 1) & 1];
+    a.lcnt = rb.lcnt;
+    a.status = rb.status;
+    a.k = k;
+    a.bc = rb.bc;
+    const uint32_t grid = std::max<uint32_t>(ceil_div(a.count, kBlock * kSplitPerThread), 1);
+    k_split<<<grid, kBlock, 0, s>>>(a);
+    hip_check(hipGetLastError(), "split launch");
 }
 
 void launch_hubs(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t s) {
@@ -1051,7 +1083,6 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     a.k = level;
     a.k_max = 0xFFFFFFFFu;
     a.hash_only = 1;
-    a.all_levels = 1;
     const uint32_t grid = std::max<uint32_t>(g.n_hub_chunks + g.n_solo + a.n_iso_blocks + g.n_tiles, 1);
     if (g.label_bytes == 2)
         k_iterate<uint16_t><<<grid, kBlock, 0, s>>>(a);
@@ -1086,8 +1117,8 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     hip_check(hipGetLastError(), "hash level hub finish launch");
 }
 
-void launch_graph_stop(const RunBuffers& rb, uint32_t k, uint32_t k_max, bool stop, hipStream_t s) {
-    k_graph_stop<<<ceil_div(rb.bc.n_graphs, kBlock), kBlock, 0, s>>>(rb.bc, k, k_max, stop ? 1u : 0u, rb.status);
+void launch_graph_stop(const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop, hipStream_t s) {
+    k_graph_stop<<<ceil_div(rb.bc.n_graphs, kBlock), kBlock, 0, s>>>(rb.bc, k, lag, k_max, stop ? 1u : 0u, rb.status);
     hip_check(hipGetLastError(), "graph stop launch");
 }
 

@@ -100,7 +100,7 @@ void run(bsim_ctx* ctx, const bsim_graph& graph, const bsim_params& p, bsim_noal
     g.hub_table_slots = ctx->hub_table_slots;
     stage_graph(g, ctx->stage_host, arena, s);
     RunBuffers rb;
-    alloc_run_buffers(g, p.k_max, (p.flags & BSIM_STOP_AT_FIXPOINT) != 0, rb, arena, s);
+    alloc_run_buffers(g, rb, arena, s);
     LoopResult lr = run_refinement(ctx, g, p, rb, nullptr, arena, nullptr, false);
     FinalOut fo;
     finalize(g, rb.rep, edges, fo, arena, arena, s);

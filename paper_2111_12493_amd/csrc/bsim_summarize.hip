@@ -1,15 +1,14 @@
 // bsim_summarize.hip -- host driver of one batch summarization.
 //
-// Device round trips per call: one after staging (tile and hub counts), one
-// per queued chunk of refinement launches (the sticky done flag, read while
-// the next chunk is already queued), two in finalize (block and edge
-// counts).  Refinement launches are queued in chunks that double up to
-// ctx->chunk_max, so a run of thousands of iterations (long k-chaining)
-// costs only the kernels themselves plus a few early-exit launches.
+// Device round trips per call: one after staging (tile and hub counts), two
+// in finalize (block and edge counts).  The refinement loop has none: the
+// host queues a few launches ahead of what the device reports through pinned
+// memory, so a run of thousands of iterations (long k-chaining) costs only
+// the kernels themselves plus a few early-exit launches.
 #include <algorithm>
-#include <functional>
 #include <cstdlib>
 #include <cstring>
+#include <thread>
 
 #include "bsim_api_internal.h"
 
@@ -110,192 +109,158 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
     }
 
     LoopResult lr;
-    // launch k tests level k-2, so launch k_max + 2 always sees the cap
-    const uint64_t k_last = static_cast<uint64_t>(p.k_max) + 2;
-    uint64_t k = 1;
-    // Launches queued per stop-flag check.  The host waits for the previous
-    // chunk's status while the current one runs, so a chunk only has to
-    // outlast that round trip; every launch queued past the stop is wasted
-    // (an early-exit launch still dispatches its whole grid).  So the chunk
-    // is capped at about 4 ms of estimated work (a refinement launch streams
-    // roughly 40,000 edges per microsecond): one launch at a time for a graph
-    // of 2^30 edges, chunks doubling up to chunk_max for small graphs and
-    // long k-chaining.  A batched run covers many small graphs that stop
-    // within a few levels, and its launches are large: it starts shorter.
-    const double est_us = (static_cast<double>(g.m) + g.n) / 40000.0 + 10.0;
-    const uint32_t chunk_cap =
-        static_cast<uint32_t>(std::max(1.0, std::min<double>(ctx->chunk_max, 4000.0 / est_us)));
-    uint32_t chunk = std::min<uint32_t>(rb.bc.gid ? 2u : 4u, chunk_cap);
-    int pending = -1;
-    hipEvent_t* ev = ctx->loop_ev;  // created with the ctx
-    bool done = false;
-    bool prev_taken = false;
-    std::vector<hipEvent_t> timers;  // (start, after refinement, after hubs) per timed launch
+    // Launch k tests level k - lag.  With lag 1 it knows the classes of the
+    // level just hashed, and a run hashes no level past its last; with
+    // tail_split_ppm = 0 the test looks one level further back, so level
+    // k_done + 1 is hashed and dropped.
+    const uint32_t lag = ctx->tail_split_ppm ? 1u : 2u;
+    const uint64_t k_last = static_cast<uint64_t>(p.k_max) + lag;
+    const bool all = sink && !sink->levels.empty();
+    // The host follows the run through the words that block 0 of every launch
+    // writes to pinned memory, and queues at most `ahead` launches past the
+    // last one it has seen: enough that the device never waits for the host,
+    // few enough that a run of three or four levels does not queue twenty
+    // launches that find it over (a check per chunk of launches did: 28
+    // launches for three levels, 195 of the 690 us a 1,000-vertex graph
+    // kept the device busy).  An early exit still dispatches its whole grid
+    // (about 2 ns a workgroup), so past kLargeGrid workgroups, where one
+    // would cost more than the host's round trip of some 10 us, the stop test
+    // runs as a launch of one workgroup and the host waits for its answer.
+    constexpr uint32_t kLargeGrid = 16384;
+    const bool large = iteration_grid(g, 3, all) > kLargeGrid || ctx->chunk_max == 1;
+    const uint32_t ahead = std::min<uint32_t>(ctx->chunk_max, 4);
+    uint64_t* const report = ctx->report_host;
+    for (uint32_t i = 0; i < kReportRing; i++) report[i] = 0;
+    bool done = false, prev_taken = false;
+    uint64_t seen = 0;  // launches whose word the host has read
+    auto read_report = [&](uint64_t kk, bool wait) {
+        volatile uint64_t* w = &report[kk & (kReportRing - 1)];
+        const uint32_t tag = report_tag(static_cast<uint32_t>(kk));
+        uint64_t x = 0;
+        for (uint32_t spin = 1;; spin++) {
+            x = *w;
+            if (static_cast<uint32_t>(x >> 32) >> 3 == tag >> 3) break;
+            if (!wait) return false;
+            if (spin % 64 == 0) std::this_thread::yield();
+            if (spin % 16384 == 0) {
+                // the device is done (or has failed) without a word
+                const hipError_t e = hipStreamQuery(s);
+                if (e == hipErrorNotReady) continue;
+                hip_check(e, "refinement");
+                x = *w;
+                if (static_cast<uint32_t>(x >> 32) >> 3 == tag >> 3) break;
+                throw DeviceError{BSIM_E_DEVICE, "refinement did not report its stop test"};
+            }
+        }
+        seen = kk;
+        const uint32_t flags = static_cast<uint32_t>(x >> 32);
+        if (flags & kReportError)
+            throw DeviceError{BSIM_E_DEVICE, "a hub hash bucket could not be split to fit its table"};
+        if (!rb.bc.gid && kk >= lag) lr.blocks_per_iter.push_back(static_cast<uint32_t>(x));
+        if (flags & kReportDone) {
+            done = true;
+            lr.k_done = static_cast<uint32_t>(kk - lag);
+            lr.fixpoint = flags & kReportFixpoint ? 1u : 0u;
+        }
+        return true;
+    };
+    std::vector<hipEvent_t> timers;  // (start, after hashes, after hubs, after the split) per timed launch
     std::vector<uint32_t> timed_k;   // the launches timed
-    std::vector<uint8_t> timed_split;  // ... and whether each ran as a split launch
     struct TimerGuard {
         std::vector<hipEvent_t>& t;
         ~TimerGuard() {
             for (hipEvent_t e : t) (void)hipEventDestroy(e);
         }
     } timer_guard{timers};
-    // Queue refinement launch kk: fused, or as its split half then its hash
-    // half.  ends_run, if given, runs between the halves and says whether the
-    // split half ended the run; the hash half then only records the stop.
-    auto issue = [&](uint32_t kk, bool split_first, const std::function<bool()>& ends_run) {
-        if (sink && !sink->levels.empty()) {
+    auto issue = [&](uint32_t kk) {
+        if (all) {
             // keep every level: iteration kk reads levels[kk-1], writes levels[kk]
             const uint32_t top = static_cast<uint32_t>(sink->levels.size()) - 1;
             rb.h[(kk - 1) & 1] = sink->levels[std::min(kk - 1, top)];
             rb.h[kk & 1] = sink->levels[std::min(kk, top)];
         }
-        hipEvent_t et[3] = {nullptr, nullptr, nullptr};
+        if (rb.bc.gid && kk + 1ull > rb.bc.hist_cap) {
+            // launch kk writes level kk of the per-graph history: grow it
+            // while no launch is in flight
+            hip_check(hipStreamSynchronize(s), "history sync");
+            const uint64_t cap = std::max<uint64_t>(2ull * rb.bc.hist_cap, kk + 1ull);
+            const size_t G = rb.bc.n_graphs;
+            uint32_t* nh = arena.alloc<uint32_t>(cap * G);
+            hip_check(hipMemsetAsync(nh, 0, cap * G * 4, s), "history clear");
+            hip_check(hipMemcpyAsync(nh, rb.bc.hist, static_cast<size_t>(rb.bc.hist_cap) * G * 4,
+                                     hipMemcpyDeviceToDevice, s), "history copy");
+            rb.bc.hist = nh;
+            rb.bc.hist_cap = static_cast<uint32_t>(cap);
+        }
+        if (rb.bc.gid) launch_graph_stop(rb, kk, lag, p.k_max, stop, s);
+        const bool hashes = kk <= p.k_max;
+        if (large || !hashes) {
+            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report, true, s);
+            if (!hashes) return;
+            read_report(kk, true);
+            if (done) return;
+        }
+        hipEvent_t et[4] = {nullptr, nullptr, nullptr, nullptr};
         const bool timed = use_timers && ctx->time_launches && kk % ctx->time_launches == 0;
+        auto mark = [&](int i) {
+            if (timed) hip_check(hipEventRecord(et[i], s), "event");
+        };
         if (timed) {
             timed_k.push_back(kk);
-            timed_split.push_back(split_first ? 1 : 0);
             for (hipEvent_t& e : et) {
                 hip_check(hipEventCreate(&e), "event");
                 timers.push_back(e);
             }
-            hip_check(hipEventRecord(et[0], s), "event");
         }
-        const bool all = sink && !sink->levels.empty();
-        if (rb.bc.gid) launch_graph_stop(rb, kk, p.k_max, stop, s);
-        bool stop_only = false;
-        if (split_first) {
-            launch_iteration(g, rb, kk, p.k_max, stop, all, s, kPhaseSplit);
-            stop_only = ends_run && ends_run();
-            launch_iteration(g, rb, kk, p.k_max, stop, all, s, kPhaseHash, stop_only);
-        } else {
-            launch_iteration(g, rb, kk, p.k_max, stop, all, s);
-        }
+        mark(0);
+        launch_iteration(g, rb, kk, lag, p.k_max, stop, all, large ? nullptr : report, false, s);
+        mark(1);
+        launch_hubs(g, rb, kk, s);
+        mark(2);
         if (rep_prev && kk == p.k_max && g.n) {
-            // launch k splits level k-1 and nothing after it in the launch
-            // changes the classes: rep now names the (k_max-1)-classes, or
-            // the final ones of a run that stopped earlier at a fixpoint
+            // the (k_max-1)-classes, or the final ones of a run that stopped
+            // earlier at a fixpoint
             hip_check(hipMemcpyAsync(rep_prev, rb.rep, static_cast<size_t>(g.n) * 4, hipMemcpyDeviceToDevice, s),
                       "previous classes");
             prev_taken = true;
         }
-        if (timed) hip_check(hipEventRecord(et[1], s), "event");
-        if (kk <= p.k_max && !stop_only) launch_hubs(g, rb, kk, s);
-        if (timed) hip_check(hipEventRecord(et[2], s), "event");
+        launch_split(g, rb, kk, s);
+        mark(3);
         lr.launches++;
-        if (split_first) lr.split_launches++;
+        if (lag == 1) lr.split_launches++;
     };
-    // One launch per stop check (launches of milliseconds, or chunk_max 1):
-    // the host waits for every launch anyway, so it reads the founded count
-    // of the level the launch split.  A level that founds few classes is
-    // often the last to change; the next launch then runs its split half
-    // first and hashes only if the run goes on, instead of hashing a level
-    // that the fixpoint test discards (at most kMaxSplitLaunches per run).
-    constexpr uint32_t kMaxSplitLaunches = 8;
-    const bool one_by_one = !rb.bc.gid && stop && ctx->tail_split_ppm && (chunk_cap == 1 || ctx->chunk_max == 1);
     try {
-        if (one_by_one) {
-            bool split_first = false;
-            for (uint64_t kq = 1; kq <= k_last && !done; kq++) {
-                const uint32_t kk = static_cast<uint32_t>(kq);
-                // the stop test of the hash half (level kk-1) from the split
-                // half's founded count: a fixpoint or the level cap
-                bool predicted = false;
-                const std::function<bool()> ends_run = [&]() {
-                    hip_check(hipMemcpyAsync(ctx->count_host, rb.lcnt + ((kk - 1) & (kStripeRing - 1)) * kStripes,
-                                             kStripes * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "count copy");
-                    hip_check(hipStreamSynchronize(s), "split wait");
-                    uint64_t c = 0;
-                    for (int i = 0; i < kStripes; i++) c += ctx->count_host[i];
-                    const uint32_t lv = kk - 1;
-                    predicted = (lv >= 1 && c == 0) || lv >= p.k_max;
-                    return predicted;
-                };
-                issue(kk, split_first, ends_run);
-                hip_check(hipMemcpyAsync(&ctx->status_host[0], rb.status, sizeof(RunStatus), hipMemcpyDeviceToHost,
-                                         s), "status copy");
-                // launch kk completed the split of level kk-1 (k_init: level 0)
-                hip_check(hipMemcpyAsync(ctx->count_host, rb.lcnt + ((kk - 1) & (kStripeRing - 1)) * kStripes,
-                                         kStripes * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "count copy");
-                hip_check(hipStreamSynchronize(s), "status wait");
-                done = ctx->status_host[0].done != 0;
-                if (predicted && !done)
-                    throw DeviceError{BSIM_E_DEVICE, "internal: a stop-only launch found the run going on"};
-                uint64_t founded = 0;
-                for (int i = 0; i < kStripes; i++) founded += ctx->count_host[i];
-                split_first = lr.split_launches < kMaxSplitLaunches &&
-                              founded * 1000000ull <= static_cast<uint64_t>(ctx->tail_split_ppm) * g.n;
-            }
-            if (!done) throw DeviceError{BSIM_E_DEVICE, "refinement did not reach its stop test"};
-        }
-        while (!done) {
-            if (k <= k_last) {
-                const uint32_t c = static_cast<uint32_t>(std::min<uint64_t>(chunk, k_last - k + 1));
-                if (rb.bc.gid && k + c > rb.bc.hist_cap) {
-                    // launch kk writes level kk-1 of the per-graph history: grow it
-                    // while no launch is in flight
-                    hip_check(hipStreamSynchronize(s), "history sync");
-                    const uint64_t cap = std::max<uint64_t>(2ull * rb.bc.hist_cap, k + c + 1);
-                    const size_t G = rb.bc.n_graphs;
-                    uint32_t* nh = arena.alloc<uint32_t>(cap * G);
-                    hip_check(hipMemsetAsync(nh, 0, cap * G * 4, s), "history clear");
-                    hip_check(hipMemcpyAsync(nh, rb.bc.hist, static_cast<size_t>(rb.bc.hist_cap) * G * 4,
-                                             hipMemcpyDeviceToDevice, s), "history copy");
-                    rb.bc.hist = nh;
-                    rb.bc.hist_cap = static_cast<uint32_t>(cap);
-                }
-                for (uint32_t i = 0; i < c; i++, k++) issue(static_cast<uint32_t>(k), false, nullptr);
-                const int slot = pending < 0 ? 0 : (pending ^ 1);
-                hip_check(hipMemcpyAsync(&ctx->status_host[slot], rb.status, sizeof(RunStatus),
-                                         hipMemcpyDeviceToHost, s), "status copy");
-                hip_check(hipEventRecord(ev[slot], s), "status event");
-                if (pending >= 0) {
-                    hip_check(hipEventSynchronize(ev[pending]), "status wait");
-                    done = ctx->status_host[pending].done != 0;
-                }
-                pending = slot;
-                chunk = std::min<uint32_t>(chunk * 2, chunk_cap);
-            } else {
-                hip_check(hipEventSynchronize(ev[pending]), "status wait");
-                done = ctx->status_host[pending].done != 0;
-                if (!done) throw DeviceError{BSIM_E_DEVICE, "refinement did not reach its stop test"};
+        for (uint64_t kk = 1; kk <= k_last && !done; kk++) {
+            issue(static_cast<uint32_t>(kk));
+            while (!done && seen < kk && read_report(seen + 1, seen + ahead <= kk)) {
             }
         }
+        while (!done && seen < k_last) read_report(seen + 1, true);
+        if (!done) throw DeviceError{BSIM_E_DEVICE, "refinement did not reach its stop test"};
     } catch (...) {
         (void)hipStreamSynchronize(s);
         throw;
     }
-    hip_check(hipStreamSynchronize(s), "loop sync");
-    RunStatus st;
-    hip_check(hipMemcpy(&st, rb.status, sizeof(RunStatus), hipMemcpyDeviceToHost), "final status");
-    // launch j (1-based) hashed iff j <= k_done + 1: launch k_done + 2 finds
-    // the stop at level k_done and returns at once, as do all later ones; a
-    // split launch k_done + 1 finds it in its hash half and hashes nothing
-    for (size_t i = 0; i + 2 < timers.size(); i += 3) {
-        if (timed_k[i / 3] > st.k_done + 1) break;
-        if (timed_k[i / 3] == st.k_done + 1 && timed_split[i / 3]) break;
-        float a = 0.f, b = 0.f;
-        hip_check(hipEventElapsedTime(&a, timers[i], timers[i + 1]), "launch timer");
-        hip_check(hipEventElapsedTime(&b, timers[i + 1], timers[i + 2]), "launch timer");
-        lr.ms_kernels += a;
-        lr.ms_hub_kernels += b;
+    // launches past the last hashed level return at once
+    if (!timers.empty()) hip_check(hipStreamSynchronize(s), "launch timers");
+    for (size_t i = 0; 4 * i + 3 < timers.size(); i++) {
+        if (timed_k[i] > lr.k_done + lag - 1) break;
+        float t[3] = {0.f, 0.f, 0.f};
+        for (int j = 0; j < 3; j++)
+            hip_check(hipEventElapsedTime(&t[j], timers[4 * i + j], timers[4 * i + j + 1]), "launch timer");
+        lr.ms_kernels += t[0] + t[2];
+        lr.ms_hub_kernels += t[1];
         lr.n_timed++;
     }
-    if (st.error & kErrHubSplit)
-        throw DeviceError{BSIM_E_DEVICE, "a hub hash bucket could not be split to fit its table"};
     // k_max = 0, or a run whose stop was seen before launch k_max: the final
     // classes (level 0, or a fixpoint's)
     if (rep_prev && !prev_taken && g.n)
         hip_check(hipMemcpyAsync(rep_prev, rb.rep, static_cast<size_t>(g.n) * 4, hipMemcpyDeviceToDevice, s),
                   "previous classes");
-    lr.k_done = st.k_done;
-    lr.fixpoint = st.fixpoint;
     if (rb.bc.gid) {  // batched: counts and final buffers are per graph
         lr.h_final = nullptr;
         return lr;
     }
-    lr.blocks_per_iter.resize(static_cast<size_t>(lr.k_done) + 1);
-    hip_check(hipMemcpy(lr.blocks_per_iter.data(), rb.totals, (lr.k_done + 1) * 4, hipMemcpyDeviceToHost),
-              "block counts");
     if (sink && !sink->levels.empty())
         lr.h_final = sink->levels[std::min<size_t>(lr.k_done, sink->levels.size() - 1)];
     else
@@ -394,7 +359,7 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     const Staged& gr = view ? dv.h : g;
     const Staged& gf = view ? dv.f : g;
     RunBuffers rb;
-    alloc_run_buffers(gr, p.k_max, (p.flags & BSIM_STOP_AT_FIXPOINT) != 0, rb, arena, s);
+    alloc_run_buffers(gr, rb, arena, s);
     hip_check(hipEventRecord(ev[1], s), "event");
     const bool prev_edges = (p.flags & BSIM_PREV_LEVEL_EDGES) != 0;
     uint32_t* rep_prev = prev_edges ? arena.alloc<uint32_t>(gr.n + 1) : nullptr;
