@@ -19,13 +19,6 @@ namespace bsim {
 
 constexpr uint32_t kAppendBuf = 512;  // entries of a wave's LDS buffer
 
-// Memory order among the lanes of one wave (LDS written by some lanes, read
-// by others).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The list position of every taking thread's entry, reserved with one
 // atomic per block.  Every thread of the block calls it (it synchronizes

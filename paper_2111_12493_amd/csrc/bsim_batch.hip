@@ -266,14 +266,13 @@ void build_union(const bsim_graph* graphs, uint32_t G, Staged& u, uint32_t*& gid
 }
 
 // Capacities of a small-graph workgroup on this device: at most 1,024
-// vertices and 1,535 edges (below the hub degree, so a small graph has no
-// hub) when the device gives a workgroup the LDS for them, else half; and
+// vertices and kSmallMaxEdges edges when the device gives a workgroup the LDS for them, else half; and
 // the persistent grid (the workgroups that fit the CUs at once).
 void small_capacity(int device, uint32_t* max_v, uint32_t* max_e, uint32_t* grid) {
     int lds = 0, cus = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) lds = 65536;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 64;
-    uint32_t v = 1024, e = kHubMinDegree - 1;
+    uint32_t v = 1024, e = kSmallMaxEdges;
     while (v > 64 && small_graph_lds_bytes(v, e, nullptr) + 1024 > static_cast<uint64_t>(lds)) {
         v /= 2;
         e /= 2;

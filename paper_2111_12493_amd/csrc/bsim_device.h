@@ -142,52 +142,79 @@ __device__ __forceinline__ uint32_t lds_insert_bounded(uint64_t* tab, uint32_t s
     return 2u;
 }
 
-// Tile layout in LDS: s_off[i] = first edge of local vertex i relative to
-// the tile's first edge (i = 0..nv), s_seg[j] = local vertex owning edge j.
-// Requires nv <= kTileMaxVerts and ne = s_off[nv] < kTileMaxEdges.
-// s_seg must be 8-byte aligned.  Ends with a barrier.
-__device__ inline void tile_segments(uint32_t nv, const uint32_t* s_off, uint8_t* s_seg,
-                                     uint32_t* s_red) {
-    constexpr uint32_t kWords = kTileMaxEdges / 8;  // owner-map words, one per thread
-    const uint32_t tid = threadIdx.x;
-    uint64_t* seg64 = reinterpret_cast<uint64_t*>(s_seg);
-    // zero the owner map, then mark each non-empty segment start
-    if (tid < kWords) seg64[tid] = 0;
-    __syncthreads();
-    for (uint32_t i = tid; i < nv; i += kBlock)
-        if (s_off[i + 1] > s_off[i]) s_seg[s_off[i]] = static_cast<uint8_t>(i);
-    __syncthreads();
-    // inclusive max-scan over the owner map: thread t owns bytes 8t..8t+7
-    // (threads past the map scan zeros, which leave a max unchanged)
-    const uint64_t word = tid < kWords ? seg64[tid] : 0;
-    uint32_t run = 0;
-#pragma unroll
-    for (int r = 0; r < 8; r++) run = max(run, static_cast<uint32_t>((word >> (8 * r)) & 0xFF));
-    uint32_t incl = run;
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), d, 64));
-        if (lane >= static_cast<uint32_t>(d)) incl = max(incl, y);
-    }
-    uint32_t excl = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), 1, 64));
-    if (lane == 0) excl = 0;
-    if (lane == 63) s_red[tid >> 6] = incl;
-    __syncthreads();
-    for (uint32_t wv = 0; wv < (tid >> 6); wv++) excl = max(excl, s_red[wv]);
-    uint64_t out = 0;
-    uint32_t cur = excl;
-#pragma unroll
-    for (int r = 0; r < 8; r++) {
-        cur = max(cur, static_cast<uint32_t>((word >> (8 * r)) & 0xFF));
-        out |= static_cast<uint64_t>(cur) << (8 * r);
-    }
-    if (tid < kWords) seg64[tid] = out;
-    __syncthreads();
+// Order the LDS accesses of one wave: its LDS operations execute in program
+// order, so only the compiler has to be held.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-static_assert(kTileMaxEdges % 8 == 0 && kTileMaxEdges / 8 <= kBlock,
-              "tile_segments keeps one 8-byte owner-map word per thread");
-static_assert(kTileMaxVerts <= 256, "owner map stores vertex indices in one byte");
+// x of the lane that the DPP control names, 0 where there is none or the
+// lane's row is not in kRows.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_or_0(uint32_t x) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), kCtrl, kRows, 0xf, false));
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_or_0(uint64_t x) {
+    return (static_cast<uint64_t>(dpp_or_0<kCtrl, kRows>(static_cast<uint32_t>(x >> 32))) << 32) |
+           dpp_or_0<kCtrl, kRows>(static_cast<uint32_t>(x));
+}
+
+// Inclusive sum over the 64 lanes in registers: four shifts within the rows
+// of 16 lanes, then the totals of row 0 and 2 to the next row, then that of
+// the lower half to the upper.
+template <typename T>
+__device__ __forceinline__ T wave_incl_sum(T x) {
+    x += dpp_or_0<0x111, 0xf>(x);
+    x += dpp_or_0<0x112, 0xf>(x);
+    x += dpp_or_0<0x114, 0xf>(x);
+    x += dpp_or_0<0x118, 0xf>(x);
+    x += dpp_or_0<0x142, 0xa>(x);
+    x += dpp_or_0<0x143, 0xc>(x);
+    return x;
+}
+
+// Which vertex of a tile owns each of a lane's kLaneEdges consecutive edges
+// (lane l holds local edges [l kLaneEdges, (l + 1) kLaneEdges)).  Lane i < nv
+// passes the first local edge of vertex i; every vertex of a tile has edges.
+// `marks` is kTileMaxEdges bytes of the wave's LDS, 8-byte aligned, free
+// again on return.
+struct LaneOwners {
+    uint64_t starts;   // byte q: 1 if edge q of this lane begins a vertex
+    uint32_t before;   // vertices that begin in earlier lanes
+    // local vertex of edge q (q known at compile time)
+    __device__ __forceinline__ uint32_t of(int q) const {
+        const uint64_t upto = q == 7 ? starts : starts & ((1ull << (8 * (q + 1))) - 1);
+        return before + static_cast<uint32_t>(__popcll(upto)) - 1;
+    }
+    __device__ __forceinline__ bool begins(int q) const { return (starts >> (8 * q)) & 1; }
+};
+__device__ __forceinline__ LaneOwners lane_owners(uint8_t* marks, bool mine, uint32_t off) {
+    static_assert(kLaneEdges == 8, "one 8-byte word of marks per lane");
+    uint64_t* word = reinterpret_cast<uint64_t*>(marks) + lane_id();
+    *word = 0;
+    wave_sync();
+    if (mine) marks[off] = 1;
+    wave_sync();
+    LaneOwners o;
+    o.starts = *word;
+    wave_sync();
+    const uint32_t c = static_cast<uint32_t>(__popcll(o.starts));
+    o.before = wave_incl_sum(c) - c;
+    return o;
+}
+
+// The same as a byte per local edge in LDS (owner[j], kTileMaxEdges bytes),
+// for kernels that walk a tile's edges lane by lane.
+__device__ __forceinline__ void tile_owners(uint8_t* owner, bool mine, uint32_t off) {
+    const LaneOwners o = lane_owners(owner, mine, off);
+    uint64_t word = 0;
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) word |= static_cast<uint64_t>(o.of(q) & 0xFF) << (8 * q);
+    reinterpret_cast<uint64_t*>(owner)[lane_id()] = word;
+    wave_sync();
+}
 
 }  // namespace bsim

@@ -86,42 +86,41 @@ __global__ void __launch_bounds__(kBlock) k_fin_ids(const uint8_t* __restrict__ 
 // ------------------------------------------------------------ edge keys
 
 struct KeyShared {
-    uint32_t off[kTileMaxVerts + 1];
-    uint32_t red[kBlock / 64];
-    alignas(8) uint8_t seg[kTileMaxEdges];
+    uint64_t src[kTileMaxVerts];        // block of the tile's vertices, in place
+    alignas(8) uint8_t owner[kTileMaxEdges];
 };
 
+// One wave per tile; solo vertices and hubs by a workgroup each.
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_edge_keys(
     const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt,
     const LabT* __restrict__ lab, const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst,
-    const uint4* __restrict__ tiles, const uint32_t* __restrict__ act, uint32_t n_tiles,
-    const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int lb, int bb,
-    uint64_t* __restrict__ keys) {
-    __shared__ KeyShared S;
+    const uint4* __restrict__ tiles, const uint32_t* __restrict__ act, const uint32_t* __restrict__ act_off,
+    uint32_t n_tiles, const uint32_t* __restrict__ solo_v, uint32_t n_solo, const uint32_t* __restrict__ hub_v,
+    uint32_t n_hubs, int lb, int bb, uint64_t* __restrict__ keys) {
+    __shared__ KeyShared sh[kWaves];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < n_hubs) {
-        const uint32_t v = hub_v[blockIdx.x];
+    if (blockIdx.x < n_hubs + n_solo) {
+        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
         const uint64_t src = static_cast<uint64_t>(bid[v]) << (lb + bb);
         for (uint32_t e = row_off[v] + tid; e < row_off[v + 1]; e += kBlock)
             keys[e] = src | (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
         return;
     }
-    const uint32_t tile = blockIdx.x - n_hubs;
+    const uint32_t lane = lane_id(), tile = (blockIdx.x - n_hubs - n_solo) * kWaves + (tid >> 6);
     if (tile >= n_tiles) return;
+    KeyShared& S = sh[tid >> 6];
     const uint4 td = tiles[tile];
-    const uint32_t i0 = td.x, nv = td.y - i0;
-    const uint32_t ebase = td.z;
-    const uint32_t ne = td.w - ebase;
-    for (uint32_t i = tid; i < nv; i += kBlock) S.off[i] = row_off[act[i0 + i]] - ebase;
-    if (tid == 0) S.off[nv] = ne;
-    __syncthreads();
-    tile_segments(nv, S.off, S.seg, S.red);
-    for (uint32_t j = tid; j < ne; j += kBlock) {
-        const uint32_t e = ebase + j;
-        const uint32_t v = act[i0 + S.seg[j]];
-        keys[e] = (static_cast<uint64_t>(bid[v]) << (lb + bb)) |
-                  (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
+    const uint32_t nv = td.y - td.x, ne = td.w - td.z;
+    uint32_t off = 0;
+    if (lane < nv) {
+        S.src[lane] = static_cast<uint64_t>(bid[act[td.x + lane]]) << (lb + bb);
+        off = act_off[td.x + lane] - td.z;
+    }
+    tile_owners(S.owner, lane < nv, off);
+    for (uint32_t j = lane; j < ne; j += 64) {
+        const uint32_t e = td.z + j;
+        keys[e] = S.src[S.owner[j]] | (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
     }
 }
 
@@ -377,7 +376,7 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
     const uint32_t m = static_cast<uint32_t>(g.m);
     uint64_t* ka = arena.alloc<uint64_t>(m);
     uint64_t* kb = arena.alloc<uint64_t>(m);
-    const uint32_t grid = std::max<uint32_t>(g.n_hubs + g.n_tiles, 1);
+    const uint32_t grid = std::max<uint32_t>(g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves), 1);
     if (g.src) {
         if (g.label_bytes == 2)
             k_edge_keys_coo<uint16_t><<<ceil_div(m, kBlock), kBlock, 0, s>>>(
@@ -388,15 +387,13 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
     } else if (g.label_bytes == 2)
         k_edge_keys<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
                                                       static_cast<const uint16_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tiles, g.act,
-                                                      g.n_tiles, g.hub_v, g.n_hubs,
-                                                      lb, bb, ka);
+                                                      g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo,
+                                                      g.hub_v, g.n_hubs, lb, bb, ka);
     else
         k_edge_keys<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
                                                       static_cast<const uint32_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tiles, g.act,
-                                                      g.n_tiles, g.hub_v, g.n_hubs,
-                                                      lb, bb, ka);
+                                                      g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo,
+                                                      g.hub_v, g.n_hubs, lb, bb, ka);
     hip_check(hipGetLastError(), "edge key launch");
     uint64_t* sorted = radix_sort(ka, kb, m, 2 * bb + lb, arena, s);
     uint32_t* flag = arena.alloc<uint32_t>(m);

@@ -34,12 +34,14 @@ constexpr uint64_t kCE = mix64(4);  // per-pair domain
 //
 // The refinement kernel works on "tiles": runs of consecutive vertices whose
 // out-edges are contiguous in the CSR.  A tile holds at most kTileMaxVerts
-// vertices and fewer than kTileMaxEdges edges, so its per-vertex
-// de-duplication tables (two slots per edge) fit one block's LDS.  Vertices
-// with kTileMaxEdges or more out-edges ("hubs") are cut into chunks of
-// kTileMaxEdges edges whose blocks write their mixed pair keys to a per-hub
-// scratch area; a second launch de-duplicates each hub's keys in LDS, split
-// by the top key bits into buckets that fit a large LDS table.
+// vertices (one lane each) and kTileMaxEdges edges, and one wave works on it
+// alone: its steps need no workgroup barrier, and the waves of a workgroup
+// drift apart, so one's loads cover another's LDS work.  A vertex with more
+// out-edges is "solo" up to kSoloMaxEdges, a workgroup's work, and a "hub"
+// beyond: cut into chunks of kChunkEdges edges whose blocks write their mixed
+// pair keys to a per-hub scratch area; a second launch de-duplicates each
+// hub's keys in LDS, split by the top key bits into buckets that fit a large
+// LDS table.
 //
 // Classes.  Every alive vertex v keeps rep[v], a member of its current
 // class.  The k-class of v is (its (k-1)-class, h^k(v)) (the bisimulation
@@ -50,21 +52,18 @@ constexpr uint64_t kCE = mix64(4);  // per-pair domain
 // late iteration of a long chain run inserts a handful of keys.
 
 constexpr int kBlock = 256;              // threads per block (4 wave64s)
-// The refinement kernel is latency bound: its speed follows the number of
-// blocks resident per CU, which its LDS sets (160 KiB per CU).  Tiles of
-// fewer than 1,536 edges keep a block under 32 KiB, five blocks per CU.
-constexpr int kTileMaxEdges = 1536;      // a tile holds fewer edges than this
-constexpr int kTileMaxVerts = 256;
-constexpr int kEdgesPerThread = kTileMaxEdges / kBlock;  // 6
-constexpr int kTableSlots = 2 * kTileMaxEdges;           // 3072 x 8 B = 24 KiB
-constexpr uint32_t kHubMinDegree = kTileMaxEdges;  // a hub would not fit an empty tile
-// A hub of at most kSoloMaxEdges edges is a "solo" block of the refinement
-// launch: one block gathers all its edges and de-duplicates them in one
-// table over the block's tile arrays (kSoloSlots, a prime, with double
-// hashing, load <= 0.9); larger hubs take the chunk / bucket path.
-constexpr uint32_t kSoloMaxEdges = 2 * kTileMaxEdges;   // 3072
-constexpr uint32_t kSoloSlots = 3449;                   // prime, 27,592 B
-constexpr int kSoloPerThread = (kSoloMaxEdges + kBlock - 1) / kBlock;  // 12
+// A wave's LDS is an 8-byte key and two 2-byte table slots per edge, 6 KiB at
+// 512 edges: 24 KiB a workgroup, six of them (24 waves) per CU.
+constexpr int kLaneEdges = 8;                         // edges per lane of a tile
+constexpr int kTileMaxEdges = 64 * kLaneEdges;        // 512
+constexpr int kTileMaxVerts = 64;
+constexpr int kWaves = kBlock / 64;                   // tiles per workgroup
+constexpr uint32_t kSoloMaxEdges = kBlock * kLaneEdges;  // 2048: the workgroup's keys fit the same LDS
+// Edges of a hub chunk block (3,072 of them: k_hub 2 % faster, k_iterate 5 to
+// 8 % slower).
+constexpr int kChunkEdges = 1536;
+constexpr int kChunkPerThread = kChunkEdges / kBlock;
+constexpr uint32_t kSmallMaxEdges = 1535;             // edges of a graph that fits the small-graph launch
 // Vertices without out-edges: h^k = M(t ^ M(C_S)) for every k >= 1, so they
 // need no tile.  Light blocks of kIsoPerBlock of them run their split test
 // and write their hash while it can still change the buffers (levels 1 and 2
@@ -74,15 +73,24 @@ constexpr uint32_t kIsoPerBlock = kBlock * kIsoPerThread;
 constexpr int kHubBlock = 512;           // threads per hub-bucket block
 constexpr int kMaxHubLogB = 8;           // at most 256 hash buckets per hub
 constexpr uint32_t kHubTableDefault = 4096;  // LDS slots per hub-bucket block (32 KiB)
+constexpr uint32_t kHubTableMax = 16384;     // at most
+// Keys of a bucket that fit the LDS of a table of `slots` 8-byte slots
+// together with `slots` 2-byte ones.  Three keys to four slots take a round
+// or two more than one to two, but twice the buckets double the runs that
+// every chunk block writes: on 2^27 vertices / 2^30 edges k_hub took 2.93 ms
+// per level that way instead of 2.30, and k_iterate 0.6 ms more.
+__host__ __device__ constexpr uint32_t hub_rounds_cap(uint32_t slots) { return slots / 4 * 3; }
+constexpr uint32_t kHubRoundsMax = hub_rounds_cap(kHubTableMax) / kHubBlock;  // keys per thread
 constexpr int kHubOffStride = (1 << kMaxHubLogB) + 1;  // bucket offsets per hub chunk
 // Striped per-level claim counters, each on a cache line of its own: atomics
 // on one line are served one after the other, and every wave that founds
-// classes adds to a stripe.  With the 64 stripes packed in two lines level 0
-// of 2^27 vertices took 10.7 ms, on lines of their own 2.4 ms.
-constexpr int kStripes = 64;
+// classes adds to a stripe.  With 64 stripes packed in two lines level 0 of
+// 2^27 vertices took 10.7 ms, on lines of their own 2.4 ms.  Every wave of a
+// refinement launch reads them all, so there are no more than needed.
+constexpr int kStripes = 16;
 constexpr int kStripePitch = 32;         // words between counters
 constexpr int kStripeRing = 4;
-constexpr int kListPerStripe = 4096;     // claimed split-table slots remembered per stripe
+constexpr int kListPerStripe = 16384;    // claimed split-table slots remembered per stripe
 constexpr uint32_t kNoRep = 0xFFFFFFFEu; // virtual class of every vertex before level 0
 
 // Device-side status of a refinement run.
@@ -161,7 +169,9 @@ struct IterArgs {
     uint64_t* h_next;       // h^k
     const uint8_t* alive;   // nullable
     const uint4* tiles;         // positions [x, y) of the tile-vertex list, edges [z, w)
-    const uint32_t* act;        // tile vertices (out-degree 1..kHubMinDegree-1), ascending
+    const uint32_t* act;        // tile vertices (out-degree 1..kTileMaxEdges), ascending
+    const uint32_t* act_off;    // their first edges
+    uint64_t m;
     const uint32_t* iso;        // vertices without out-edges, ascending
     const uint32_t* hc_hub;     // hub chunk block -> hub index
     const uint32_t* hc_e0;      // hub chunk block -> first edge
@@ -174,7 +184,7 @@ struct IterArgs {
     uint32_t* totals;       // totals[j mod kStripeRing] = n_j
     RunStatus* status;
     uint64_t* report;       // pinned host words (nullable)
-    const uint32_t* solo_v;     // solo hub vertices
+    const uint32_t* solo_v;     // vertices of kTileMaxEdges + 1..kSoloMaxEdges out-edges
     uint32_t n_tiles;
     uint32_t n_hub_chunks;
     uint32_t n_solo;
@@ -193,9 +203,10 @@ struct IterArgs {
 struct SplitArgs {
     const uint64_t* h;      // h^k
     uint32_t* rep;
-    const uint32_t* act;    // tile vertices, then hubs: the vertices tested from level 2 on
+    const uint32_t* act;    // tile, solo and hub vertices: those tested from level 2 on
+    const uint32_t* solo_v;
     const uint32_t* hub_v;
-    uint32_t n_act;
+    uint32_t n_act, n_solo;
     uint32_t count;         // vertices tested at this level
     SplitTable test_tab;    // receives the split-offs
     SplitTable clr_tab;     // filled at level k-1, cleared here
@@ -215,7 +226,6 @@ struct HubArgs {
     const uint32_t* hub_nchunks;
     const uint32_t* hc_e0;
     const uint32_t* hub_v;
-    const uint32_t* hub_deg;
     const uint32_t* hub_logb;
     const uint32_t* hb_hub;
     const uint32_t* hb_bucket;
@@ -375,15 +385,16 @@ struct Staged {
     uint32_t n_tiles = 0;
     uint4* tiles = nullptr;          // tile: positions [x, y) of `act`, edges [z, w)
     uint32_t n_act = 0;
-    uint32_t* act = nullptr;         // vertices of out-degree 1..kHubMinDegree-1
+    uint32_t* act = nullptr;         // vertices of out-degree 1..kTileMaxEdges
+    uint32_t* act_off = nullptr;     // their first edges
     uint32_t n_iso = 0;
     uint32_t* iso = nullptr;         // vertices without out-edges (dead ones included)
-    uint32_t n_hubs = 0;             // all hubs: n_hubs - n_solo chunked ones, then the solo ones
     uint32_t n_solo = 0;
+    uint32_t* solo_v = nullptr;      // vertices of kTileMaxEdges + 1..kSoloMaxEdges out-edges
+    uint32_t n_hubs = 0;
     uint32_t n_hub_chunks = 0;
     uint32_t n_hub_blocks = 0;       // hub-bucket blocks of the second launch
-    uint32_t* hub_v = nullptr;       // by degree, descending (solo hubs last)
-    uint32_t* hub_deg = nullptr;
+    uint32_t* hub_v = nullptr;       // by degree, descending
     uint32_t* hub_logb = nullptr;
     uint32_t* hub_chunk0 = nullptr;   // first chunk block of the hub
     uint32_t* hub_nchunks = nullptr;
@@ -394,15 +405,13 @@ struct Staged {
     uint32_t* hb_hub = nullptr;
     uint32_t* hb_bucket = nullptr;
     uint32_t hub_table_slots = 0;
-    std::vector<uint32_t> host_hub_v;
-    std::vector<uint32_t> host_hub_deg;
 };
 
 // What staging copies back, in pinned memory: the validation status, the
-// counts (hubs, tile vertices, vertices without out-edges, tiles) and the
-// first hubs as (vertex, degree, first edge).  The ids of 4,096 hubs are
-// 48 KiB, a copy that costs hardly more than the counts alone; a graph needs
-// 6.3 million edges to have more.
+// counts (hubs, tile vertices, solo vertices, tiles) and the first hubs as
+// (vertex, degree, first edge).  4,096 hubs are 48 KiB, a copy that costs
+// hardly more than the counts alone; a graph needs 8.4 million edges to have
+// more.
 constexpr uint32_t kStageHubs = 4096;
 struct StageHost {
     RunStatus st;
@@ -466,7 +475,7 @@ void launch_hubs(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t 
 struct HashScratch {
     uint64_t* hub_keys = nullptr;
     uint32_t* hub_boff = nullptr;
-    uint64_t* hub_acc = nullptr;   // zero, kept zero by the launches
+    uint64_t* hub_acc = nullptr;   // (sum, finished buckets) per hub: zero, kept zero by the launches
     RunStatus* status = nullptr;   // zero (never done)
 };
 void alloc_hash_scratch(const Staged& g, HashScratch& hs, Arena& arena, hipStream_t s);

@@ -5,15 +5,15 @@
 // Level k >= 1 is then
 //   k_iterate  stop test of level k-1 (every block takes the same decision
 //              from the level's founded counts; block 0 records it), then
-//              h^k: a tile block gathers h^{k-1} of its out-edge targets
+//              h^k: a tile's wave gathers h^{k-1} of its out-edge targets
 //              (SignalMessages), de-duplicates the (label, hash) pair keys of
-//              each vertex in a per-vertex open-addressing region of an LDS
-//              table (MergeMessages' hash table), sums the mixed distinct
-//              keys (the order-independent Hash) and writes h^k; a hub chunk
-//              block writes its mixed keys to the hub's scratch area instead;
-//   k_hub      de-duplicates each hub's scratch keys bucket by bucket in LDS
-//              and adds each bucket's distinct sum to the hub's accumulator;
-//              k_hub_finish turns the sums into h^k;
+//              each vertex in an LDS table (MergeMessages' hash table), sums
+//              the mixed distinct keys (the order-independent Hash) and
+//              writes h^k; a hub chunk block writes its mixed keys to the
+//              hub's scratch area instead;
+//   k_hub      de-duplicates each hub's scratch keys bucket by bucket in LDS,
+//              adds each bucket's distinct sum to the hub's accumulator and
+//              turns a hub's complete sum into h^k;
 //   k_split    the classes of level k: a vertex whose h^k differs from its
 //              representative's joins (or founds) the class (rep, h^k) in the
 //              split table; the number of founded classes is n_k - n_{k-1}.
@@ -220,43 +220,52 @@ __global__ void __launch_bounds__(kBlock) k_init(const uint64_t* __restrict__ t,
 
 // ------------------------------------------------------------ launch k
 
-struct IterShared {
-    uint64_t tab[kTableSlots];
-    uint64_t acc[kTileMaxVerts];
-    uint32_t off[kTileMaxVerts + 1];
-    uint32_t red[kBlock / 64];
-    uint32_t ctl[4];
-    alignas(8) uint8_t seg[kTileMaxEdges];
+// A wave's keys and table slots, a workgroup's of a solo vertex, or a chunk
+// block's bucket counts.
+struct WaveLds {
+    uint64_t f[kTileMaxEdges];
+    uint16_t slot[2 * kTileMaxEdges];
 };
+struct SoloLds {
+    uint64_t f[kSoloMaxEdges];
+    uint16_t slot[2 * kSoloMaxEdges];
+};
+union IterShared {
+    WaveLds wave[kWaves];
+    SoloLds solo;
+    uint32_t hist[(1 << kMaxHubLogB) + 1];
+};
+static_assert(sizeof(SoloLds) == kWaves * sizeof(WaveLds), "a solo vertex fills the workgroup's LDS exactly");
 
-static_assert(offsetof(IterShared, red) >= kSoloSlots * sizeof(uint64_t),
-              "a solo block's table must end before the block's control words");
-static_assert(kTileMaxEdges >= (kBlock / 64) * 8, "a solo block's wave sums live in seg");
-
-__device__ __forceinline__ bool run_hash(const IterArgs& a) { return a.k <= a.k_max; }
-
-// The sticky done flag as this wave sees it (only to skip loads; see tile_block).
-__device__ __forceinline__ bool early_done(const IterArgs& a) {
-    return !a.hash_only && __hip_atomic_load(&a.status->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+// Stop test of level k - lag as every wave takes it; true when the run is
+// done.  Block 0's first wave also keeps the class count, records the final
+// status when the run stops, and reports to the host.
+struct StopInputs {
+    uint32_t done, cnt, tot;
+};
+__device__ __forceinline__ StopInputs stop_inputs(const IterArgs& a) {
+    StopInputs p{0, 0, 0};
+    if (a.hash_only) return p;
+    p.done = __hip_atomic_load(&a.status->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.k >= a.lag && !a.bc.gid) {
+        const uint32_t lv = a.k - a.lag;
+        if (lane_id() < static_cast<uint32_t>(kStripes)) p.cnt = stripe_count(a.lcnt, lv, lane_id());
+        p.tot = lv ? a.totals[(lv - 1) & (kStripeRing - 1)] : 0u;
+    }
+    return p;
 }
-
-// Stop test of level k - lag (wave 0), from the values loaded at block start:
-// S.ctl[0] = 1 when the run is done.  Block 0 also keeps the class count,
-// records the final status when the run stops, and reports to the host.
-// Visible to the block after its next barrier.
-__device__ __forceinline__ void stop_decision(const IterArgs& a, IterShared& S, uint32_t p_done,
-                                              uint32_t p_cnt, uint32_t p_tot) {
-    const uint32_t tid = threadIdx.x, k = a.k;
-    if (tid >= 64) return;
-    uint32_t ex = p_done, fix = 0, nl = 0;
+__device__ __forceinline__ bool stop_decision(const IterArgs& a, const StopInputs& p) {
+    if (a.hash_only) return false;
+    const uint32_t k = a.k;
+    uint32_t ex = p.done, fix = 0, nl = 0;
     // batched runs: the per-graph stop launch before this one sets done
-    if (!ex && k >= a.lag && !a.bc.gid && !a.hash_only) {
+    if (!ex && k >= a.lag && !a.bc.gid) {
         const uint32_t lv = k - a.lag;
-        const uint32_t c = wave_sum_u32(p_cnt);
-        nl = lv == 0 ? c : p_tot + c;
+        const uint32_t c = wave_sum_u32(p.cnt);
+        nl = lv == 0 ? c : p.tot + c;
         fix = (lv >= 1 && c == 0) ? 1u : 0u;
         if ((a.stop && fix) || lv >= a.k_max) ex = 1;
-        if (tid == 0 && blockIdx.x == 0) {
+        if (threadIdx.x == 0 && blockIdx.x == 0) {
             a.totals[lv & (kStripeRing - 1)] = nl;
             if (ex) {
                 a.status->k_done = lv;
@@ -265,176 +274,216 @@ __device__ __forceinline__ void stop_decision(const IterArgs& a, IterShared& S, 
             }
         }
     }
-    if (tid == 0) {
-        S.ctl[0] = ex;
-        if (blockIdx.x == 0 && a.report) {
-            const uint32_t flags = (ex ? kReportDone : 0u) | (fix ? kReportFixpoint : 0u) |
-                                   (a.status->error ? kReportError : 0u);
-            // one word: the host needs no ordering between the parts
-            __hip_atomic_store(&a.report[k & (kReportRing - 1)],
-                               (static_cast<uint64_t>(report_tag(k) | flags) << 32) | nl, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0 && blockIdx.x == 0 && a.report) {
+        const uint32_t flags = (ex ? kReportDone : 0u) | (fix ? kReportFixpoint : 0u) |
+                               (a.status->error ? kReportError : 0u);
+        // one word: the host needs no ordering between the parts
+        __hip_atomic_store(&a.report[k & (kReportRing - 1)],
+                           (static_cast<uint64_t>(report_tag(k) | flags) << 32) | nl, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    return ex != 0;
+}
+
+// kLaneEdges consecutive edges of a lane from edge e on (those at or past m
+// are not read): whole vectors where all of them exist, whatever their
+// alignment.  Targets and labels are read once per launch: non-temporal, so
+// they do not push the gathered hashes out of L2.
+template <typename LabT>
+__device__ __forceinline__ void load_edges(const uint32_t* __restrict__ tgt, const LabT* __restrict__ lab, uint64_t e,
+                                           uint32_t count, uint64_t m, uint32_t (&w)[kLaneEdges],
+                                           uint32_t (&l)[kLaneEdges]) {
+    typedef uint32_t T4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint16_t H8 __attribute__((ext_vector_type(8), aligned(2)));
+    if (count && e + kLaneEdges <= m) {
+#pragma unroll
+        for (int q = 0; q < kLaneEdges; q += 4) {
+            const T4 x = __builtin_nontemporal_load(reinterpret_cast<const T4*>(tgt + e + q));
+#pragma unroll
+            for (int i = 0; i < 4; i++) w[q + i] = x[i];
         }
+        if (sizeof(LabT) == 2) {
+            const H8 x = __builtin_nontemporal_load(reinterpret_cast<const H8*>(lab + e));
+#pragma unroll
+            for (int q = 0; q < kLaneEdges; q++) l[q] = x[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < kLaneEdges; q += 4) {
+                const T4 x = __builtin_nontemporal_load(reinterpret_cast<const T4*>(lab + e + q));
+#pragma unroll
+                for (int i = 0; i < 4; i++) l[q + i] = x[i];
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) {
+        const bool in = static_cast<uint32_t>(q) < count;
+        w[q] = in ? tgt[e + q] : 0u;
+        l[q] = in ? static_cast<uint32_t>(lab[e + q]) : 0u;
     }
 }
 
-// A tile block.  Its latency is a chain of dependent memory round trips, so
-// every load is issued before the first barrier: tile bounds -> offsets,
-// edge targets and labels -> neighbour hashes.  Nothing is written before
-// the stop decision.
-// Returns false when the run is done.
+// Table slot of a key in round r (2^kBits slots): a window of the key's bits
+// that moves with the round (whole windows of one half, then of the other),
+// shifted by the owner, so that equal keys of different vertices of a tile
+// never share a slot.
+template <int kBits>
+__device__ __forceinline__ uint32_t slot_of(uint64_t f, uint32_t owner, uint32_t round) {
+    constexpr uint32_t kPer = 32 / kBits;
+    const uint32_t half = (round / kPer) & 1 ? static_cast<uint32_t>(f >> 32) : static_cast<uint32_t>(f);
+    return ((half >> ((round % kPer) * kBits)) + owner) & ((1u << kBits) - 1);
+}
+
+// A tile, by one wave: h^k of up to 64 vertices and 512 edges.
+//
+// A lane holds eight consecutive edges.  Per edge: gather h^{k-1} of the
+// target, mix the pair key, decide whether it is the first of its key in its
+// vertex, and sum the first ones per vertex.
+//   De-duplication works in rounds on a table of 2-byte slots without
+// atomics: every undecided key writes its position to its slot and reads the
+// slot back.  The position that stayed is the key's representative if the
+// keys are equal (then this one is a repeat), itself if it won, and another
+// key otherwise: those keys go to the next round, with another slot.  Equal
+// keys of a vertex always share their slots and so never part, and keys of
+// earlier rounds no longer matter, so the table is neither cleared nor
+// searched.  Every contested slot decides at least one key, so the rounds
+// end; at two slots per edge three or four are usual.
+//   The sum per vertex is a difference of running sums over the tile's edges
+// (mod 2^64), read where a vertex's edges end.
+//
+// Bound: with hashes in the last-level cache the gather's requests, else its
+// DRAM lines.  The workgroup form before (tiles of 1,536 edges, 64-bit
+// compare-and-swap per key, a 64-bit LDS add per distinct key, eight
+// workgroup barriers, 29 KiB per workgroup of four waves) took 103 us per
+// level on R-MAT 2^20 / 2^23 with chains, where this one takes 68; 17.1 and
+// 16.3 ms on R-MAT 2^27 / 2^30, 2.64 ms both on 2^24 / 2^27 uniform, where
+// nearly every gather is a request past L2 (some 50 G a second of them).
 template <typename LabT>
-__device__ bool tile_block(const IterArgs& a, uint32_t tile, IterShared& S, uint32_t p_done, uint32_t p_cnt,
-                           uint32_t p_tot) {
-    const uint32_t tid = threadIdx.x, k = a.k;
-    const bool hash = run_hash(a);
+__device__ __forceinline__ void wave_tile(const IterArgs& a, uint32_t tile, WaveLds& L, const StopInputs& p) {
+    const uint32_t lane = lane_id();
     const uint4 td = a.tiles[tile];
-    const uint32_t i0 = td.x, nv = td.y - i0;
-    const uint32_t ebase = td.z;
-    // A launch queued after the stop finds the sticky done flag set; every
-    // block of it then takes the same stop decision, so its waves may skip
-    // their loads at once (the exit itself still follows stop_decision).
-    const bool skip = early_done(a);
-    const uint32_t ne = skip ? 0u : td.w - ebase;
-    const bool mine = !skip && tid < nv;
-    const uint32_t v = mine ? a.act[i0 + tid] : 0u;
-    uint32_t ro0 = 0;
-    uint64_t tv = 0;
+    // (a queued launch past the stop skips its loads at once)
+    const uint32_t nv = p.done ? 0u : td.y - td.x, ne = p.done ? 0u : td.w - td.z;
+    const bool mine = lane < nv;
+    const uint32_t v = mine ? a.act[td.x + lane] : 0u;
+    const uint32_t off = mine ? a.act_off[td.x + lane] - td.z : 0u;
+    const uint32_t j0 = lane * kLaneEdges;
+    const uint32_t cnt = j0 < ne ? min(ne - j0, static_cast<uint32_t>(kLaneEdges)) : 0u;
+    uint32_t w[kLaneEdges], l[kLaneEdges];
+    load_edges(a.tgt, static_cast<const LabT*>(a.lab), static_cast<uint64_t>(td.z) + j0, cnt, a.m, w, l);
+    uint64_t f[kLaneEdges];
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) f[q] = static_cast<uint32_t>(q) < cnt ? a.h_prev[w[q]] : 0;
+    const uint64_t tv = mine ? a.t[v] : 0;
     // batched runs: a graph that stopped at level L keeps its level-L state
-    bool act_hash = true;
-    if (mine) {
-        ro0 = a.row_off[v];
-        if (a.bc.gid) {
-            const uint32_t gi = a.bc.gid[v];
-            act_hash = !(a.bc.ext && a.bc.ext[gi]) && k <= a.bc.done_level[gi];
-        }
-        if (hash) tv = a.t[v];
+    bool write = mine;
+    if (mine && a.bc.gid) {
+        const uint32_t gi = a.bc.gid[v];
+        write = !(a.bc.ext && a.bc.ext[gi]) && a.k <= a.bc.done_level[gi];
     }
-    const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
-    uint32_t w[kEdgesPerThread];
-    uint32_t l[kEdgesPerThread];
-    uint64_t hv[kEdgesPerThread];
+    const LaneOwners own = lane_owners(reinterpret_cast<uint8_t*>(L.slot), mine, off);
+    if (stop_decision(a, p)) return;
+    uint32_t todo = 0;
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
-        const uint32_t j = tid + r * kBlock;
-        w[r] = 0;
-        l[r] = 0;
-        if (hash && j < ne) {
-            // targets and labels are read once per launch: non-temporal, so
-            // they do not push the gathered hashes out of L2
-            w[r] = __builtin_nontemporal_load(&a.tgt[ebase + j]);
-            l[r] = static_cast<uint32_t>(__builtin_nontemporal_load(&lab[ebase + j]));
-        }
+    for (int q = 0; q < kLaneEdges; q++) {
+        if (static_cast<uint32_t>(q) < cnt) f[q] = mix64(f[q] ^ a.salt[l[q]] ^ kCE);
+        // a zero term adds nothing to the sum, repeated or not
+        if (static_cast<uint32_t>(q) < cnt && f[q]) todo |= 1u << q;
+        L.f[q * 64 + lane] = f[q];
     }
+    constexpr int kBits = 10;
+    static_assert(2 * kTileMaxEdges == 1 << kBits, "two slots per edge");
+    uint32_t first = 0;  // bit q: edge q is the first of its key
+    for (uint32_t round = 0; __ballot(todo != 0); round++) {
+        wave_sync();
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
-        const uint32_t j = tid + r * kBlock;
-        hv[r] = (hash && j < ne) ? a.h_prev[w[r]] ^ a.salt[l[r]] : 0;
-    }
-    stop_decision(a, S, p_done, p_cnt, p_tot);
-    if (hash) {
-        if (mine) {
-            S.off[tid] = ro0 - ebase;
-            S.acc[tid] = 0;
-        }
-        if (tid == 0) S.off[nv] = ne;
-    }
-    __syncthreads();
-    if (S.ctl[0]) return false;
-    if (!hash) return true;
-    for (uint32_t j = tid; j < 2 * ne; j += kBlock) S.tab[j] = 0;
-    tile_segments(nv, S.off, S.seg, S.red);
-    // De-duplicate the mixed keys per vertex.  Most keys are distinct and
-    // most home slots empty, so every key first tries its home slot, with
-    // all of a thread's attempts in flight together; the few keys whose home
-    // slot holds another key probe on from there.
-    uint64_t f[kEdgesPerThread];
-    uint32_t seg[kEdgesPerThread], slot[kEdgesPerThread], lo[kEdgesPerThread], hi[kEdgesPerThread];
+        for (int q = 0; q < kLaneEdges; q++)
+            if ((todo >> q) & 1) L.slot[slot_of<kBits>(f[q], own.of(q), round)] = static_cast<uint16_t>(q * 64 + lane);
+        wave_sync();
+        // (a decided key reads what its slot holds too, and drops it)
+        uint32_t got[kLaneEdges];
+        uint64_t key[kLaneEdges];
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
-        const uint32_t j = tid + r * kBlock;
-        f[r] = 0;  // a zero term adds nothing to the sum, repeated or not
-        if (j < ne) {
-            f[r] = mix64(hv[r] ^ kCE);
-            const uint32_t i = S.seg[j];
-            seg[r] = i;
-            lo[r] = 2 * S.off[i];
-            hi[r] = 2 * S.off[i + 1];
-            slot[r] = lo[r] + static_cast<uint32_t>(
-                                  (static_cast<uint64_t>(static_cast<uint32_t>(f[r])) * (hi[r] - lo[r])) >> 32);
-        }
-    }
-    uint64_t old[kEdgesPerThread];
+        for (int q = 0; q < kLaneEdges; q++)
+            got[q] = L.slot[slot_of<kBits>(f[q], own.of(q), round)] & (kTileMaxEdges - 1);
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++)
-        if (f[r] != 0)
-            old[r] = atomicCAS(reinterpret_cast<unsigned long long*>(&S.tab[slot[r]]), 0ull,
-                               static_cast<unsigned long long>(f[r]));
+        for (int q = 0; q < kLaneEdges; q++) key[q] = L.f[got[q]];
+        uint32_t won = 0, same = 0;
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
-        if (f[r] == 0 || old[r] == f[r]) continue;
-        bool fresh = old[r] == 0;
-        if (!fresh) {
-            const uint32_t next = slot[r] + 1 == hi[r] ? lo[r] : slot[r] + 1;
-            fresh = lds_insert(S.tab, next, lo[r], hi[r], f[r]) != 0;
+        for (int q = 0; q < kLaneEdges; q++) {
+            won |= static_cast<uint32_t>(got[q] == static_cast<uint32_t>(q * 64) + lane) << q;
+            same |= static_cast<uint32_t>(key[q] == f[q]) << q;
         }
-        if (fresh)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&S.acc[seg[r]]), static_cast<unsigned long long>(f[r]));
+        first |= todo & won;
+        todo &= ~same;  // (the winner reads its own key)
     }
-    __syncthreads();
+    // running sums of the distinct keys
+    uint64_t run = 0;
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) {
+        run += (first >> q) & 1 ? f[q] : 0;
+        f[q] = run;
+    }
+    const uint64_t before = wave_incl_sum(run) - run;
+    const bool next_begins = __shfl_down(static_cast<int>(own.starts & 1), 1, 64) != 0;
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) {
+        const bool ends = static_cast<uint32_t>(q) < cnt &&
+                          (j0 + q + 1 == ne || (q + 1 < kLaneEdges ? own.begins(q + 1) : next_begins));
+        if (ends) L.f[own.of(q)] = before + f[q];
+    }
+    wave_sync();
     // (a tile vertex has edges, so it is alive)
-    if (mine && act_hash) a.h_next[v] = mix64(tv ^ mix64(kCS + S.acc[tid]));
-    return true;
+    if (write) {
+        const uint64_t sum = L.f[lane] - (lane ? L.f[lane - 1] : 0);
+        a.h_next[v] = mix64(tv ^ mix64(kCS + sum));
+    }
 }
 
-// A hub chunk block: kTileMaxEdges edges of one hub.  Loads first, as in
-// tile_block.
+// A hub chunk block: kChunkEdges edges of one hub, their nonzero keys grouped
+// by hash bucket (top logb bits) so that each hub-bucket block reads only its
+// own keys; the order within a bucket is free.
 template <typename LabT>
-__device__ bool hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, uint32_t p_done, uint32_t p_cnt,
-                                uint32_t p_tot) {
+__device__ void hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, const StopInputs& p) {
     const uint32_t tid = threadIdx.x;
-    const bool hash = run_hash(a);
     const uint32_t hi = a.hc_hub[blk];
     const uint32_t e0 = a.hc_e0[blk];
     const uint32_t v = a.hub_v[hi];
     const uint32_t logb = a.hub_logb[hi];
     const uint64_t koff = a.hub_key_off[hi];
     const uint32_t vbeg = a.row_off[v], vend = a.row_off[v + 1];
-    const uint32_t ne = early_done(a) ? 0u : min(static_cast<uint32_t>(kTileMaxEdges), vend - e0);
+    const uint32_t ne = p.done ? 0u : min(static_cast<uint32_t>(kChunkEdges), vend - e0);
     const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
-    uint32_t w[kEdgesPerThread];
-    uint32_t l[kEdgesPerThread];
-    uint64_t hv[kEdgesPerThread];
+    uint32_t w[kChunkPerThread];
+    uint32_t l[kChunkPerThread];
+    uint64_t hv[kChunkPerThread];
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
+    for (int r = 0; r < kChunkPerThread; r++) {
         const uint32_t j = tid + r * kBlock;
         w[r] = 0;
         l[r] = 0;
-        if (hash && j < ne) {
-            w[r] = a.tgt[e0 + j];
-            l[r] = static_cast<uint32_t>(lab[e0 + j]);
+        if (j < ne) {
+            w[r] = __builtin_nontemporal_load(&a.tgt[e0 + j]);
+            l[r] = static_cast<uint32_t>(__builtin_nontemporal_load(&lab[e0 + j]));
         }
     }
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
+    for (int r = 0; r < kChunkPerThread; r++) {
         const uint32_t j = tid + r * kBlock;
-        hv[r] = (hash && j < ne) ? a.h_prev[w[r]] ^ a.salt[l[r]] : 0;
+        hv[r] = j < ne ? a.h_prev[w[r]] ^ a.salt[l[r]] : 0;
     }
-    stop_decision(a, S, p_done, p_cnt, p_tot);
-    __syncthreads();
-    if (S.ctl[0]) return false;
-    if (!hash) return true;
+    if (stop_decision(a, p)) return;  // uniform over the block
     uint64_t* __restrict__ out = a.hub_keys + koff + (e0 - vbeg);
-    // group the chunk's nonzero keys by hash bucket (top logb bits) so each
-    // hub-bucket block reads only its own keys; order within a bucket is free
     const uint32_t nb = 1u << logb;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(S.tab);
+    uint32_t* hist = S.hist;
     for (uint32_t b = tid; b <= nb; b += kBlock) hist[b] = 0;
     __syncthreads();
-    uint64_t f[kEdgesPerThread];
-    uint32_t rank[kEdgesPerThread];
+    uint64_t f[kChunkPerThread];
+    uint32_t rank[kChunkPerThread];
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
+    for (int r = 0; r < kChunkPerThread; r++) {
         const uint32_t j = tid + r * kBlock;
         f[r] = j < ne ? mix64(hv[r] ^ kCE) : 0;
         rank[r] = 0;
@@ -444,112 +493,102 @@ __device__ bool hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, 
         }
     }
     __syncthreads();
-    if (tid == 0) {  // exclusive prefix over at most 256 buckets
+    if (tid < 64) {  // exclusive prefix over at most 256 buckets, by one wave
         uint32_t run = 0;
-        for (uint32_t b = 0; b < nb; b++) {
-            const uint32_t c = hist[b];
-            hist[b] = run;
-            run += c;
+        for (uint32_t b0 = 0; b0 < nb; b0 += 64) {
+            const uint32_t c = b0 + tid < nb ? hist[b0 + tid] : 0u;
+            const uint32_t incl = wave_incl_sum(c);
+            if (b0 + tid < nb) hist[b0 + tid] = run + incl - c;
+            run += static_cast<uint32_t>(__shfl(static_cast<int>(incl), 63, 64));
         }
-        hist[nb] = run;
+        if (tid == 0) hist[nb] = run;
     }
     __syncthreads();
     uint32_t* boff = a.hub_boff + static_cast<uint64_t>(blk) * kHubOffStride;
     for (uint32_t b = tid; b <= nb; b += kBlock) boff[b] = hist[b];
 #pragma unroll
-    for (int r = 0; r < kEdgesPerThread; r++) {
+    for (int r = 0; r < kChunkPerThread; r++) {
         if (f[r] != 0) {
             const uint32_t b = logb ? static_cast<uint32_t>(f[r] >> (64 - logb)) : 0u;
             out[hist[b] + rank[r]] = f[r];
         }
     }
-    return true;
 }
 
-// A solo hub block: one hub vertex of at most kSoloMaxEdges edges, all its
-// pair keys de-duplicated in the whole LDS table.
+// A vertex of more edges than a tile holds and at most kSoloMaxEdges: the
+// rounds of wave_tile over the workgroup, all keys of one owner.
 template <typename LabT>
-__device__ bool solo_block(const IterArgs& a, uint32_t v, IterShared& S, uint32_t p_done, uint32_t p_cnt,
-                           uint32_t p_tot) {
+__device__ void solo_block(const IterArgs& a, uint32_t v, SoloLds& L, const StopInputs& p) {
+    __shared__ uint64_t s_sum[kWaves];
     const uint32_t tid = threadIdx.x, k = a.k;
-    const bool hash = run_hash(a);
     const uint32_t e0 = a.row_off[v];
-    const uint32_t ne = early_done(a) ? 0u : a.row_off[v + 1] - e0;
-    bool act_hash = true;
-    if (a.bc.gid) act_hash = k <= a.bc.done_level[a.bc.gid[v]];
-    const uint64_t tv = hash ? a.t[v] : 0;
+    const uint32_t ne = p.done ? 0u : a.row_off[v + 1] - e0;
+    bool write = tid == 0;
+    if (a.bc.gid) write = write && k <= a.bc.done_level[a.bc.gid[v]];
+    const uint64_t tv = a.t[v];
     const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
-    uint32_t w[kSoloPerThread];
-    uint32_t l[kSoloPerThread];
-    uint64_t hv[kSoloPerThread];
+    uint32_t w[kLaneEdges];
+    uint32_t l[kLaneEdges];
+    uint64_t f[kLaneEdges];
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++) {
+    for (int r = 0; r < kLaneEdges; r++) {
         const uint32_t j = tid + r * kBlock;
         w[r] = 0;
         l[r] = 0;
-        if (hash && j < ne) {
-            w[r] = a.tgt[e0 + j];
-            l[r] = static_cast<uint32_t>(lab[e0 + j]);
+        if (j < ne) {
+            w[r] = __builtin_nontemporal_load(&a.tgt[e0 + j]);
+            l[r] = static_cast<uint32_t>(__builtin_nontemporal_load(&lab[e0 + j]));
         }
     }
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++) {
+    for (int r = 0; r < kLaneEdges; r++) f[r] = tid + r * kBlock < ne ? a.h_prev[w[r]] ^ a.salt[l[r]] : 0;
+    if (stop_decision(a, p)) return;  // uniform over the block
+    constexpr int kBits = 12;
+    static_assert(2 * kSoloMaxEdges == 1 << kBits, "two slots per edge");
+    uint32_t todo = 0;
+#pragma unroll
+    for (int r = 0; r < kLaneEdges; r++) {
         const uint32_t j = tid + r * kBlock;
-        hv[r] = (hash && j < ne) ? a.h_prev[w[r]] ^ a.salt[l[r]] : 0;
+        if (j < ne) {
+            f[r] = mix64(f[r] ^ kCE);
+            L.f[j] = f[r];
+            if (f[r]) todo |= 1u << r;
+        }
     }
-    // the table spans tab, acc and off (the arrays a tile block uses)
-    uint64_t* tab = S.tab;
-    stop_decision(a, S, p_done, p_cnt, p_tot);
-    for (uint32_t j = tid; j < kSoloSlots; j += kBlock) tab[j] = 0;
-    __syncthreads();
-    if (S.ctl[0]) return false;
-    if (!hash) return true;
-    // home-slot attempts first, all in flight together (see tile_block)
     uint64_t acc = 0;
-    uint64_t f[kSoloPerThread], old[kSoloPerThread];
+    for (uint32_t round = 0; __syncthreads_or(todo != 0); round++) {
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++) {
-        const uint32_t j = tid + r * kBlock;
-        f[r] = j < ne ? mix64(hv[r] ^ kCE) : 0;
-    }
-    // double hashing: home slot from the low key bits, step from the high
-    // bits; the table size is prime, so every step visits every slot
-    uint32_t home[kSoloPerThread];
+        for (int r = 0; r < kLaneEdges; r++)
+            if ((todo >> r) & 1) L.slot[slot_of<kBits>(f[r], 0, round)] = static_cast<uint16_t>(tid + r * kBlock);
+        __syncthreads();
+        uint32_t got[kLaneEdges];
+        uint64_t key[kLaneEdges];
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++)
-        home[r] = static_cast<uint32_t>((static_cast<uint64_t>(static_cast<uint32_t>(f[r])) * kSoloSlots) >> 32);
+        for (int r = 0; r < kLaneEdges; r++) got[r] = L.slot[slot_of<kBits>(f[r], 0, round)] & (kSoloMaxEdges - 1);
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++)
-        if (f[r] != 0)
-            old[r] = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[home[r]]), 0ull,
-                               static_cast<unsigned long long>(f[r]));
+        for (int r = 0; r < kLaneEdges; r++) key[r] = L.f[got[r]];
 #pragma unroll
-    for (int r = 0; r < kSoloPerThread; r++) {
-        if (f[r] == 0 || old[r] == f[r]) continue;
-        bool fresh = old[r] == 0;
-        if (!fresh) {
-            const uint32_t step = 1u + static_cast<uint32_t>(f[r] >> 32) % (kSoloSlots - 1);
-            fresh = lds_insert_step(tab, home[r], step, kSoloSlots, f[r]) != 0;
+        for (int r = 0; r < kLaneEdges; r++) {
+            if (!((todo >> r) & 1)) continue;
+            if (got[r] == tid + r * kBlock) acc += f[r];
+            if (key[r] == f[r]) todo &= ~(1u << r);
         }
-        if (fresh) acc += f[r];
     }
     acc = wave_sum_u64(acc);
-    uint64_t* wsum = reinterpret_cast<uint64_t*>(S.seg);  // outside the table
-    if (lane_id() == 0) wsum[tid >> 6] = acc;
+    if (lane_id() == 0) s_sum[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0 && act_hash) {
+    if (write) {
         uint64_t sum = 0;
-        for (int i = 0; i < kBlock / 64; i++) sum += wsum[i];
+        for (int i = 0; i < kWaves; i++) sum += s_sum[i];
         a.h_next[v] = mix64(tv ^ mix64(kCS + sum));
     }
-    return true;
 }
 
 // kIsoPerBlock vertices without out-edges: h^k = M(t ^ M(C_S)) for every
 // k >= 1, written where the hash buffer does not hold it yet.
-__device__ bool iso_block(const IterArgs& a, uint32_t blk, IterShared& S, uint32_t p_done, uint32_t p_cnt,
-                          uint32_t p_tot) {
+__device__ void iso_block(const IterArgs& a, uint32_t blk, const StopInputs& p) {
     const uint32_t tid = threadIdx.x, k = a.k;
+    if (stop_decision(a, p)) return;
     uint32_t v[kIsoPerThread];
     uint64_t tv[kIsoPerThread];
     bool mine[kIsoPerThread], live[kIsoPerThread];
@@ -569,48 +608,42 @@ __device__ bool iso_block(const IterArgs& a, uint32_t blk, IterShared& S, uint32
             tv[r] = a.t[v[r]];
         }
     }
-    stop_decision(a, S, p_done, p_cnt, p_tot);
-    __syncthreads();
-    if (S.ctl[0]) return false;
 #pragma unroll
     for (int r = 0; r < kIsoPerThread; r++)
         if (mine[r]) a.h_next[v[r]] = live[r] ? mix64(tv[r] ^ mix64(kCS)) : 0;
-    return true;
-}
-
-// A block with no tile (an empty graph still needs its stop test).
-__device__ void null_block(const IterArgs& a, IterShared& S, uint32_t p_done, uint32_t p_cnt, uint32_t p_tot) {
-    stop_decision(a, S, p_done, p_cnt, p_tot);
 }
 
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_iterate(IterArgs a) {
     __shared__ IterShared S;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t k = a.k;
-    // stop-test inputs (level k - lag), loaded together with everything else
-    uint32_t p_done = 0, p_cnt = 0, p_tot = 0;
-    if (tid < 64) {
-        p_done = __hip_atomic_load(&a.status->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (k >= a.lag && !a.bc.gid && !a.hash_only) {
-            const uint32_t lv = k - a.lag;
-            p_cnt = stripe_count(a.lcnt, lv, tid);
-            p_tot = lv ? a.totals[(lv - 1) & (kStripeRing - 1)] : 0u;
-        }
+    const StopInputs p = stop_inputs(a);  // loaded together with everything else
+    uint32_t b = blockIdx.x;
+    if (a.stop_only) {
+        (void)stop_decision(a, p);
+        return;
     }
-    const uint32_t b = blockIdx.x;
-    if (a.stop_only)
-        null_block(a, S, p_done, p_cnt, p_tot);
-    else if (b < a.n_hub_chunks)
-        hub_chunk_block<LabT>(a, b, S, p_done, p_cnt, p_tot);
-    else if (b - a.n_hub_chunks < a.n_solo)
-        solo_block<LabT>(a, a.solo_v[b - a.n_hub_chunks], S, p_done, p_cnt, p_tot);
-    else if (b - a.n_hub_chunks - a.n_solo < a.n_iso_blocks)
-        iso_block(a, b - a.n_hub_chunks - a.n_solo, S, p_done, p_cnt, p_tot);
-    else if (b - a.n_hub_chunks - a.n_solo - a.n_iso_blocks < a.n_tiles)
-        tile_block<LabT>(a, b - a.n_hub_chunks - a.n_solo - a.n_iso_blocks, S, p_done, p_cnt, p_tot);
+    if (b < a.n_hub_chunks) {
+        hub_chunk_block<LabT>(a, b, S, p);
+        return;
+    }
+    b -= a.n_hub_chunks;
+    if (b < a.n_solo) {
+        solo_block<LabT>(a, a.solo_v[b], S.solo, p);
+        return;
+    }
+    b -= a.n_solo;
+    if (b < a.n_iso_blocks) {
+        iso_block(a, b, p);
+        return;
+    }
+    b -= a.n_iso_blocks;
+    // one tile per wave (the tile number is the same in all its lanes)
+    const uint32_t wv = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    const uint32_t tile = b * kWaves + wv;
+    if (tile < a.n_tiles)
+        wave_tile<LabT>(a, tile, S.wave[wv], p);
     else
-        null_block(a, S, p_done, p_cnt, p_tot);
+        (void)stop_decision(a, p);  // (an empty graph still needs its stop test)
 }
 
 // ------------------------------------------------------------ classes of level k
@@ -665,7 +698,13 @@ __global__ void __launch_bounds__(kBlock) k_split(SplitArgs a) {
         const uint32_t i = first + q * kBlock;
         probe[q] = i < a.count;
         v[q] = 0;
-        if (probe[q]) v[q] = k == 1 ? i : i < a.n_act ? a.act[i] : a.hub_v[i - a.n_act];
+        if (!probe[q]) continue;
+        if (k == 1)
+            v[q] = i;
+        else if (i < a.n_act)
+            v[q] = a.act[i];
+        else
+            v[q] = i - a.n_act < a.n_solo ? a.solo_v[i - a.n_act] : a.hub_v[i - a.n_act - a.n_solo];
     }
 #pragma unroll
     for (int q = 0; q < kSplitPerThread; q++) {
@@ -705,50 +744,115 @@ __global__ void __launch_bounds__(kBlock) k_split(SplitArgs a) {
 
 // ------------------------------------------------------------ hub buckets
 
-constexpr int kMaxHubRuns = 256;  // chunk runs staged in LDS at a time
+// One workgroup per hash bucket of a hub: the bucket's keys, one run per chunk
+// of the hub, are de-duplicated and their sum added to the hub's; the
+// workgroup that finishes a hub's last bucket turns the sum into h^k.
+//
+// A bucket of at most hub_rounds_cap keys, as the schedule aims at, goes
+// through the rounds of wave_tile (keys and 2-byte slots in LDS, no atomics).
+// Larger ones (a hub past 2^8 buckets, a key repeated very often) go to a
+// 64-bit open-addressing table whose distinct keys are counted, and are
+// re-split by further hash bits when the count passes the table's limit.
+//
+// Bound at few hubs: a chain of dependent loads (schedule, run bounds, keys)
+// and the rounds' barriers.  With the table alone, whose distinct count is
+// one LDS counter, a serial prefix over the runs and a second launch to
+// finish the hubs, a level took 29.5 + 4.8 us on R-MAT 2^20 / 2^23; now 12.6.
+// On 2^27 / 2^30, with thousands of buckets in flight, 2.48 and 2.30 ms.
+constexpr uint32_t kMaxHubRuns = kHubBlock;  // chunk runs staged in LDS at a time
 
-// Stage the runs of chunks [cb, cb+ncb) of this bucket: s_src[i] = scratch
-// offset of run i, s_run = exclusive prefix of run lengths (s_run[ncb] = total).
-__device__ void stage_runs(const HubArgs& a, uint32_t c0, uint32_t cb, uint32_t ncb, uint32_t bucket,
-                           uint32_t e_first, uint32_t* s_run, uint32_t* s_src) {
+struct HubRuns {
+    uint32_t at[kMaxHubRuns + 1];  // exclusive prefix of the run lengths
+    uint32_t src[kMaxHubRuns];     // scratch offset of each run
+    uint32_t red[kHubBlock / 64];
+};
+
+// Stage the runs of chunks [cb, cb + ncb) of this bucket; returns their keys.
+__device__ uint32_t stage_runs(const HubArgs& a, uint32_t c0, uint32_t cb, uint32_t ncb, uint32_t bucket,
+                               uint32_t e_first, HubRuns& R) {
     const uint32_t tid = threadIdx.x;
+    uint32_t len = 0;
     __syncthreads();
     if (tid < ncb) {
         const uint32_t blk = c0 + cb + tid;
         const uint32_t* boff = a.hub_boff + static_cast<uint64_t>(blk) * kHubOffStride;
-        s_src[tid] = (a.hc_e0[blk] - e_first) + boff[bucket];
-        s_run[tid + 1] = boff[bucket + 1] - boff[bucket];
+        const uint32_t b0 = boff[bucket];
+        R.src[tid] = (a.hc_e0[blk] - e_first) + b0;
+        len = boff[bucket + 1] - b0;
     }
+    const uint32_t incl = wave_incl_sum(len);
+    if (lane_id() == 63) R.red[tid >> 6] = incl;
     __syncthreads();
-    if (tid == 0) {
-        s_run[0] = 0;
-        for (uint32_t i = 1; i <= ncb; i++) s_run[i] += s_run[i - 1];
+    uint32_t base = 0, total = 0;
+    for (uint32_t i = 0; i < kHubBlock / 64; i++) {
+        if (i < (tid >> 6)) base += R.red[i];
+        total += R.red[i];
     }
+    if (tid < ncb) R.at[tid] = base + incl - len;
+    if (tid == 0) R.at[ncb] = total;
     __syncthreads();
+    return total;
 }
 
-__global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
-    extern __shared__ uint64_t s_tab[];
-    __shared__ uint64_t s_red64[kHubBlock / 64];
-    __shared__ uint32_t s_ctl[4];
-    __shared__ uint32_t s_run[kMaxHubRuns + 1];   // prefix of run lengths
-    __shared__ uint32_t s_src[kMaxHubRuns];       // scratch offset of each run
+// Key j of the staged runs.
+__device__ __forceinline__ uint64_t run_key(const HubRuns& R, uint32_t ncb, const uint64_t* __restrict__ keys,
+                                            uint32_t j) {
+    uint32_t lo = 0, hi = ncb;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (R.at[mid] <= j) lo = mid; else hi = mid;
+    }
+    return keys[R.src[lo] + (j - R.at[lo])];
+}
+
+// Sum of the distinct keys of a staged bucket that fits: this thread's share.
+__device__ uint64_t hub_rounds(const HubArgs& a, const HubRuns& R, uint32_t ncb, uint32_t total,
+                               const uint64_t* __restrict__ keys, uint64_t* s_mem) {
     const uint32_t tid = threadIdx.x;
-    if (*reinterpret_cast<volatile uint32_t*>(&a.status->done)) return;
-    const uint32_t hi = a.hb_hub[blockIdx.x];
-    const uint32_t bucket = a.hb_bucket[blockIdx.x];
-    const uint32_t logb = a.hub_logb[hi];
-    const uint32_t c0 = a.hub_chunk0[hi], nc = a.hub_nchunks[hi];
-    const uint64_t* __restrict__ keys = a.hub_keys + a.hub_key_off[hi];
+    const uint32_t cap = hub_rounds_cap(a.table_slots), mask = a.table_slots - 1;
+    const uint32_t bits = static_cast<uint32_t>(__popc(mask)), per = 32 / bits;
+    uint64_t* lf = s_mem;
+    uint16_t* slot = reinterpret_cast<uint16_t*>(s_mem + cap);
+    static_assert(kHubRoundsMax <= 32, "a bit per key of a thread");
+    uint32_t todo = 0;
+    for (uint32_t r = 0, j = tid; j < total; r++, j += kHubBlock) {
+        lf[j] = run_key(R, ncb, keys, j);  // (a zero key is not in the scratch)
+        todo |= 1u << r;
+    }
+    uint64_t acc = 0;
+    for (uint32_t round = 0; __syncthreads_or(todo != 0); round++) {
+        const uint32_t sh = (round % per) * bits;
+        const bool upper = (round / per) & 1;
+        auto at = [&](uint64_t f) {
+            return ((upper ? static_cast<uint32_t>(f >> 32) : static_cast<uint32_t>(f)) >> sh) & mask;
+        };
+        for (uint32_t left = todo; left; left &= left - 1) {
+            const uint32_t j = (static_cast<uint32_t>(__ffs(static_cast<int>(left))) - 1) * kHubBlock + tid;
+            slot[at(lf[j])] = static_cast<uint16_t>(j);
+        }
+        __syncthreads();
+        for (uint32_t left = todo; left; left &= left - 1) {
+            const uint32_t bit = left & (0u - left);
+            const uint32_t j = (static_cast<uint32_t>(__ffs(static_cast<int>(left))) - 1) * kHubBlock + tid;
+            const uint64_t f = lf[j];
+            const uint32_t got = slot[at(f)];
+            if (got == j) acc += f;
+            if (lf[got] == f) todo &= ~bit;
+        }
+    }
+    return acc;
+}
+
+// The same for a bucket of any size: see k_hub.
+__device__ uint64_t hub_table(const HubArgs& a, HubRuns& R, uint32_t c0, uint32_t nc, uint32_t bucket, uint32_t logb,
+                              uint32_t e_first, const uint64_t* __restrict__ keys, uint64_t* s_tab) {
+    __shared__ uint32_t s_ctl[2];
+    const uint32_t tid = threadIdx.x;
     const uint32_t mask = a.table_slots - 1;
     volatile uint32_t* ctl = s_ctl;
-    const uint32_t e_first = a.hc_e0[c0];
-
-    // The bucket's keys form one run per chunk of the hub.  They are inserted
-    // into one LDS table (runs staged kMaxHubRuns chunks at a time).  Only
-    // distinct keys occupy slots; a bucket with more distinct keys than the
-    // table limit is re-split by further hash bits and re-read, which ends
-    // because distinct keys differ in some bit (depth capped for safety).
+    // Only distinct keys occupy slots; a bucket with more distinct keys than
+    // the table limit is re-split by further hash bits and re-read, which
+    // ends because distinct keys differ in some bit (depth capped for safety).
     uint64_t sum = 0;
     for (uint32_t extra = 0;; extra++) {
         if (extra > kMaxHubExtraBits) {
@@ -763,29 +867,19 @@ __global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
             __syncthreads();
             for (uint32_t j = tid; j < a.table_slots; j += kHubBlock) s_tab[j] = 0;
             if (tid == 0) {
-                ctl[1] = 0;  // distinct keys inserted
-                ctl[2] = 0;  // overflow
+                ctl[0] = 0;  // distinct keys inserted
+                ctl[1] = 0;  // overflow
             }
             for (uint32_t cb = 0; cb < nc && !overflow; cb += kMaxHubRuns) {
-                const uint32_t ncb = min(static_cast<uint32_t>(kMaxHubRuns), nc - cb);
-                stage_runs(a, c0, cb, ncb, bucket, e_first, s_run, s_src);
-                const uint32_t total = s_run[ncb];
+                const uint32_t ncb = min(kMaxHubRuns, nc - cb);
+                const uint32_t total = stage_runs(a, c0, cb, ncb, bucket, e_first, R);
                 for (uint32_t j0 = 0; j0 < total; j0 += 4 * kHubBlock) {
-                    if (ctl[2]) break;
+                    if (ctl[1]) break;
                     uint64_t f[4];
 #pragma unroll
                     for (int r = 0; r < 4; r++) {
                         const uint32_t j = j0 + r * kHubBlock + tid;
-                        f[r] = 0;
-                        if (j < total) {
-                            // run containing j: binary search over the run prefix
-                            uint32_t lo = 0, hi2 = ncb;
-                            while (hi2 - lo > 1) {
-                                const uint32_t mid = (lo + hi2) >> 1;
-                                if (s_run[mid] <= j) lo = mid; else hi2 = mid;
-                            }
-                            f[r] = keys[s_src[lo] + (j - s_run[lo])];
-                        }
+                        f[r] = j < total ? run_key(R, ncb, keys, j) : 0;
                     }
 #pragma unroll
                     for (int r = 0; r < 4; r++) {
@@ -796,44 +890,62 @@ __global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
                         if (got == 1u) {
                             sum += f[r];
                             // count distinct keys only: duplicates never overflow
-                            if (atomicAdd(const_cast<uint32_t*>(&ctl[1]), 1u) + 1 >= a.table_limit) ctl[2] = 1;
+                            if (atomicAdd(const_cast<uint32_t*>(&ctl[0]), 1u) + 1 >= a.table_limit) ctl[1] = 1;
                         } else if (got == 2u) {
-                            ctl[2] = 1;
+                            ctl[1] = 1;
                         }
                     }
                 }
                 __syncthreads();
-                overflow = ctl[2] != 0;
+                overflow = ctl[1] != 0;
             }
         }
         if (!overflow) break;
     }
-    __syncthreads();
-    // block sum
-    uint64_t x = wave_sum_u64(sum);
-    if (lane_id() == 0) s_red64[tid >> 6] = x;
-    __syncthreads();
-    if (tid == 0) {
-        uint64_t bsum = 0;
-        for (int i = 0; i < kHubBlock / 64; i++) bsum += s_red64[i];
-        __hip_atomic_fetch_add(&a.hub_acc[hi], bsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    return sum;
 }
 
-// h^k of each chunked hub from the sum of its buckets' distinct keys.  The
-// sums are read here, one launch after the bucket blocks added them, so the
-// bucket blocks need no fence or completion count (an agent-scope fence on
-// this chip writes back or invalidates the whole L2 of the block's XCD);
-// each sum is cleared for the next level.
-__global__ void __launch_bounds__(kBlock) k_hub_finish(const uint64_t* t, const uint32_t* hub_v, uint64_t* hub_acc,
-                                                       uint32_t n_big, uint64_t* h_next, const RunStatus* status,
-                                                       uint32_t k, BatchCtl bc) {
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n_big || status->done) return;  // a done run added nothing
-    const uint64_t acc = hub_acc[i];
-    hub_acc[i] = 0;
-    const uint32_t v = hub_v[i];
-    if (!bc.gid || k <= bc.done_level[bc.gid[v]]) h_next[v] = mix64(t[v] ^ mix64(kCS + acc));
+__global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
+    extern __shared__ uint64_t s_mem[];
+    __shared__ uint64_t s_red64[kHubBlock / 64];
+    __shared__ HubRuns R;
+    const uint32_t tid = threadIdx.x;
+    if (*reinterpret_cast<volatile uint32_t*>(&a.status->done)) return;
+    const uint32_t hi = a.hb_hub[blockIdx.x];
+    const uint32_t bucket = a.hb_bucket[blockIdx.x];
+    const uint32_t logb = a.hub_logb[hi];
+    const uint32_t c0 = a.hub_chunk0[hi], nc = a.hub_nchunks[hi];
+    const uint64_t* __restrict__ keys = a.hub_keys + a.hub_key_off[hi];
+    const uint32_t e_first = a.hc_e0[c0];
+    uint64_t sum;
+    const uint32_t total = nc <= kMaxHubRuns ? stage_runs(a, c0, 0, nc, bucket, e_first, R) : 0xFFFFFFFFu;
+    if (total <= hub_rounds_cap(a.table_slots))
+        sum = hub_rounds(a, R, nc, total, keys, s_mem);
+    else
+        sum = hub_table(a, R, c0, nc, bucket, logb, e_first, keys, s_mem);
+    sum = wave_sum_u64(sum);
+    if (lane_id() == 0) s_red64[tid >> 6] = sum;
+    __syncthreads();
+    if (tid != 0) return;
+    uint64_t bsum = 0;
+    for (int i = 0; i < kHubBlock / 64; i++) bsum += s_red64[i];
+    // The hub's sum, then its count of finished buckets.  Both are device
+    // atomics and the second is issued once the first has returned, so the
+    // workgroup that counts the last bucket reads the whole sum, without
+    // fences (an agent-scope fence on this chip writes back or invalidates
+    // the whole L2 of the block's XCD).  It clears both for the next level.
+    unsigned long long* acc = reinterpret_cast<unsigned long long*>(a.hub_acc) + 2ull * hi;
+    const uint64_t was = __hip_atomic_fetch_add(acc, static_cast<unsigned long long>(bsum), __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(was) : "memory");
+    const uint64_t n_done = __hip_atomic_fetch_add(acc + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n_done + 1 != (1ull << logb)) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(n_done) : "memory");
+    const uint64_t all = __hip_atomic_fetch_add(acc, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    acc[0] = 0;
+    acc[1] = 0;
+    const uint32_t v = a.hub_v[hi];
+    if (!a.bc.gid || a.k <= a.bc.done_level[a.bc.gid[v]]) a.h_next[v] = mix64(a.t[v] ^ mix64(kCS + all));
 }
 
 // ------------------------------------------------------------ batched stop
@@ -874,7 +986,7 @@ uint32_t query_hub_table_slots(int device, bool device_max) {
     // keep room for the block's static LDS.  Keys arrive grouped by bucket,
     // so small tables cost no extra reads and let several blocks share a CU.
     uint64_t avail = bytes > 4096 ? static_cast<uint64_t>(bytes) - 4096 : 4096;
-    uint64_t slots = std::min<uint64_t>(avail / 8, device_max ? 16384 : kHubTableDefault);
+    uint64_t slots = std::min<uint64_t>(avail / 8, device_max ? kHubTableMax : kHubTableDefault);
     uint32_t p = 1;
     while (2ull * p <= slots) p <<= 1;
     return p;
@@ -927,10 +1039,10 @@ void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_
     rb.totals = arena.alloc<uint32_t>(kStripeRing);
     rb.hub_keys = arena.alloc<uint64_t>(g.hub_keys_total + 1);
     rb.hub_boff = arena.alloc<uint32_t>((static_cast<size_t>(g.n_hub_chunks) + 1) * kHubOffStride);
-    rb.hub_acc = arena.alloc<uint64_t>(g.n_hubs + 1);
+    rb.hub_acc = arena.alloc<uint64_t>(2ull * g.n_hubs + 2);
     rb.status = arena.alloc<RunStatus>(1);
     clear(rb.lcnt, kStripeRing * kStripes * kStripePitch * 4);
-    clear(rb.hub_acc, (g.n_hubs + 1) * 8ull);
+    clear(rb.hub_acc, (g.n_hubs + 1) * 16ull);
     clear(rb.status, sizeof(RunStatus));
     k_clear<<<std::min<uint32_t>(ceil_div(words, kBlock), 8192), kBlock, 0, s>>>(c);
     hip_check(hipGetLastError(), "clear run buffers");
@@ -946,7 +1058,7 @@ void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_
 
 uint32_t iteration_grid(const Staged& g, uint32_t k, bool all_levels) {
     const uint32_t iso = k <= 2 || all_levels ? ceil_div(g.n_iso, kIsoPerBlock) : 0u;
-    return std::max<uint32_t>(g.n_hub_chunks + g.n_solo + iso + g.n_tiles, 1);
+    return std::max<uint32_t>(g.n_hub_chunks + g.n_solo + iso + ceil_div(g.n_tiles, kWaves), 1);
 }
 
 void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop,
@@ -965,6 +1077,8 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.alive = g.alive;
     a.tiles = g.tiles;
     a.act = g.act;
+    a.act_off = g.act_off;
+    a.m = g.m;
     a.iso = g.iso;
     a.n_iso = g.n_iso;
     a.n_iso_blocks = k <= 2 || all_levels ? ceil_div(g.n_iso, kIsoPerBlock) : 0u;
@@ -981,7 +1095,7 @@ void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_
     a.n_tiles = g.n_tiles;
     a.n_hub_chunks = g.n_hub_chunks;
     a.n_solo = g.n_solo;
-    a.solo_v = g.hub_v ? g.hub_v + (g.n_hubs - g.n_solo) : nullptr;
+    a.solo_v = g.solo_v;
     a.k = k;
     a.k_max = k_max;
     a.stop = stop ? 1u : 0u;
@@ -999,9 +1113,11 @@ void launch_split(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t
     a.h = rb.h[k & 1];
     a.rep = rb.rep;
     a.act = g.act;
+    a.solo_v = g.solo_v;
     a.hub_v = g.hub_v;
     a.n_act = g.n_act;
-    a.count = k == 1 ? g.n : g.n_act + g.n_hubs;
+    a.n_solo = g.n_solo;
+    a.count = k == 1 ? g.n : g.n_act + g.n_solo + g.n_hubs;
     a.test_tab = rb.tab[k & 1];
     a.clr_tab = rb.tab[(k - 1) & 1];
     a.lcnt = rb.lcnt;
@@ -1024,7 +1140,6 @@ void launch_hubs(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t 
     a.hub_nchunks = g.hub_nchunks;
     a.hc_e0 = g.hc_e0;
     a.hub_v = g.hub_v;
-    a.hub_deg = g.hub_deg;
     a.hub_logb = g.hub_logb;
     a.hb_hub = g.hb_hub;
     a.hb_bucket = g.hb_bucket;
@@ -1037,18 +1152,14 @@ void launch_hubs(const Staged& g, const RunBuffers& rb, uint32_t k, hipStream_t 
     a.bc = rb.bc;
     k_hub<<<g.n_hub_blocks, kHubBlock, static_cast<size_t>(g.hub_table_slots) * 8, s>>>(a);
     hip_check(hipGetLastError(), "hub launch");
-    const uint32_t n_big = g.n_hubs - g.n_solo;
-    k_hub_finish<<<ceil_div(n_big, kBlock), kBlock, 0, s>>>(rb.t, g.hub_v, rb.hub_acc, n_big, rb.h[k & 1],
-                                                              rb.status, k, rb.bc);
-    hip_check(hipGetLastError(), "hub finish launch");
 }
 
 void alloc_hash_scratch(const Staged& g, HashScratch& hs, Arena& arena, hipStream_t s) {
     hs.hub_keys = arena.alloc<uint64_t>(g.hub_keys_total + 1);
     hs.hub_boff = arena.alloc<uint32_t>((static_cast<size_t>(g.n_hub_chunks) + 1) * kHubOffStride);
-    hs.hub_acc = arena.alloc<uint64_t>(g.n_hubs + 1);
+    hs.hub_acc = arena.alloc<uint64_t>(2ull * g.n_hubs + 2);
     hs.status = arena.alloc<RunStatus>(1);
-    hip_check(hipMemsetAsync(hs.hub_acc, 0, (g.n_hubs + 1) * 8ull, s), "hub acc");
+    hip_check(hipMemsetAsync(hs.hub_acc, 0, (g.n_hubs + 1) * 16ull, s), "hub acc");
     hip_check(hipMemsetAsync(hs.status, 0, sizeof(RunStatus), s), "status");
 }
 
@@ -1065,6 +1176,8 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     a.alive = g.alive;
     a.tiles = g.tiles;
     a.act = g.act;
+    a.act_off = g.act_off;
+    a.m = g.m;
     a.iso = g.iso;
     a.n_iso = g.n_iso;
     a.n_iso_blocks = ceil_div(g.n_iso, kIsoPerBlock);
@@ -1079,11 +1192,11 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     a.n_tiles = g.n_tiles;
     a.n_hub_chunks = g.n_hub_chunks;
     a.n_solo = g.n_solo;
-    a.solo_v = g.hub_v ? g.hub_v + (g.n_hubs - g.n_solo) : nullptr;
+    a.solo_v = g.solo_v;
     a.k = level;
     a.k_max = 0xFFFFFFFFu;
     a.hash_only = 1;
-    const uint32_t grid = std::max<uint32_t>(g.n_hub_chunks + g.n_solo + a.n_iso_blocks + g.n_tiles, 1);
+    const uint32_t grid = iteration_grid(g, level, true);
     if (g.label_bytes == 2)
         k_iterate<uint16_t><<<grid, kBlock, 0, s>>>(a);
     else
@@ -1099,7 +1212,6 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     h.hub_nchunks = g.hub_nchunks;
     h.hc_e0 = g.hc_e0;
     h.hub_v = g.hub_v;
-    h.hub_deg = g.hub_deg;
     h.hub_logb = g.hub_logb;
     h.hb_hub = g.hb_hub;
     h.hb_bucket = g.hb_bucket;
@@ -1111,10 +1223,6 @@ void launch_hash_level(const Staged& g, const uint64_t* t, const uint64_t* h_pre
     h.k = level;
     k_hub<<<g.n_hub_blocks, kHubBlock, static_cast<size_t>(g.hub_table_slots) * 8, s>>>(h);
     hip_check(hipGetLastError(), "hash level hub launch");
-    const uint32_t n_big = g.n_hubs - g.n_solo;
-    k_hub_finish<<<ceil_div(n_big, kBlock), kBlock, 0, s>>>(t, g.hub_v, hs.hub_acc, n_big, h_next, hs.status,
-                                                              level, BatchCtl{});
-    hip_check(hipGetLastError(), "hash level hub finish launch");
 }
 
 void launch_graph_stop(const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop, hipStream_t s) {

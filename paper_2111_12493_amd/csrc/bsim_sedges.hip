@@ -360,48 +360,61 @@ __global__ void __launch_bounds__(kBlock) k_seg_claim(const uint32_t* __restrict
 }
 
 struct FillShared {
-    uint32_t off[kTileMaxVerts + 1];
     uint32_t base[kTileMaxVerts];
-    uint32_t red[kBlock / 64];
-    alignas(8) uint8_t seg[kTileMaxEdges];
+    alignas(8) uint8_t owner[kTileMaxEdges];
 };
 
-// Every edge (v, l, w) writes l << bb | block(w) into v's claimed range.
+// Every edge (v, l, w) writes l << bb | block(w) into v's claimed range: one
+// wave per tile, the eight gathers of a lane in flight together; solo
+// vertices and hubs by a workgroup each.
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_seg_fill(
     const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt, const LabT* __restrict__ lab,
     const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst, const uint32_t* __restrict__ estart,
     const uint32_t* __restrict__ voff, const uint4* __restrict__ tiles, const uint32_t* __restrict__ act,
-    uint32_t n_tiles, const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int bb, uint64_t* __restrict__ vals) {
-    __shared__ FillShared S;
+    const uint32_t* __restrict__ act_off, uint32_t n_tiles, const uint32_t* __restrict__ solo_v, uint32_t n_solo,
+    const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int bb, uint64_t* __restrict__ vals) {
+    __shared__ FillShared sh[kWaves];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < n_hubs) {
-        const uint32_t v = hub_v[blockIdx.x];
+    if (blockIdx.x < n_hubs + n_solo) {
+        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
         const uint32_t e0 = row_off[v], e1 = row_off[v + 1];
         uint64_t* out = vals + estart[bid[v]] + voff[v];
         for (uint32_t e = e0 + tid; e < e1; e += kBlock)
             out[e - e0] = (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
         return;
     }
-    const uint32_t tile = blockIdx.x - n_hubs;
+    const uint32_t lane = lane_id();
+    const uint32_t wv = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(tid >> 6)));
+    const uint32_t tile = (blockIdx.x - n_hubs - n_solo) * kWaves + wv;
     if (tile >= n_tiles) return;
+    FillShared& S = sh[wv];
     const uint4 td = tiles[tile];
-    const uint32_t i0 = td.x, nv = td.y - i0;
-    const uint32_t ebase = td.z;
-    const uint32_t ne = td.w - ebase;
-    for (uint32_t i = tid; i < nv; i += kBlock) {
-        const uint32_t v = act[i0 + i];
-        const uint32_t o = row_off[v] - ebase;
-        S.off[i] = o;
-        // the value of local edge j of this vertex goes to base + j (mod 2^32)
-        S.base[i] = estart[bid[v]] + voff[v] - o;
+    const uint32_t nv = td.y - td.x, ne = td.w - td.z;
+    uint32_t w[kLaneEdges], l[kLaneEdges];
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) {
+        const uint32_t j = q * 64 + lane;
+        w[q] = l[q] = 0;
+        if (j < ne) {
+            w[q] = __builtin_nontemporal_load(&tgt[td.z + j]);
+            l[q] = static_cast<uint32_t>(__builtin_nontemporal_load(&lab[td.z + j]));
+        }
     }
-    if (tid == 0) S.off[nv] = ne;
-    __syncthreads();
-    tile_segments(nv, S.off, S.seg, S.red);
-    for (uint32_t j = tid; j < ne; j += kBlock) {
-        const uint32_t e = ebase + j;
-        vals[S.base[S.seg[j]] + j] = (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
+    uint32_t off = 0;
+    if (lane < nv) {
+        const uint32_t v = act[td.x + lane];
+        off = act_off[td.x + lane] - td.z;
+        // the value of local edge j of this vertex goes to base + j (mod 2^32)
+        S.base[lane] = estart[bid[v]] + voff[v] - off;
+    }
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) w[q] = q * 64 + lane < ne ? bid_dst[w[q]] : 0u;
+    tile_owners(S.owner, lane < nv, off);
+#pragma unroll
+    for (int q = 0; q < kLaneEdges; q++) {
+        const uint32_t j = q * 64 + lane;
+        if (j < ne) vals[S.base[S.owner[j]] + j] = (static_cast<uint64_t>(l[q]) << bb) | w[q];
     }
 }
 
@@ -540,7 +553,7 @@ __global__ void __launch_bounds__(kBlock) k_seg_unpack(const uint64_t* __restric
 
 bool bucketed_summary_edges_fit(const Staged& g, int lb, int bb) {
     const int vb = lb + bb;
-    if (g.src || g.m == 0 || g.n_tiles + g.n_hubs == 0) return false;
+    if (g.src || g.m == 0 || g.n_tiles + g.n_solo + g.n_hubs == 0) return false;
     if (vb + kOrdBits > 64) return false;
     // huge segments are ranked: at most m / (kSegBigMax + 1) of them
     return vb + bit_width(g.m / (kSegBigMax + 1)) <= 64;
@@ -562,13 +575,15 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
     scan_exclusive(ecount, estart, nb, estart + nb, arena, s);
     // 2. values
     uint64_t* vals = arena.alloc<uint64_t>(m);
-    const uint32_t grid = g.n_hubs + g.n_tiles;
+    const uint32_t grid = g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves);
     if (g.label_bytes == 2)
         k_seg_fill<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint16_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tiles, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
+                                                     dst_ids, estart, voff, g.tiles, g.act, g.act_off, g.n_tiles,
+                                                     g.solo_v, g.n_solo, g.hub_v, g.n_hubs, bb, vals);
     else
         k_seg_fill<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint32_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tiles, g.act, g.n_tiles, g.hub_v, g.n_hubs, bb, vals);
+                                                     dst_ids, estart, voff, g.tiles, g.act, g.act_off, g.n_tiles,
+                                                     g.solo_v, g.n_solo, g.hub_v, g.n_hubs, bb, vals);
     // 3. size classes
     uint32_t* uniq = arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1);
     auto list_cap = [&](uint32_t above) { return std::min<uint64_t>(nb, m / (above + 1ull) + 1); };

@@ -4,15 +4,13 @@
 // Staging validates the CSR (paper Sec. 3.1 Phase 0 co-locates every vertex
 // with its out-edges; here that is the out-edge CSR itself), computes the
 // label salts, and cuts the vertex range into tiles and hub buckets:
-//   * a vertex with kHubMinDegree or more out-edges (too many for one tile)
-//     is a hub;
-//   * every other vertex with out-edges belongs to exactly one tile, a run of
-//     consecutive such vertices packed greedily (within kStageVerts vertices)
-//     up to kTileMaxEdges - 1 edges and kTileMaxVerts vertices; a non-hub
-//     vertex always fits an empty tile;
-//   * a hub of degree d is cut into chunks of kTileMaxEdges edges that write
-//     its mixed pair keys to d scratch slots, and into 2^b hash buckets that
-//     each fit the LDS table of the hub-bucket launch.
+//   * a vertex of 1..kTileMaxEdges out-edges belongs to exactly one tile, a
+//     run of consecutive such vertices packed greedily (within kStageVerts
+//     vertices) up to kTileMaxEdges edges and kTileMaxVerts vertices;
+//   * one of up to kSoloMaxEdges is a workgroup's work by itself;
+//   * one of more is a hub: of degree d it is cut into chunks of kChunkEdges
+//     edges that write its mixed pair keys to d scratch slots, and into 2^b
+//     hash buckets that each fit the LDS table of the hub-bucket launch.
 #include <algorithm>
 
 #include "bsim_resolve.h"  // host_radix_sort
@@ -139,18 +137,17 @@ namespace {
 
 // Staging is two passes over the row offsets with a one-block scan between
 // them, and one pass over the edges beside the first.  A workgroup owns
-// kStageVerts consecutive vertices: it classifies them (hub, tile vertex, no
-// out-edges), compacts the tile vertices' edge ranges in LDS and packs them
-// into tiles, so a tile never leaves its workgroup's vertices.  The first
-// pass counts (hubs, tile vertices, vertices without out-edges, tiles), the
-// scan places the counts, the second pass repeats the work and writes the
-// lists.  Repeating it costs 4 bytes per vertex; carrying flags, positions
+// kStageVerts consecutive vertices: it classifies them (hub, solo, tile
+// vertex, no out-edges), compacts the tile vertices' edge ranges in LDS and
+// packs them into tiles, so a tile never leaves its workgroup's vertices.
+// The first pass counts (hubs, tile vertices, solo vertices, tiles), the scan
+// places the counts, the second pass repeats the work and writes the lists.  Repeating it costs 4 bytes per vertex; carrying flags, positions
 // and three separate scans and compactions between passes cost 72.
 //
 // Packing is greedy.  Row ends grow with the vertex, so the vertices that
-// still fit a tile starting at edge a are a prefix (row end - a below
-// kTileMaxEdges; a hub between two tile vertices exceeds that by itself):
-// one wave tests 64 candidates per ballot, at most four ballots a tile.  A
+// still fit a tile starting at edge a are a prefix (row end - a at most
+// kTileMaxEdges; a solo vertex or hub between two tile vertices exceeds that
+// by itself): one ballot of a wave finds a tile's end.  A
 // single lane walking its window vertex by vertex took 106-185 us whatever
 // the graph's size, twice per call.
 //
@@ -163,16 +160,16 @@ constexpr uint32_t kStageVerts = 2048;
 constexpr uint32_t kStageRounds = kStageVerts / kBlock;
 constexpr uint32_t kStageGroups = kStageVerts / 64;  // 64-vertex groups: (round, wave)
 static_assert(kStageGroups <= 64, "one wave scans the group counts");
-static_assert(kTileMaxVerts % 64 == 0, "packing tests whole ballots");
+static_assert(kTileMaxVerts == 64, "packing tests one ballot");
 
 struct StageShared {
     uint32_t off[kStageVerts + 1];
     uint32_t a[kStageVerts];        // edge ranges of the tile vertices
     uint32_t b[kStageVerts];
-    uint32_t act[kStageGroups];     // tile vertices and hubs per group
+    uint32_t act[kStageGroups];     // tile vertices, solo vertices and hubs per group
+    uint32_t solo[kStageGroups];
     uint32_t hub[kStageGroups];
     uint32_t red[kBlock / 64];
-    uint32_t n_act;
 };
 
 struct StageArgs {
@@ -184,13 +181,15 @@ struct StageArgs {
     const uint32_t* tgt;
     const void* lab;
     uint32_t n_vblk;     // vertex blocks (the grid's first)
-    uint4* cnt;          // per vertex block: hubs, tile vertices, no out-edges, tiles
+    uint4* cnt;          // per vertex block: hubs, tile vertices, solo vertices, tiles
     uint32_t wide;       // tgt and lab are aligned for four edges per load
     uint32_t* act;
+    uint32_t* act_off;
     uint32_t* iso;
+    uint32_t* solo;
     uint32_t* hubs;      // (vertex, degree, first edge) each
     uint4* tiles;
-    uint32_t hub_cap, tile_cap;
+    uint32_t hub_cap, solo_cap, tile_cap;
     RunStatus* status;
 };
 
@@ -201,14 +200,9 @@ __device__ uint32_t pack_tiles(const StageShared& S, uint32_t na, uint32_t base,
     uint32_t made = 0;
     for (uint32_t start = 0; start < na; made++) {
         const uint32_t a0 = S.a[start];
-        uint32_t end = start;
-        for (uint32_t q = 0; q < kTileMaxVerts / 64; q++) {
-            const uint32_t j = start + q * 64 + lane;
-            const bool fits = j < na && S.b[j] - a0 < static_cast<uint32_t>(kTileMaxEdges);
-            const uint32_t c = static_cast<uint32_t>(__popcll(__ballot(fits)));
-            end += c;
-            if (c < 64) break;
-        }
+        const uint32_t j = start + lane;
+        const bool fits = j < na && S.b[j] - a0 <= static_cast<uint32_t>(kTileMaxEdges);
+        uint32_t end = start + static_cast<uint32_t>(__popcll(__ballot(fits)));
         if (end == start) end = start + 1;  // offsets that are not monotone: the call fails later
         if (out && lane == 0 && made < room) out[made] = make_uint4(base + start, base + end, a0, S.b[end - 1]);
         start = end;
@@ -223,7 +217,7 @@ __device__ void stage_vertices(const StageArgs& a, StageShared& S) {
     const uint32_t cnt = min(kStageVerts, a.n - base);
     for (uint32_t i = tid; i <= cnt; i += kBlock) S.off[i] = a.row_off[base + i];
     __syncthreads();
-    uint32_t err = 0, types = 0, is_act = 0, is_hub = 0;  // bit r: round r's vertex
+    uint32_t err = 0, types = 0, is_act = 0, is_solo = 0, is_hub = 0;  // bit r: round r's vertex
 #pragma unroll
     for (uint32_t r = 0; r < kStageRounds; r++) {
         const uint32_t i = r * kBlock + tid, v = base + i;
@@ -241,41 +235,50 @@ __device__ void stage_vertices(const StageArgs& a, StageShared& S) {
                 types = max(types, t1 - t0);
             }
         }
-        const bool edges = in && y > x;
-        const bool hub = edges && y - x >= kHubMinDegree;
-        if (hub) is_hub |= 1u << r;
-        if (edges && !hub) is_act |= 1u << r;
-        const uint64_t ba = __ballot(edges && !hub), bh = __ballot(hub);
+        const uint32_t d = in && y > x ? y - x : 0u;
+        const bool act = d && d <= static_cast<uint32_t>(kTileMaxEdges);
+        const bool hub = d > kSoloMaxEdges, solo = d && !act && !hub;
+        is_act |= static_cast<uint32_t>(act) << r;
+        is_solo |= static_cast<uint32_t>(solo) << r;
+        is_hub |= static_cast<uint32_t>(hub) << r;
+        const uint64_t ba = __ballot(act), bs = __ballot(solo), bh = __ballot(hub);
         if (lane == 0) {
-            S.act[r * (kBlock / 64) + wv] = static_cast<uint32_t>(__popcll(ba));
-            S.hub[r * (kBlock / 64) + wv] = static_cast<uint32_t>(__popcll(bh));
+            S.act[r * kWaves + wv] = static_cast<uint32_t>(__popcll(ba));
+            S.solo[r * kWaves + wv] = static_cast<uint32_t>(__popcll(bs));
+            S.hub[r * kWaves + wv] = static_cast<uint32_t>(__popcll(bh));
         }
     }
     __syncthreads();
     // exclusive prefixes of the group counts, one group per lane
-    const uint32_t ca = lane < kStageGroups ? S.act[lane] : 0, ch = lane < kStageGroups ? S.hub[lane] : 0;
-    const uint32_t ia = wave_incl_scan(ca), ih = wave_incl_scan(ch);
-    const uint32_t na = static_cast<uint32_t>(__shfl(static_cast<int>(ia), 63, 64));
-    const uint32_t nh = static_cast<uint32_t>(__shfl(static_cast<int>(ih), 63, 64));
+    const bool grp_lane = lane < kStageGroups;
+    const uint32_t ca = grp_lane ? S.act[lane] : 0, cs = grp_lane ? S.solo[lane] : 0, ch = grp_lane ? S.hub[lane] : 0;
+    const uint32_t ia = wave_incl_scan(ca), is = wave_incl_scan(cs), ih = wave_incl_scan(ch);
+    auto from = [](uint32_t x, uint32_t l) {
+        return static_cast<uint32_t>(__shfl(static_cast<int>(x), static_cast<int>(l), 64));
+    };
+    const uint32_t na = from(ia, 63), ns = from(is, 63), nh = from(ih, 63);
     uint4 at = make_uint4(0, 0, 0, 0);
     if (kEmit) at = a.cnt[blockIdx.x];
+    const uint32_t iso_at = base - at.x - at.y - at.z;
 #pragma unroll
     for (uint32_t r = 0; r < kStageRounds; r++) {
         const uint32_t i = r * kBlock + tid, v = base + i;
-        const uint32_t grp = r * (kBlock / 64) + wv;
-        const uint32_t ga = static_cast<uint32_t>(__shfl(static_cast<int>(ia - ca), static_cast<int>(grp), 64));
-        const uint32_t gh = static_cast<uint32_t>(__shfl(static_cast<int>(ih - ch), static_cast<int>(grp), 64));
-        const bool act = (is_act >> r) & 1, hub = (is_hub >> r) & 1;
+        const uint32_t grp = r * kWaves + wv;
+        const bool act = (is_act >> r) & 1, solo = (is_solo >> r) & 1, hub = (is_hub >> r) & 1;
         const uint64_t lt = (1ull << lane) - 1;
-        const uint32_t pa = ga + static_cast<uint32_t>(__popcll(__ballot(act) & lt));
-        const uint32_t ph = gh + static_cast<uint32_t>(__popcll(__ballot(hub) & lt));
+        const uint32_t pa = from(ia - ca, grp) + static_cast<uint32_t>(__popcll(__ballot(act) & lt));
         if (act) {
             S.a[pa] = S.off[i];
             S.b[pa] = S.off[i + 1];
         }
-        if (kEmit && i < cnt) {
+        if (kEmit) {
+            const uint32_t ps = from(is - cs, grp) + static_cast<uint32_t>(__popcll(__ballot(solo) & lt));
+            const uint32_t ph = from(ih - ch, grp) + static_cast<uint32_t>(__popcll(__ballot(hub) & lt));
             if (act) {
                 a.act[at.y + pa] = v;
+                a.act_off[at.y + pa] = S.off[i];
+            } else if (solo) {
+                if (at.z + ps < a.solo_cap) a.solo[at.z + ps] = v;
             } else if (hub) {
                 if (at.x + ph < a.hub_cap) {
                     uint32_t* h = a.hubs + 3ull * (at.x + ph);
@@ -283,8 +286,8 @@ __device__ void stage_vertices(const StageArgs& a, StageShared& S) {
                     h[1] = S.off[i + 1] - S.off[i];
                     h[2] = S.off[i];
                 }
-            } else {
-                a.iso[at.z + (i - pa - ph)] = v;
+            } else if (i < cnt) {
+                a.iso[iso_at + (i - pa - ps - ph)] = v;
             }
         }
     }
@@ -307,7 +310,7 @@ __device__ void stage_vertices(const StageArgs& a, StageShared& S) {
     if (wv == 0) {
         uint4* out = kEmit && at.w < a.tile_cap ? a.tiles + at.w : nullptr;
         const uint32_t made = pack_tiles(S, na, at.y, out, kEmit ? a.tile_cap - at.w : 0u);
-        if (!kEmit && lane == 0) a.cnt[blockIdx.x] = make_uint4(nh, na, cnt - na - nh, made);
+        if (!kEmit && lane == 0) a.cnt[blockIdx.x] = make_uint4(nh, na, ns, made);
     }
 }
 
@@ -447,42 +450,38 @@ void schedule_hubs(Staged& g, const uint32_t* info, Arena& arena, hipStream_t s)
         }
         host_radix_sort(key, order, 32, k2, v2);
     }
-    // a hub of degree d > kSoloMaxEdges: ceil(d / kTileMaxEdges) chunk
-    // blocks, and 2^b bucket blocks so that a bucket expects at most 3/4
-    // of the LDS slots; the others are solo blocks (no chunks, no buckets)
-    const uint64_t per_bucket = std::max<uint64_t>(1, uint64_t(g.hub_table_slots) * 3 / 4);
-    uint32_t n_big = 0, n_chunks = 0, n_blocks = 0;
+    // a hub of degree d: ceil(d / kChunkEdges) chunk blocks, and 2^b bucket
+    // blocks so that a bucket expects at most 11/12 of the keys that its
+    // rounds take (2,816 of 3,072 by default, five standard deviations)
+    const uint64_t per_bucket = std::max<uint64_t>(1, uint64_t(g.hub_table_slots) * 11 / 16);
+    uint32_t n_chunks = 0, n_blocks = 0;
     std::vector<uint32_t> logb(nh, 0);
     for (uint32_t i = 0; i < nh; i++) {
         const uint32_t d = info[3ull * order[i] + 1];
-        if (d <= kSoloMaxEdges) break;  // by degree: the solo hubs follow
-        n_big = i + 1;
         const uint64_t want = (d + per_bucket - 1) / per_bucket;
         logb[i] = std::min<uint32_t>(static_cast<uint32_t>(bit_width(next_pow2(want)) - 1), kMaxHubLogB);
-        n_chunks += ceil_div(d, kTileMaxEdges);
+        n_chunks += ceil_div(d, kChunkEdges);
         n_blocks += 1u << logb[i];
     }
     // every array of the schedule in one upload
-    std::vector<uint32_t> up(2ull * nh + 5ull * nh + 2ull * n_chunks + 2ull * n_blocks);
+    std::vector<uint32_t> up(6ull * nh + 2ull * n_chunks + 2ull * n_blocks);
     uint64_t* key_off = reinterpret_cast<uint64_t*>(up.data());  // first: 8-byte entries
     uint32_t* hv = up.data() + 2ull * nh;
-    uint32_t *hd = hv + nh, *hl = hd + nh, *hc0 = hl + nh, *hnc = hc0 + nh;
+    uint32_t *hl = hv + nh, *hc0 = hl + nh, *hnc = hc0 + nh;
     uint32_t *ch = hnc + nh, *ce = ch + n_chunks, *bh = ce + n_chunks, *bb = bh + n_blocks;
     uint64_t keys = 0;
     uint32_t nc = 0, nb = 0;
     for (uint32_t i = 0; i < nh; i++) {
         const uint32_t* h = info + 3ull * order[i];
         hv[i] = h[0];
-        hd[i] = h[1];
         hl[i] = logb[i];
         key_off[i] = keys;
         hc0[i] = nc;
-        hnc[i] = i < n_big ? ceil_div(h[1], kTileMaxEdges) : 0;
-        if (i >= n_big) continue;
+        hnc[i] = ceil_div(h[1], kChunkEdges);
         keys += h[1];
         for (uint32_t c = 0; c < hnc[i]; c++) {
             ch[nc] = i;
-            ce[nc++] = h[2] + c * kTileMaxEdges;
+            ce[nc++] = h[2] + c * kChunkEdges;
         }
         for (uint32_t b = 0; b < (1u << logb[i]); b++) {
             bh[nb] = i;
@@ -493,15 +492,11 @@ void schedule_hubs(Staged& g, const uint32_t* info, Arena& arena, hipStream_t s)
     // (pageable memory: the call returns once the source has been read)
     hip_check(hipMemcpyAsync(d, up.data(), up.size() * 4, hipMemcpyHostToDevice, s), "hub schedule");
     auto dev = [&](const uint32_t* host) { return d + (host - up.data()); };
-    g.host_hub_v.assign(hv, hv + nh);
-    g.host_hub_deg.assign(hd, hd + nh);
-    g.n_solo = nh - n_big;
     g.n_hub_chunks = n_chunks;
     g.n_hub_blocks = n_blocks;
     g.hub_keys_total = keys;
     g.hub_key_off = reinterpret_cast<uint64_t*>(d);
     g.hub_v = dev(hv);
-    g.hub_deg = dev(hd);
     g.hub_logb = dev(hl);
     g.hub_chunk0 = dev(hc0);
     g.hub_nchunks = dev(hnc);
@@ -516,7 +511,8 @@ void schedule_hubs(Staged& g, const uint32_t* info, Arena& arena, hipStream_t s)
 void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     const uint32_t n = g.n;
     // status, counts and hub list lie together, as in StageHost
-    const uint32_t hub_cap = static_cast<uint32_t>(g.m / kHubMinDegree) + 1;
+    const uint32_t hub_cap = static_cast<uint32_t>(g.m / (kSoloMaxEdges + 1)) + 1;
+    const uint32_t solo_cap = static_cast<uint32_t>(g.m / (kTileMaxEdges + 1)) + 1;
     const size_t head = sizeof(RunStatus) + sizeof(host->counts);
     uint8_t* dev = arena.alloc<uint8_t>(head + 12ull * hub_cap);
     RunStatus* status = reinterpret_cast<RunStatus*>(dev);
@@ -524,12 +520,12 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     uint32_t* hubs = reinterpret_cast<uint32_t*>(dev + head);
     hip_check(hipMemsetAsync(dev, 0, head, s), "stage status");
     // tiles: one that its edges end is followed by a vertex with which it
-    // would reach kTileMaxEdges (two neighbours share that sum, and the
-    // first vertex of a tile counts for itself and its predecessor), one
-    // that its vertices end holds kTileMaxVerts, one that a hub ends
-    // precedes that hub, and every workgroup's last tile may be short
+    // would pass kTileMaxEdges (a vertex counts for its own tile and, first
+    // in it, for the one before), one that its vertices end holds
+    // kTileMaxVerts, one that a solo vertex or hub ends precedes that
+    // vertex, and every workgroup's last tile may be short
     const uint32_t n_vblk = ceil_div(n, kStageVerts);
-    const uint64_t tile_cap = 2 * g.m / kTileMaxEdges + n / kTileMaxVerts + hub_cap + n_vblk + 1;
+    const uint64_t tile_cap = 2 * g.m / (kTileMaxEdges + 1) + n / kTileMaxVerts + solo_cap + n_vblk + 1;
     StageArgs a{};
     a.row_off = g.row_off;
     a.type_off = g.type_off;
@@ -545,10 +541,13 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
                  ? 1u
                  : 0u;
     a.act = g.act = arena.alloc<uint32_t>(n + 1ull);
+    a.act_off = g.act_off = arena.alloc<uint32_t>(n + 1ull);
     a.iso = g.iso = arena.alloc<uint32_t>(n + 1ull);
+    a.solo = g.solo_v = arena.alloc<uint32_t>(solo_cap);
     a.hubs = hubs;
     a.tiles = g.tiles = arena.alloc<uint4>(tile_cap);
     a.hub_cap = hub_cap;
+    a.solo_cap = solo_cap;
     a.tile_cap = static_cast<uint32_t>(tile_cap);
     a.status = status;
     if (n > 0) {
@@ -576,13 +575,12 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     if (!g.trusted) g.max_label = host->st.max_label;
     g.n_hubs = host->counts[0];
     g.n_act = host->counts[1];
-    g.n_iso = host->counts[2];
+    g.n_solo = host->counts[2];
     g.n_tiles = host->counts[3];
-    if (g.n_hubs > hub_cap || g.n_tiles > tile_cap)
+    g.n_iso = n - g.n_hubs - g.n_act - g.n_solo;
+    if (g.n_hubs > hub_cap || g.n_solo > solo_cap || g.n_tiles > tile_cap)
         throw DeviceError{BSIM_E_DEVICE, "internal: a staging list outgrew its bound"};
-    g.host_hub_v.clear();
-    g.host_hub_deg.clear();
-    g.n_solo = g.n_hub_chunks = g.n_hub_blocks = 0;
+    g.n_hub_chunks = g.n_hub_blocks = 0;
     g.hub_keys_total = 0;
     if (g.n_hubs > with) {
         std::vector<uint32_t> all(3ull * g.n_hubs);
