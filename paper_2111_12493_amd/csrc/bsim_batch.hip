@@ -317,8 +317,7 @@ void batch_summarize(bsim_ctx* ctx, const bsim_graph* graphs, uint32_t G, const 
     const bool view = (p.flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS)) != 0;
     DirectedView dv;
     if (view) {
-        direction_view(u, p.flags, nullptr, dv, arena, s);
-        stage_graph(dv.h, ctx->stage_host, arena, s);
+        direction_view(u, p.flags, nullptr, !(p.flags & BSIM_NO_SUMMARY_EDGES), dv, ctx->stage_host, arena, s);
     }
     const Staged& ur = view ? dv.h : u;
     const Staged& uf = view ? dv.f : u;

@@ -2,18 +2,21 @@
 // Sec. 2.5) as graph views in front of the unchanged refinement kernels.
 //
 // From a staged, validated graph g the device builds
-//   f  the kept edges: those whose label is in the label set P_l (all edges
-//      when there is none), in their own direction, with a per-edge source;
-//      the summary edges are taken from f;
+//   f  the kept edges: those whose label is in the label set P_l (g itself
+//      when there is none), in their own direction; the summary edges are
+//      taken from f;
 //   h  the graph the signatures read: f itself (forward), f reversed
 //      (backward: the pairs of w are its incoming edges (v, l, w)), or f
 //      plus f reversed (both), the reversed copies on labels L + l with
 //      L = max label + 1.  The salt table of h maps label L + l to
 //      M(C_L + 2^31 + l), so an incoming l-edge is salted as an outgoing
 //      edge of label l + 2^31 (a range input labels never reach).
-// Every step is a streaming pass or a scatter over the edges; the order of
-// the edges within a row of h does not matter, since a signature is a set.
-#include "bsim_internal.h"
+// The reversal is a radix sort of the edges by target.  Counting the targets
+// and scattering by a cursor per target, two atomics per edge, serializes on
+// the hubs' counters: on R-MAT 2^22 / 2^25 that took 7.0 ms where the sort
+// and its passes take 1.4.  The order of the edges within a row of h does
+// not matter, since a signature is a set.
+#include "bsim_device.h"
 
 namespace bsim {
 namespace {
@@ -43,10 +46,42 @@ __global__ void __launch_bounds__(kBlock) k_kept_rows(const uint32_t* __restrict
     f_row_off[v] = e < m ? kpos[e] : *m_kept;
 }
 
-// Copy every kept edge (all edges when keep is null) to its position, with
-// the row it leaves from: the largest v with row_off[v] <= e.
+// The source of every edge, from the tile schedule: one wave per tile, solo
+// vertices and hubs by a workgroup each.
+__global__ void __launch_bounds__(kBlock) k_edge_sources(const uint32_t* __restrict__ row_off,
+                                                         const uint4* __restrict__ tiles,
+                                                         const uint32_t* __restrict__ act,
+                                                         const uint32_t* __restrict__ act_off, uint32_t n_tiles,
+                                                         const uint32_t* __restrict__ solo_v, uint32_t n_solo,
+                                                         const uint32_t* __restrict__ hub_v, uint32_t n_hubs,
+                                                         uint32_t* __restrict__ src) {
+    __shared__ struct {
+        uint32_t v[kTileMaxVerts];
+        alignas(8) uint8_t owner[kTileMaxEdges];
+    } sh[kWaves];
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x < n_hubs + n_solo) {
+        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
+        for (uint32_t e = row_off[v] + tid; e < row_off[v + 1]; e += kBlock) src[e] = v;
+        return;
+    }
+    const uint32_t lane = lane_id(), tile = (blockIdx.x - n_hubs - n_solo) * kWaves + (tid >> 6);
+    if (tile >= n_tiles) return;
+    auto& S = sh[tid >> 6];
+    const uint4 td = tiles[tile];
+    const uint32_t nv = td.y - td.x, ne = td.w - td.z;
+    uint32_t off = 0;
+    if (lane < nv) {
+        S.v[lane] = act[td.x + lane];
+        off = act_off[td.x + lane] - td.z;
+    }
+    tile_owners(S.owner, lane < nv, off);
+    for (uint32_t j = lane; j < ne; j += 64) src[td.z + j] = S.v[S.owner[j]];
+}
+
+// The kept edges, in order.
 template <typename LabT>
-__global__ void __launch_bounds__(kBlock) k_kept_edges(const uint32_t* __restrict__ row_off, uint32_t n,
+__global__ void __launch_bounds__(kBlock) k_kept_edges(const uint32_t* __restrict__ src,
                                                        const uint32_t* __restrict__ tgt,
                                                        const LabT* __restrict__ lab, uint32_t m,
                                                        const uint32_t* __restrict__ keep,
@@ -54,68 +89,106 @@ __global__ void __launch_bounds__(kBlock) k_kept_edges(const uint32_t* __restric
                                                        uint32_t* __restrict__ f_src, uint32_t* __restrict__ f_tgt,
                                                        LabT* __restrict__ f_lab) {
     const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m || (keep && !keep[e])) return;
-    uint32_t lo = 0, hi = n;  // row_off[lo] <= e < row_off[hi]
-    while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (row_off[mid] <= e) lo = mid; else hi = mid;
-    }
-    const uint32_t p = keep ? kpos[e] : e;
-    f_src[p] = lo;
+    if (e >= m || !keep[e]) return;
+    const uint32_t p = kpos[e];
+    f_src[p] = src[e];
     f_tgt[p] = tgt[e];
     f_lab[p] = lab[e];
 }
 
-__global__ void __launch_bounds__(kBlock) k_count_targets(const uint32_t* __restrict__ tgt, uint32_t m,
-                                                          uint32_t* __restrict__ indeg) {
+// Sort keys of the reversal: the target above the source and the label, or,
+// where the three do not fit 64 bits, above the edge's number.
+struct RevKey {
+    int lab_bits, src_bits;  // both 0: the low 32 bits are the edge
+    __host__ __device__ int low() const { return src_bits ? lab_bits + src_bits : 32; }
+};
+
+template <typename LabT>
+__global__ void __launch_bounds__(kBlock) k_rev_keys(const uint32_t* __restrict__ src,
+                                                     const uint32_t* __restrict__ tgt,
+                                                     const LabT* __restrict__ lab, uint32_t m, RevKey rk,
+                                                     uint64_t* __restrict__ keys) {
     const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e < m) atomicAdd(&indeg[tgt[e]], 1u);
+    if (e >= m) return;
+    const uint64_t rest = rk.src_bits ? (static_cast<uint64_t>(src[e]) << rk.lab_bits) | lab[e] : e;
+    keys[e] = (static_cast<uint64_t>(tgt[e]) << rk.low()) | rest;
 }
 
-// Both directions: a row holds the vertex's kept out-edges, then its kept
-// in-edges; cursor[v] starts where the in-edges begin.
-__global__ void __launch_bounds__(kBlock) k_both_degrees(const uint32_t* __restrict__ f_row_off,
-                                                         const uint32_t* __restrict__ indeg, uint32_t n,
-                                                         uint32_t* __restrict__ deg) {
+// first[w] = position of the first sorted key with target >= w, w = 0..n.
+// An edge writes the entries of the targets between its predecessor's and its
+// own, up to kRevGap of them; the rest of a longer gap (a graph whose edges
+// end in few vertices) keeps kNoFirst and is searched entry by entry.
+constexpr uint32_t kRevGap = 64, kNoFirst = 0xFFFFFFFFu;
+
+__global__ void __launch_bounds__(kBlock) k_rev_first(const uint64_t* __restrict__ keys, uint32_t m, uint32_t n,
+                                                      int low, uint32_t* __restrict__ first) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i > m) return;
+    const uint32_t lo = i ? static_cast<uint32_t>(keys[i - 1] >> low) + 1 : 0u;
+    const uint32_t hi = i < m ? static_cast<uint32_t>(keys[i] >> low) : n;
+    for (uint32_t w = lo; w <= hi && w - lo < kRevGap; w++) first[w] = i;
+}
+
+__global__ void __launch_bounds__(kBlock) k_rev_gaps(const uint64_t* __restrict__ keys, uint32_t m, uint32_t n,
+                                                     int low, uint32_t* __restrict__ first) {
+    const uint32_t w = blockIdx.x * kBlock + threadIdx.x;
+    if (w > n || first[w] != kNoFirst) return;
+    uint32_t lo = 0, hi = m;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (static_cast<uint32_t>(keys[mid] >> low) < w) lo = mid + 1; else hi = mid;
+    }
+    first[w] = lo;
+}
+
+// Row offsets of h: with both directions a row holds the vertex's kept
+// out-edges, then its kept in-edges.
+__global__ void __launch_bounds__(kBlock) k_both_rows(const uint32_t* __restrict__ f_row_off,
+                                                      const uint32_t* __restrict__ first, uint32_t n,
+                                                      uint32_t* __restrict__ h_row_off) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v < n) deg[v] = (f_row_off[v + 1] - f_row_off[v]) + indeg[v];
+    if (v <= n) h_row_off[v] = f_row_off[v] + first[v];
 }
 
-__global__ void __launch_bounds__(kBlock) k_both_cursor(const uint32_t* __restrict__ f_row_off,
-                                                        const uint32_t* __restrict__ h_row_off, uint32_t n,
-                                                        uint32_t* __restrict__ cursor) {
-    const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v < n) cursor[v] = h_row_off[v] + (f_row_off[v + 1] - f_row_off[v]);
+// Each kept edge (v, l, w) as the edge (w, l + label_add, v) of row w: sorted
+// key i goes to position i, past the out-edges of rows 0..w with both
+// directions (f_row_off set).
+template <typename LabT>
+__global__ void __launch_bounds__(kBlock) k_rev_edges(const uint64_t* __restrict__ keys, uint32_t m, RevKey rk,
+                                                      const uint32_t* __restrict__ f_src,
+                                                      const LabT* __restrict__ f_lab,
+                                                      const uint32_t* __restrict__ f_row_off, uint32_t label_add,
+                                                      uint32_t* __restrict__ h_tgt, uint32_t* __restrict__ h_lab) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= m) return;
+    const uint64_t k = keys[i];
+    const uint32_t w = static_cast<uint32_t>(k >> rk.low());
+    uint32_t v, l;
+    if (rk.src_bits) {
+        v = static_cast<uint32_t>(k >> rk.lab_bits) & ((1u << rk.src_bits) - 1);
+        l = static_cast<uint32_t>(k) & ((1u << rk.lab_bits) - 1);
+    } else {
+        v = f_src[static_cast<uint32_t>(k)];
+        l = static_cast<uint32_t>(f_lab[static_cast<uint32_t>(k)]);
+    }
+    const uint32_t p = f_row_off ? f_row_off[w + 1] + i : i;
+    h_tgt[p] = v;
+    h_lab[p] = l + label_add;
 }
 
+// The kept out-edges in their rows of h: before edge e lie the in-edges of
+// the rows before its own.
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_copy_out(const uint32_t* __restrict__ f_src,
                                                      const uint32_t* __restrict__ f_tgt,
-                                                     const LabT* __restrict__ f_lab,
-                                                     const uint32_t* __restrict__ f_row_off, uint32_t m,
-                                                     const uint32_t* __restrict__ h_row_off,
+                                                     const LabT* __restrict__ f_lab, uint32_t m,
+                                                     const uint32_t* __restrict__ first,
                                                      uint32_t* __restrict__ h_tgt, uint32_t* __restrict__ h_lab) {
     const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
     if (e >= m) return;
-    const uint32_t v = f_src[e];
-    const uint32_t p = h_row_off[v] + (e - f_row_off[v]);
+    const uint32_t p = first[f_src[e]] + e;
     h_tgt[p] = f_tgt[e];
     h_lab[p] = static_cast<uint32_t>(f_lab[e]);
-}
-
-// Each kept edge (v, l, w) as the edge (w, l + label_add, v) of row w.
-template <typename LabT>
-__global__ void __launch_bounds__(kBlock) k_scatter_reverse(const uint32_t* __restrict__ f_src,
-                                                            const uint32_t* __restrict__ f_tgt,
-                                                            const LabT* __restrict__ f_lab, uint32_t m,
-                                                            uint32_t label_add, uint32_t* __restrict__ cursor,
-                                                            uint32_t* __restrict__ h_tgt,
-                                                            uint32_t* __restrict__ h_lab) {
-    const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m) return;
-    const uint32_t p = atomicAdd(&cursor[f_tgt[e]], 1u);
-    h_tgt[p] = f_src[e];
-    h_lab[p] = static_cast<uint32_t>(f_lab[e]) + label_add;
 }
 
 template <typename LabT>
@@ -123,21 +196,17 @@ void build_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* la
                 Arena& arena, hipStream_t s) {
     const uint32_t n = g.n, m = static_cast<uint32_t>(g.m);
     const LabT* lab = static_cast<const LabT*>(g.lab);
+    const bool reversed = (flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS)) != 0;
     Staged& f = out.f;
-    f = Staged{};
-    f.n = n;
-    f.label_bytes = g.label_bytes;
-    f.type_off = g.type_off;
-    f.type_ids = g.type_ids;
-    f.alive = g.alive;
-    f.max_label = g.max_label;
-    f.hub_table_slots = g.hub_table_slots;
-    // the kept edges
+    f = g;
+    out.f_staged = true;
+    uint32_t* src = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
+    if (m)
+        k_edge_sources<<<g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves), kBlock, 0, s>>>(
+            g.row_off, g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo, g.hub_v, g.n_hubs, src);
     uint32_t m_f = m;
-    const uint32_t* keep = nullptr;
-    const uint32_t* kpos = nullptr;
-    uint32_t* f_row_off = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
     if (labels) {
+        // the kept edges
         const uint32_t mask_size = g.max_label + 1;
         uint8_t* mask = arena.alloc<uint8_t>(mask_size);
         hip_check(hipMemsetAsync(mask, 0, mask_size, s), "label mask");
@@ -148,38 +217,42 @@ void build_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* la
             const uint32_t ni = static_cast<uint32_t>(labels->size());
             k_label_mask<<<ceil_div(ni, kBlock), kBlock, 0, s>>>(ids, ni, mask, mask_size);
         }
-        uint32_t* kf = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
-        uint32_t* kp = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
+        uint32_t* keep = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
+        uint32_t* kpos = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
         uint32_t* total = arena.alloc<uint32_t>(1);
-        if (m) k_keep_flags<LabT><<<ceil_div(m, kBlock), kBlock, 0, s>>>(lab, m, mask, kf);
-        scan_exclusive(kf, kp, m, total, arena, s);
-        k_kept_rows<<<ceil_div(static_cast<uint64_t>(n) + 1, kBlock), kBlock, 0, s>>>(g.row_off, n, m, kp, total,
+        uint32_t* f_row_off = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
+        if (m) k_keep_flags<LabT><<<ceil_div(m, kBlock), kBlock, 0, s>>>(lab, m, mask, keep);
+        scan_exclusive(keep, kpos, m, total, arena, s);
+        k_kept_rows<<<ceil_div(static_cast<uint64_t>(n) + 1, kBlock), kBlock, 0, s>>>(g.row_off, n, m, kpos, total,
                                                                                       f_row_off);
         hip_check(hipMemcpyAsync(&m_f, total, 4, hipMemcpyDeviceToHost, s), "kept edge count");
         hip_check(hipStreamSynchronize(s), "kept edge count");
-        keep = kf;
-        kpos = kp;
-    } else {
-        hip_check(hipMemcpyAsync(f_row_off, g.row_off, (static_cast<size_t>(n) + 1) * 4, hipMemcpyDeviceToDevice, s),
-                  "rows");
+        uint32_t* f_src = arena.alloc<uint32_t>(static_cast<size_t>(m_f) + 1);
+        uint32_t* f_tgt = arena.alloc<uint32_t>(static_cast<size_t>(m_f) + 1);
+        LabT* f_lab = arena.alloc<LabT>(static_cast<size_t>(m_f) + 1);
+        if (m)
+            k_kept_edges<LabT><<<ceil_div(m, kBlock), kBlock, 0, s>>>(src, g.tgt, lab, m, keep, kpos, f_src, f_tgt,
+                                                                      f_lab);
+        f = Staged{};
+        f.n = n;
+        f.m = m_f;
+        f.label_bytes = g.label_bytes;
+        f.row_off = f_row_off;
+        f.tgt = f_tgt;
+        f.lab = f_lab;
+        f.type_off = g.type_off;
+        f.type_ids = g.type_ids;
+        f.alive = g.alive;
+        f.max_label = g.max_label;
+        f.hub_table_slots = g.hub_table_slots;
+        f.trusted = true;
+        out.f_staged = false;
+        src = f_src;
     }
-    f.m = m_f;
-    f.row_off = f_row_off;
-    uint32_t* f_src = arena.alloc<uint32_t>(static_cast<size_t>(m_f) + 1);
-    uint32_t* f_tgt = arena.alloc<uint32_t>(static_cast<size_t>(m_f) + 1);
-    LabT* f_lab = arena.alloc<LabT>(static_cast<size_t>(m_f) + 1);
-    if (m) k_kept_edges<LabT><<<ceil_div(m, kBlock), kBlock, 0, s>>>(g.row_off, n, g.tgt, lab, m, keep, kpos, f_src,
-                                                                     f_tgt, f_lab);
-    f.src = f_src;
-    f.tgt = f_tgt;
-    f.lab = f_lab;
     hip_check(hipGetLastError(), "kept edges");
-
     Staged& h = out.h;
-    if (!(flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS))) {
+    if (!reversed) {
         h = f;
-        h.src = nullptr;  // h gets a tile schedule of its own
-        h.trusted = true;
         return;
     }
     const bool both = (flags & BSIM_BOTH_DIRECTIONS) != 0;
@@ -188,32 +261,29 @@ void build_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* la
         throw DeviceError{BSIM_E_UNSUPPORTED, "both edge directions together reach 2^32 edges"};
     const uint32_t L = g.max_label + 1;
     if (both && L > (1u << 24)) throw DeviceError{BSIM_E_UNSUPPORTED, "edge labels must be < 2^24"};
-    uint32_t* indeg = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
-    hip_check(hipMemsetAsync(indeg, 0, (static_cast<size_t>(n) + 1) * 4, s), "in-degrees");
-    if (m_f) k_count_targets<<<ceil_div(m_f, kBlock), kBlock, 0, s>>>(f_tgt, m_f, indeg);
-    uint32_t* h_row_off = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
-    uint32_t* cursor = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
+    const LabT* f_lab = static_cast<const LabT*>(f.lab);
+    const int vbits = std::max(1, bit_width(n ? n - 1 : 0)), lbits = std::max(1, bit_width(g.max_label));
+    const RevKey rk = 2 * vbits + lbits <= 64 && vbits < 32 ? RevKey{lbits, vbits} : RevKey{0, 0};
+    uint64_t* keys = arena.alloc<uint64_t>(static_cast<size_t>(m_f) + 1);
+    uint64_t* keys2 = arena.alloc<uint64_t>(static_cast<size_t>(m_f) + 1);
+    uint32_t* first = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
+    uint32_t* h_row_off = both ? arena.alloc<uint32_t>(static_cast<size_t>(n) + 1) : first;
     uint32_t* h_tgt = arena.alloc<uint32_t>(m_h + 1);
     uint32_t* h_lab = arena.alloc<uint32_t>(m_h + 1);
-    const uint32_t gn = std::max<uint32_t>(ceil_div(n, kBlock), 1);
-    if (both) {
-        uint32_t* deg = arena.alloc<uint32_t>(static_cast<size_t>(n) + 1);
-        if (n) k_both_degrees<<<gn, kBlock, 0, s>>>(f_row_off, indeg, n, deg);
-        scan_exclusive(deg, h_row_off, n, h_row_off + n, arena, s);
-        if (n) k_both_cursor<<<gn, kBlock, 0, s>>>(f_row_off, h_row_off, n, cursor);
-        if (m_f) {
-            k_copy_out<LabT><<<ceil_div(m_f, kBlock), kBlock, 0, s>>>(f_src, f_tgt, f_lab, f_row_off, m_f, h_row_off,
-                                                                      h_tgt, h_lab);
-            k_scatter_reverse<LabT><<<ceil_div(m_f, kBlock), kBlock, 0, s>>>(f_src, f_tgt, f_lab, m_f, L, cursor,
-                                                                             h_tgt, h_lab);
-        }
-    } else {
-        scan_exclusive(indeg, h_row_off, n, h_row_off + n, arena, s);
-        hip_check(hipMemcpyAsync(cursor, h_row_off, static_cast<size_t>(n) * 4, hipMemcpyDeviceToDevice, s),
-                  "cursors");
-        if (m_f)
-            k_scatter_reverse<LabT><<<ceil_div(m_f, kBlock), kBlock, 0, s>>>(f_src, f_tgt, f_lab, m_f, 0u, cursor,
-                                                                             h_tgt, h_lab);
+    const uint32_t gm = std::max<uint32_t>(ceil_div(m_f, kBlock), 1);
+    if (m_f) {
+        k_rev_keys<LabT><<<gm, kBlock, 0, s>>>(src, f.tgt, f_lab, m_f, rk, keys);
+        keys = radix_sort(keys, keys2, m_f, rk.low() + vbits, arena, s, rk.low());
+    }
+    const uint32_t gn = ceil_div(static_cast<uint64_t>(n) + 1, kBlock);
+    hip_check(hipMemsetAsync(first, 0xFF, (static_cast<size_t>(n) + 1) * 4, s), "reversed rows");
+    k_rev_first<<<ceil_div(static_cast<uint64_t>(m_f) + 1, kBlock), kBlock, 0, s>>>(keys, m_f, n, rk.low(), first);
+    k_rev_gaps<<<gn, kBlock, 0, s>>>(keys, m_f, n, rk.low(), first);
+    if (both) k_both_rows<<<gn, kBlock, 0, s>>>(f.row_off, first, n, h_row_off);
+    if (m_f) {
+        k_rev_edges<LabT><<<gm, kBlock, 0, s>>>(keys, m_f, rk, src, f_lab, both ? f.row_off : nullptr, both ? L : 0u,
+                                                h_tgt, h_lab);
+        if (both) k_copy_out<LabT><<<gm, kBlock, 0, s>>>(src, f.tgt, f_lab, m_f, first, h_tgt, h_lab);
     }
     hip_check(hipGetLastError(), "direction view");
     h = Staged{};
@@ -234,12 +304,19 @@ void build_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* la
 
 }  // namespace
 
-void direction_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* labels, DirectedView& out,
-                    Arena& arena, hipStream_t s) {
+void direction_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* labels, bool want_edges,
+                    DirectedView& out, StageHost* host, Arena& arena, hipStream_t s) {
     if (g.label_bytes == 2)
         build_view<uint16_t>(g, flags, labels, out, arena, s);
     else
         build_view<uint32_t>(g, flags, labels, out, arena, s);
+    stage_graph(out.h, host, arena, s);
+    if (out.f_staged) return;
+    // the kept edges need a schedule of their own only for the summary edges
+    if (!(flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS)))
+        out.f = out.h;
+    else if (want_edges)
+        stage_graph(out.f, host, arena, s);
 }
 
 }  // namespace bsim

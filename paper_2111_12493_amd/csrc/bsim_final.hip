@@ -263,13 +263,13 @@ __global__ void __launch_bounds__(kBlock) k_unpack(const uint64_t* __restrict__ 
 
 }  // namespace
 
-// Sort m keys ascending on bits [0, bits); returns the buffer holding the
+// Sort m keys ascending on bits [lo, bits); returns the buffer holding the
 // result (a or b).
-uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& arena, hipStream_t s) {
+uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& arena, hipStream_t s, int lo) {
     if (m <= 1) return a;
     const uint32_t nblk = ceil_div(m, kSortTile);
     uint32_t* hist = arena.alloc<uint32_t>(static_cast<size_t>(nblk) * 256);
-    for (int shift = 0; shift < bits; shift += 8) {
+    for (int shift = lo; shift < bits; shift += 8) {
         k_sort_hist<<<nblk, kBlock, 0, s>>>(a, m, shift, nblk, hist);
         scan_exclusive(hist, hist, nblk * 256, nullptr, arena, s);
         k_sort_scatter<<<nblk, kBlock, 0, s>>>(a, b, m, shift, nblk, hist);

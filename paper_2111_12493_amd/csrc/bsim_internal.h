@@ -424,17 +424,18 @@ struct StageHost {
 void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s);
 
 // The graphs of the direction and label parameterizations (Sec. 2.4), built
-// on the device from a staged graph g: f = the edges whose label is in
-// *labels (all edges for labels == nullptr), with per-edge sources, for the
-// summary edges; h = the graph the signatures read (f, f reversed for
-// BSIM_BACKWARD, f plus f reversed on labels max_label + 1 + l for
-// BSIM_BOTH_DIRECTIONS), to be staged and refined.  Arrays live in arena.
+// on the device from a staged graph g and staged themselves: f = the edges
+// whose label is in *labels (all edges for labels == nullptr), for the
+// summary edges (staged if want_edges); h = the graph the signatures read (f,
+// f reversed for BSIM_BACKWARD, f plus f reversed on labels max_label + 1 + l
+// for BSIM_BOTH_DIRECTIONS).  Arrays live in arena.
 struct DirectedView {
     Staged f;
     Staged h;
+    bool f_staged = false;
 };
-void direction_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* labels, DirectedView& out,
-                    Arena& arena, hipStream_t s);
+void direction_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* labels, bool want_edges,
+                    DirectedView& out, StageHost* host, Arena& arena, hipStream_t s);
 
 // Per-run buffers of the refinement loop.
 struct RunBuffers {
@@ -498,9 +499,9 @@ void launch_small_graphs(const Staged& g, const RunBuffers& rb, const SmallPlan&
 // device_max: the largest table the device allows (else the default size).
 uint32_t query_hub_table_slots(int device, bool device_max = false);
 
-// Sort m 64-bit keys ascending on bits [0, bits); returns a or b, whichever
-// holds the result.
-uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& arena, hipStream_t s);
+// Sort m 64-bit keys ascending on bits [lo, bits), stable; returns a or b,
+// whichever holds the result.
+uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& arena, hipStream_t s, int lo = 0);
 
 // Finalize (a8): block ids, block sizes, sorted distinct quotient edges.
 struct FinalOut {

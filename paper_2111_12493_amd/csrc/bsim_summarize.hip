@@ -353,8 +353,7 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     const bool view = labels || (p.flags & (BSIM_BACKWARD | BSIM_BOTH_DIRECTIONS));
     DirectedView dv;
     if (view) {
-        direction_view(g, p.flags, labels, dv, arena, s);
-        stage_graph(dv.h, ctx->stage_host, arena, s);
+        direction_view(g, p.flags, labels, !(p.flags & BSIM_NO_SUMMARY_EDGES), dv, ctx->stage_host, arena, s);
     }
     const Staged& gr = view ? dv.h : g;
     const Staged& gf = view ? dv.f : g;
