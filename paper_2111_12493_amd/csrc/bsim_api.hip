@@ -83,6 +83,11 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
         bsim_ctx_free(c);
         return BSIM_E_NOMEM;
     }
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->final_host), sizeof(FinalHost), hipHostMallocDefault) !=
+        hipSuccess) {
+        bsim_ctx_free(c);
+        return BSIM_E_NOMEM;
+    }
     if (hipHostMalloc(reinterpret_cast<void**>(&c->count_host), kStripes * sizeof(uint32_t),
                       hipHostMallocDefault) != hipSuccess) {
         bsim_ctx_free(c);
@@ -116,6 +121,7 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->status_host) (void)hipHostFree(ctx->status_host);
     if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
+    if (ctx->final_host) (void)hipHostFree(ctx->final_host);
     if (ctx->count_host) (void)hipHostFree(ctx->count_host);
     if (ctx->report_host) (void)hipHostFree(ctx->report_host);
     delete ctx;

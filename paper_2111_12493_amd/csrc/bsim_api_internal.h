@@ -14,6 +14,7 @@ struct bsim_ctx {
     std::string err;
     bsim::RunStatus* status_host = nullptr;  // pinned, 4 entries
     bsim::StageHost* stage_host = nullptr;   // pinned: what staging copies back
+    bsim::FinalHost* final_host = nullptr;   // pinned: what finalize copies back
     uint64_t* report_host = nullptr;         // pinned: kReportRing words, written by refinement launches
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;
@@ -104,7 +105,7 @@ int noalloc_scratch_init(int device, std::string* err);
 // finalize with summary edges into the classes named by rep_prev (their
 // first-occurrence block ids) instead of the final blocks.
 void finalize_prev_level(const Staged& g, const uint32_t* rep, const uint32_t* rep_prev, bool want_edges,
-                         FinalOut& out, Arena& arena, Arena& keep, hipStream_t s);
+                         FinalOut& out, FinalHost* host, Arena& arena, Arena& keep, hipStream_t s);
 
 // Assemble a bsim_result from finalize output (takes ownership of `keep`);
 // hashes_preset: an array of n entries in `keep` to receive the hashes.

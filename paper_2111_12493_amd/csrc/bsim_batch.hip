@@ -393,8 +393,8 @@ void batch_summarize(bsim_ctx* ctx, const bsim_graph* graphs, uint32_t G, const 
 
     Arena keep(s);
     FinalOut fo;
-    finalize(uf, rb.rep, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, arena, keep, s);
-    if (fo.n_blocks != bbase[G]) throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in batch finalize"};
+    fo.n_blocks = static_cast<uint32_t>(bbase[G]);
+    finalize(uf, rb.rep, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, ctx->final_host, arena, keep, s);
     uint64_t* d_bbase = upload_vec(arena, bbase, s);
     uint64_t* hashes = keep.alloc<uint64_t>(u.n + 1ull);
     if (u.n)

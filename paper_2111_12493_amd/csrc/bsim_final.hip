@@ -7,10 +7,11 @@
 // (the block of the smallest vertex is 0), which depends only on the
 // partition:
 //   1. the smallest vertex of each class (atomicMin per class);
-//   2. an exclusive scan over "v is its class's smallest vertex" flags gives
-//      every such vertex its block id;
-//   3. every vertex takes the id of its class's smallest vertex; block sizes
-//      are counted per thread block in LDS first.
+//   2. a bit per vertex "v is its class's smallest vertex", counted per
+//      workgroup; an exclusive scan of the counts gives every such vertex its
+//      block id, which it leaves under its class's name;
+//   3. every vertex takes the id under its class's name; the members besides
+//      the smallest are counted per workgroup in LDS first.
 // Summary edges (Sec. 2.6: edges between vertex summaries) are the distinct
 // (block(v), l, block(w)) triples: packed into one 64-bit key per edge,
 // sorted by an LSD radix sort over the used bits, de-duplicated and unpacked.
@@ -20,60 +21,151 @@ namespace bsim {
 
 namespace {
 
-// Smallest vertex of every class (classes are named by their representative).
+// Smallest vertex of every class.  Classes are named by a member vertex
+// (kOwn: cmin starts as the identity, and only vertices below their
+// representative can lower it) or by a slot of a class index (cmin starts at
+// the largest value).  A class of millions of vertices would have every wave
+// in flight lower the same word: the lanes of a wave that share a class send
+// its smallest, for the first kMinRounds classes among them.  On the names of
+// a resident state of 2^22 R-MAT vertices 480 us became 148, on 2^22 R-MAT
+// vertices of a summary 252 us became 43.
+constexpr int kMinRounds = 4;
+
+__global__ void __launch_bounds__(kBlock) k_fin_init(uint32_t* __restrict__ cmin, uint32_t n) {
+    const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
+    if (v < n) cmin[v] = v;
+}
+
+template <bool kOwn>
 __global__ void __launch_bounds__(kBlock) k_fin_min(const uint32_t* __restrict__ rep,
-                                                    const uint8_t* __restrict__ alive, uint32_t n,
-                                                    uint32_t* cmin) {
-    uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v >= n || (alive && !alive[v])) return;
-    const uint32_t r = rep[v];
-    // the minimum only decreases: skip the atomic once it is below v
-    if (cmin[r] > v) atomicMin(&cmin[r], v);
+                                                    const uint8_t* __restrict__ alive, uint32_t n, uint32_t* cmin) {
+    const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
+    bool pending = v < n && (!alive || alive[v]);
+    const uint32_t r = pending ? rep[v] : 0u;
+    if (kOwn) pending = pending && v < r;
+    for (int round = 0; round < kMinRounds; round++) {
+        const uint64_t ball = __ballot(pending);
+        if (!ball) return;
+        const uint32_t leader = static_cast<uint32_t>(__ffsll(static_cast<long long>(ball)) - 1);
+        const uint32_t lr = static_cast<uint32_t>(__shfl(static_cast<int>(r), static_cast<int>(leader), 64));
+        if (pending && r == lr) {
+            // (the first lane holds the smallest vertex.)  The minimum only
+            // decreases: nothing to do once it is below v, as the device sees
+            // it now; a line of this CU's cache could show the first value
+            // for as long as the kernel runs
+            if (lane_id() == leader &&
+                __hip_atomic_load(&cmin[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v)
+                atomicMin(&cmin[r], v);
+            pending = false;
+        }
+    }
+    if (pending && cmin[r] > v) atomicMin(&cmin[r], v);
 }
 
-__global__ void __launch_bounds__(kBlock) k_fin_rep(const uint32_t* __restrict__ rep,
-                                                    const uint8_t* __restrict__ alive, uint32_t n,
-                                                    const uint32_t* __restrict__ cmin,
-                                                    uint32_t* __restrict__ isrep) {
-    uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v >= n) return;
-    isrep[v] = (!alive || alive[v]) && cmin[rep[v]] == v ? 1u : 0u;
-}
-
-// Block ids, and block sizes counted in an LDS table per block of
-// kIdsPerBlock vertices first, so a block holding millions of vertices
-// costs one global atomic per thread block rather than one per vertex.
+// Workgroups of kIdsPerBlock vertices, a 64-bit word per 64 of them.
 constexpr int kIdsPerThread = 8;
 constexpr int kIdsPerBlock = kBlock * kIdsPerThread;
+constexpr int kIdsWords = kIdsPerBlock / 64;
 constexpr int kIdsSlots = 2 * kIdsPerBlock;
 
+__global__ void __launch_bounds__(kBlock) k_fin_first(const uint32_t* __restrict__ rep,
+                                                      const uint8_t* __restrict__ alive, uint32_t n,
+                                                      const uint32_t* __restrict__ cmin,
+                                                      uint64_t* __restrict__ first, uint32_t* __restrict__ count) {
+    __shared__ uint32_t s_red[kBlock / 64];
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kIdsPerBlock;
+    uint32_t c = 0;
+#pragma unroll
+    for (int r = 0; r < kIdsPerThread; r++) {
+        const uint64_t v = base + r * kBlock + threadIdx.x;
+        const bool is = v < n && (!alive || alive[v]) && cmin[rep[v]] == static_cast<uint32_t>(v);
+        const uint64_t bal = __ballot(is);
+        if (lane_id() == 0) first[static_cast<uint64_t>(blockIdx.x) * kIdsWords + r * kWaves + (threadIdx.x >> 6)] = bal;
+        c += static_cast<uint32_t>(__popcll(bal));
+    }
+    if (lane_id() == 0) s_red[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBlock / 64; i++) c += s_red[i];
+        count[blockIdx.x] = c;
+    }
+}
+
+// The block id of every class's smallest vertex, under the class's name
+// (cmin is not read any more), and a size of one for the block.
+__global__ void __launch_bounds__(kBlock) k_fin_name(const uint32_t* __restrict__ rep,
+                                                     const uint64_t* __restrict__ first,
+                                                     const uint32_t* __restrict__ start, uint32_t* __restrict__ name,
+                                                     uint32_t* __restrict__ sizes) {
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kIdsPerBlock;
+    const uint64_t* word = first + static_cast<uint64_t>(blockIdx.x) * kIdsWords;
+    const uint32_t lane = lane_id();
+    // vertices before each word's: one word per lane (kIdsWords <= 64)
+    const uint32_t c = lane < static_cast<uint32_t>(kIdsWords) ? static_cast<uint32_t>(__popcll(word[lane])) : 0u;
+    const uint32_t excl = wave_incl_sum(c) - c;
+    const uint32_t id0 = start[blockIdx.x];
+#pragma unroll
+    for (int r = 0; r < kIdsPerThread; r++) {
+        const uint32_t g = r * kWaves + (threadIdx.x >> 6);
+        const uint64_t w = word[g];
+        const uint32_t before = static_cast<uint32_t>(__shfl(static_cast<int>(excl), static_cast<int>(g), 64));
+        if ((w >> lane) & 1) {
+            const uint32_t id = id0 + before + static_cast<uint32_t>(__popcll(w & ((1ull << lane) - 1)));
+            name[rep[base + r * kBlock + threadIdx.x]] = id;
+            sizes[id] = 1;
+        }
+    }
+}
+
+// Block ids.  Members besides the smallest are counted in an LDS table per
+// workgroup first, so a block holding millions of vertices costs one global
+// atomic per workgroup rather than one per vertex; most blocks hold one
+// vertex and cost none.
+//
+// Bound: rep and the ids streamed, the names gathered.  With a rank array
+// gathered through the class minimum and every vertex counted, 2^24 uniform
+// vertices took 669 us and 2^27 R-MAT vertices 5.5 ms; now 54 us and 3.2 ms
+// (the naming pass adds 34 and 390 us).
 __global__ void __launch_bounds__(kBlock) k_fin_ids(const uint8_t* __restrict__ alive, uint32_t n,
                                                     const uint32_t* __restrict__ rep,
-                                                    const uint32_t* __restrict__ cmin,
-                                                    const uint32_t* __restrict__ rank,
-                                                    uint32_t* __restrict__ block_ids,
-                                                    uint32_t* __restrict__ sizes) {
+                                                    const uint32_t* __restrict__ name,
+                                                    const uint64_t* __restrict__ first,
+                                                    uint32_t* __restrict__ block_ids, uint32_t* __restrict__ sizes) {
     __shared__ uint32_t s_key[kIdsSlots];
     __shared__ uint32_t s_cnt[kIdsSlots];
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kIdsPerBlock;
+    const uint64_t* word = first + static_cast<uint64_t>(blockIdx.x) * kIdsWords;
+    const uint32_t lane = lane_id();
+    uint32_t bid[kIdsPerThread];
+    uint32_t more = 0;  // bit r: a member to be counted
+#pragma unroll
+    for (int r = 0; r < kIdsPerThread; r++) {
+        const uint64_t v = base + r * kBlock + threadIdx.x;
+        bid[r] = 0xFFFFFFFFu;
+        if (v < n && (!alive || alive[v])) {
+            bid[r] = name[rep[v]];
+            if (!((word[r * kWaves + (threadIdx.x >> 6)] >> lane) & 1)) more |= 1u << r;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kIdsPerThread; r++) {
+        const uint64_t v = base + r * kBlock + threadIdx.x;
+        if (v < n) block_ids[v] = bid[r];
+    }
+    if (!__syncthreads_or(more != 0)) return;
     for (int i = threadIdx.x; i < kIdsSlots; i += kBlock) {
         s_key[i] = 0xFFFFFFFFu;
         s_cnt[i] = 0;
     }
     __syncthreads();
-    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kIdsPerBlock;
+#pragma unroll
     for (int r = 0; r < kIdsPerThread; r++) {
-        const uint64_t vv = base + static_cast<uint64_t>(r) * kBlock + threadIdx.x;
-        if (vv >= n) break;
-        const uint32_t v = static_cast<uint32_t>(vv);
-        uint32_t bid = 0xFFFFFFFFu;
-        if (!alive || alive[v]) bid = rank[cmin[rep[v]]];
-        block_ids[v] = bid;
-        if (bid == 0xFFFFFFFFu) continue;
-        uint32_t slot = (bid * 2654435761u) & (kIdsSlots - 1);
+        if (!((more >> r) & 1)) continue;
+        uint32_t slot = (bid[r] * 2654435761u) & (kIdsSlots - 1);
         for (;;) {
             uint32_t cur = s_key[slot];
-            if (cur == 0xFFFFFFFFu) cur = atomicCAS(&s_key[slot], 0xFFFFFFFFu, bid);
-            if (cur == 0xFFFFFFFFu || cur == bid) break;
+            if (cur == 0xFFFFFFFFu) cur = atomicCAS(&s_key[slot], 0xFFFFFFFFu, bid[r]);
+            if (cur == 0xFFFFFFFFu || cur == bid[r]) break;
             slot = (slot + 1) & (kIdsSlots - 1);
         }
         atomicAdd(&s_cnt[slot], 1u);
@@ -281,38 +373,39 @@ uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& aren
 
 namespace {
 
-// First-occurrence block ids of the classes named by `rep` into ids[n], the
-// block sizes into sizes_preset or a new array of `arena`; returns the
-// block count.
-uint32_t number_blocks(const Staged& g, const uint32_t* rep, uint32_t* ids, uint32_t** sizes_out, Arena& arena,
-                       hipStream_t s, uint32_t* sizes_preset = nullptr, uint64_t n_ids = 0) {
+// First-occurrence block ids of the nb classes named by `rep` into ids[n],
+// the block sizes into sizes_preset or a new array of `arena`; *seen receives
+// the number of classes found.
+void number_blocks(const Staged& g, const uint32_t* rep, uint32_t nb, uint32_t* ids, uint32_t** sizes_out,
+                   uint32_t* seen, Arena& arena, hipStream_t s, uint32_t* sizes_preset = nullptr,
+                   uint64_t n_ids = 0) {
     const uint32_t n = g.n;
     // class names are vertex ids, or below n_ids when given
-    const uint64_t ids_cap = std::max<uint64_t>(n, n_ids);
-    uint32_t* cmin = arena.alloc<uint32_t>(ids_cap + 1);
-    uint32_t* isrep = arena.alloc<uint32_t>(n);
-    uint32_t* rank = arena.alloc<uint32_t>(n);
-    uint32_t* total = arena.alloc<uint32_t>(1);
-    const uint32_t gb = std::max<uint32_t>(ceil_div(n, kBlock), 1);
-    hip_check(hipMemsetAsync(cmin, 0xFF, (ids_cap + 1) * 4, s), "class minima");
-    if (n) {
-        k_fin_min<<<gb, kBlock, 0, s>>>(rep, g.alive, n, cmin);
-        k_fin_rep<<<gb, kBlock, 0, s>>>(rep, g.alive, n, cmin, isrep);
-    }
-    scan_exclusive(isrep, rank, n, total, arena, s);
-    uint32_t nb = 0;
-    hip_check(hipMemcpyAsync(&nb, total, 4, hipMemcpyDeviceToHost, s), "block count");
-    hip_check(hipStreamSynchronize(s), "block count sync");
-    uint32_t* sizes = sizes_preset ? sizes_preset : arena.alloc<uint32_t>(nb + 1);
-    hip_check(hipMemsetAsync(sizes, 0, (static_cast<size_t>(nb) + 1) * 4, s), "sizes");
-    if (n) k_fin_ids<<<ceil_div(n, kIdsPerBlock), kBlock, 0, s>>>(g.alive, n, rep, cmin, rank, ids, sizes);
-    hip_check(hipGetLastError(), "finalize launch");
+    const uint64_t names = n_ids ? n_ids : n;
+    uint32_t* name = arena.alloc<uint32_t>(names + 1);
+    const uint32_t gb = ceil_div(n, kIdsPerBlock);
+    uint64_t* first = arena.alloc<uint64_t>(static_cast<size_t>(gb) * kIdsWords + 1);
+    uint32_t* count = arena.alloc<uint32_t>(gb + 1ull);
+    uint32_t* sizes = sizes_preset ? sizes_preset : arena.alloc<uint32_t>(nb + 1ull);
     *sizes_out = sizes;
-    return nb;
+    if (!n) return;
+    const uint32_t gv = ceil_div(n, kBlock);
+    if (n_ids) {
+        hip_check(hipMemsetAsync(name, 0xFF, names * 4, s), "class minima");
+        k_fin_min<false><<<gv, kBlock, 0, s>>>(rep, g.alive, n, name);
+    } else {
+        k_fin_init<<<gv, kBlock, 0, s>>>(name, n);
+        k_fin_min<true><<<gv, kBlock, 0, s>>>(rep, g.alive, n, name);
+    }
+    k_fin_first<<<gb, kBlock, 0, s>>>(rep, g.alive, n, name, first, count);
+    scan_exclusive(count, count, gb, seen, arena, s);
+    k_fin_name<<<gb, kBlock, 0, s>>>(rep, first, count, name, sizes);
+    k_fin_ids<<<gb, kBlock, 0, s>>>(g.alive, n, rep, name, first, ids, sizes);
+    hip_check(hipGetLastError(), "finalize launch");
 }
 
 void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_prev, bool want_edges,
-                    FinalOut& out, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids);
+                    FinalOut& out, FinalHost* host, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids);
 
 // Block ids and sizes are numbered in the call's work memory and copied
 // into the result's own arrays at the end: the kernels that count the sizes
@@ -320,14 +413,14 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
 // 10-20 % slower on rmat27 when these arrays were result allocations of
 // their own beside the work memory's other random-access arrays.
 void finalize_impl(const Staged& g, const uint32_t* rep, const uint32_t* rep_prev, bool want_edges,
-                   FinalOut& out, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids = 0) {
+                   FinalOut& out, FinalHost* host, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids = 0) {
     if (out.preset) {
-        finalize_edges(g, rep, rep_prev, want_edges, out, arena, keep, s, n_ids);
+        finalize_edges(g, rep, rep_prev, want_edges, out, host, arena, keep, s, n_ids);
         return;
     }
     uint32_t* ids = keep.alloc<uint32_t>(g.n);
     out.block_ids = arena.alloc<uint32_t>(g.n);
-    finalize_edges(g, rep, rep_prev, want_edges, out, arena, keep, s, n_ids);
+    finalize_edges(g, rep, rep_prev, want_edges, out, host, arena, keep, s, n_ids);
     uint32_t* sizes = keep.alloc<uint32_t>(out.n_blocks + 1ull);
     if (g.n)
         hip_check(hipMemcpyAsync(ids, out.block_ids, static_cast<size_t>(g.n) * 4, hipMemcpyDeviceToDevice, s),
@@ -339,24 +432,24 @@ void finalize_impl(const Staged& g, const uint32_t* rep, const uint32_t* rep_pre
 }
 
 void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_prev, bool want_edges,
-                    FinalOut& out, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids) {
+                    FinalOut& out, FinalHost* host, Arena& arena, Arena& keep, hipStream_t s, uint64_t n_ids) {
     const uint32_t n = g.n;
-    const uint32_t nb = number_blocks(g, rep, out.block_ids, &out.block_sizes, arena, s,
-                                      out.preset ? out.block_sizes : nullptr, n_ids);
-    out.n_blocks = nb;
-    // the target end of a summary edge: the final blocks, or the blocks of
-    // the previous level's classes
-    const uint32_t* dst_ids = out.block_ids;
-    uint32_t nb_dst = nb;
-    if (rep_prev && want_edges && g.m) {
-        uint32_t* ids = arena.alloc<uint32_t>(n);
-        uint32_t* sizes = nullptr;
-        nb_dst = number_blocks(g, rep_prev, ids, &sizes, arena, s);
-        dst_ids = ids;
-    }
-    uint32_t* total = arena.alloc<uint32_t>(1);
+    const uint32_t nb = out.n_blocks;
+    // the counts that come back to the host, together
+    FinalHost* dev = arena.alloc<FinalHost>(1);
+    hip_check(hipMemsetAsync(dev, 0, sizeof(FinalHost), s), "finalize counts");
+    number_blocks(g, rep, nb, out.block_ids, &out.block_sizes, dev->blocks, arena, s,
+                  out.preset ? out.block_sizes : nullptr, n_ids);
+    const std::function<const FinalHost&()> fetch = [&]() -> const FinalHost& {
+        hip_check(hipMemcpyAsync(host, dev, sizeof(FinalHost), hipMemcpyDeviceToHost, s), "finalize counts");
+        hip_check(hipStreamSynchronize(s), "finalize counts");
+        if (host->blocks[0] != nb)
+            throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
+        return *host;
+    };
     out.n_se = 0;
     if (!want_edges || g.m == 0) {
+        fetch();
         if (!out.preset) {
             out.se_src = keep.alloc<uint32_t>(1);
             out.se_label = keep.alloc<uint32_t>(1);
@@ -364,11 +457,24 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
         }
         return;
     }
+    // the target end of a summary edge: the final blocks, or the blocks of
+    // the previous level's classes
+    const uint32_t* dst_ids = out.block_ids;
+    uint32_t nb_dst = nb;
+    if (rep_prev) {
+        uint32_t* ids = arena.alloc<uint32_t>(n);
+        uint32_t* sizes = nullptr;
+        nb_dst = out.n_prev_blocks;
+        number_blocks(g, rep_prev, nb_dst, ids, &sizes, dev->prev_blocks, arena, s);
+        dst_ids = ids;
+    }
     const uint32_t nb_max = std::max(nb, nb_dst);
     const int bb = std::max(1, bit_width(nb_max ? nb_max - 1 : 0));
     const int lb = std::max(1, bit_width(g.max_label));
     if (bucketed_summary_edges_fit(g, lb, bb)) {
-        bucketed_summary_edges(g, out.block_ids, nb, dst_ids, lb, bb, out, arena, keep, s);
+        bucketed_summary_edges(g, out.block_ids, nb, dst_ids, lb, bb, out, dev, fetch, arena, keep, s);
+        if (rep_prev && host->prev_blocks[0] != nb_dst)
+            throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
         return;
     }
     if (2 * bb + lb > 64)
@@ -399,10 +505,11 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
     uint32_t* flag = arena.alloc<uint32_t>(m);
     uint32_t* pos = arena.alloc<uint32_t>(m);
     k_unique_flags<<<ceil_div(m, kBlock), kBlock, 0, s>>>(sorted, m, flag);
-    scan_exclusive(flag, pos, m, total, arena, s);
-    uint32_t nse = 0;
-    hip_check(hipMemcpyAsync(&nse, total, 4, hipMemcpyDeviceToHost, s), "edge count");
-    hip_check(hipStreamSynchronize(s), "edge count sync");
+    scan_exclusive(flag, pos, m, dev->edges, arena, s);
+    fetch();
+    if (rep_prev && host->prev_blocks[0] != nb_dst)
+        throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
+    const uint32_t nse = host->edges[0];
     out.n_se = nse;
     if (!out.preset) {
         out.se_src = keep.alloc<uint32_t>(nse);
@@ -416,14 +523,14 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
 
 }  // namespace
 
-void finalize(const Staged& g, const uint32_t* rep, bool want_edges, FinalOut& out, Arena& arena,
+void finalize(const Staged& g, const uint32_t* rep, bool want_edges, FinalOut& out, FinalHost* host, Arena& arena,
               Arena& keep, hipStream_t s, uint64_t n_ids) {
-    finalize_impl(g, rep, nullptr, want_edges, out, arena, keep, s, n_ids);
+    finalize_impl(g, rep, nullptr, want_edges, out, host, arena, keep, s, n_ids);
 }
 
 void finalize_prev_level(const Staged& g, const uint32_t* rep, const uint32_t* rep_prev, bool want_edges,
-                         FinalOut& out, Arena& arena, Arena& keep, hipStream_t s) {
-    finalize_impl(g, rep, rep_prev, want_edges, out, arena, keep, s);
+                         FinalOut& out, FinalHost* host, Arena& arena, Arena& keep, hipStream_t s) {
+    finalize_impl(g, rep, rep_prev, want_edges, out, host, arena, keep, s);
 }
 
 }  // namespace bsim

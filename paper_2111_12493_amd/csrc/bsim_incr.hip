@@ -1390,8 +1390,9 @@ bsim_result* finish(bsim_state* st, Arena& arena, float* ms_cls, ResultReserve* 
     FinalOut fo;
     if (rr) fo = rr->fo;
     // the classes of level k_done, named by their slots in that level's table
-    finalize(g, st->ci_cid[k_done].p, !(st->flags & BSIM_NO_SUMMARY_EDGES), fo, arena, keep, s, st->ci_cap);
-    if (fo.n_blocks != nk[k_done]) throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
+    fo.n_blocks = static_cast<uint32_t>(nk[k_done]);
+    finalize(g, st->ci_cid[k_done].p, !(st->flags & BSIM_NO_SUMMARY_EDGES), fo, st->ctx->final_host, arena, keep, s,
+             st->ci_cap);
     LoopResult lr;
     lr.k_done = k_done;
     lr.fixpoint = fix;

@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -357,9 +358,9 @@ inline uint64_t split_table_slots(uint64_t n) { return table_slots(n + n / 2 + 1
 // ------------------------------------------------------- library internals
 
 // Exclusive prefix sum of n uint32 values (out may alias in); the total is
-// written to total_dev[0] when total_dev is non-null.
+// written to total_dev[0] and total2_dev[0] where they are non-null.
 void scan_exclusive(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total_dev,
-                    Arena& arena, hipStream_t s);
+                    Arena& arena, hipStream_t s, uint32_t* total2_dev = nullptr);
 
 // Graph after staging: device CSR plus the tile / hub schedule.
 struct Staged {
@@ -509,13 +510,24 @@ struct FinalOut {
     // (block_ids and block_sizes for n + 1 entries, the summary-edge columns
     // for m + 1), and finalize allocates none of them
     bool preset = false;
-    uint32_t n_blocks = 0;
+    uint32_t n_blocks = 0;        // in: the refinement's class count
+    uint32_t n_prev_blocks = 0;   // in: that of the previous level, for its summary edges
     uint64_t n_se = 0;
     uint32_t* block_ids = nullptr;
     uint32_t* block_sizes = nullptr;
     uint32_t* se_src = nullptr;
     uint32_t* se_label = nullptr;
     uint32_t* se_dst = nullptr;
+};
+
+// Counts that finalize brings back to the host (pinned there), each on a cache
+// line of its own: many workgroups add to the segment counts.
+struct FinalHost {
+    uint32_t blocks[32];
+    uint32_t prev_blocks[32];
+    uint32_t med[32], big[32], huge[32];  // segments by size class
+    uint32_t huge_values[32];
+    uint32_t edges[32];
 };
 
 // Class index of a resident state, one per level (bsim_cindex.hip): a hash
@@ -554,11 +566,14 @@ void ci_update(const CiLevel& L, const uint32_t* cid_prev, const uint64_t* h, co
 // block (bid, nb blocks) and sorted within each block; false from the fit
 // test means the keys or the layout need the global sort instead.
 bool bucketed_summary_edges_fit(const Staged& g, int lb, int bb);
+// dev: the device's counts; fetch brings them to the host.
 void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, const uint32_t* dst_ids, int lb,
-                            int bb, FinalOut& out, Arena& arena, Arena& keep, hipStream_t s);
+                            int bb, FinalOut& out, FinalHost* dev, const std::function<const FinalHost&()>& fetch,
+                            Arena& arena, Arena& keep, hipStream_t s);
 
-// Blocks are the classes given by rep[] (first-occurrence numbering).
-void finalize(const Staged& g, const uint32_t* rep, bool want_edges, FinalOut& out, Arena& arena,
+// Blocks are the out.n_blocks classes given by rep[] (first-occurrence
+// numbering); host: pinned.
+void finalize(const Staged& g, const uint32_t* rep, bool want_edges, FinalOut& out, FinalHost* host, Arena& arena,
               Arena& keep, hipStream_t s, uint64_t n_ids = 0);
 
 }  // namespace bsim

@@ -103,9 +103,8 @@ void run(bsim_ctx* ctx, const bsim_graph& graph, const bsim_params& p, bsim_noal
     alloc_run_buffers(g, rb, arena, s);
     LoopResult lr = run_refinement(ctx, g, p, rb, nullptr, arena, nullptr, false);
     FinalOut fo;
-    finalize(g, rb.rep, edges, fo, arena, arena, s);
-    if (fo.n_blocks != lr.blocks_per_iter.back())
-        throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
+    fo.n_blocks = lr.blocks_per_iter.back();
+    finalize(g, rb.rep, edges, fo, ctx->final_host, arena, arena, s);
     // results into the caller's arrays
     if (n) {
         hip_check(hipMemcpyAsync(out.hashes, lr.h_final, n * 8, hipMemcpyDeviceToDevice, s), "hashes");

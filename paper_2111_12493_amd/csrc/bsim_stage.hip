@@ -68,8 +68,42 @@ __global__ void __launch_bounds__(kBlock) k_scan_reduce(const uint32_t* __restri
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
+// Up to kScanSmall values in one launch of one workgroup: three launches take
+// some 15 us in a stream of small kernels whatever they do, this one 4 to 6.
+constexpr uint32_t kScanSmallItems = 16;
+constexpr uint32_t kScanSmall = 1024 * kScanSmallItems;
+
+__global__ void __launch_bounds__(1024) k_scan_small(const uint32_t* in, uint32_t* out, uint32_t n,
+                                                     uint32_t* total, uint32_t* total2) {
+    __shared__ uint32_t s_w[16];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const uint32_t per = (n + 1023) / 1024;  // <= kScanSmallItems
+    const uint32_t j0 = tid * per;
+    uint32_t v[kScanSmallItems], x = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kScanSmallItems; i++) {
+        v[i] = i < per && j0 + i < n ? in[j0 + i] : 0u;
+        x += v[i];
+    }
+    const uint32_t inc = wave_incl_scan(x);
+    if (lane == 63) s_w[wid] = inc;
+    __syncthreads();
+    uint32_t run = inc - x, tot = 0;
+    for (uint32_t i = 0; i < 16; i++) {
+        if (i < wid) run += s_w[i];
+        tot += s_w[i];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kScanSmallItems; i++) {
+        if (i < per && j0 + i < n) out[j0 + i] = run;
+        run += v[i];
+    }
+    if (tid == 0 && total) *total = tot;
+    if (tid == 0 && total2) *total2 = tot;
+}
+
 __global__ void __launch_bounds__(1024) k_scan_spine(uint32_t* __restrict__ sums, uint32_t nb,
-                                                    uint32_t* __restrict__ total) {
+                                                    uint32_t* __restrict__ total, uint32_t* __restrict__ total2) {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_carry;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -93,6 +127,7 @@ __global__ void __launch_bounds__(1024) k_scan_spine(uint32_t* __restrict__ sums
         __syncthreads();
     }
     if (threadIdx.x == 0 && total) *total = s_carry;
+    if (threadIdx.x == 0 && total2) *total2 = s_carry;
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_down(const uint32_t* in, uint32_t* out, uint32_t n,
@@ -118,15 +153,16 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const uint32_t* in, uint32
 }  // namespace
 
 void scan_exclusive(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total_dev,
-                    Arena& arena, hipStream_t s) {
-    if (n == 0) {
-        if (total_dev) hip_check(hipMemsetAsync(total_dev, 0, sizeof(uint32_t), s), "scan");
+                    Arena& arena, hipStream_t s, uint32_t* total2_dev) {
+    if (n <= kScanSmall) {
+        k_scan_small<<<1, 1024, 0, s>>>(in, out, n, total_dev, total2_dev);
+        hip_check(hipGetLastError(), "scan launch");
         return;
     }
     uint32_t nb = ceil_div(n, kScanTile);
     uint32_t* sums = arena.alloc<uint32_t>(nb);
     k_scan_reduce<<<nb, kBlock, 0, s>>>(in, n, sums);
-    k_scan_spine<<<1, 1024, 0, s>>>(sums, nb, total_dev);
+    k_scan_spine<<<1, 1024, 0, s>>>(sums, nb, total_dev, total2_dev);
     k_scan_down<<<nb, kBlock, 0, s>>>(in, out, n, sums);
     hip_check(hipGetLastError(), "scan launch");
 }

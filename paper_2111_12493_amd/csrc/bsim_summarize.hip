@@ -365,12 +365,14 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     LoopResult lr = run_refinement(ctx, gr, p, rb, nullptr, arena, rep_prev);
     hip_check(hipEventRecord(ev[2], s), "event");
     FinalOut fo;
+    fo.n_blocks = lr.blocks_per_iter.back();
+    // (at a fixpoint the previous level's count is the same)
+    fo.n_prev_blocks = lr.blocks_per_iter[lr.k_done && lr.k_done == p.k_max ? lr.k_done - 1 : lr.k_done];
     if (prev_edges)
-        finalize_prev_level(gf, rb.rep, rep_prev, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, arena, keep, s);
+        finalize_prev_level(gf, rb.rep, rep_prev, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, ctx->final_host, arena, keep,
+                            s);
     else
-        finalize(gf, rb.rep, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, arena, keep, s);
-    if (fo.n_blocks != lr.blocks_per_iter.back())
-        throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
+        finalize(gf, rb.rep, !(p.flags & BSIM_NO_SUMMARY_EDGES), fo, ctx->final_host, arena, keep, s);
     bsim_result* r = make_result(ctx, g, lr, lr.h_final, fo, keep, p.flags);
     hip_check(hipEventRecord(ev[3], s), "event");
     hip_check(hipEventSynchronize(ev[3]), "event");
