@@ -2,6 +2,7 @@
 // and results.  The call sequence of bsim_summarize follows Algorithm 4:
 // initialization (type hashes), k hash-messaging phases, FindAndMerge; the
 // phase loop stops at the fixpoint as described in bsim.h.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -36,6 +37,146 @@ void ctx_back_arena(bsim_ctx* ctx, Arena& arena, size_t at_least) {
 
 void ctx_note_demand(bsim_ctx* ctx, const Arena& arena) {
     if (ctx->keep_work) ctx->work_want = std::max(ctx->work_want, arena.demand());
+}
+
+void* PinnedPool::take(size_t bytes, size_t* cap) {
+    // powers of two below 1 MiB, whole MiB above, so that calls of about one
+    // size find each other's blocks
+    const size_t want = bytes <= (1u << 20) ? static_cast<size_t>(next_pow2(std::max<size_t>(bytes, 4096)))
+                                            : (bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1);
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t best = free_.size();
+        for (size_t i = 0; i < free_.size(); i++)
+            if (free_[i].second >= want && free_[i].second <= 2 * want &&
+                (best == free_.size() || free_[i].second < free_[best].second))
+                best = i;
+        if (best < free_.size()) {
+            void* p = free_[best].first;
+            *cap = free_[best].second;
+            kept_ -= *cap;
+            free_[best] = free_.back();
+            free_.pop_back();
+            return p;
+        }
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    *cap = want;
+    return p;
+}
+
+void PinnedPool::give(void* p, size_t cap) {
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (!closed_ && kept_ + cap <= kPinnedKeep) {
+            try {
+                free_.emplace_back(p, cap);
+                kept_ += cap;
+                return;
+            } catch (const std::bad_alloc&) {
+            }
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+void PinnedPool::close() {
+    std::vector<std::pair<void*, size_t>> all;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        closed_ = true;
+        all.swap(free_);
+        kept_ = 0;
+    }
+    for (auto& b : all) (void)hipHostFree(b.first);
+}
+
+HostBlock::HostBlock(const std::shared_ptr<PinnedPool>& from, size_t bytes) {
+    // (pinning gigabytes takes longer than the copy that it speeds up)
+    if (from && bytes <= PinnedPool::kPinnedKeep) p = from->take(bytes, &cap);
+    if (p) {
+        pool = from;
+        return;
+    }
+    p = malloc(bytes ? bytes : 8);
+    if (!p) throw DeviceError{BSIM_E_NOMEM, "host result allocation failed"};
+}
+
+HostBlock::~HostBlock() {
+    if (pool)
+        pool->give(p, cap);
+    else
+        free(p);
+}
+
+namespace {
+
+constexpr int kCopyRanges = 8;
+struct CopyArgs {
+    uint32_t* dst[kCopyRanges];
+    const uint32_t* src[kCopyRanges];
+    uint32_t words[kCopyRanges];
+};
+
+__global__ void __launch_bounds__(kBlock) k_copy_ranges(CopyArgs a) {
+    const uint32_t first = blockIdx.x * kBlock + threadIdx.x, step = gridDim.x * kBlock;
+#pragma unroll
+    for (int i = 0; i < kCopyRanges; i++)
+        for (uint32_t j = first; j < a.words[i]; j += step) a.dst[i][j] = a.src[i][j];
+}
+
+}  // namespace
+
+// Below kCopyOne bytes the launch of a copy costs more than its bytes.
+constexpr size_t kCopyOne = 1u << 20;
+
+void copy_ranges(void* const* dst, const void* const* src, const size_t* bytes, int n, hipStream_t s) {
+    size_t total = 0, most = 0;
+    for (int i = 0; i < n; i++) {
+        total += bytes[i];
+        most = std::max(most, bytes[i]);
+    }
+    if (!total) return;
+    if (total > kCopyOne || n > kCopyRanges) {
+        for (int i = 0; i < n; i++)
+            if (bytes[i]) hip_check(hipMemcpyAsync(dst[i], src[i], bytes[i], hipMemcpyDefault, s), "copy");
+        return;
+    }
+    CopyArgs a{};
+    for (int i = 0; i < n; i++) {
+        a.dst[i] = static_cast<uint32_t*>(dst[i]);
+        a.src[i] = static_cast<const uint32_t*>(src[i]);
+        a.words[i] = static_cast<uint32_t>(bytes[i] / 4);
+    }
+    k_copy_ranges<<<std::max<uint32_t>(ceil_div(most / 4, kBlock), 1), kBlock, 0, s>>>(a);
+    hip_check(hipGetLastError(), "copy launch");
+}
+
+// Pageable arrays come back through the runtime's staging buffer, with every
+// page of fresh memory touched for the first time on the way: 125 MB of a
+// batched call's results took 33 ms that way; into pinned blocks that later
+// calls use again they take 2.3.
+std::shared_ptr<HostBlock> host_arrays(bsim_ctx* ctx, void* const* dev, const size_t* bytes, void** base) {
+    size_t at[6], total = 0;
+    for (int i = 0; i < 6; i++) {
+        at[i] = total;
+        total += (bytes[i] + 63) & ~size_t(63);
+    }
+    auto block = std::make_shared<HostBlock>(ctx->host_pool, total);
+    for (int i = 0; i < 6; i++) base[i] = static_cast<char*>(block->p) + at[i];
+    if (block->pool) {
+        copy_ranges(base, dev, bytes, 6, ctx->stream);
+    } else {
+        for (int i = 0; i < 6; i++)
+            if (bytes[i])
+                hip_check(hipMemcpyAsync(base[i], dev[i], bytes[i], hipMemcpyDeviceToHost, ctx->stream), "result copy");
+    }
+    hip_check(hipStreamSynchronize(ctx->stream), "result sync");
+    return block;
 }
 
 void ctx_release_work(bsim_ctx* ctx) {
@@ -73,31 +214,16 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->hub_table_slots = query_hub_table_slots(device);
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->status_host), 4 * sizeof(RunStatus),
-                      hipHostMallocDefault) != hipSuccess) {
-        delete c;
-        return BSIM_E_NOMEM;
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->stage_host), sizeof(StageHost), hipHostMallocDefault) !=
-        hipSuccess) {
-        bsim_ctx_free(c);
-        return BSIM_E_NOMEM;
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->final_host), sizeof(FinalHost), hipHostMallocDefault) !=
-        hipSuccess) {
-        bsim_ctx_free(c);
-        return BSIM_E_NOMEM;
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->count_host), kStripes * sizeof(uint32_t),
-                      hipHostMallocDefault) != hipSuccess) {
-        bsim_ctx_free(c);
-        return BSIM_E_NOMEM;
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->report_host), kReportRing * sizeof(uint64_t),
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->pinned), sizeof(CtxPinned),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         bsim_ctx_free(c);
         return BSIM_E_NOMEM;
     }
+    c->status_host = c->pinned->status;
+    c->stage_host = &c->pinned->stage;
+    c->final_host = &c->pinned->fin;
+    c->count_host = c->pinned->count;
+    c->report_host = c->pinned->report;
     // the allocation-free entry point's scratch on this device (once per device)
     const int rc = noalloc_scratch_init(device, &c->err);
     if (rc != BSIM_OK) {
@@ -119,11 +245,8 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     (void)hipSetDevice(ctx->device);
     ctx_release_work(ctx);
     (void)hipStreamSynchronize(ctx->stream);
-    if (ctx->status_host) (void)hipHostFree(ctx->status_host);
-    if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
-    if (ctx->final_host) (void)hipHostFree(ctx->final_host);
-    if (ctx->count_host) (void)hipHostFree(ctx->count_host);
-    if (ctx->report_host) (void)hipHostFree(ctx->report_host);
+    ctx->host_pool->close();
+    if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
 }
 
@@ -315,7 +438,6 @@ SharedArrays::~SharedArrays() {
         for (void* q : device_ptrs) (void)hipFreeAsync(q, stream);
         (void)hipStreamSynchronize(stream);
     }
-    for (void* q : host_ptrs) free(q);
 }
 }  // namespace bsim
 
@@ -328,7 +450,6 @@ void bsim_result_free(bsim_result* r) {
             for (void* q : p->device_ptrs) (void)hipFreeAsync(q, p->stream);
             (void)hipStreamSynchronize(p->stream);
         }
-        for (void* q : p->host_ptrs) free(q);
         delete p;
     }
     delete r;
@@ -369,7 +490,15 @@ int bsim_result_copy(const bsim_result* r, const char* field, void* dst, uint32_
                              ? hipMemcpyHostToDevice
                              : (dst_mem_kind == BSIM_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice);
     if (hipSetDevice(p->device) != hipSuccess) return BSIM_E_DEVICE;
-    if (hipMemcpyAsync(dst, src, bytes, kind, p->stream) != hipSuccess) return BSIM_E_DEVICE;
+    if (kind == hipMemcpyDeviceToDevice && reinterpret_cast<uintptr_t>(dst) % 4 == 0) {
+        try {
+            copy_ranges(&dst, &src, &bytes, 1, p->stream);
+        } catch (const DeviceError& e) {
+            return e.status;
+        }
+    } else if (hipMemcpyAsync(dst, src, bytes, kind, p->stream) != hipSuccess) {
+        return BSIM_E_DEVICE;
+    }
     if (hipStreamSynchronize(p->stream) != hipSuccess) return BSIM_E_DEVICE;
     return BSIM_OK;
 }

@@ -3,19 +3,68 @@
 
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
 #include "bsim_internal.h"
 
+namespace bsim {
+
+// Pinned host memory that a context's calls move their arrays through: the
+// host arrays of results, and the uploads of small graphs.  Blocks come back
+// when their result is freed, on any thread, and are kept for later calls up
+// to kPinnedKeep bytes; the context's end gives the kept ones back, and
+// blocks still out then are freed as they come.
+class PinnedPool {
+  public:
+    static constexpr size_t kPinnedKeep = 512ull << 20;
+    // A block of at least `bytes`; nullptr when there is no pinned memory.
+    // *cap: its size, for give().
+    void* take(size_t bytes, size_t* cap);
+    void give(void* p, size_t cap);
+    void close();
+
+  private:
+    std::mutex mu_;
+    std::vector<std::pair<void*, size_t>> free_;
+    size_t kept_ = 0;
+    bool closed_ = false;
+};
+
+// One block, owned: pinned from the pool, or ordinary memory where that failed.
+struct HostBlock {
+    std::shared_ptr<PinnedPool> pool;  // nullptr: ordinary memory
+    void* p = nullptr;
+    size_t cap = 0;
+    HostBlock(const std::shared_ptr<PinnedPool>& from, size_t bytes);
+    ~HostBlock();
+    HostBlock(const HostBlock&) = delete;
+    HostBlock& operator=(const HostBlock&) = delete;
+};
+
+// What the device and the host tell each other during a call, in one pinned
+// allocation.
+struct CtxPinned {
+    RunStatus status[4];
+    StageHost stage;
+    FinalHost fin;
+    uint32_t count[64];
+    uint64_t report[kReportRing];
+};
+
+}  // namespace bsim
+
 struct bsim_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     std::string err;
-    bsim::RunStatus* status_host = nullptr;  // pinned, 4 entries
-    bsim::StageHost* stage_host = nullptr;   // pinned: what staging copies back
-    bsim::FinalHost* final_host = nullptr;   // pinned: what finalize copies back
-    uint64_t* report_host = nullptr;         // pinned: kReportRing words, written by refinement launches
+    bsim::CtxPinned* pinned = nullptr;
+    bsim::RunStatus* status_host = nullptr;  // parts of *pinned: 4 entries
+    bsim::StageHost* stage_host = nullptr;   // what staging copies back
+    bsim::FinalHost* final_host = nullptr;   // what finalize copies back
+    uint64_t* report_host = nullptr;         // kReportRing words, written by refinement launches
+    std::shared_ptr<bsim::PinnedPool> host_pool = std::make_shared<bsim::PinnedPool>();
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;
     uint32_t hub_table_slots = 8192;  // LDS slots per hub-bucket block on this device
@@ -24,7 +73,7 @@ struct bsim_ctx {
     // 0: the stop test looks two levels back, so that one level past the last
     // is hashed; else it knows the level just hashed
     uint32_t tail_split_ppm = 100;
-    uint32_t* count_host = nullptr;   // pinned scratch for counts (kStripes entries)
+    uint32_t* count_host = nullptr;   // part of *pinned: scratch for counts, 64 entries
     // batched calls: schedules picked by the autotuner, per size class
     uint32_t autotune = 1;
     struct BatchTune {
@@ -50,7 +99,7 @@ struct SharedArrays {
     int device = 0;
     hipStream_t stream = nullptr;
     std::vector<void*> device_ptrs;
-    std::vector<void*> host_ptrs;
+    std::shared_ptr<HostBlock> host;
     ~SharedArrays();
 };
 
@@ -59,7 +108,7 @@ struct ResultPriv {
     int device = 0;
     hipStream_t stream = nullptr;
     std::vector<void*> device_ptrs;
-    std::vector<void*> host_ptrs;
+    std::shared_ptr<HostBlock> host;
     std::vector<uint32_t> blocks_per_iter;
     std::shared_ptr<SharedArrays> shared;
 };
@@ -70,7 +119,18 @@ struct DeviceGraph {
     Staged g;
 };
 
-void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s);
+// pool: pinned memory for the upload of a small graph; *block (nullable with
+// pool) keeps it until the upload is done.
+void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
+                  const std::shared_ptr<PinnedPool>& pool = nullptr, std::shared_ptr<HostBlock>* block = nullptr);
+
+// Queue up to 8 device-visible copies in one launch where they are small (a
+// copy apiece otherwise); bytes are multiples of 4, addresses 4-byte aligned.
+void copy_ranges(void* const* dst, const void* const* src, const size_t* bytes, int n, hipStream_t s);
+
+// The six result arrays copied from dev[] into one block of host memory;
+// base[i] = their places.  Returns once they are there.
+std::shared_ptr<HostBlock> host_arrays(bsim_ctx* ctx, void* const* dev, const size_t* bytes, void** base);
 
 // Per-level hash storage handed to the refinement loop.  With `levels`
 // empty the loop double-buffers; otherwise levels[k] receives h^k.

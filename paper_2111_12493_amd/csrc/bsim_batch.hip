@@ -420,13 +420,10 @@ void batch_summarize(bsim_ctx* ctx, const bsim_graph* graphs, uint32_t G, const 
     const size_t sizes[6] = {u.n * 8ull, u.n * 4ull, fo.n_blocks * 4ull, nse * 4ull, nse * 4ull, nse * 4ull};
     void* base[6];
     const bool host = (p.flags & BSIM_RESULT_ON_HOST) != 0;
-    for (int i = 0; i < 6; i++) {
-        if (host) {
-            base[i] = malloc(sizes[i] ? sizes[i] : 8);
-            if (!base[i]) throw DeviceError{BSIM_E_NOMEM, "host result allocation failed"};
-            shared->host_ptrs.push_back(base[i]);
-            if (sizes[i]) hip_check(hipMemcpyAsync(base[i], dev[i], sizes[i], hipMemcpyDeviceToHost, s), "result copy");
-        } else {
+    if (host) {
+        shared->host = host_arrays(ctx, dev, sizes, base);
+    } else {
+        for (int i = 0; i < 6; i++) {
             base[i] = dev[i];
             keep.detach(dev[i]);
             shared->device_ptrs.push_back(dev[i]);

@@ -15,6 +15,7 @@
 // Summary edges (Sec. 2.6: edges between vertex summaries) are the distinct
 // (block(v), l, block(w)) triples: packed into one 64-bit key per edge,
 // sorted by an LSD radix sort over the used bits, de-duplicated and unpacked.
+#include "bsim_api_internal.h"
 #include "bsim_device.h"
 
 namespace bsim {
@@ -422,11 +423,10 @@ void finalize_impl(const Staged& g, const uint32_t* rep, const uint32_t* rep_pre
     out.block_ids = arena.alloc<uint32_t>(g.n);
     finalize_edges(g, rep, rep_prev, want_edges, out, host, arena, keep, s, n_ids);
     uint32_t* sizes = keep.alloc<uint32_t>(out.n_blocks + 1ull);
-    if (g.n)
-        hip_check(hipMemcpyAsync(ids, out.block_ids, static_cast<size_t>(g.n) * 4, hipMemcpyDeviceToDevice, s),
-                  "block ids");
-    hip_check(hipMemcpyAsync(sizes, out.block_sizes, (out.n_blocks + 1ull) * 4, hipMemcpyDeviceToDevice, s),
-              "block sizes");
+    void* const dst[2] = {ids, sizes};
+    const void* const src[2] = {out.block_ids, out.block_sizes};
+    const size_t bytes[2] = {static_cast<size_t>(g.n) * 4, static_cast<size_t>(out.n_blocks) * 4};
+    copy_ranges(dst, src, bytes, 2, s);
     out.block_ids = ids;
     out.block_sizes = sizes;
 }

@@ -41,7 +41,8 @@ void validate_params(const bsim_graph& graph, const bsim_params& p, bool directi
                                               "bsim_summarize without a state only"};
 }
 
-void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s) {
+void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
+                  const std::shared_ptr<PinnedPool>& pool, std::shared_ptr<HostBlock>* block) {
     g.n = in.n_vertices;
     g.m = in.n_edges;
     g.label_bytes = in.label_bytes;
@@ -55,25 +56,39 @@ void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s) 
         return;
     }
     const size_t n = in.n_vertices, m = in.n_edges;
-    uint32_t* ro = arena.alloc<uint32_t>(n + 1);
-    hip_check(hipMemcpyAsync(ro, in.row_off, (n + 1) * 4, hipMemcpyHostToDevice, s), "upload row_off");
-    uint32_t* to = arena.alloc<uint32_t>(n + 1);
-    hip_check(hipMemcpyAsync(to, in.type_off, (n + 1) * 4, hipMemcpyHostToDevice, s), "upload type_off");
     // type_off[n] tells how many type ids follow; read it from the host copy
     const size_t nt = in.type_off[n];
-    uint32_t* ti = arena.alloc<uint32_t>(nt + 1);
-    if (nt) hip_check(hipMemcpyAsync(ti, in.type_ids, nt * 4, hipMemcpyHostToDevice, s), "upload types");
-    uint32_t* tg = arena.alloc<uint32_t>(m + 1);
-    void* lb = arena.alloc<uint8_t>(m * in.label_bytes + 4);
-    if (m) {
-        hip_check(hipMemcpyAsync(tg, in.targets, m * 4, hipMemcpyHostToDevice, s), "upload targets");
-        hip_check(hipMemcpyAsync(lb, in.labels, m * in.label_bytes, hipMemcpyHostToDevice, s), "upload labels");
+    // (the arrays one after the other, each from a 256-byte boundary)
+    const void* from[6] = {in.row_off, in.type_off, in.type_ids, in.targets, in.labels, in.alive};
+    const size_t bytes[6] = {(n + 1) * 4, (n + 1) * 4, nt * 4, m * 4, m * in.label_bytes, in.alive ? n : 0};
+    size_t at[6], total = 0;
+    for (int i = 0; i < 6; i++) {
+        at[i] = total;
+        total += (bytes[i] + 16 + 255) & ~size_t(255);
     }
-    uint8_t* al = nullptr;
-    if (in.alive) {
-        al = arena.alloc<uint8_t>(n + 1);
-        hip_check(hipMemcpyAsync(al, in.alive, n, hipMemcpyHostToDevice, s), "upload alive");
+    // A small graph goes up in one copy from pinned memory: five copies from
+    // pageable memory, each through the runtime's staging, took 110 us of a
+    // 1,000-vertex graph's 456.  Past kUploadOne the extra pass over the host's
+    // arrays would cost more than the copies' overhead.
+    constexpr size_t kUploadOne = 1u << 20;
+    uint8_t* dev = arena.alloc<uint8_t>(total);
+    std::shared_ptr<HostBlock> up;
+    if (pool && total <= kUploadOne) up = std::make_shared<HostBlock>(pool, total);
+    if (up && up->pool) {
+        for (int i = 0; i < 6; i++)
+            if (bytes[i]) memcpy(static_cast<uint8_t*>(up->p) + at[i], from[i], bytes[i]);
+        hip_check(hipMemcpyAsync(dev, up->p, total, hipMemcpyHostToDevice, s), "upload graph");
+        *block = up;
+    } else {
+        for (int i = 0; i < 6; i++)
+            if (bytes[i]) hip_check(hipMemcpyAsync(dev + at[i], from[i], bytes[i], hipMemcpyHostToDevice, s), "upload graph");
     }
+    uint32_t* ro = reinterpret_cast<uint32_t*>(dev + at[0]);
+    uint32_t* to = reinterpret_cast<uint32_t*>(dev + at[1]);
+    uint32_t* ti = reinterpret_cast<uint32_t*>(dev + at[2]);
+    uint32_t* tg = reinterpret_cast<uint32_t*>(dev + at[3]);
+    void* lb = dev + at[4];
+    uint8_t* al = in.alive ? dev + at[5] : nullptr;
     g.row_off = ro;
     g.type_off = to;
     g.type_ids = ti;
@@ -297,14 +312,7 @@ bsim_result* make_result(bsim_ctx* ctx, const Staged& g, const LoopResult& lr, c
         const size_t sizes[] = {static_cast<size_t>(g.n) * 8, static_cast<size_t>(g.n) * 4,
                                 static_cast<size_t>(fo.n_blocks) * 4, fo.n_se * 4, fo.n_se * 4, fo.n_se * 4};
         void* host[6];
-        for (int i = 0; i < 6; i++) {
-            host[i] = malloc(sizes[i] ? sizes[i] : 8);
-            if (!host[i]) throw DeviceError{BSIM_E_NOMEM, "host result allocation failed"};
-            p->host_ptrs.push_back(host[i]);
-            if (sizes[i])
-                hip_check(hipMemcpyAsync(host[i], dev[i], sizes[i], hipMemcpyDeviceToHost, s), "result copy");
-        }
-        hip_check(hipStreamSynchronize(s), "result sync");
+        p->host = host_arrays(ctx, dev, sizes, host);
         keep.release();
         r->mem_kind = BSIM_MEM_HOST;
         r->hashes = static_cast<uint64_t*>(host[0]);
@@ -345,7 +353,8 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     } guard{ev};
     hip_check(hipEventRecord(ev[0], s), "event");
     Staged g;
-    upload_graph(graph, g, arena, s);
+    std::shared_ptr<HostBlock> upload;  // until the call's end
+    upload_graph(graph, g, arena, s, ctx->host_pool, &upload);
     g.hub_table_slots = ctx->hub_table_slots;
     stage_graph(g, ctx->stage_host, arena, s);
     // direction / label parameterizations: refine the view h, take the
