@@ -9,6 +9,12 @@ namespace bsim {
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 
+// salt(l) = M(C_L + l); at and past in_base (when nonzero) the salts of
+// incoming edges: label in_base + l is salted as label l + 2^31.
+__device__ __forceinline__ uint64_t label_salt(uint32_t l, uint32_t in_base) {
+    return mix64(kCL + ((in_base && l >= in_base) ? 0x80000000ull + (l - in_base) : static_cast<uint64_t>(l)));
+}
+
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int d) {
     uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(static_cast<uint32_t>(x)), d, 64));
     uint32_t hi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(static_cast<uint32_t>(x >> 32)), d, 64));

@@ -32,9 +32,17 @@ namespace {
 // vertices of a summary 252 us became 43.
 constexpr int kMinRounds = 4;
 
-__global__ void __launch_bounds__(kBlock) k_fin_init(uint32_t* __restrict__ cmin, uint32_t n) {
+// Class minima before k_fin_min: the name itself (own) or none.  The launch
+// also clears the words that later launches of the call count in: three
+// clears and the salts' launch fewer (those are in k_types now) took a call on
+// 1,000 edges from 362 to 350 us.
+__global__ void __launch_bounds__(kBlock) k_fin_init(uint32_t* __restrict__ cmin, uint32_t n, bool own,
+                                                     uint32_t* __restrict__ zero, uint32_t n_zero,
+                                                     uint32_t* __restrict__ zero2, uint32_t n_zero2) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
-    if (v < n) cmin[v] = v;
+    if (v < n) cmin[v] = own ? v : 0xFFFFFFFFu;
+    if (v < n_zero) zero[v] = 0;
+    if (v < n_zero2) zero2[v] = 0;
 }
 
 template <bool kOwn>
@@ -376,10 +384,12 @@ namespace {
 
 // First-occurrence block ids of the nb classes named by `rep` into ids[n],
 // the block sizes into sizes_preset or a new array of `arena`; *seen receives
-// the number of classes found.
+// the number of classes found.  zero, zero2: words cleared on the way, also
+// with no vertices.
 void number_blocks(const Staged& g, const uint32_t* rep, uint32_t nb, uint32_t* ids, uint32_t** sizes_out,
                    uint32_t* seen, Arena& arena, hipStream_t s, uint32_t* sizes_preset = nullptr,
-                   uint64_t n_ids = 0) {
+                   uint64_t n_ids = 0, uint32_t* zero = nullptr, uint32_t n_zero = 0, uint32_t* zero2 = nullptr,
+                   uint32_t n_zero2 = 0) {
     const uint32_t n = g.n;
     // class names are vertex ids, or below n_ids when given
     const uint64_t names = n_ids ? n_ids : n;
@@ -389,15 +399,16 @@ void number_blocks(const Staged& g, const uint32_t* rep, uint32_t nb, uint32_t* 
     uint32_t* count = arena.alloc<uint32_t>(gb + 1ull);
     uint32_t* sizes = sizes_preset ? sizes_preset : arena.alloc<uint32_t>(nb + 1ull);
     *sizes_out = sizes;
+    const uint64_t wide = std::max<uint64_t>({names, n_zero, n_zero2, 1});
+    k_fin_init<<<ceil_div(wide, kBlock), kBlock, 0, s>>>(name, static_cast<uint32_t>(names), n_ids == 0, zero, n_zero,
+                                                         zero2, n_zero2);
+    hip_check(hipGetLastError(), "finalize launch");
     if (!n) return;
     const uint32_t gv = ceil_div(n, kBlock);
-    if (n_ids) {
-        hip_check(hipMemsetAsync(name, 0xFF, names * 4, s), "class minima");
+    if (n_ids)
         k_fin_min<false><<<gv, kBlock, 0, s>>>(rep, g.alive, n, name);
-    } else {
-        k_fin_init<<<gv, kBlock, 0, s>>>(name, n);
+    else
         k_fin_min<true><<<gv, kBlock, 0, s>>>(rep, g.alive, n, name);
-    }
     k_fin_first<<<gb, kBlock, 0, s>>>(rep, g.alive, n, name, first, count);
     scan_exclusive(count, count, gb, seen, arena, s);
     k_fin_name<<<gb, kBlock, 0, s>>>(rep, first, count, name, sizes);
@@ -437,9 +448,17 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
     const uint32_t nb = out.n_blocks;
     // the counts that come back to the host, together
     FinalHost* dev = arena.alloc<FinalHost>(1);
-    hip_check(hipMemsetAsync(dev, 0, sizeof(FinalHost), s), "finalize counts");
+    // a summary edge's target end: the final blocks, or the blocks of the
+    // previous level
+    const uint32_t nb_dst = rep_prev ? out.n_prev_blocks : nb;
+    const uint32_t nb_max = std::max(nb, nb_dst);
+    const int bb = std::max(1, bit_width(nb_max ? nb_max - 1 : 0));
+    const int lb = std::max(1, bit_width(g.max_label));
+    const bool bucketed = want_edges && g.m && bucketed_summary_edges_fit(g, lb, bb);
+    uint32_t* ecount = bucketed ? arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1) : nullptr;
     number_blocks(g, rep, nb, out.block_ids, &out.block_sizes, dev->blocks, arena, s,
-                  out.preset ? out.block_sizes : nullptr, n_ids);
+                  out.preset ? out.block_sizes : nullptr, n_ids, reinterpret_cast<uint32_t*>(dev),
+                  sizeof(FinalHost) / 4, ecount, bucketed ? nb + 1 : 0u);
     const std::function<const FinalHost&()> fetch = [&]() -> const FinalHost& {
         hip_check(hipMemcpyAsync(host, dev, sizeof(FinalHost), hipMemcpyDeviceToHost, s), "finalize counts");
         hip_check(hipStreamSynchronize(s), "finalize counts");
@@ -457,22 +476,15 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
         }
         return;
     }
-    // the target end of a summary edge: the final blocks, or the blocks of
-    // the previous level's classes
     const uint32_t* dst_ids = out.block_ids;
-    uint32_t nb_dst = nb;
     if (rep_prev) {
         uint32_t* ids = arena.alloc<uint32_t>(n);
         uint32_t* sizes = nullptr;
-        nb_dst = out.n_prev_blocks;
         number_blocks(g, rep_prev, nb_dst, ids, &sizes, dev->prev_blocks, arena, s);
         dst_ids = ids;
     }
-    const uint32_t nb_max = std::max(nb, nb_dst);
-    const int bb = std::max(1, bit_width(nb_max ? nb_max - 1 : 0));
-    const int lb = std::max(1, bit_width(g.max_label));
-    if (bucketed_summary_edges_fit(g, lb, bb)) {
-        bucketed_summary_edges(g, out.block_ids, nb, dst_ids, lb, bb, out, dev, fetch, arena, keep, s);
+    if (bucketed) {
+        bucketed_summary_edges(g, out.block_ids, nb, dst_ids, lb, bb, ecount, out, dev, fetch, arena, keep, s);
         if (rep_prev && host->prev_blocks[0] != nb_dst)
             throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
         return;

@@ -1226,6 +1226,7 @@ void full_levels(bsim_state* st, uint32_t j0, Arena& arena) {
     g.max_label = st->max_label;
     g.trusted = true;
     stage_graph(g, st->ctx->stage_host, arena, s);
+    launch_salts(g, s);
     HashScratch hs;
     alloc_hash_scratch(g, hs, arena, s);
     for (uint32_t j = j0; j <= st->K; j++) {

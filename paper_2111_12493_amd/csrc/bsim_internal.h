@@ -422,7 +422,9 @@ struct StageHost {
 
 // Validate the CSR and build the tile / hub schedule (a1).  Throws
 // DeviceError with BSIM_E_INVALID / BSIM_E_RANGE on malformed input.
+// g.salt is allocated; launch_init fills it, or launch_salts.
 void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s);
+void launch_salts(const Staged& g, hipStream_t s);
 
 // The graphs of the direction and label parameterizations (Sec. 2.4), built
 // on the device from a staged graph g and staged themselves: f = the edges
@@ -456,7 +458,7 @@ struct RunBuffers {
 
 void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_t s);
 
-// Level 0: type hashes, h^0 = t, the type classes (rep) and n_0.
+// Level 0: label salts, type hashes, h^0 = t, the type classes (rep) and n_0.
 void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_t s);
 
 // Launch k: stop test of level k - lag, h^k (tiles and hub chunks).
@@ -566,10 +568,12 @@ void ci_update(const CiLevel& L, const uint32_t* cid_prev, const uint64_t* h, co
 // block (bid, nb blocks) and sorted within each block; false from the fit
 // test means the keys or the layout need the global sort instead.
 bool bucketed_summary_edges_fit(const Staged& g, int lb, int bb);
-// dev: the device's counts; fetch brings them to the host.
+// ecount: nb + 1 zero words; dev: the device's counts, which fetch brings to
+// the host.
 void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, const uint32_t* dst_ids, int lb,
-                            int bb, FinalOut& out, FinalHost* dev, const std::function<const FinalHost&()>& fetch,
-                            Arena& arena, Arena& keep, hipStream_t s);
+                            int bb, uint32_t* ecount, FinalOut& out, FinalHost* dev,
+                            const std::function<const FinalHost&()>& fetch, Arena& arena, Arena& keep,
+                            hipStream_t s);
 
 // Blocks are the out.n_blocks classes given by rep[] (first-occurrence
 // numbering); host: pinned.

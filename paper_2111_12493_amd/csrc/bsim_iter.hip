@@ -162,12 +162,14 @@ __device__ __forceinline__ void record_founders(const SplitTable& T, uint32_t* l
 
 // ------------------------------------------------------------ level 0
 
-// t(v) and h^0 = t for every vertex (0 for a dead one).
+// t(v) and h^0 = t for every vertex (0 for a dead one), and the label salts.
 __global__ void __launch_bounds__(kBlock) k_types(const uint32_t* __restrict__ type_off,
                                                   const uint32_t* __restrict__ type_ids,
                                                   const uint8_t* __restrict__ alive, uint32_t n, int untyped,
-                                                  uint64_t* __restrict__ t, uint64_t* __restrict__ h0) {
+                                                  uint64_t* __restrict__ t, uint64_t* __restrict__ h0,
+                                                  uint64_t* __restrict__ salt, uint32_t nsalt, uint32_t in_base) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
+    if (v < nsalt) salt[v] = label_salt(v, in_base);
     if (v < n) {
         uint64_t tv = 0;
         if (!alive || alive[v]) {
@@ -1050,8 +1052,10 @@ void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_
 
 void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_t s) {
     const uint32_t n = g.n;
-    const uint32_t grid = std::max<uint32_t>(ceil_div(n, kBlock), 1);
-    k_types<<<grid, kBlock, 0, s>>>(g.type_off, g.type_ids, g.alive, n, untyped ? 1 : 0, rb.t, rb.h[0]);
+    const uint32_t nsalt = g.max_label + 1;
+    k_types<<<ceil_div(std::max(n, nsalt), kBlock), kBlock, 0, s>>>(g.type_off, g.type_ids, g.alive, n,
+                                                                    untyped ? 1 : 0, rb.t, rb.h[0], g.salt, nsalt,
+                                                                    g.in_label_base);
     k_init<<<std::max<uint32_t>(ceil_div(n, kBlock * kSplitPerThread), 1), kBlock, 0, s>>>(rb.t, g.alive, n, rb.rep, rb.tab[0], rb.lcnt, rb.bc);
     hip_check(hipGetLastError(), "init launch");
 }

@@ -578,17 +578,16 @@ bool bucketed_summary_edges_fit(const Staged& g, int lb, int bb) {
 }
 
 void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, const uint32_t* dst_ids, int lb,
-                            int bb, FinalOut& out, FinalHost* dev, const std::function<const FinalHost&()>& fetch,
-                            Arena& arena, Arena& keep, hipStream_t s) {
+                            int bb, uint32_t* ecount, FinalOut& out, FinalHost* dev,
+                            const std::function<const FinalHost&()>& fetch, Arena& arena, Arena& keep,
+                            hipStream_t s) {
     const uint32_t n = g.n;
     const uint32_t m = static_cast<uint32_t>(g.m);
     const int vb = lb + bb;
     // 1. segments: per-vertex claims, then their placement (every edge
     // leaves an alive vertex, so the segments hold m values)
-    uint32_t* ecount = arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1);
     uint32_t* voff = arena.alloc<uint32_t>(n);
     uint32_t* estart = arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1);
-    hip_check(hipMemsetAsync(ecount, 0, (static_cast<size_t>(nb) + 1) * 4, s), "segment counts");
     k_seg_claim<<<ceil_div(n, kBlock), kBlock, 0, s>>>(g.row_off, bid, n, ecount, voff);
     scan_exclusive(ecount, estart, nb, estart + nb, arena, s);
     // 2. values

@@ -14,7 +14,7 @@
 #include <algorithm>
 
 #include "bsim_resolve.h"  // host_radix_sort
-#include "bsim_internal.h"
+#include "bsim_device.h"
 
 namespace bsim {
 
@@ -205,7 +205,7 @@ struct StageShared {
     uint32_t act[kStageGroups];     // tile vertices, solo vertices and hubs per group
     uint32_t solo[kStageGroups];
     uint32_t hub[kStageGroups];
-    uint32_t red[kBlock / 64];
+    uint32_t red[2 * kWaves];
 };
 
 struct StageArgs {
@@ -218,6 +218,7 @@ struct StageArgs {
     const void* lab;
     uint32_t n_vblk;     // vertex blocks (the grid's first)
     uint4* cnt;          // per vertex block: hubs, tile vertices, solo vertices, tiles
+    uint4* seen;         // per block: error bits, most types, largest label
     uint32_t wide;       // tgt and lab are aligned for four edges per load
     uint32_t* act;
     uint32_t* act_off;
@@ -333,20 +334,21 @@ __device__ void stage_vertices(const StageArgs& a, StageShared& S) {
             types = max(types, static_cast<uint32_t>(__shfl_xor(static_cast<int>(types), d, 64)));
             err |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(err), d, 64));
         }
-        // the maximum only grows: a wave that cannot raise it (nearly all of
-        // them once a few have run) issues no atomic; same-address atomics
-        // serialize across the chip
-        if (lane == 0) {
-            if (types > __hip_atomic_load(&a.status->max_types, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                atomicMax(&a.status->max_types, types);
-            if (err) atomicOr(&a.status->error, err);
-        }
+        if (lane == 0) S.red[wv] = err << 16 | min(types, 0xFFFFu);  // (more than 4,096 types are refused)
     }
     __syncthreads();
     if (wv == 0) {
         uint4* out = kEmit && at.w < a.tile_cap ? a.tiles + at.w : nullptr;
         const uint32_t made = pack_tiles(S, na, at.y, out, kEmit ? a.tile_cap - at.w : 0u);
-        if (!kEmit && lane == 0) a.cnt[blockIdx.x] = make_uint4(nh, na, ns, made);
+        if (!kEmit && lane == 0) {
+            a.cnt[blockIdx.x] = make_uint4(nh, na, ns, made);
+            uint32_t e = 0, t = 0;
+            for (int i = 0; i < kWaves; i++) {
+                e |= S.red[i] >> 16;
+                t = max(t, S.red[i] & 0xFFFFu);
+            }
+            a.seen[blockIdx.x] = make_uint4(e, t, 0, 0);
+        }
     }
 }
 
@@ -391,13 +393,17 @@ __device__ void stage_edges(const StageArgs& a, uint32_t* s_red) {
         mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), d, 64)));
         err |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(err), d, 64));
     }
-    if (err && (threadIdx.x & 63) == 0) atomicOr(&a.status->error, err);
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = mx;
+    if ((threadIdx.x & 63) == 0) {
+        s_red[threadIdx.x >> 6] = mx;
+        s_red[kWaves + (threadIdx.x >> 6)] = err;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kBlock / 64; i++) mx = max(mx, s_red[i]);
-        if (mx && mx > __hip_atomic_load(&a.status->max_label, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(&a.status->max_label, mx);
+        for (int i = 1; i < kWaves; i++) {
+            mx = max(mx, s_red[i]);
+            err |= s_red[kWaves + i];
+        }
+        a.seen[blockIdx.x] = make_uint4(err, 0, mx, 0);
     }
 }
 
@@ -417,10 +423,12 @@ __global__ void __launch_bounds__(kBlock) k_stage_emit(StageArgs a) {
     stage_vertices<true>(a, S);
 }
 
-// Exclusive scan of the per-block counts in place; totals to total[0..3].
+// Exclusive scan of the per-block counts in place, totals to total[0..3]; and
+// the status from what the nseen blocks saw.
 constexpr uint32_t kSpineItems = 4;
 
-__global__ void __launch_bounds__(1024) k_stage_spine(uint4* cnt, uint32_t nb, uint32_t* total) {
+__global__ void __launch_bounds__(1024) k_stage_spine(uint4* cnt, uint32_t nb, const uint4* __restrict__ seen,
+                                                      uint32_t nseen, RunStatus* status, uint32_t* total) {
     __shared__ uint4 s_w[16];
     const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     uint4 carry = make_uint4(0, 0, 0, 0);
@@ -452,7 +460,28 @@ __global__ void __launch_bounds__(1024) k_stage_spine(uint4* cnt, uint32_t nb, u
         }
         __syncthreads();
     }
+    uint32_t err = 0, types = 0, label = 0;
+    for (uint32_t j = threadIdx.x; j < nseen; j += 1024) {
+        const uint4 x = seen[j];
+        err |= x.x;
+        types = max(types, x.y);
+        label = max(label, x.z);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        err |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(err), d, 64));
+        types = max(types, static_cast<uint32_t>(__shfl_xor(static_cast<int>(types), d, 64)));
+        label = max(label, static_cast<uint32_t>(__shfl_xor(static_cast<int>(label), d, 64)));
+    }
+    if (lane == 0) s_w[wid] = make_uint4(err, types, label, 0);
+    __syncthreads();
     if (threadIdx.x == 0) {
+        for (uint32_t i = 1; i < 16; i++) {
+            err |= s_w[i].x;
+            types = max(types, s_w[i].y);
+            label = max(label, s_w[i].z);
+        }
+        *status = RunStatus{0, 0, 0, err, label, types, {0, 0}};
         total[0] = carry.x;
         total[1] = carry.y;
         total[2] = carry.z;
@@ -460,13 +489,9 @@ __global__ void __launch_bounds__(1024) k_stage_spine(uint4* cnt, uint32_t nb, u
     }
 }
 
-// salt(l) = M(C_L + l); at and past in_base (when nonzero) the salts of
-// incoming edges: label in_base + l is salted as label l + 2^31
 __global__ void __launch_bounds__(kBlock) k_salt(uint64_t* salt, uint32_t count, uint32_t in_base) {
-    uint32_t l = blockIdx.x * kBlock + threadIdx.x;
-    if (l >= count) return;
-    const uint64_t x = (in_base && l >= in_base) ? 0x80000000ull + (l - in_base) : static_cast<uint64_t>(l);
-    salt[l] = mix64(kCL + x);
+    const uint32_t l = blockIdx.x * kBlock + threadIdx.x;
+    if (l < count) salt[l] = label_salt(l, in_base);
 }
 
 // The hub schedule, on the host (a graph of 2^30 edges has some 10^5 hubs):
@@ -554,7 +579,6 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     RunStatus* status = reinterpret_cast<RunStatus*>(dev);
     uint32_t* counts = reinterpret_cast<uint32_t*>(dev + sizeof(RunStatus));
     uint32_t* hubs = reinterpret_cast<uint32_t*>(dev + head);
-    hip_check(hipMemsetAsync(dev, 0, head, s), "stage status");
     // tiles: one that its edges end is followed by a vertex with which it
     // would pass kTileMaxEdges (a vertex counts for its own tile and, first
     // in it, for the one before), one that its vertices end holds
@@ -571,7 +595,10 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     a.tgt = g.tgt;
     a.lab = g.lab;
     a.n_vblk = n_vblk;
+    const uint32_t n_eblk =
+        n && g.m && !g.trusted ? std::min<uint32_t>(ceil_div(g.m, 4 * kBlock), 2048) : 0u;
     a.cnt = arena.alloc<uint4>(n_vblk + 1ull);
+    a.seen = arena.alloc<uint4>(n_vblk + n_eblk + 1ull);
     a.wide = (reinterpret_cast<uintptr_t>(g.tgt) % 16 == 0 &&
               reinterpret_cast<uintptr_t>(g.lab) % (4 * g.label_bytes) == 0)
                  ? 1u
@@ -587,15 +614,14 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
     a.tile_cap = static_cast<uint32_t>(tile_cap);
     a.status = status;
     if (n > 0) {
-        const uint32_t n_eblk = g.m && !g.trusted ? std::min<uint32_t>(ceil_div(g.m, 4 * kBlock), 2048) : 0u;
         if (g.label_bytes == 2)
             k_stage_count<uint16_t><<<n_vblk + n_eblk, kBlock, 0, s>>>(a);
         else
             k_stage_count<uint32_t><<<n_vblk + n_eblk, kBlock, 0, s>>>(a);
-        k_stage_spine<<<1, 1024, 0, s>>>(a.cnt, n_vblk, counts);
-        k_stage_emit<<<n_vblk, kBlock, 0, s>>>(a);
-        hip_check(hipGetLastError(), "stage launch");
     }
+    k_stage_spine<<<1, 1024, 0, s>>>(a.cnt, n_vblk, a.seen, n_vblk + n_eblk, status, counts);
+    if (n > 0) k_stage_emit<<<n_vblk, kBlock, 0, s>>>(a);
+    hip_check(hipGetLastError(), "stage launch");
     // one copy brings the counts and, for most graphs, every hub
     const uint32_t with = std::min(hub_cap, kStageHubs);
     hip_check(hipMemcpyAsync(host, dev, head + 12ull * with, hipMemcpyDeviceToHost, s), "stage counts");
@@ -627,9 +653,11 @@ void stage_graph(Staged& g, StageHost* host, Arena& arena, hipStream_t s) {
         schedule_hubs(g, host->hubs, arena, s);
     }
 
-    // label salts
-    uint32_t nsalt = g.max_label + 1;
-    g.salt = arena.alloc<uint64_t>(nsalt);
+    g.salt = arena.alloc<uint64_t>(g.max_label + 1ull);
+}
+
+void launch_salts(const Staged& g, hipStream_t s) {
+    const uint32_t nsalt = g.max_label + 1;
     k_salt<<<ceil_div(nsalt, kBlock), kBlock, 0, s>>>(g.salt, nsalt, g.in_label_base);
     hip_check(hipGetLastError(), "salt launch");
 }
