@@ -12,9 +12,10 @@
 //   2. every edge writes its value l << bb | block(w) into its vertex's range;
 //   3. every segment is sorted and de-duplicated in place, by size:
 //        1 value          nothing to do;
-//        2..256           one wave sorts the segments starting in 256
-//                         consecutive positions, LDS radix sort on
-//                         (segment ordinal, value);
+//        2..256           one wave takes the segments starting in 256
+//                         consecutive positions; where all are short, every
+//                         value counts the ones of its segment up to it,
+//                         else an LDS radix sort on (segment ordinal, value);
 //        257..16,384      one workgroup per segment, LDS radix sort;
 //        more             one global LSD radix sort over all such segments
 //                         on (segment rank, value);
@@ -31,11 +32,13 @@ namespace {
 constexpr uint32_t kSegSmallMax = 256;     // tile-packed segments hold at most this many values
 constexpr uint32_t kSegMedMax = 4096;      // one 256-thread workgroup per segment
 constexpr uint32_t kSegBigMax = 16384;     // one 1,024-thread workgroup per segment
-constexpr uint32_t kSortIpt = 16;          // values per thread in an LDS sort (at most)
+constexpr uint32_t kSortIpt = 16;          // values per thread in a medium segment's sort (at most)
 constexpr uint32_t kSmallBlock = 64;       // a small tile is one wave
 constexpr uint32_t kSmallRange = 256;      // segment starts per small tile
 constexpr uint32_t kSmallCap = 512;        // values per small tile: kSmallRange + kSegSmallMax - 1 fit
 constexpr uint32_t kSmallMaxSeg = kSmallCap / 2;             // segments of >= 2 values
+constexpr uint32_t kSmallRounds = kSmallCap / kSmallBlock;   // values per lane
+constexpr uint32_t kRankMax = 128;          // longest segment that k_seg_small ranks by counting
 constexpr int kOrdBits = 8;                                  // tile ordinals < 256
 constexpr uint32_t kUnpackTile = kBlock * 16;
 constexpr uint32_t kUnpackCache = 4096;    // block offsets a tile keeps in LDS
@@ -43,7 +46,6 @@ constexpr uint32_t kBigBlock = 1024;
 
 static_assert(kSmallRange + kSegSmallMax <= kSmallCap, "a small tile must hold its segments");
 static_assert(kSmallMaxSeg <= (1u << kOrdBits), "tile ordinals must fit their field");
-static_assert(kSmallCap <= kSmallBlock * kSortIpt, "a small tile fits the sort's registers");
 static_assert(kBigBlock * kSortIpt == kSegBigMax && kBlock * kSortIpt == kSegMedMax, "sort capacities");
 
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
@@ -145,15 +147,16 @@ struct SegArgs {
 template <int NT>
 __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uint32_t nseg) {
     constexpr uint32_t W = NT / 64;
+    constexpr uint32_t kIpt = NT == kSmallBlock ? kSmallRounds : kSortIpt;
     constexpr uint32_t DPT = NT >= 256 ? 1 : 256 / NT;  // digits per thread in the prefix step
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const uint32_t ipt = (cnt + NT - 1) / NT;  // rounds per wave; element = (w * ipt + r) * 64 + lane
     const uint64_t vmask = (1ull << a.vb) - 1;
     const uint64_t lt = (1ull << lane) - 1;
-    uint64_t key[kSortIpt];
+    uint64_t key[kIpt];
     uint64_t kor = 0, kand = ~0ull;
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; r++) {
+    for (uint32_t r = 0; r < kIpt; r++) {
         key[r] = ~0ull;
         const uint32_t i = (w * ipt + r) * 64 + lane;
         if (r < ipt && i < cnt) {
@@ -184,14 +187,14 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
         diff = o ^ n;
     }
     __syncthreads();
-    uint32_t lr[kSortIpt];
+    uint32_t lr[kIpt];
     for (int shift = 0; shift < 64; shift += 8) {
         if (((diff >> shift) & 0xFF) == 0) continue;  // uniform over the block
         for (uint32_t d = lane; d < 256; d += 64) S.wc[w * 256 + d] = 0;
         __builtin_amdgcn_wave_barrier();
         // wave-local stable ranks per digit
 #pragma unroll
-        for (uint32_t r = 0; r < kSortIpt; r++) {
+        for (uint32_t r = 0; r < kIpt; r++) {
             if (r >= ipt) continue;
             const uint32_t i = (w * ipt + r) * 64 + lane;
             const bool valid = i < cnt;
@@ -228,7 +231,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
                 }
         __syncthreads();
 #pragma unroll
-        for (uint32_t r = 0; r < kSortIpt; r++) {
+        for (uint32_t r = 0; r < kIpt; r++) {
             if (r >= ipt) continue;
             const uint32_t i = (w * ipt + r) * 64 + lane;
             if (i < cnt) {
@@ -238,7 +241,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
         }
         __syncthreads();
 #pragma unroll
-        for (uint32_t r = 0; r < kSortIpt; r++) {
+        for (uint32_t r = 0; r < kIpt; r++) {
             if (r >= ipt) continue;
             const uint32_t i = (w * ipt + r) * 64 + lane;
             if (i < cnt) key[r] = S.buf[i];
@@ -247,18 +250,18 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     // key[r] now holds sorted element (w * ipt + r) * 64 + lane; publish the
     // order for the neighbour comparison
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; r++) {
+    for (uint32_t r = 0; r < kIpt; r++) {
         if (r >= ipt) continue;
         const uint32_t i = (w * ipt + r) * 64 + lane;
         if (i < cnt) S.buf[i] = key[r];
     }
     __syncthreads();
     // distinct positions: first occurrences counted in element order
-    uint32_t dloc[kSortIpt];
+    uint32_t dloc[kIpt];
     uint32_t firsts = 0;  // bit r: element of round r is a first occurrence
     uint32_t wrun = 0;
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; r++) {
+    for (uint32_t r = 0; r < kIpt; r++) {
         if (r >= ipt) continue;
         const uint32_t i = (w * ipt + r) * 64 + lane;
         const bool first = i < cnt && (i == 0 || key[r] != S.buf[i - 1]);
@@ -273,7 +276,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     for (uint32_t i = 0; i < w; i++) wbase += S.red[i];
     // every segment start is a first occurrence: it records the segment's base
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; r++) {
+    for (uint32_t r = 0; r < kIpt; r++) {
         if (r >= ipt) continue;
         const uint32_t i = (w * ipt + r) * 64 + lane;
         if (i < cnt) {
@@ -283,7 +286,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     }
     __syncthreads();
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; r++) {
+    for (uint32_t r = 0; r < kIpt; r++) {
         if (r >= ipt) continue;
         const uint32_t i = (w * ipt + r) * 64 + lane;
         if (i >= cnt) continue;
@@ -295,11 +298,107 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     }
 }
 
+// A tile of short segments, as one wave: a value's place in its segment is the
+// number of values up to it, so it reads its segment once from LDS (lanes of
+// one segment read one address).  Equal values get one place; the one whose
+// number is found there after all have written is kept, and the places taken
+// before it are its rank.
+template <typename V>
+__device__ void rank_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uint32_t nseg) {
+    const uint32_t lane = lane_id();
+    V* val = reinterpret_cast<V*>(S.buf);
+    uint8_t* own = reinterpret_cast<uint8_t*>(S.wc);
+    for (uint32_t o = lane; o < nseg; o += 64)
+        for (uint32_t i = S.lofs[o]; i < S.lofs[o + 1]; i++) own[i] = static_cast<uint8_t>(o);
+    wave_sync();
+    V x[kSmallRounds];
+    uint32_t seg[kSmallRounds];  // first position << 16 | length
+    uint32_t to[kSmallRounds];   // where the segment starts in vals
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++) {
+        const uint32_t i = r * 64 + lane;
+        x[r] = 0;
+        seg[r] = to[r] = 0;
+        if (i < cnt) {
+            const uint32_t o = own[i], s0 = S.lofs[o];
+            seg[r] = s0 << 16 | (S.lofs[o + 1] - s0);
+            to[r] = S.est[o];
+            x[r] = static_cast<V>(a.vals[to[r] + (i - s0)]);
+        }
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++)
+        if (r * 64 + lane < cnt) val[r * 64 + lane] = x[r];
+    wave_sync();
+    uint32_t at[kSmallRounds];  // place of the value in the tile
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++) {
+        if (r * 64 >= cnt) continue;  // uniform
+        const uint32_t s0 = seg[r] >> 16, len = seg[r] & 0xFFFF;
+        uint32_t upto = 0;
+        for (uint32_t j = 0; j < len; j += 4) {
+            // (up to three reads past the segment stay inside the LDS block)
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) upto += (val[s0 + j + k] <= x[r]) & (j + k < len);
+        }
+        at[r] = s0 + upto - 1;
+    }
+    wave_sync();
+    // the values are in registers: their place now holds who wrote there
+    uint16_t* mark = reinterpret_cast<uint16_t*>(S.buf);
+    uint16_t* before = mark + kSmallCap;
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++) mark[r * 64 + lane] = 0xFFFF;
+    wave_sync();
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++)
+        if (r * 64 + lane < cnt) mark[at[r]] = static_cast<uint16_t>(r * 64 + lane);
+    wave_sync();
+    uint32_t kept = 0;
+    bool all = true;
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++) {
+        const uint32_t i = r * 64 + lane;
+        const bool mine = i < cnt && mark[at[r]] == i;
+        kept |= static_cast<uint32_t>(mine) << r;
+        all = all && (mine || i >= cnt);
+    }
+    if (__all(all)) {
+#pragma unroll
+        for (uint32_t r = 0; r < kSmallRounds; r++)
+            if (r * 64 + lane < cnt) a.vals[to[r] + at[r] - (seg[r] >> 16)] = x[r];
+        for (uint32_t o = lane; o < nseg; o += 64) a.uniq[S.blk[o]] = S.lofs[o + 1] - S.lofs[o];
+        return;
+    }
+    // before[p]: taken places below p
+    uint32_t run = 0;
+    const uint64_t lt = (1ull << lane) - 1;
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++) {
+        const uint64_t bal = __ballot(mark[r * 64 + lane] != 0xFFFF);
+        before[r * 64 + lane] = static_cast<uint16_t>(run + static_cast<uint32_t>(__popcll(bal & lt)));
+        run += static_cast<uint32_t>(__popcll(bal));
+    }
+    if (lane == 0) before[kSmallCap] = static_cast<uint16_t>(run);
+    wave_sync();
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; r++)
+        if ((kept >> r) & 1) a.vals[to[r] + before[at[r]] - before[seg[r] >> 16]] = x[r];
+    for (uint32_t o = lane; o < nseg; o += 64) a.uniq[S.blk[o]] = before[S.lofs[o + 1]] - before[S.lofs[o]];
+}
+
 // Small segments (2..256 values): tile t takes the small segments whose
-// first value lies in [t R, (t + 1) R), R = kSmallRange, packs them back to
-// back and sorts them as one key set (segment ordinal << vb | value).  A
-// tile is one wave, so the sort's barriers cost next to nothing and many
+// first value lies in [t R, (t + 1) R), R = kSmallRange, and packs them back
+// to back.  A tile is one wave, so its barriers cost next to nothing and many
 // tiles share a CU.
+//
+// Counting reads a value's whole segment, the radix sort takes some five
+// passes of eight ballots a value whatever the length.  With radix alone the
+// 2^27 values of a uniform graph (8 a segment) took 3.2 ms, now 1.06; R-MAT
+// graphs, whose tiles are mixed, by the longest segment that is counted:
+//   kRankMax          0     24    64    128   256
+//   2^24 vertices     1.63  1.41  1.23  1.17  1.56 ms
+//   2^27              12.5        10.2  9.60
 __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
     extern __shared__ uint64_t smem_small[];
     const SortSmem S = carve<kSmallBlock>(reinterpret_cast<uint8_t*>(smem_small), kSmallCap, kSmallMaxSeg);
@@ -307,26 +406,38 @@ __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
     const uint32_t b_lo = a.tile_first[t];
     const uint32_t b_hi = t + 1 < a.n_tiles ? a.tile_first[t + 1] : a.nb;
     uint32_t nseg = 0, cnt = 0;
+    bool lengthy = false;
     for (uint32_t c = b_lo; c < b_hi; c += kSmallBlock) {  // uniform trip count
         const uint32_t b = c + threadIdx.x;
-        uint32_t sz = 0;
-        if (b < b_hi) sz = a.estart[b + 1] - a.estart[b];
+        uint32_t sz = 0, e0 = 0;
+        if (b < b_hi) {
+            e0 = a.estart[b];
+            sz = a.estart[b + 1] - e0;
+        }
         const bool small = sz >= 2 && sz <= kSegSmallMax;
-        uint32_t tot = 0;
-        const uint32_t packed = block_excl_scan<kSmallBlock>(small ? (1u << 20) | sz : 0u, S.red, &tot);
+        lengthy = lengthy || (small && sz > kRankMax);
+        const uint32_t mine = small ? (1u << 20) | sz : 0u;
+        const uint32_t incl = wave_incl_sum(mine);
+        const uint32_t tot = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
         if (small) {
+            const uint32_t packed = incl - mine;
             const uint32_t o = nseg + (packed >> 20);
             S.lofs[o] = cnt + (packed & 0xFFFFF);
             S.blk[o] = b;
-            S.est[o] = a.estart[b];
+            S.est[o] = e0;
         }
         nseg += tot >> 20;
         cnt += tot & 0xFFFFF;
     }
     if (nseg == 0) return;  // uniform
     if (threadIdx.x == 0) S.lofs[nseg] = cnt;
-    __syncthreads();
-    sort_tile<kSmallBlock>(a, S, cnt, nseg);
+    wave_sync();
+    if (__any(lengthy))
+        sort_tile<kSmallBlock>(a, S, cnt, nseg);
+    else if (a.vb <= 32)
+        rank_tile<uint32_t>(a, S, cnt, nseg);
+    else
+        rank_tile<uint64_t>(a, S, cnt, nseg);
 }
 
 // Medium segments: one workgroup per listed segment, or fewer than launched
