@@ -527,7 +527,7 @@ struct FinalOut {
 struct FinalHost {
     uint32_t blocks[32];
     uint32_t prev_blocks[32];
-    uint32_t med[32], big[32], huge[32];  // segments by size class
+    uint32_t mid[32], med[32], big[32], huge[32];  // segments by size class
     uint32_t huge_values[32];
     uint32_t edges[32];
 };

@@ -12,57 +12,72 @@
 //   2. every edge writes its value l << bb | block(w) into its vertex's range;
 //   3. every segment is sorted and de-duplicated in place, by size:
 //        1 value          nothing to do;
-//        2..256           one wave takes the segments starting in 256
-//                         consecutive positions; where all are short, every
-//                         value counts the ones of its segment up to it,
-//                         else an LDS radix sort on (segment ordinal, value);
-//        257..16,384      one workgroup per segment, LDS radix sort;
+//        2..128           one wave takes the segments starting in 256
+//                         consecutive positions; every value counts the ones
+//                         of its segment up to it;
+//        129..16,384      one wave (up to 512 values) or workgroup per segment (of
+//                         256 threads up to 4,096 values, else 1,024): the
+//                         values go to buckets by their highest bits that
+//                         differ, and each counts the ones of its bucket up
+//                         to it; LDS radix sort where a bucket is too long;
 //        more             one global LSD radix sort over all such segments
 //                         on (segment rank, value);
 //   4. an exclusive scan of the per-block distinct counts places the output;
 //      the distinct values are unpacked to (src, label, dst).
-// The LDS radix sorts rank digits with wave ballots into per-wave counters
-// and skip every digit on which a segment's keys agree.
+// Repeated values end at one place, and the value found there last is kept.
 #include "bsim_device.h"
 
 namespace bsim {
 
 namespace {
 
-constexpr uint32_t kSegSmallMax = 256;     // tile-packed segments hold at most this many values
-constexpr uint32_t kSegMedMax = 4096;      // one 256-thread workgroup per segment
-constexpr uint32_t kSegBigMax = 16384;     // one 1,024-thread workgroup per segment
-constexpr uint32_t kSortIpt = 16;          // values per thread in a medium segment's sort (at most)
+constexpr uint32_t kSegSmallMax = 128;     // tile-packed segments hold at most this many values
+constexpr uint32_t kSortIpt = 16;          // values per thread of a longer segment (at most)
+constexpr uint32_t kSegMidMax = 512;       // one wave per segment
+constexpr uint32_t kSegMedMax = kBlock * kSortIpt;   // one 256-thread workgroup per segment
+constexpr uint32_t kBigBlock = 1024;
+constexpr uint32_t kSegBigMax = kBigBlock * kSortIpt;  // one 1,024-thread workgroup per segment
 constexpr uint32_t kSmallBlock = 64;       // a small tile is one wave
 constexpr uint32_t kSmallRange = 256;      // segment starts per small tile
-constexpr uint32_t kSmallCap = 512;        // values per small tile: kSmallRange + kSegSmallMax - 1 fit
-constexpr uint32_t kSmallMaxSeg = kSmallCap / 2;             // segments of >= 2 values
+constexpr uint32_t kSmallCap = 384;        // values per small tile
 constexpr uint32_t kSmallRounds = kSmallCap / kSmallBlock;   // values per lane
-constexpr uint32_t kRankMax = 128;          // longest segment that k_seg_small ranks by counting
-constexpr int kOrdBits = 8;                                  // tile ordinals < 256
+constexpr uint32_t kSmallMaxSeg = kSmallRange / 2;           // segments of >= 2 values
+constexpr uint32_t kBucketMax = 128;       // longest bucket whose values are ranked by counting
 constexpr uint32_t kUnpackTile = kBlock * 16;
 constexpr uint32_t kUnpackCache = 4096;    // block offsets a tile keeps in LDS
-constexpr uint32_t kBigBlock = 1024;
 
-static_assert(kSmallRange + kSegSmallMax <= kSmallCap, "a small tile must hold its segments");
-static_assert(kSmallMaxSeg <= (1u << kOrdBits), "tile ordinals must fit their field");
-static_assert(kBigBlock * kSortIpt == kSegBigMax && kBlock * kSortIpt == kSegMedMax, "sort capacities");
+static_assert(kSmallRange + kSegSmallMax - 1 <= kSmallCap, "a small tile must hold its segments");
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(x), d, 64));
-        if (lane >= static_cast<uint32_t>(d)) x += y;
-    }
-    return x;
+// A segment is sorted by a group of NT threads: one wave of a workgroup
+// (NT = 64), or the workgroup.
+template <int NT>
+__device__ __forceinline__ uint32_t group_tid() { return NT == 64 ? lane_id() : threadIdx.x; }
+
+template <int NT>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (NT == 64)
+        wave_sync();
+    else
+        __syncthreads();
 }
 
-// Exclusive scan over the NT threads of a block; *total gets the sum.  All
-// threads must call it.  `red` needs NT / 64 entries.
 template <int NT>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* red, uint32_t* total) {
-    const uint32_t incl = wave_incl_scan(x);
+__device__ __forceinline__ bool group_any(bool x) {
+    if constexpr (NT == 64)
+        return __any(x);
+    else
+        return __syncthreads_or(x);
+}
+
+// Exclusive scan over the group; *total gets the sum.  All threads must call
+// it.  `red` needs NT / 64 entries.
+template <int NT>
+__device__ __forceinline__ uint32_t group_excl_scan(uint32_t x, uint32_t* red, uint32_t* total) {
+    const uint32_t incl = wave_incl_sum(x);
+    if constexpr (NT == 64) {
+        *total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+        return incl - x;
+    }
     const uint32_t w = threadIdx.x >> 6;
     if (lane_id() == 63) red[w] = incl;
     __syncthreads();
@@ -90,43 +105,24 @@ __device__ __forceinline__ uint32_t last_le(const uint32_t* off, uint32_t lo, ui
     return lo;
 }
 
-// Shared state of one LDS sort: the keys of the tile, the per-wave digit
-// counters and the segment table.
-struct SortSmem {
-    uint64_t* buf;       // [cap]
-    uint32_t* wc;        // [NT / 64][256]
-    uint32_t* red;       // [16]
-    uint32_t* misc;      // [8]
-    uint32_t* lofs;      // [max_seg + 1] first position of each segment in the tile
-    uint32_t* blk;       // [max_seg] its block
-    uint32_t* est;       // [max_seg] its first value in vals[]
-    uint32_t* dbase;     // [max_seg] distinct values before it in the tile
-};
-
+// LDS of one segment's sort.  The largest class fills a CU's memory with its
+// keys and counters and is sorted by radix passes alone.
+constexpr uint16_t kNoMark = 0xFFFF;
 template <int NT>
-__device__ SortSmem carve(uint8_t* p, uint32_t cap, uint32_t max_seg) {
-    SortSmem S;
-    S.buf = reinterpret_cast<uint64_t*>(p);
-    p += 8ull * cap;
-    S.wc = reinterpret_cast<uint32_t*>(p);
-    p += 4ull * (NT / 64) * 256;
-    S.red = reinterpret_cast<uint32_t*>(p);
-    p += 4 * 16;
-    S.misc = reinterpret_cast<uint32_t*>(p);
-    p += 4 * 8;
-    S.lofs = reinterpret_cast<uint32_t*>(p);
-    p += 4ull * (max_seg + 1);
-    S.blk = reinterpret_cast<uint32_t*>(p);
-    p += 4ull * max_seg;
-    S.est = reinterpret_cast<uint32_t*>(p);
-    p += 4ull * max_seg;
-    S.dbase = reinterpret_cast<uint32_t*>(p);
-    return S;
-}
-
-__host__ __device__ constexpr uint64_t sort_smem_bytes(uint32_t nt, uint32_t cap, uint32_t max_seg) {
-    return 8ull * cap + 4ull * (nt / 64) * 256 + 4 * 16 + 4 * 8 + 4ull * (max_seg + 1) + 12ull * max_seg;
-}
+struct SegSmem {
+    static constexpr bool kBucketed = NT < kBigBlock;
+    static constexpr uint32_t kIpt = NT == 64 ? kSegMidMax / 64 : kSortIpt;  // keys per thread
+    static constexpr uint32_t kCap = NT * kIpt;
+    static constexpr uint32_t kCounters = kBucketed ? NT * 8 : NT * 4;
+    uint64_t* buf;   // [kCap] keys
+    uint32_t* wc;    // [kCounters] bucket bounds, or a digit's counters per wave
+    uint32_t* red;   // [16]
+    uint16_t* mark;  // [kCap] which key has each place, kNoMark where none has
+    __device__ explicit SegSmem(uint64_t* p)
+        : buf(p), wc(reinterpret_cast<uint32_t*>(p + kCap)), red(wc + kCounters),
+          mark(reinterpret_cast<uint16_t*>(red + 16)) {}
+    static constexpr uint64_t bytes() { return (kBucketed ? 10ull : 8ull) * kCap + 4ull * kCounters + 4 * 16; }
+};
 
 struct SegArgs {
     uint64_t* vals;             // bucketed values, sorted and compacted in place
@@ -135,63 +131,50 @@ struct SegArgs {
     uint32_t* uniq;             // distinct values per block
     const uint32_t* tile_first; // small tiles: first block whose segment starts in the tile
     uint32_t n_tiles;
-    const uint32_t* list;       // medium segments: their blocks
-    const uint32_t* n_list;     // and their number
+    const uint32_t *l_mid, *l_med, *l_big;   // longer segments by class: their blocks
+    const uint32_t *n_mid, *n_med, *n_big;   // and their number
     int vb;                     // value bits
 };
 
-// Sort the tile's cnt keys (ordinal << vb | value), de-duplicate, and write
-// every segment's distinct values back to the front of its segment.  The
-// segment table (lofs, blk, est, nseg) is set up by the caller, followed by
-// a barrier.
+// The differing bits of the group's keys (kor, kand: a thread's own).
 template <int NT>
-__device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uint32_t nseg) {
+__device__ uint64_t differing_bits(const SegSmem<NT>& S, uint64_t kor, uint64_t kand) {
     constexpr uint32_t W = NT / 64;
-    constexpr uint32_t kIpt = NT == kSmallBlock ? kSmallRounds : kSortIpt;
-    constexpr uint32_t DPT = NT >= 256 ? 1 : 256 / NT;  // digits per thread in the prefix step
-    const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const uint32_t ipt = (cnt + NT - 1) / NT;  // rounds per wave; element = (w * ipt + r) * 64 + lane
-    const uint64_t vmask = (1ull << a.vb) - 1;
-    const uint64_t lt = (1ull << lane) - 1;
-    uint64_t key[kIpt];
-    uint64_t kor = 0, kand = ~0ull;
-#pragma unroll
-    for (uint32_t r = 0; r < kIpt; r++) {
-        key[r] = ~0ull;
-        const uint32_t i = (w * ipt + r) * 64 + lane;
-        if (r < ipt && i < cnt) {
-            const uint32_t o = nseg == 1 ? 0u : last_le(S.lofs, 0, nseg, i);
-            key[r] = (static_cast<uint64_t>(o) << a.vb) | a.vals[S.est[o] + (i - S.lofs[o])];
-            kor |= key[r];
-            kand &= key[r];
-        }
-    }
-    // bits on which the keys differ: only their digits need a pass
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         kor |= shfl_xor_u64(kor, d);
         kand &= shfl_xor_u64(kand, d);
     }
-    if (lane == 0) {
-        S.buf[2 * w] = kor;
-        S.buf[2 * w + 1] = kand;
+    if (lane_id() == 0) {
+        S.buf[2 * (group_tid<NT>() >> 6)] = kor;
+        S.buf[2 * (group_tid<NT>() >> 6) + 1] = kand;
     }
-    __syncthreads();
-    uint64_t diff = 0;
-    {
-        uint64_t o = 0, n = ~0ull;
-        for (uint32_t i = 0; i < W; i++) {
-            o |= S.buf[2 * i];
-            n &= S.buf[2 * i + 1];
-        }
-        diff = o ^ n;
+    group_sync<NT>();
+    uint64_t o = 0, n = ~0ull;
+    for (uint32_t i = 0; i < W; i++) {
+        o |= S.buf[2 * i];
+        n &= S.buf[2 * i + 1];
     }
-    __syncthreads();
+    group_sync<NT>();
+    return o ^ n;
+}
+
+// Sort the segment's cnt keys by radix passes over the digits with differing
+// bits: digits are ranked with wave ballots into per-wave counters.  key[r]
+// is element (w * ipt + r) * 64 + lane, before and after (~0 past the end).
+template <int NT>
+__device__ void radix_segment(const SegSmem<NT>& S, uint32_t cnt, uint32_t ipt, uint64_t diff,
+                              uint64_t (&key)[SegSmem<NT>::kIpt]) {
+    constexpr uint32_t W = NT / 64;
+    constexpr uint32_t DPT = NT >= 256 ? 1 : 256 / NT;  // digits per thread in the prefix step
+    const uint32_t tid = group_tid<NT>(), lane = lane_id(), w = tid >> 6;
+    const uint64_t lt = (1ull << lane) - 1;
+    constexpr uint32_t kIpt = SegSmem<NT>::kIpt;
     uint32_t lr[kIpt];
     for (int shift = 0; shift < 64; shift += 8) {
-        if (((diff >> shift) & 0xFF) == 0) continue;  // uniform over the block
+        if (((diff >> shift) & 0xFF) == 0) continue;  // uniform over the group
         for (uint32_t d = lane; d < 256; d += 64) S.wc[w * 256 + d] = 0;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         // wave-local stable ranks per digit
 #pragma unroll
         for (uint32_t r = 0; r < kIpt; r++) {
@@ -211,7 +194,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
             base = static_cast<uint32_t>(__shfl(static_cast<int>(base), static_cast<int>(leader), 64));
             lr[r] = base + static_cast<uint32_t>(__popcll(peers & lt));
         }
-        __syncthreads();
+        group_sync<NT>();
         // digit d of wave w starts at (keys of smaller digits) + (digit d in
         // earlier waves); thread t owns digits [t DPT, (t + 1) DPT)
         const bool owner = tid * DPT < 256;
@@ -220,7 +203,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
             for (uint32_t c = 0; c < DPT; c++)
                 for (uint32_t i = 0; i < W; i++) tot += S.wc[i * 256 + tid * DPT + c];
         uint32_t all = 0;
-        uint32_t run = block_excl_scan<NT>(owner ? tot : 0u, S.red, &all);
+        uint32_t run = group_excl_scan<NT>(owner ? tot : 0u, S.red, &all);
         if (owner)
             for (uint32_t c = 0; c < DPT; c++)
                 for (uint32_t i = 0; i < W; i++) {
@@ -229,7 +212,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
                     S.wc[i * 256 + d] = run;
                     run += cc;
                 }
-        __syncthreads();
+        group_sync<NT>();
 #pragma unroll
         for (uint32_t r = 0; r < kIpt; r++) {
             if (r >= ipt) continue;
@@ -239,7 +222,7 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
                 S.buf[S.wc[w * 256 + dig] + lr[r]] = key[r];
             }
         }
-        __syncthreads();
+        group_sync<NT>();
 #pragma unroll
         for (uint32_t r = 0; r < kIpt; r++) {
             if (r >= ipt) continue;
@@ -247,69 +230,27 @@ __device__ void sort_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
             if (i < cnt) key[r] = S.buf[i];
         }
     }
-    // key[r] now holds sorted element (w * ipt + r) * 64 + lane; publish the
-    // order for the neighbour comparison
-#pragma unroll
-    for (uint32_t r = 0; r < kIpt; r++) {
-        if (r >= ipt) continue;
-        const uint32_t i = (w * ipt + r) * 64 + lane;
-        if (i < cnt) S.buf[i] = key[r];
-    }
-    __syncthreads();
-    // distinct positions: first occurrences counted in element order
-    uint32_t dloc[kIpt];
-    uint32_t firsts = 0;  // bit r: element of round r is a first occurrence
-    uint32_t wrun = 0;
-#pragma unroll
-    for (uint32_t r = 0; r < kIpt; r++) {
-        if (r >= ipt) continue;
-        const uint32_t i = (w * ipt + r) * 64 + lane;
-        const bool first = i < cnt && (i == 0 || key[r] != S.buf[i - 1]);
-        const uint64_t bal = __ballot(first);
-        dloc[r] = wrun + static_cast<uint32_t>(__popcll(bal & lt));
-        wrun += static_cast<uint32_t>(__popcll(bal));
-        if (first) firsts |= 1u << r;
-    }
-    if (lane == 0) S.red[w] = wrun;
-    __syncthreads();
-    uint32_t wbase = 0;
-    for (uint32_t i = 0; i < w; i++) wbase += S.red[i];
-    // every segment start is a first occurrence: it records the segment's base
-#pragma unroll
-    for (uint32_t r = 0; r < kIpt; r++) {
-        if (r >= ipt) continue;
-        const uint32_t i = (w * ipt + r) * 64 + lane;
-        if (i < cnt) {
-            const uint32_t o = static_cast<uint32_t>(key[r] >> a.vb);
-            if (S.lofs[o] == i) S.dbase[o] = wbase + dloc[r];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t r = 0; r < kIpt; r++) {
-        if (r >= ipt) continue;
-        const uint32_t i = (w * ipt + r) * 64 + lane;
-        if (i >= cnt) continue;
-        const uint32_t o = static_cast<uint32_t>(key[r] >> a.vb);
-        const uint32_t d = wbase + dloc[r] - S.dbase[o];
-        const bool first = (firsts >> r) & 1;
-        if (first) a.vals[S.est[o] + d] = key[r] & vmask;
-        if (i + 1 == S.lofs[o + 1]) a.uniq[S.blk[o]] = d + (first ? 1u : 0u);
-    }
 }
 
-// A tile of short segments, as one wave: a value's place in its segment is the
-// number of values up to it, so it reads its segment once from LDS (lanes of
-// one segment read one address).  Equal values get one place; the one whose
-// number is found there after all have written is kept, and the places taken
-// before it are its rank.
+// LDS of a small tile.
+struct SmallSmem {
+    uint64_t val[kSmallCap + 4];       // the values, then the places
+    uint8_t own[kSmallCap];            // segment of each value
+    uint32_t lofs[kSmallMaxSeg + 1];   // first position of each segment in the tile
+    uint32_t blk[kSmallMaxSeg];        // its block
+    uint32_t est[kSmallMaxSeg];        // its first value in vals[]
+};
+
+// A value's place in its segment is the number of values up to it, so it reads
+// its segment once from LDS (lanes of one segment read one address).  Equal
+// values get one place; the one whose number is found there after all have
+// written is kept, and the places taken before it are its rank.
 template <typename V>
-__device__ void rank_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uint32_t nseg) {
+__device__ void rank_tile(const SegArgs& a, SmallSmem& S, uint32_t cnt, uint32_t nseg) {
     const uint32_t lane = lane_id();
-    V* val = reinterpret_cast<V*>(S.buf);
-    uint8_t* own = reinterpret_cast<uint8_t*>(S.wc);
+    V* val = reinterpret_cast<V*>(S.val);
     for (uint32_t o = lane; o < nseg; o += 64)
-        for (uint32_t i = S.lofs[o]; i < S.lofs[o + 1]; i++) own[i] = static_cast<uint8_t>(o);
+        for (uint32_t i = S.lofs[o]; i < S.lofs[o + 1]; i++) S.own[i] = static_cast<uint8_t>(o);
     wave_sync();
     V x[kSmallRounds];
     uint32_t seg[kSmallRounds];  // first position << 16 | length
@@ -320,7 +261,7 @@ __device__ void rank_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
         x[r] = 0;
         seg[r] = to[r] = 0;
         if (i < cnt) {
-            const uint32_t o = own[i], s0 = S.lofs[o];
+            const uint32_t o = S.own[i], s0 = S.lofs[o];
             seg[r] = s0 << 16 | (S.lofs[o + 1] - s0);
             to[r] = S.est[o];
             x[r] = static_cast<V>(a.vals[to[r] + (i - s0)]);
@@ -345,7 +286,7 @@ __device__ void rank_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     }
     wave_sync();
     // the values are in registers: their place now holds who wrote there
-    uint16_t* mark = reinterpret_cast<uint16_t*>(S.buf);
+    uint16_t* mark = reinterpret_cast<uint16_t*>(S.val);
     uint16_t* before = mark + kSmallCap;
 #pragma unroll
     for (uint32_t r = 0; r < kSmallRounds; r++) mark[r * 64 + lane] = 0xFFFF;
@@ -387,26 +328,22 @@ __device__ void rank_tile(const SegArgs& a, const SortSmem& S, uint32_t cnt, uin
     for (uint32_t o = lane; o < nseg; o += 64) a.uniq[S.blk[o]] = before[S.lofs[o + 1]] - before[S.lofs[o]];
 }
 
-// Small segments (2..256 values): tile t takes the small segments whose
+// Small segments (2..128 values): tile t takes the small segments whose
 // first value lies in [t R, (t + 1) R), R = kSmallRange, and packs them back
-// to back.  A tile is one wave, so its barriers cost next to nothing and many
-// tiles share a CU.
+// to back.  A tile is one wave with 5 KB of LDS, so many share a CU.
 //
-// Counting reads a value's whole segment, the radix sort takes some five
-// passes of eight ballots a value whatever the length.  With radix alone the
-// 2^27 values of a uniform graph (8 a segment) took 3.2 ms, now 1.06; R-MAT
-// graphs, whose tiles are mixed, by the longest segment that is counted:
-//   kRankMax          0     24    64    128   256
-//   2^24 vertices     1.63  1.41  1.23  1.17  1.56 ms
-//   2^27              12.5        10.2  9.60
+// Counting reads a value's whole segment, a radix sort takes some five passes
+// of eight ballots a value whatever the length: with radix the 2^27 values of
+// a uniform graph (8 a segment) took 3.2 ms.  Counted beside a radix sort for
+// tiles with a segment of 129 to 256 values they took 1.06 ms, and 1.17 (9.6)
+// ms on R-MAT graphs of 2^24 (2^27) vertices, 1.56 where those were counted
+// too; with those segments in a class of their own 0.70 and 0.46 (4.1).
 __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
-    extern __shared__ uint64_t smem_small[];
-    const SortSmem S = carve<kSmallBlock>(reinterpret_cast<uint8_t*>(smem_small), kSmallCap, kSmallMaxSeg);
+    __shared__ SmallSmem S;
     const uint32_t t = blockIdx.x;
     const uint32_t b_lo = a.tile_first[t];
     const uint32_t b_hi = t + 1 < a.n_tiles ? a.tile_first[t + 1] : a.nb;
     uint32_t nseg = 0, cnt = 0;
-    bool lengthy = false;
     for (uint32_t c = b_lo; c < b_hi; c += kSmallBlock) {  // uniform trip count
         const uint32_t b = c + threadIdx.x;
         uint32_t sz = 0, e0 = 0;
@@ -415,7 +352,6 @@ __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
             sz = a.estart[b + 1] - e0;
         }
         const bool small = sz >= 2 && sz <= kSegSmallMax;
-        lengthy = lengthy || (small && sz > kRankMax);
         const uint32_t mine = small ? (1u << 20) | sz : 0u;
         const uint32_t incl = wave_incl_sum(mine);
         const uint32_t tot = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
@@ -432,31 +368,190 @@ __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
     if (nseg == 0) return;  // uniform
     if (threadIdx.x == 0) S.lofs[nseg] = cnt;
     wave_sync();
-    if (__any(lengthy))
-        sort_tile<kSmallBlock>(a, S, cnt, nseg);
-    else if (a.vb <= 32)
+    if (a.vb <= 32)
         rank_tile<uint32_t>(a, S, cnt, nseg);
     else
         rank_tile<uint64_t>(a, S, cnt, nseg);
 }
 
-// Medium segments: one workgroup per listed segment, or fewer than launched
-// when the host did not wait for the list's length.
+// Place of a segment's live keys by counting: to buckets by their highest
+// differing bits, then each key counts the ones of its bucket up to it.  On
+// return S.mark holds a key per taken place of the first *total, S.buf the
+// keys; false where a bucket is too long (S.buf and S.wc are free again).
 template <int NT>
-__global__ void __launch_bounds__(NT) k_seg_medium(SegArgs a) {
-    extern __shared__ uint64_t smem_med[];
-    const SortSmem S = carve<NT>(reinterpret_cast<uint8_t*>(smem_med), NT * kSortIpt, 1);
-    if (blockIdx.x >= *a.n_list) return;
-    const uint32_t b = a.list[blockIdx.x];
-    const uint32_t cnt = a.estart[b + 1] - a.estart[b];
-    if (threadIdx.x == 0) {
-        S.lofs[0] = 0;
-        S.lofs[1] = cnt;
-        S.blk[0] = b;
-        S.est[0] = a.estart[b];
+__device__ bool rank_segment(const SegSmem<NT>& S, uint32_t ipt, uint64_t diff, const uint64_t (&key)[SegSmem<NT>::kIpt],
+                             uint32_t live, uint32_t* total) {
+    constexpr uint32_t kIpt = SegSmem<NT>::kIpt;
+    constexpr uint32_t kBuckets = SegSmem<NT>::kCounters;
+    constexpr int kBucketBits = NT == 64 ? 9 : 11;
+    static_assert(kBuckets == 1u << kBucketBits, "one bucket per digit");
+    const uint32_t tid = group_tid<NT>(), lane = lane_id(), w = tid >> 6;
+    const int top = 64 - __clzll(static_cast<long long>(diff));
+    const int shift = top > kBucketBits ? top - kBucketBits : 0;
+    auto bucket = [&](uint64_t k) { return static_cast<uint32_t>(k >> shift) & (kBuckets - 1); };
+    for (int attempt = 0;; attempt++) {
+        uint4* own = reinterpret_cast<uint4*>(&S.wc[8 * tid]);
+        own[0] = own[1] = make_uint4(0, 0, 0, 0);
+        group_sync<NT>();
+#pragma unroll
+        for (uint32_t r = 0; r < kIpt; r++)
+            if ((live >> r) & 1) atomicAdd(&S.wc[bucket(key[r])], 1u);
+        group_sync<NT>();
+        const uint4 c = own[0], d = own[1];
+        const uint32_t longest = max(max(max(c.x, c.y), max(c.z, c.w)), max(max(d.x, d.y), max(d.z, d.w)));
+        const uint32_t half = c.x + c.y + c.z + c.w;
+        const uint32_t at = group_excl_scan<NT>(half + d.x + d.y + d.z + d.w, S.red, total);
+        own[0] = make_uint4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
+        own[1] = make_uint4(at + half, at + half + d.x, at + half + d.x + d.y, at + half + d.x + d.y + d.z);
+        const bool over = group_any<NT>(longest > kBucketMax);
+        group_sync<NT>();
+        if (!over) break;
+        if (attempt) return false;
+        // A long bucket is mostly one value repeated (or values close
+        // together, which the radix passes take).  Drop repeats: every key
+        // writes its position to a slot, and one that finds another position
+        // of the same key there goes.
+        uint16_t* slot = reinterpret_cast<uint16_t*>(S.wc);
+#pragma unroll
+        for (uint32_t r = 0; r < kIpt; r++)
+            if ((live >> r) & 1) S.buf[(w * ipt + r) * 64 + lane] = key[r];
+        for (int round = 0; round < 2; round++) {
+            const uint64_t odd = round ? 0x9E3779B97F4A7C15ull : 0xD6E8FEB86659FD93ull;
+            auto home = [&](uint64_t k) { return static_cast<uint32_t>(k * odd >> (63 - kBucketBits)); };
+            group_sync<NT>();
+#pragma unroll
+            for (uint32_t r = 0; r < kIpt; r++)
+                if ((live >> r) & 1) slot[home(key[r])] = static_cast<uint16_t>((w * ipt + r) * 64 + lane);
+            group_sync<NT>();
+#pragma unroll
+            for (uint32_t r = 0; r < kIpt; r++)
+                if ((live >> r) & 1) {
+                    const uint32_t i = slot[home(key[r])];
+                    if (i != (w * ipt + r) * 64 + lane && S.buf[i] == key[r]) live &= ~(1u << r);
+                }
+        }
+        group_sync<NT>();
     }
-    __syncthreads();
-    sort_tile<NT>(a, S, cnt, 1);
+    // scattered, a bucket's counter holds its end
+#pragma unroll
+    for (uint32_t r = 0; r < kIpt; r++)
+        if ((live >> r) & 1) S.buf[atomicAdd(&S.wc[bucket(key[r])], 1u)] = key[r];
+    const uint32_t jpt = (*total + NT - 1) / NT;
+    for (uint32_t r = 0; r < jpt; r++) S.mark[(w * jpt + r) * 64 + lane] = kNoMark;
+    group_sync<NT>();
+    for (uint32_t r = 0; r < jpt; r++) {
+        const uint32_t i = (w * jpt + r) * 64 + lane;
+        if (i >= *total) break;
+        const uint64_t k = S.buf[i];
+        const uint32_t d = bucket(k), s0 = d ? S.wc[d - 1] : 0u, len = S.wc[d] - s0;
+        uint32_t upto = 0;
+        for (uint32_t j = 0; j < len; j += 8) {
+            // (up to seven reads past the bucket stay inside the LDS block)
+#pragma unroll
+            for (uint32_t q = 0; q < 8; q++) upto += (S.buf[s0 + j + q] <= k) & (j + q < len);
+        }
+        S.mark[s0 + upto - 1] = static_cast<uint16_t>(i);
+    }
+    group_sync<NT>();
+    return true;
+}
+
+// One longer segment: the group's threads sort block b's.
+template <int NT>
+__device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
+    const SegSmem<NT> S(smem);
+    constexpr uint32_t kIpt = SegSmem<NT>::kIpt;
+    const uint32_t e0 = a.estart[b], cnt = a.estart[b + 1] - e0;
+    uint64_t* vals = a.vals + e0;
+    const uint32_t tid = group_tid<NT>(), lane = lane_id(), w = tid >> 6;
+    uint32_t ipt = (cnt + NT - 1) / NT;  // rounds per wave; element = (w * ipt + r) * 64 + lane
+    uint64_t key[kIpt];
+    uint64_t kor = 0, kand = ~0ull;
+    uint32_t live = 0;  // bit r: key[r] is a value
+#pragma unroll
+    for (uint32_t r = 0; r < kIpt; r++) {
+        key[r] = ~0ull;
+        const uint32_t i = (w * ipt + r) * 64 + lane;
+        if (r < ipt && i < cnt) {
+            key[r] = vals[i];
+            kor |= key[r];
+            kand &= key[r];
+            live |= 1u << r;
+        }
+    }
+    const uint64_t diff = differing_bits(S, kor, kand);
+    if (diff == 0) {  // one value (uniform)
+        if (tid == 0) {
+            vals[0] = key[0];
+            a.uniq[b] = 1;
+        }
+        return;
+    }
+    uint32_t total = cnt;
+    bool ranked = false;
+    if constexpr (SegSmem<NT>::kBucketed) ranked = rank_segment<NT>(S, ipt, diff, key, live, &total);
+    if (ranked) {
+        ipt = (total + NT - 1) / NT;
+    } else {
+        total = cnt;
+        radix_segment<NT>(S, cnt, ipt, diff, key);
+#pragma unroll
+        for (uint32_t r = 0; r < kIpt; r++) {
+            const uint32_t i = (w * ipt + r) * 64 + lane;
+            if (r < ipt && i < cnt) S.buf[i] = key[r];
+        }
+        group_sync<NT>();
+    }
+    // the key of place i if it is a distinct one's: the distinct values in order
+    auto distinct_at = [&](uint32_t i) -> uint32_t {
+        if (ranked) return S.mark[i];
+        return i < total && (i == 0 || S.buf[i - 1] != S.buf[i]) ? i : kNoMark;
+    };
+    uint32_t mine = 0;
+    for (uint32_t r = 0; r < ipt; r++)
+        mine += static_cast<uint32_t>(__popcll(__ballot(distinct_at((w * ipt + r) * 64 + lane) != kNoMark)));
+    if (lane == 0) S.red[w] = mine;
+    group_sync<NT>();
+    uint32_t at = 0, distinct = 0;
+    for (uint32_t i = 0; i < NT / 64; i++) {
+        if (i < w) at += S.red[i];
+        distinct += S.red[i];
+    }
+    for (uint32_t r = 0; r < ipt; r++) {
+        const uint32_t i = distinct_at((w * ipt + r) * 64 + lane);
+        const uint64_t bal = __ballot(i != kNoMark);
+        if (i != kNoMark) vals[at + static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1)))] = S.buf[i];
+        at += static_cast<uint32_t>(__popcll(bal));
+    }
+    if (tid == 0) a.uniq[b] = distinct;
+}
+
+// Longer segments, listed by class: a workgroup of 256 takes one of more than
+// 512 values, or four shorter ones, a wave each; one of 1,024 takes one of
+// more than 4,096.  The grid is for n_med and n_mid (n_big) segments, which is
+// more than there are when the host did not wait for the lists' lengths.
+//
+// Bound by LDS latency at the twelve waves a CU that its memory allows.  On
+// R-MAT graphs of 2^24 (2^27) vertices radix passes alone took 1.02 (8.2) ms
+// for the segments of more than 256 values and some 0.7 (5.5) of k_seg_small
+// for the shorter ones; buckets take 1.21 (11.1) ms for both together.  A bound
+// of 64 values a bucket instead of 128 sends more segments to the radix passes:
+// 0.23 (0.6) ms slower.  Both classes are one launch because a graph of 2^20
+// edges waits 34 + 40 us for two, 35 for one.
+__global__ void __launch_bounds__(kBlock) k_seg_medium(SegArgs a, uint32_t n_med) {
+    extern __shared__ uint64_t smem_med[];
+    if (blockIdx.x < n_med) {
+        if (blockIdx.x < *a.n_med) sort_segment<kBlock>(a, smem_med, a.l_med[blockIdx.x]);
+        return;
+    }
+    const uint32_t wv = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    const uint32_t i = (blockIdx.x - n_med) * kWaves + wv;
+    if (i < *a.n_mid) sort_segment<64>(a, smem_med + wv * (SegSmem<64>::bytes() / 8), a.l_mid[i]);
+}
+
+__global__ void __launch_bounds__(kBigBlock) k_seg_big(SegArgs a) {
+    extern __shared__ uint64_t smem_big[];
+    if (blockIdx.x < *a.n_big) sort_segment<kBigBlock>(a, smem_big, a.l_big[blockIdx.x]);
 }
 
 // ------------------------------------------------------------ set-up passes
@@ -541,13 +636,13 @@ constexpr int kClassPerThread = 8;
 constexpr uint32_t kClassPerBlock = kBlock * kClassPerThread;
 
 __global__ void __launch_bounds__(kBlock) k_seg_class(const uint32_t* __restrict__ estart, uint32_t nb,
-                                                      uint32_t* __restrict__ uniq, uint32_t* __restrict__ l_med,
-                                                      uint32_t* __restrict__ l_big, uint32_t* __restrict__ l_huge,
-                                                      FinalHost* __restrict__ ctr) {
-    __shared__ uint32_t s_n[3], s_at[3], s_huge;
+                                                      uint32_t* __restrict__ uniq, uint32_t* __restrict__ l_mid,
+                                                      uint32_t* __restrict__ l_med, uint32_t* __restrict__ l_big,
+                                                      uint32_t* __restrict__ l_huge, FinalHost* __restrict__ ctr) {
+    __shared__ uint32_t s_n[4], s_at[4], s_huge;
     const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kClassPerBlock;
-    if (threadIdx.x < 3) s_n[threadIdx.x] = 0;
-    if (threadIdx.x == 3) s_huge = 0;
+    if (threadIdx.x < 4) s_n[threadIdx.x] = 0;
+    if (threadIdx.x == 4) s_huge = 0;
     __syncthreads();
     uint32_t cls[kClassPerThread], pos[kClassPerThread];
 #pragma unroll
@@ -557,18 +652,18 @@ __global__ void __launch_bounds__(kBlock) k_seg_class(const uint32_t* __restrict
         if (b >= nb) continue;
         const uint32_t sz = estart[b + 1] - estart[b];
         if (sz <= 1) uniq[b] = sz;
-        cls[r] = sz > kSegBigMax ? 3u : sz > kSegMedMax ? 2u : sz > kSegSmallMax ? 1u : 0u;
+        cls[r] = sz > kSegBigMax ? 4u : sz > kSegMedMax ? 3u : sz > kSegMidMax ? 2u : sz > kSegSmallMax ? 1u : 0u;
         if (cls[r]) pos[r] = atomicAdd(&s_n[cls[r] - 1], 1u);
-        if (cls[r] == 3) atomicAdd(&s_huge, sz);
+        if (cls[r] == 4) atomicAdd(&s_huge, sz);
     }
     __syncthreads();
-    if (threadIdx.x < 3 && s_n[threadIdx.x]) {
-        uint32_t* c[3] = {ctr->med, ctr->big, ctr->huge};
+    if (threadIdx.x < 4 && s_n[threadIdx.x]) {
+        uint32_t* c[4] = {ctr->mid, ctr->med, ctr->big, ctr->huge};
         s_at[threadIdx.x] = atomicAdd(c[threadIdx.x], s_n[threadIdx.x]);
     }
-    if (threadIdx.x == 3 && s_huge) atomicAdd(ctr->huge_values, s_huge);
+    if (threadIdx.x == 4 && s_huge) atomicAdd(ctr->huge_values, s_huge);
     __syncthreads();
-    uint32_t* lists[3] = {l_med, l_big, l_huge};
+    uint32_t* lists[4] = {l_mid, l_med, l_big, l_huge};
 #pragma unroll
     for (int r = 0; r < kClassPerThread; r++)
         if (cls[r])
@@ -683,7 +778,6 @@ __global__ void __launch_bounds__(kBlock) k_seg_unpack(const uint64_t* __restric
 bool bucketed_summary_edges_fit(const Staged& g, int lb, int bb) {
     const int vb = lb + bb;
     if (g.src || g.m == 0 || g.n_tiles + g.n_solo + g.n_hubs == 0) return false;
-    if (vb + kOrdBits > 64) return false;
     // huge segments are ranked: at most m / (kSegBigMax + 1) of them
     return vb + bit_width(g.m / (kSegBigMax + 1)) <= 64;
 }
@@ -718,11 +812,14 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
     auto list_cap = [&](uint32_t above) {
         return static_cast<uint32_t>(std::min<uint64_t>(nb, m / (above + 1ull)));
     };
-    const uint32_t cap_med = list_cap(kSegSmallMax), cap_big = list_cap(kSegMedMax), cap_huge = list_cap(kSegBigMax);
+    const uint32_t cap_mid = list_cap(kSegSmallMax), cap_med = list_cap(kSegMidMax), cap_big = list_cap(kSegMedMax),
+                   cap_huge = list_cap(kSegBigMax);
+    uint32_t* l_mid = arena.alloc<uint32_t>(cap_mid);
     uint32_t* l_med = arena.alloc<uint32_t>(cap_med);
     uint32_t* l_big = arena.alloc<uint32_t>(cap_big);
     uint32_t* l_huge = arena.alloc<uint32_t>(cap_huge);
-    k_seg_class<<<ceil_div(nb, kClassPerBlock), kBlock, 0, s>>>(estart, nb, uniq, l_med, l_big, l_huge, dev);
+    k_seg_class<<<ceil_div(nb, kClassPerBlock), kBlock, 0, s>>>(estart, nb, uniq, l_mid, l_med, l_big, l_huge,
+                                                                dev);
     hip_check(hipGetLastError(), "segment launch");
     SegArgs a{};
     a.vals = vals;
@@ -737,30 +834,28 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
                                                                                        n_st, tf);
         a.tile_first = tf;
         a.n_tiles = n_st;
-        k_seg_small<<<n_st, kSmallBlock, sort_smem_bytes(kSmallBlock, kSmallCap, kSmallMaxSeg), s>>>(a);
+        k_seg_small<<<n_st, kSmallBlock, 0, s>>>(a);
     }
     // the lists' lengths, while the small segments are sorted; a graph too
     // small for a huge segment launches as many workgroups as its lists can
-    // hold instead (at most 63 and 3) and does not wait
-    uint32_t n_med = cap_med, n_big = cap_big, n_huge = 0, huge_elems = 0;
+    // hold instead (at most 127, 31 and 3) and does not wait
+    uint32_t n_mid = cap_mid, n_med = cap_med, n_big = cap_big, n_huge = 0, huge_elems = 0;
     if (cap_huge) {
         const FinalHost& c = fetch();
-        n_med = c.med[0], n_big = c.big[0], n_huge = c.huge[0], huge_elems = c.huge_values[0];
+        n_mid = c.mid[0], n_med = c.med[0], n_big = c.big[0], n_huge = c.huge[0], huge_elems = c.huge_values[0];
     }
-    if (n_med) {
-        a.list = l_med;
-        a.n_list = dev->med;
-        const uint64_t bytes = sort_smem_bytes(kBlock, kSegMedMax, 1);
-        k_seg_medium<kBlock><<<n_med, kBlock, bytes, s>>>(a);
+    a.l_mid = l_mid, a.l_med = l_med, a.l_big = l_big;
+    a.n_mid = dev->mid, a.n_med = dev->med, a.n_big = dev->big;
+    if (n_med || n_mid) {
+        constexpr uint64_t bytes = std::max(SegSmem<kBlock>::bytes(), kWaves * SegSmem<64>::bytes());
+        k_seg_medium<<<n_med + ceil_div(n_mid, kWaves), kBlock, bytes, s>>>(a, n_med);
     }
     if (n_big) {
-        a.list = l_big;
-        a.n_list = dev->big;
-        const uint64_t bytes = sort_smem_bytes(kBigBlock, kSegBigMax, 1);
-        hip_check(hipFuncSetAttribute(reinterpret_cast<const void*>(k_seg_medium<kBigBlock>),
+        const uint64_t bytes = SegSmem<kBigBlock>::bytes();
+        hip_check(hipFuncSetAttribute(reinterpret_cast<const void*>(k_seg_big),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)),
                   "large-segment LDS");
-        k_seg_medium<kBigBlock><<<n_big, kBigBlock, bytes, s>>>(a);
+        k_seg_big<<<n_big, kBigBlock, bytes, s>>>(a);
     }
     hip_check(hipGetLastError(), "segment sort launch");
     if (n_huge) {
