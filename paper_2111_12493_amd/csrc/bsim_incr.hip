@@ -271,38 +271,71 @@ __global__ void k_clear_tidx(const uint32_t* __restrict__ tl, uint32_t nT, uint3
 
 // ---------------------------------------------------------------- out-edge merge
 
-// keep[e] (written to kpos before the scan): does old edge e survive?
+// Which old edges go: a bit per edge (words[e / 64]) and a word's number of
+// them, for the scan.  A change touches few rows, so an edge's place after the
+// merge is its old place in its row, less the row's removed edges before it:
+// flags and positions of four bytes per edge, written, scanned and read back,
+// took 650 us on 2^26 edges; a word per 64 edges takes 220.
+// Entries per thread of a merge pass, their loads under way together: with one
+// each, k_fwd_removed took 278 us on 2^26 edges, k_fwd_copy 420 and k_rev_copy
+// 325; with four 200, 337 (4.8 TB/s) and 218 (4.9).
+constexpr uint32_t kMergeItems = 4;
+
+struct Removed {
+    const uint64_t* words;
+    const uint32_t* before;  // removed edges before the word
+    __device__ uint32_t upto(uint32_t e) const {
+        return before[e >> 6] + static_cast<uint32_t>(__popcll(words[e >> 6] & ((1ull << (e & 63)) - 1)));
+    }
+};
+
 template <typename LabT>
-__global__ void k_fwd_keep(const uint32_t* __restrict__ src, const uint32_t* __restrict__ tgt,
+__global__ void k_fwd_removed(const uint32_t* __restrict__ src, const uint32_t* __restrict__ tgt,
                            const LabT* __restrict__ lab, uint32_t m, const uint32_t* __restrict__ dflag,
                            const uint8_t* __restrict__ alive, const uint32_t* __restrict__ chg_lo,
                            const uint32_t* __restrict__ chg_hi, const uint32_t* __restrict__ cw,
                            const uint32_t* __restrict__ cl, const uint32_t* __restrict__ cf,
-                           uint32_t* __restrict__ exist, uint32_t* __restrict__ keep) {
-    const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m) return;
-    const uint32_t v = src[e];
-    uint32_t k = 1;
-    if (dflag[v] & kFlagRows) {
-        const uint32_t w = tgt[e];
-        if (!alive[v] || !alive[w]) {
-            k = 0;
-        } else {
-            uint32_t lo = chg_lo[v], hi = chg_hi[v];
-            const uint32_t l = static_cast<uint32_t>(lab[e]);
-            // changes of v are sorted by (w, l)
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                const uint32_t mw = cw[mid], ml = cl[mid];
-                if (mw < w || (mw == w && ml < l)) lo = mid + 1; else hi = mid;
-            }
-            if (lo < chg_hi[v] && cw[lo] == w && cl[lo] == l) {
-                if (cf[lo] & kChgDeleted) k = 0;
-                else exist[lo] = 1;
+                           uint32_t* __restrict__ exist, uint64_t* __restrict__ words,
+                           uint32_t* __restrict__ count) {
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kBlock * kMergeItems + (threadIdx.x >> 6) * 64 * kMergeItems;
+    uint32_t v[kMergeItems], f[kMergeItems];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        const uint64_t e = base + q * 64 + lane_id();
+        v[q] = e < m ? src[e] : 0u;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) f[q] = base + q * 64 + lane_id() < m ? dflag[v[q]] & kFlagRows : 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        const uint64_t e = base + q * 64 + lane_id();
+        bool goes = false;
+        if (f[q]) {
+            const uint32_t w = tgt[e];
+            if (!alive[v[q]] || !alive[w]) {
+                goes = true;
+            } else {
+                uint32_t lo = chg_lo[v[q]], hi = chg_hi[v[q]];
+                const uint32_t end = hi;
+                const uint32_t l = static_cast<uint32_t>(lab[e]);
+                // changes of v are sorted by (w, l)
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    const uint32_t mw = cw[mid], ml = cl[mid];
+                    if (mw < w || (mw == w && ml < l)) lo = mid + 1; else hi = mid;
+                }
+                if (lo < end && cw[lo] == w && cl[lo] == l) {
+                    if (cf[lo] & kChgDeleted) goes = true;
+                    else exist[lo] = 1;
+                }
             }
         }
+        const uint64_t bits = __ballot(goes);
+        if (lane_id() == 0 && e <= m) {
+            words[e >> 6] = bits;
+            count[e >> 6] = static_cast<uint32_t>(__popcll(bits));
+        }
     }
-    keep[e] = k;
 }
 
 // Is change c appended as a new edge?
@@ -315,12 +348,17 @@ __global__ void k_app_flags(const uint32_t* __restrict__ cf, const uint32_t* __r
 }
 
 __global__ void k_fwd_deg(uint32_t n_new, uint32_t n_old, const uint32_t* __restrict__ off_old,
-                          const uint32_t* __restrict__ kpos, const uint32_t* __restrict__ chg_lo,
+                          Removed gone, const uint32_t* __restrict__ dflag, const uint32_t* __restrict__ chg_lo,
                           const uint32_t* __restrict__ chg_hi, const uint32_t* __restrict__ apos,
                           uint32_t* __restrict__ kept, uint32_t* __restrict__ deg) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
     if (v >= n_new) return;
-    const uint32_t k = v < n_old ? kpos[off_old[v + 1]] - kpos[off_old[v]] : 0u;
+    uint32_t k = 0;
+    if (v < n_old) {
+        const uint32_t e0 = off_old[v], e1 = off_old[v + 1];
+        k = e1 - e0;
+        if (dflag[v] & kFlagRows) k -= gone.upto(e1) - gone.upto(e0);
+    }
     const uint32_t a = apos[chg_hi[v]] - apos[chg_lo[v]];
     kept[v] = k;
     deg[v] = k + a;
@@ -329,17 +367,37 @@ __global__ void k_fwd_deg(uint32_t n_new, uint32_t n_old, const uint32_t* __rest
 template <typename LabT>
 __global__ void k_fwd_copy(const uint32_t* __restrict__ src, const uint32_t* __restrict__ tgt,
                            const LabT* __restrict__ lab, uint32_t m, const uint32_t* __restrict__ off_old,
-                           const uint32_t* __restrict__ kpos, const uint32_t* __restrict__ off_new,
+                           Removed gone, const uint32_t* __restrict__ dflag, const uint32_t* __restrict__ off_new,
                            uint32_t* __restrict__ src2, uint32_t* __restrict__ tgt2, LabT* __restrict__ lab2) {
-    const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m) return;
-    const uint32_t ke = kpos[e];
-    if (kpos[e + 1] == ke) return;
-    const uint32_t v = src[e];
-    const uint32_t p = off_new[v] + (ke - kpos[off_old[v]]);
-    src2[p] = v;
-    tgt2[p] = tgt[e];
-    lab2[p] = lab[e];
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kBlock * kMergeItems + threadIdx.x;
+    uint32_t v[kMergeItems], w[kMergeItems], l[kMergeItems], p[kMergeItems], f[kMergeItems];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        const uint64_t e = base + q * kBlock;
+        v[q] = w[q] = l[q] = 0;
+        if (e < m) v[q] = src[e], w[q] = tgt[e], l[q] = lab[e];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        p[q] = f[q] = 0;
+        if (base + q * kBlock < m) {
+            p[q] = off_new[v[q]] + (static_cast<uint32_t>(base) + q * kBlock - off_old[v[q]]);
+            f[q] = dflag[v[q]] & kFlagRows;
+        }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        const uint64_t at = base + q * kBlock;
+        if (at >= m) break;
+        if (f[q]) {
+            const uint32_t e = static_cast<uint32_t>(at);
+            if (gone.words[e >> 6] >> (e & 63) & 1) continue;
+            p[q] -= gone.upto(e) - gone.upto(off_old[v[q]]);
+        }
+        src2[p[q]] = v[q];
+        tgt2[p[q]] = w[q];
+        lab2[p[q]] = static_cast<LabT>(l[q]);
+    }
 }
 
 template <typename LabT>
@@ -359,32 +417,27 @@ __global__ void k_fwd_append(const uint32_t* __restrict__ cu, const uint32_t* __
 
 // ---------------------------------------------------------------- type lists
 
-__global__ void k_typ_keep(const uint32_t* __restrict__ own, uint32_t nt, const uint32_t* __restrict__ dflag,
-                           uint32_t* __restrict__ keep) {
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < nt) keep[i] = (dflag[own[i]] & kFlagTypes) ? 0u : 1u;
-}
-
+// (a vertex whose types change keeps none of its entries: no position but a
+// vertex's own start is needed)
 __global__ void k_typ_deg(uint32_t n_new, uint32_t n_old, const uint32_t* __restrict__ off_old,
-                          const uint32_t* __restrict__ kpos, const uint32_t* __restrict__ tidx,
+                          const uint32_t* __restrict__ tidx,
                           const uint32_t* __restrict__ tl_off, uint32_t* __restrict__ deg) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
     if (v >= n_new) return;
     const uint32_t ti = tidx[v];
     if (ti) deg[v] = tl_off[ti] - tl_off[ti - 1];
-    else deg[v] = v < n_old ? kpos[off_old[v + 1]] - kpos[off_old[v]] : 0u;
+    else deg[v] = v < n_old ? off_old[v + 1] - off_old[v] : 0u;
 }
 
 __global__ void k_typ_copy(const uint32_t* __restrict__ own, const uint32_t* __restrict__ ids, uint32_t nt,
-                           const uint32_t* __restrict__ off_old, const uint32_t* __restrict__ kpos,
+                           const uint32_t* __restrict__ off_old, const uint32_t* __restrict__ dflag,
                            const uint32_t* __restrict__ off_new, uint32_t* __restrict__ own2,
                            uint32_t* __restrict__ ids2) {
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= nt) return;
-    const uint32_t ki = kpos[i];
-    if (kpos[i + 1] == ki) return;
     const uint32_t v = own[i];
-    const uint32_t p = off_new[v] + (ki - kpos[off_old[v]]);
+    if (dflag[v] & kFlagTypes) return;
+    const uint32_t p = off_new[v] + (i - off_old[v]);
     own2[p] = v;
     ids2[p] = ids[i];
 }
@@ -435,12 +488,20 @@ __global__ void k_rev_deg(uint32_t n_new, uint32_t n_old, const uint32_t* __rest
 __global__ void k_rev_copy(const uint32_t* __restrict__ own, const uint32_t* __restrict__ srcs, uint32_t rm,
                            const uint32_t* __restrict__ off_old, const uint32_t* __restrict__ off_new,
                            uint32_t* __restrict__ own2, uint32_t* __restrict__ srcs2) {
-    const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= rm) return;
-    const uint32_t w = own[e];
-    const uint32_t p = off_new[w] + (e - off_old[w]);
-    own2[p] = w;
-    srcs2[p] = srcs[e];
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kBlock * kMergeItems + threadIdx.x;
+    uint32_t w[kMergeItems], u[kMergeItems], p[kMergeItems];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++) {
+        const uint64_t e = base + q * kBlock;
+        w[q] = u[q] = 0;
+        if (e < rm) w[q] = own[e], u[q] = srcs[e];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++)
+        p[q] = base + q * kBlock < rm ? off_new[w[q]] + (static_cast<uint32_t>(base) + q * kBlock - off_old[w[q]]) : 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeItems; q++)
+        if (base + q * kBlock < rm) own2[p[q]] = w[q], srcs2[p[q]] = u[q];
 }
 
 __global__ void k_rev_append(const uint32_t* __restrict__ rw, const uint32_t* __restrict__ ru, uint32_t nr,
@@ -837,7 +898,8 @@ struct bsim_state {
     DevBuf<uint64_t> ci_ctr;
     DevBuf<uint32_t> ci_dmark, ci_d, ci_q[2], ci_n;  // ci_n: lengths of ci_d, ci_q[0], ci_q[1]
     uint32_t ci_rebuild_from = 0;  // levels from this one on are rebuilt at the next update (> K: none)
-    DevBuf<uint32_t> kpos, chunk_owner, big_done;
+    DevBuf<uint64_t> gone;   // removed edges of a merge: a word per 64, then their counts
+    DevBuf<uint32_t> chunk_owner, big_done;
     DevBuf<BigEntry> big;
     DevBuf<uint64_t> big_acc, scratch;
     DevBuf<IncCounters> cnt;
@@ -874,7 +936,7 @@ struct bsim_state {
         for (auto& l : levels) l.release(s);
         salt.release(s), dflag.release(s), bmark.release(s), fmark.release(s), cflag.release(s);
         chg_lo.release(s), chg_hi.release(s), tidx.release(s), kept.release(s), deg.release(s);
-        blist.release(s), kpos.release(s), chunk_owner.release(s);
+        blist.release(s), gone.release(s), chunk_owner.release(s);
         big_done.release(s), big.release(s), big_acc.release(s), scratch.release(s), cnt.release(s);
         status.release(s), work.release(s);
         for (auto& b : ci_slot) b.release(s);
@@ -993,6 +1055,10 @@ __global__ void k_set_ranges(const uint32_t* __restrict__ gk, const uint32_t* __
     }
 }
 
+// 8-byte words of bsim_state::gone for m old edges.
+uint64_t gone_words(uint64_t m) { return (m / 64 + 1) + (m / 64 + 2) / 2; }
+
+// The merges leave the new lengths in ctx->count_host, for apply_batch.
 template <typename LabT>
 void merge_edges(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& arena) {
     hipStream_t s = st->s;
@@ -1006,7 +1072,7 @@ void merge_edges(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& are
     st->src[c ^ 1].ensure(m_cap + 1, 0, s);
     st->tgt[c ^ 1].ensure(m_cap + 1, 0, s);
     st->lab[c ^ 1].ensure((m_cap + 1) * sizeof(LabT), 0, s);
-    st->kpos.ensure(std::max<uint64_t>(m_old, st->nt) + 1, 0, s);
+    st->gone.ensure(gone_words(m_old), 0, s);
     uint32_t* d_cu = upload(arena, hb.cu, s);
     uint32_t* d_cw = upload(arena, hb.cw, s);
     uint32_t* d_cl = upload(arena, hb.cl, s);
@@ -1014,28 +1080,27 @@ void merge_edges(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& are
     uint32_t* exist = arena.alloc<uint32_t>(nc + 1);
     uint32_t* apos = arena.alloc<uint32_t>(nc + 1);
     hip_check(hipMemsetAsync(exist, 0, (nc + 1) * 4ull, s), "exist");
-    hip_check(hipMemsetAsync(apos, 0, (nc + 1) * 4ull, s), "apos");
-    uint32_t* kpos = st->kpos.p;
+    const uint32_t nw = m_old / 64 + 1;
+    uint64_t* words = st->gone.p;
+    uint32_t* before = reinterpret_cast<uint32_t*>(words + nw);
     const LabT* lab = reinterpret_cast<const LabT*>(st->lab[c].p);
-    hip_check(hipMemsetAsync(kpos, 0, (m_old + 1) * 4ull, s), "kpos");
-    if (m_old) {
-        k_fwd_keep<LabT><<<grid_for(m_old), kBlock, 0, s>>>(st->src[c].p, st->tgt[c].p, lab, m_old, st->dflag.p,
-                                                          st->alive.p, st->chg_lo.p, st->chg_hi.p, d_cw, d_cl,
-                                                          d_cf, exist, kpos);
-        scan_exclusive(kpos, kpos, m_old, kpos + m_old, arena, s);
-    }
+    k_fwd_removed<LabT><<<grid_for(ceil_div(64ull * nw, kMergeItems)), kBlock, 0, s>>>(
+        st->src[c].p, st->tgt[c].p, lab, m_old, st->dflag.p, st->alive.p, st->chg_lo.p, st->chg_hi.p, d_cw, d_cl,
+        d_cf, exist, words, before);
+    scan_exclusive(before, before, nw, nullptr, arena, s);
+    const Removed gone{words, before};
     if (nc) {
         k_app_flags<<<grid_for(nc), kBlock, 0, s>>>(d_cf, exist, nc, apos);
         scan_exclusive(apos, apos, nc, apos + nc, arena, s);
     }
-    k_fwd_deg<<<grid_for(n_new), kBlock, 0, s>>>(n_new, n_old, st->row_off[c].p, kpos, st->chg_lo.p,
+    k_fwd_deg<<<grid_for(n_new), kBlock, 0, s>>>(n_new, n_old, st->row_off[c].p, gone, st->dflag.p, st->chg_lo.p,
                                                  st->chg_hi.p, apos, st->kept.p, st->deg.p);
     uint32_t* off_new = st->row_off[c ^ 1].p;
     scan_exclusive(st->deg.p, off_new, n_new, off_new + n_new, arena, s);
-    const uint32_t m_new = read_u32(off_new + n_new, s);
+    hip_check(hipMemcpyAsync(&st->ctx->count_host[0], off_new + n_new, 4, hipMemcpyDeviceToHost, s), "edge count");
     if (m_old)
-        k_fwd_copy<LabT><<<grid_for(m_old), kBlock, 0, s>>>(st->src[c].p, st->tgt[c].p, lab, m_old,
-                                                          st->row_off[c].p, kpos, off_new, st->src[c ^ 1].p,
+        k_fwd_copy<LabT><<<grid_for(ceil_div(m_old, kMergeItems)), kBlock, 0, s>>>(st->src[c].p, st->tgt[c].p, lab, m_old,
+                                                          st->row_off[c].p, gone, st->dflag.p, off_new, st->src[c ^ 1].p,
                                                           st->tgt[c ^ 1].p,
                                                           reinterpret_cast<LabT*>(st->lab[c ^ 1].p));
     if (nc)
@@ -1044,7 +1109,6 @@ void merge_edges(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& are
                                                          reinterpret_cast<LabT*>(st->lab[c ^ 1].p));
     hip_check(hipGetLastError(), "edge merge");
     st->cur ^= 1;
-    st->m = m_new;
 }
 
 void merge_types(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& arena) {
@@ -1057,30 +1121,23 @@ void merge_types(bsim_state* st, const HostBatch& hb, uint32_t n_old, Arena& are
     if (cap >= (1ull << 32)) throw DeviceError{BSIM_E_UNSUPPORTED, "too many type entries"};
     st->type_own[c ^ 1].ensure(cap + 1, 0, s);
     st->type_ids[c ^ 1].ensure(cap + 1, 0, s);
-    st->kpos.ensure(std::max<uint64_t>(st->m, nt_old) + 1, 0, s);
-    uint32_t* kpos = st->kpos.p;
     uint32_t* d_tl = upload(arena, hb.tl, s);
     uint32_t* d_off = upload(arena, hb.tl_off, s);
     uint32_t* d_ids = upload(arena, hb.tl_ids, s);
-    hip_check(hipMemsetAsync(kpos, 0, (nt_old + 1) * 4ull, s), "kpos");
-    if (nt_old) {
-        k_typ_keep<<<grid_for(nt_old), kBlock, 0, s>>>(st->type_own[c].p, nt_old, st->dflag.p, kpos);
-        scan_exclusive(kpos, kpos, nt_old, kpos + nt_old, arena, s);
-    }
-    k_typ_deg<<<grid_for(n_new), kBlock, 0, s>>>(n_new, n_old, st->type_off[c].p, kpos, st->tidx.p, d_off,
+    k_typ_deg<<<grid_for(n_new), kBlock, 0, s>>>(n_new, n_old, st->type_off[c].p, st->tidx.p, d_off,
                                                  st->deg.p);
     uint32_t* off_new = st->type_off[c ^ 1].p;
     scan_exclusive(st->deg.p, off_new, n_new, off_new + n_new, arena, s);
     if (nt_old)
         k_typ_copy<<<grid_for(nt_old), kBlock, 0, s>>>(st->type_own[c].p, st->type_ids[c].p, nt_old,
-                                                       st->type_off[c].p, kpos, off_new, st->type_own[c ^ 1].p,
+                                                       st->type_off[c].p, st->dflag.p, off_new, st->type_own[c ^ 1].p,
                                                        st->type_ids[c ^ 1].p);
     if (nT)
         k_typ_write<<<grid_for(nT), kBlock, 0, s>>>(d_tl, nT, d_off, d_ids, off_new, st->type_own[c ^ 1].p,
                                                     st->type_ids[c ^ 1].p);
     hip_check(hipGetLastError(), "type merge");
+    hip_check(hipMemcpyAsync(&st->ctx->count_host[1], off_new + n_new, 4, hipMemcpyDeviceToHost, s), "type count");
     st->tcur ^= 1;
-    st->nt = read_u32(off_new + n_new, s);
 }
 
 void merge_reverse(bsim_state* st, const HostBatch& hb, Arena& arena) {
@@ -1104,7 +1161,7 @@ void merge_reverse(bsim_state* st, const HostBatch& hb, Arena& arena) {
     uint32_t* off_new = st->rev_off[c ^ 1].p;
     scan_exclusive(st->deg.p, off_new, n_new, off_new + n_new, arena, s);
     if (st->rm)
-        k_rev_copy<<<grid_for(st->rm), kBlock, 0, s>>>(st->rev_own[c].p, st->rev_src[c].p,
+        k_rev_copy<<<grid_for(ceil_div(st->rm, kMergeItems)), kBlock, 0, s>>>(st->rev_own[c].p, st->rev_src[c].p,
                                                        static_cast<uint32_t>(st->rm), st->rev_off[c].p, off_new,
                                                        st->rev_own[c ^ 1].p, st->rev_src[c ^ 1].p);
     if (nr)
@@ -1423,7 +1480,7 @@ void reserve_batch(bsim_state* st, const HostBatch& hb, ResultReserve& rr) {
         st->type_own[st->tcur ^ 1].ensure(nt_cap + 1, 0, s);
         st->type_ids[st->tcur ^ 1].ensure(nt_cap + 1, 0, s);
     }
-    st->kpos.ensure(std::max(m_cap, nt_cap) + 1, 0, s);
+    st->gone.ensure(gone_words(st->m), 0, s);
     if (!hb.rw.empty() || n_new > st->n_rev) {
         const uint64_t cap = st->rm + hb.rw.size();
         if (cap >= (1ull << 32)) throw DeviceError{BSIM_E_UNSUPPORTED, "reverse lists too long"};
@@ -1526,6 +1583,11 @@ bsim_result* apply_batch(bsim_state* st, const HostBatch& hb) {
         k_clear_tidx<<<grid_for(nT), kBlock, 0, s>>>(d_tl, nT, st->tidx.p);
     }
     if (!hb.rw.empty() || n_new > st->n_rev) merge_reverse(st, hb, arena);
+    if (ng || nd || nT) {
+        hip_check(hipStreamSynchronize(s), "merged lengths");
+        if (ng || nd) st->m = st->ctx->count_host[0];
+        if (nT) st->nt = st->ctx->count_host[1];
+    }
     st->n = n_new;
     st->max_label = std::max(st->max_label, hb.max_label);
     ensure_salt(st, st->max_label);
@@ -1640,7 +1702,7 @@ bsim_result* create_state(bsim_ctx* ctx, const bsim_graph& graph, const bsim_par
     st->src[c ^ 1].ensure(m + 1ull, 0, s);
     st->tgt[c ^ 1].ensure(m + 1ull, 0, s);
     st->lab[c ^ 1].ensure((m + 1ull) * g.label_bytes, 0, s);
-    st->kpos.ensure(std::max<uint64_t>(m, nt) + 1, 0, s);
+    st->gone.ensure(gone_words(m), 0, s);
     st->type_own[st->tcur ^ 1].ensure(nt + 1ull, 0, s);
     st->type_ids[st->tcur ^ 1].ensure(nt + 1ull, 0, s);
     st->chunk_owner.ensure(static_cast<size_t>(n) + st->m / kChunkEdges + 2, 0, s);
@@ -1699,7 +1761,7 @@ uint64_t state_bytes(const bsim_state* st) {
     for (const auto& l : st->levels) add(l);
     add(st->salt), add(st->dflag), add(st->bmark), add(st->fmark), add(st->chg_lo);
     add(st->chg_hi), add(st->tidx), add(st->kept), add(st->deg), add(st->blist), add(st->cflag);
-    add(st->kpos), add(st->chunk_owner), add(st->big_done), add(st->big), add(st->big_acc);
+    add(st->gone), add(st->chunk_owner), add(st->big_done), add(st->big), add(st->big_acc);
     add(st->scratch), add(st->work);
     for (const auto& x : st->ci_slot) add(x);
     for (const auto& x : st->ci_cnt) add(x);
