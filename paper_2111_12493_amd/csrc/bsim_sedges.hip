@@ -16,10 +16,11 @@
 //                         consecutive positions; every value counts the ones
 //                         of its segment up to it;
 //        129..16,384      one wave (up to 512 values) or workgroup per segment (of
-//                         256 threads up to 4,096 values, else 1,024): the
+//                         512 threads up to 4,096 values, else 1,024): the
 //                         values go to buckets by their highest bits that
 //                         differ, and each counts the ones of its bucket up
-//                         to it; LDS radix sort where a bucket is too long;
+//                         to it; LDS radix sort where a bucket is too long,
+//                         and for the largest class;
 //        more             one global LSD radix sort over all such segments
 //                         on (segment rank, value);
 //   4. an exclusive scan of the per-block distinct counts places the output;
@@ -32,17 +33,26 @@ namespace bsim {
 namespace {
 
 constexpr uint32_t kSegSmallMax = 128;     // tile-packed segments hold at most this many values
-constexpr uint32_t kSortIpt = 16;          // values per thread of a longer segment (at most)
 constexpr uint32_t kSegMidMax = 512;       // one wave per segment
-constexpr uint32_t kSegMedMax = kBlock * kSortIpt;   // one 256-thread workgroup per segment
+constexpr uint32_t kMedBlock = 512;
+constexpr uint32_t kMedWaves = kMedBlock / 64;
+constexpr uint32_t kSegMedMax = 4096;      // one workgroup of kMedBlock per segment
 constexpr uint32_t kBigBlock = 1024;
-constexpr uint32_t kSegBigMax = kBigBlock * kSortIpt;  // one 1,024-thread workgroup per segment
+constexpr uint32_t kSegBigMax = 16384;     // one workgroup of kBigBlock per segment
 constexpr uint32_t kSmallBlock = 64;       // a small tile is one wave
 constexpr uint32_t kSmallRange = 256;      // segment starts per small tile
 constexpr uint32_t kSmallCap = 384;        // values per small tile
 constexpr uint32_t kSmallRounds = kSmallCap / kSmallBlock;   // values per lane
 constexpr uint32_t kSmallMaxSeg = kSmallRange / 2;           // segments of >= 2 values
-constexpr uint32_t kBucketMax = 128;       // longest bucket whose values are ranked by counting
+// Segments of the wave class above which they get a launch of their own, where
+// more of their waves fit a CU; fewer do not fill the chip, and wait less
+// beside the longer ones (2^20 edges: 34 + 40 us for two launches, 28 for one).
+constexpr uint32_t kMidApart = 4096;
+// Longest bucket whose values are ranked by counting; longer ones (nearly equal
+// or repeated values) send the segment to the radix passes.  With 128 the
+// segments of 513 to 4,096 values took 7.8 ms on R-MAT 2^27, with 512 6.6; dropping repeats through a
+// table and counting again in between only added to it.
+constexpr uint32_t kBucketMax = 512;
 constexpr uint32_t kUnpackTile = kBlock * 16;
 constexpr uint32_t kUnpackCache = 4096;    // block offsets a tile keeps in LDS
 
@@ -111,9 +121,9 @@ constexpr uint16_t kNoMark = 0xFFFF;
 template <int NT>
 struct SegSmem {
     static constexpr bool kBucketed = NT < kBigBlock;
-    static constexpr uint32_t kIpt = NT == 64 ? kSegMidMax / 64 : kSortIpt;  // keys per thread
-    static constexpr uint32_t kCap = NT * kIpt;
-    static constexpr uint32_t kCounters = kBucketed ? NT * 8 : NT * 4;
+    static constexpr uint32_t kCap = NT == 64 ? kSegMidMax : NT == kMedBlock ? kSegMedMax : kSegBigMax;
+    static constexpr uint32_t kIpt = kCap / NT;  // keys per thread
+    static constexpr uint32_t kCounters = NT == 64 ? 512 : NT * 4;  // (a radix pass needs 256 a wave)
     uint64_t* buf;   // [kCap] keys
     uint32_t* wc;    // [kCounters] bucket bounds, or a digit's counters per wave
     uint32_t* red;   // [16]
@@ -374,74 +384,57 @@ __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
         rank_tile<uint64_t>(a, S, cnt, nseg);
 }
 
-// Place of a segment's live keys by counting: to buckets by their highest
+// Places of a segment's keys by counting: to buckets by their highest
 // differing bits, then each key counts the ones of its bucket up to it.  On
-// return S.mark holds a key per taken place of the first *total, S.buf the
-// keys; false where a bucket is too long (S.buf and S.wc are free again).
+// return S.mark holds a key per taken place, S.buf the keys; false where a
+// bucket is too long (S.buf and S.wc are free again).
 template <int NT>
-__device__ bool rank_segment(const SegSmem<NT>& S, uint32_t ipt, uint64_t diff, const uint64_t (&key)[SegSmem<NT>::kIpt],
-                             uint32_t live, uint32_t* total) {
+__device__ bool rank_segment(const SegSmem<NT>& S, uint32_t cnt, uint32_t ipt, uint64_t diff,
+                             const uint64_t (&key)[SegSmem<NT>::kIpt]) {
     constexpr uint32_t kIpt = SegSmem<NT>::kIpt;
     constexpr uint32_t kBuckets = SegSmem<NT>::kCounters;
     constexpr int kBucketBits = NT == 64 ? 9 : 11;
+    constexpr uint32_t kOwn = kBuckets / NT / 4;  // groups of four buckets a thread counts
     static_assert(kBuckets == 1u << kBucketBits, "one bucket per digit");
     const uint32_t tid = group_tid<NT>(), lane = lane_id(), w = tid >> 6;
     const int top = 64 - __clzll(static_cast<long long>(diff));
     const int shift = top > kBucketBits ? top - kBucketBits : 0;
     auto bucket = [&](uint64_t k) { return static_cast<uint32_t>(k >> shift) & (kBuckets - 1); };
-    for (int attempt = 0;; attempt++) {
-        uint4* own = reinterpret_cast<uint4*>(&S.wc[8 * tid]);
-        own[0] = own[1] = make_uint4(0, 0, 0, 0);
-        group_sync<NT>();
+    uint4* own = reinterpret_cast<uint4*>(S.wc) + kOwn * tid;
 #pragma unroll
-        for (uint32_t r = 0; r < kIpt; r++)
-            if ((live >> r) & 1) atomicAdd(&S.wc[bucket(key[r])], 1u);
-        group_sync<NT>();
-        const uint4 c = own[0], d = own[1];
-        const uint32_t longest = max(max(max(c.x, c.y), max(c.z, c.w)), max(max(d.x, d.y), max(d.z, d.w)));
-        const uint32_t half = c.x + c.y + c.z + c.w;
-        const uint32_t at = group_excl_scan<NT>(half + d.x + d.y + d.z + d.w, S.red, total);
-        own[0] = make_uint4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
-        own[1] = make_uint4(at + half, at + half + d.x, at + half + d.x + d.y, at + half + d.x + d.y + d.z);
-        const bool over = group_any<NT>(longest > kBucketMax);
-        group_sync<NT>();
-        if (!over) break;
-        if (attempt) return false;
-        // A long bucket is mostly one value repeated (or values close
-        // together, which the radix passes take).  Drop repeats: every key
-        // writes its position to a slot, and one that finds another position
-        // of the same key there goes.
-        uint16_t* slot = reinterpret_cast<uint16_t*>(S.wc);
+    for (uint32_t i = 0; i < kOwn; i++) own[i] = make_uint4(0, 0, 0, 0);
+    group_sync<NT>();
 #pragma unroll
-        for (uint32_t r = 0; r < kIpt; r++)
-            if ((live >> r) & 1) S.buf[(w * ipt + r) * 64 + lane] = key[r];
-        for (int round = 0; round < 2; round++) {
-            const uint64_t odd = round ? 0x9E3779B97F4A7C15ull : 0xD6E8FEB86659FD93ull;
-            auto home = [&](uint64_t k) { return static_cast<uint32_t>(k * odd >> (63 - kBucketBits)); };
-            group_sync<NT>();
+    for (uint32_t r = 0; r < kIpt; r++)
+        if (r < ipt && (w * ipt + r) * 64 + lane < cnt) atomicAdd(&S.wc[bucket(key[r])], 1u);
+    group_sync<NT>();
+    uint4 c[kOwn];
+    uint32_t longest = 0, sum = 0;
 #pragma unroll
-            for (uint32_t r = 0; r < kIpt; r++)
-                if ((live >> r) & 1) slot[home(key[r])] = static_cast<uint16_t>((w * ipt + r) * 64 + lane);
-            group_sync<NT>();
-#pragma unroll
-            for (uint32_t r = 0; r < kIpt; r++)
-                if ((live >> r) & 1) {
-                    const uint32_t i = slot[home(key[r])];
-                    if (i != (w * ipt + r) * 64 + lane && S.buf[i] == key[r]) live &= ~(1u << r);
-                }
-        }
-        group_sync<NT>();
+    for (uint32_t i = 0; i < kOwn; i++) {
+        c[i] = own[i];
+        longest = max(longest, max(max(c[i].x, c[i].y), max(c[i].z, c[i].w)));
+        sum += c[i].x + c[i].y + c[i].z + c[i].w;
     }
+    uint32_t all = 0;
+    uint32_t at = group_excl_scan<NT>(sum, S.red, &all);
+#pragma unroll
+    for (uint32_t i = 0; i < kOwn; i++) {
+        own[i] = make_uint4(at, at + c[i].x, at + c[i].x + c[i].y, at + c[i].x + c[i].y + c[i].z);
+        at += c[i].x + c[i].y + c[i].z + c[i].w;
+    }
+    const bool over = group_any<NT>(longest > kBucketMax);
+    group_sync<NT>();
+    if (over) return false;
     // scattered, a bucket's counter holds its end
 #pragma unroll
     for (uint32_t r = 0; r < kIpt; r++)
-        if ((live >> r) & 1) S.buf[atomicAdd(&S.wc[bucket(key[r])], 1u)] = key[r];
-    const uint32_t jpt = (*total + NT - 1) / NT;
-    for (uint32_t r = 0; r < jpt; r++) S.mark[(w * jpt + r) * 64 + lane] = kNoMark;
+        if (r < ipt && (w * ipt + r) * 64 + lane < cnt) S.buf[atomicAdd(&S.wc[bucket(key[r])], 1u)] = key[r];
+    for (uint32_t r = 0; r < ipt; r++) S.mark[(w * ipt + r) * 64 + lane] = kNoMark;
     group_sync<NT>();
-    for (uint32_t r = 0; r < jpt; r++) {
-        const uint32_t i = (w * jpt + r) * 64 + lane;
-        if (i >= *total) break;
+    for (uint32_t r = 0; r < ipt; r++) {
+        const uint32_t i = (w * ipt + r) * 64 + lane;
+        if (i >= cnt) break;
         const uint64_t k = S.buf[i];
         const uint32_t d = bucket(k), s0 = d ? S.wc[d - 1] : 0u, len = S.wc[d] - s0;
         uint32_t upto = 0;
@@ -464,10 +457,9 @@ __device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
     const uint32_t e0 = a.estart[b], cnt = a.estart[b + 1] - e0;
     uint64_t* vals = a.vals + e0;
     const uint32_t tid = group_tid<NT>(), lane = lane_id(), w = tid >> 6;
-    uint32_t ipt = (cnt + NT - 1) / NT;  // rounds per wave; element = (w * ipt + r) * 64 + lane
+    const uint32_t ipt = (cnt + NT - 1) / NT;  // rounds per wave; element = (w * ipt + r) * 64 + lane
     uint64_t key[kIpt];
     uint64_t kor = 0, kand = ~0ull;
-    uint32_t live = 0;  // bit r: key[r] is a value
 #pragma unroll
     for (uint32_t r = 0; r < kIpt; r++) {
         key[r] = ~0ull;
@@ -476,7 +468,6 @@ __device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
             key[r] = vals[i];
             kor |= key[r];
             kand &= key[r];
-            live |= 1u << r;
         }
     }
     const uint64_t diff = differing_bits(S, kor, kand);
@@ -487,13 +478,9 @@ __device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
         }
         return;
     }
-    uint32_t total = cnt;
     bool ranked = false;
-    if constexpr (SegSmem<NT>::kBucketed) ranked = rank_segment<NT>(S, ipt, diff, key, live, &total);
-    if (ranked) {
-        ipt = (total + NT - 1) / NT;
-    } else {
-        total = cnt;
+    if constexpr (SegSmem<NT>::kBucketed) ranked = rank_segment<NT>(S, cnt, ipt, diff, key);
+    if (!ranked) {
         radix_segment<NT>(S, cnt, ipt, diff, key);
 #pragma unroll
         for (uint32_t r = 0; r < kIpt; r++) {
@@ -505,7 +492,7 @@ __device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
     // the key of place i if it is a distinct one's: the distinct values in order
     auto distinct_at = [&](uint32_t i) -> uint32_t {
         if (ranked) return S.mark[i];
-        return i < total && (i == 0 || S.buf[i - 1] != S.buf[i]) ? i : kNoMark;
+        return i < cnt && (i == 0 || S.buf[i - 1] != S.buf[i]) ? i : kNoMark;
     };
     uint32_t mine = 0;
     for (uint32_t r = 0; r < ipt; r++)
@@ -526,27 +513,31 @@ __device__ void sort_segment(const SegArgs& a, uint64_t* smem, uint32_t b) {
     if (tid == 0) a.uniq[b] = distinct;
 }
 
-// Longer segments, listed by class: a workgroup of 256 takes one of more than
-// 512 values, or four shorter ones, a wave each; one of 1,024 takes one of
+// Longer segments, listed by class: a workgroup of 512 takes one of more than
+// 512 values, or eight shorter ones, a wave each; one of 1,024 takes one of
 // more than 4,096.  The grid is for n_med and n_mid (n_big) segments, which is
 // more than there are when the host did not wait for the lists' lengths.
 //
-// Bound by LDS latency at the twelve waves a CU that its memory allows.  On
-// R-MAT graphs of 2^24 (2^27) vertices radix passes alone took 1.02 (8.2) ms
-// for the segments of more than 256 values and some 0.7 (5.5) of k_seg_small
-// for the shorter ones; buckets take 1.21 (11.1) ms for both together.  A bound
-// of 64 values a bucket instead of 128 sends more segments to the radix passes:
-// 0.23 (0.6) ms slower.  Both classes are one launch because a graph of 2^20
-// edges waits 34 + 40 us for two, 35 for one.
-__global__ void __launch_bounds__(kBlock) k_seg_medium(SegArgs a, uint32_t n_med) {
+// Bound by LDS latency, so by the waves that fit a CU: 24 with 49 KB for eight
+// waves and at most 80 registers.  On R-MAT graphs of 2^24 (2^27) vertices the
+// segments of 513 to 4,096 values take 0.74 (6.6) ms, with 88 registers and 16
+// waves 1.00 (9.4), by radix passes alone 1.49 (11.8).
+__global__ void __launch_bounds__(kMedBlock, 6) k_seg_medium(SegArgs a, uint32_t n_med) {
     extern __shared__ uint64_t smem_med[];
     if (blockIdx.x < n_med) {
-        if (blockIdx.x < *a.n_med) sort_segment<kBlock>(a, smem_med, a.l_med[blockIdx.x]);
+        if (blockIdx.x < *a.n_med) sort_segment<kMedBlock>(a, smem_med, a.l_med[blockIdx.x]);
         return;
     }
     const uint32_t wv = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
-    const uint32_t i = (blockIdx.x - n_med) * kWaves + wv;
+    const uint32_t i = (blockIdx.x - n_med) * kMedWaves + wv;
     if (i < *a.n_mid) sort_segment<64>(a, smem_med + wv * (SegSmem<64>::bytes() / 8), a.l_mid[i]);
+}
+
+// The shorter class on its own, in 7 KB a wave (22 waves a CU): 0.21 (1.5) ms
+// on the same graphs, by radix passes 0.48 (3.9).
+__global__ void __launch_bounds__(64) k_seg_mid(SegArgs a) {
+    extern __shared__ uint64_t smem_mid[];
+    if (blockIdx.x < *a.n_mid) sort_segment<64>(a, smem_mid, a.l_mid[blockIdx.x]);
 }
 
 __global__ void __launch_bounds__(kBigBlock) k_seg_big(SegArgs a) {
@@ -858,9 +849,15 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
     }
     a.l_mid = l_mid, a.l_med = l_med, a.l_big = l_big;
     a.n_mid = dev->mid, a.n_med = dev->med, a.n_big = dev->big;
+    if (n_mid > kMidApart) {
+        k_seg_mid<<<n_mid, 64, SegSmem<64>::bytes(), s>>>(a);
+        n_mid = 0;
+    }
     if (n_med || n_mid) {
-        constexpr uint64_t bytes = std::max(SegSmem<kBlock>::bytes(), kWaves * SegSmem<64>::bytes());
-        k_seg_medium<<<n_med + ceil_div(n_mid, kWaves), kBlock, bytes, s>>>(a, n_med);
+        constexpr uint64_t with_mid = kMedWaves * SegSmem<64>::bytes();
+        constexpr uint64_t med = SegSmem<kMedBlock>::bytes();
+        static_assert(std::max(with_mid, med) <= 65536, "LDS without an attribute");
+        k_seg_medium<<<n_med + ceil_div(n_mid, kMedWaves), kMedBlock, n_mid ? std::max(with_mid, med) : med, s>>>(a, n_med);
     }
     if (n_big) {
         const uint64_t bytes = SegSmem<kBigBlock>::bytes();

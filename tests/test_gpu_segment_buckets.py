@@ -50,3 +50,9 @@ def test_class_limits(kind, max_label):
 def test_lists_shorter_than_their_grids(size):
     # too few edges for the host to wait for the lists' lengths
     check(segments([size, 5, 129, 600], "repeated", 3, size), 1, stop=False, what=size)
+
+
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_wave_segments_on_their_own(more):
+    # 4,096 segments of the wave class and one less or more, beside longer ones
+    check(segments([129] * (4096 + more) + [600, 2000], "spread", 5, 7 + more), 1, stop=False, what=more)
