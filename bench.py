@@ -515,7 +515,7 @@ def roofline(recs, g, workload):
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(workload),
             "traffic_detail": traffic_detail(workload),
-            "kernel": "k_iterate + k_hub + k_hub_finish (one refinement iteration)",
+            "kernel": "k_iterate + k_hub (one refinement iteration)",
             "algorithmic_bytes_per_launch": b_iter, "avg_launch_us": iter_us,
             "k_iterate_avg_us": kern_ms * 1e3 / max(timed, 1), "hub_kernels_avg_us": hub_ms * 1e3 / max(timed, 1),
             "timed_launches": timed,

@@ -66,9 +66,9 @@ constexpr int kChunkEdges = 1536;
 constexpr int kChunkPerThread = kChunkEdges / kBlock;
 constexpr uint32_t kSmallMaxEdges = 1535;             // edges of a graph that fits the small-graph launch
 // Vertices without out-edges: h^k = M(t ^ M(C_S)) for every k >= 1, so they
-// need no tile.  Light blocks of kIsoPerBlock of them run their split test
-// and write their hash while it can still change the buffers (levels 1 and 2
-// when two buffers alternate; every level when each level has its own array).
+// need no tile.  Light blocks of kIsoPerBlock of them write their hash while
+// it can still change the buffers (levels 1 and 2 when two buffers alternate;
+// every level when each level has its own array).
 constexpr int kIsoPerThread = 4;
 constexpr uint32_t kIsoPerBlock = kBlock * kIsoPerThread;
 constexpr int kHubBlock = 512;           // threads per hub-bucket block

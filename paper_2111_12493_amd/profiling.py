@@ -56,11 +56,6 @@ def kernel_fingerprint() -> str:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
-OWN = ("k_iterate", "k_hub", "k_init", "k_stage_vertices", "k_stage_edges", "k_pack_tiles",
-       "k_hub_degrees", "k_hub_starts", "k_salt", "k_compact_flags", "k_fin_min", "k_fin_rep",
-       "k_fin_ids", "k_edge_keys", "k_sort_hist", "k_sort_scatter", "k_unique_flags", "k_unpack",
-       "k_scan_reduce", "k_scan_spine", "k_scan_down")
-
 
 def short(name: str) -> str:
     """Kernel name without namespaces, template arguments and parameters."""
@@ -103,7 +98,7 @@ def working_launch_durations(path: str, k_done: int, n_work: int = 0, skip_runs:
         seen[k] += 1
         if run <= skip_runs:
             continue
-        if k in ("k_iterate", "k_hub", "k_hub_finish") and seen[k] <= n_work:
+        if k in ITER_KERNELS and seen[k] <= n_work:
             out[k].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
     return out
 
@@ -127,7 +122,7 @@ def counters(path: str, calib_bytes: int = 0, k_done: int = 0):
         meta[key] = (int(r["Start_Timestamp"]), r["Kernel_Name"])
     scale = {}
     if calib_bytes:
-        foreign = [per[key] for key in per if short(meta[key][1]) not in OWN]
+        foreign = [per[key] for key in per if not short(meta[key][1]).startswith("k_")]
         for c in ("FETCH_SIZE", "WRITE_SIZE"):
             vals = [cs[c] for cs in foreign if cs.get(c)]
             if vals:
@@ -153,7 +148,7 @@ def counters(path: str, calib_bytes: int = 0, k_done: int = 0):
     return out, scale
 
 
-ITER_KERNELS = ("k_iterate", "k_hub", "k_hub_finish")
+ITER_KERNELS = ("k_iterate", "k_hub")
 
 # Counter passes (rocprofv3 collects no more than 4 TCC counters at once).
 #   fetch: bytes read past L2 = 128 TCC_BUBBLE + 64 (TCC_EA0_RDREQ - TCC_BUBBLE
@@ -209,7 +204,7 @@ def pass_counters(path: str, k_done: int, n_work: int = 0, skip_runs: int = SKIP
     run = 0
     for key in sorted(per, key=lambda k: meta[k][0]):
         k = short(meta[key][1])
-        if k not in OWN and k not in ITER_KERNELS and not k.startswith("k_"):
+        if not k.startswith("k_"):
             foreign.append(per[key])
             continue
         if k == "k_init":
@@ -270,7 +265,7 @@ def summary(d: str, workload: str, k_done: int, algo_bytes: int, calib_bytes: in
         for name, src in (("fetch", fa), ("l2", la)):
             if k in src:
                 tcc.append("%s %s" % (k, " ".join("%s=%.4g" % kv for kv in sorted(src[k].items()))))
-    lines = ["# One refinement iteration (k_iterate, k_hub, k_hub_finish) on %s (%d iterations per run)"
+    lines = ["# One refinement iteration (k_iterate, k_hub) on %s (%d iterations per run)"
              % (workload, k_done), "",
              "Kernel source fingerprint (%s): %s" % (", ".join(KERNEL_SOURCES), rep["kernel_sources_sha256_16"]), "",
              "## Commands (repository root, one MI355X)", "", commands(d, workload), "", "Summaries:", "",
