@@ -171,13 +171,17 @@ __global__ void __launch_bounds__(kBlock) k_ci_build(CiLevel L, const uint32_t* 
 
 // Member counts of a rebuilt level, from the class ids (cnt cleared since
 // the rebuild): every vertex with a class counts, lanes of a wave with one
-// class add once (those the first rounds find).
+// class add once.  All lanes are grouped, however many rounds that takes: lanes
+// left to add for themselves after kGroupRounds meet at the counters of the
+// few large classes, which made an update of 1,500 operations on a 2^24-vertex
+// R-MAT state that counts two levels take 15.6 ms instead of 7.5.
 __global__ void __launch_bounds__(kBlock) k_ci_count(CiLevel L, uint32_t n) {
     const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
     const uint32_t lane = lane_id();
     const uint32_t c = v < n ? L.cid[v] : kNoClass;
-    bool pending = c != kNoClass;
-    for (int round = 0; round < kGroupRounds; round++) {
+    const bool part = c != kNoClass;
+    bool pending = part;
+    for (;;) {
         const uint64_t ball = __ballot(pending);
         if (!ball) break;
         const uint32_t leader = static_cast<uint32_t>(__ffsll(static_cast<long long>(ball)) - 1);
@@ -186,7 +190,6 @@ __global__ void __launch_bounds__(kBlock) k_ci_count(CiLevel L, uint32_t n) {
         if (lane == leader) atomicAdd(&L.cnt[lc], static_cast<uint32_t>(__popcll(same)));
         if (c == lc) pending = false;
     }
-    if (pending) atomicAdd(&L.cnt[c], 1u);
 }
 
 // The update's vertex list: candidates of list a (those with flag[v] ==
