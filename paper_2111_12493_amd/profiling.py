@@ -74,6 +74,14 @@ def stats(path: str) -> str:
     return "\n".join(lines)
 
 
+def stop_test(k: str, r: dict) -> bool:
+    """A k_iterate launch of one workgroup: the stop test that large graphs
+    run before each level.  It hashes nothing."""
+    grid = r.get("Grid_Size_X") or r.get("Grid_Size")
+    block = r.get("Workgroup_Size_X") or r.get("Workgroup_Size")
+    return k == "k_iterate" and grid == block
+
+
 # Every profiled command runs one warm-up summarization first (it sizes the
 # context's kept work buffer, so the measured runs place their temporaries
 # as the timed bench steps do); the summaries skip that run.
@@ -94,6 +102,8 @@ def working_launch_durations(path: str, k_done: int, n_work: int = 0, skip_runs:
         if k == "k_init":
             seen.clear()
             run += 1
+            continue
+        if stop_test(k, r):
             continue
         seen[k] += 1
         if run <= skip_runs:
@@ -119,7 +129,7 @@ def counters(path: str, calib_bytes: int = 0, k_done: int = 0):
     for r in csv.DictReader(open(path)):
         key = r["Dispatch_Id"]
         per[key][r["Counter_Name"]] += float(r["Counter_Value"])
-        meta[key] = (int(r["Start_Timestamp"]), r["Kernel_Name"])
+        meta[key] = (int(r["Start_Timestamp"]), r["Kernel_Name"], stop_test(short(r["Kernel_Name"]), r))
     scale = {}
     if calib_bytes:
         foreign = [per[key] for key in per if not short(meta[key][1]).startswith("k_")]
@@ -133,6 +143,8 @@ def counters(path: str, calib_bytes: int = 0, k_done: int = 0):
         k = short(meta[key][1])
         if k == "k_init":
             seen.clear()
+        if meta[key][2]:
+            continue
         seen[k] += 1
         if k_done and k in ("k_iterate", "k_hub") and seen[k] > k_done + 1:
             continue
@@ -197,7 +209,7 @@ def pass_counters(path: str, k_done: int, n_work: int = 0, skip_runs: int = SKIP
     for r in csv.DictReader(open(path)):
         key = r["Dispatch_Id"]
         per[key][r["Counter_Name"]] += float(r["Counter_Value"])
-        meta[key] = (int(r["Start_Timestamp"]), r["Kernel_Name"])
+        meta[key] = (int(r["Start_Timestamp"]), r["Kernel_Name"], stop_test(short(r["Kernel_Name"]), r))
     by_kernel = collections.defaultdict(list)
     seen = collections.Counter()
     foreign = []
@@ -210,6 +222,8 @@ def pass_counters(path: str, k_done: int, n_work: int = 0, skip_runs: int = SKIP
         if k == "k_init":
             seen.clear()
             run += 1
+        if meta[key][2]:
+            continue
         seen[k] += 1
         if run <= skip_runs:
             continue
