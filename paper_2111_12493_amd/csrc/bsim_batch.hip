@@ -266,8 +266,9 @@ void build_union(const bsim_graph* graphs, uint32_t G, Staged& u, uint32_t*& gid
 }
 
 // Capacities of a small-graph workgroup on this device: at most 1,024
-// vertices and kSmallMaxEdges edges when the device gives a workgroup the LDS for them, else half; and
-// the persistent grid (the workgroups that fit the CUs at once).
+// vertices and kSmallMaxEdges edges when the device gives a workgroup the LDS
+// for them, else half; and the persistent grid (the workgroups that fit the
+// CUs at once).  A vertex of such a graph may be a solo vertex of the union.
 void small_capacity(int device, uint32_t* max_v, uint32_t* max_e, uint32_t* grid) {
     int lds = 0, cus = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) lds = 65536;

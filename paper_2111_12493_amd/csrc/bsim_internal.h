@@ -142,8 +142,9 @@ struct BatchCtl {
     uint32_t n_graphs = 0;
     uint32_t hist_cap = 0;
     uint32_t virt_base = 0;         // level-0 virtual class of graph g: virt_base + g
-    // per graph: 1 when the persistent small-graph launch refines it (the
-    // refinement launches then leave its vertices alone), nullable
+    // per graph: 1 when the persistent small-graph launch refines it, nullable.
+    // Its vertices are in the union's tiles and lists all the same: every block
+    // of the refinement launches must leave them alone (batch_refines).
     const uint8_t* ext = nullptr;
 };
 

@@ -222,6 +222,15 @@ __global__ void __launch_bounds__(kBlock) k_init(const uint64_t* __restrict__ t,
 
 // ------------------------------------------------------------ launch k
 
+// Whether level k of graph g of a batched run is this loop's to compute: not
+// that of a graph which the small-graph launch has refined to its stop level
+// already (its hashes and classes lie in the same arrays), nor one past the
+// level at which the graph stopped.  Every block that writes hashes or classes
+// of a batched run asks it.
+__device__ __forceinline__ bool batch_refines(const BatchCtl& bc, uint32_t g, uint32_t k) {
+    return !(bc.ext && bc.ext[g]) && k <= bc.done_level[g];
+}
+
 // A wave's keys and table slots, a workgroup's of a solo vertex, or a chunk
 // block's bucket counts.
 struct WaveLds {
@@ -378,12 +387,7 @@ __device__ __forceinline__ void wave_tile(const IterArgs& a, uint32_t tile, Wave
 #pragma unroll
     for (int q = 0; q < kLaneEdges; q++) f[q] = static_cast<uint32_t>(q) < cnt ? a.h_prev[w[q]] : 0;
     const uint64_t tv = mine ? a.t[v] : 0;
-    // batched runs: a graph that stopped at level L keeps its level-L state
-    bool write = mine;
-    if (mine && a.bc.gid) {
-        const uint32_t gi = a.bc.gid[v];
-        write = !(a.bc.ext && a.bc.ext[gi]) && a.k <= a.bc.done_level[gi];
-    }
+    const bool write = mine && (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k));
     const LaneOwners own = lane_owners(reinterpret_cast<uint8_t*>(L.slot), mine, off);
     if (stop_decision(a, p)) return;
     uint32_t todo = 0;
@@ -522,11 +526,10 @@ __device__ void hub_chunk_block(const IterArgs& a, uint32_t blk, IterShared& S, 
 template <typename LabT>
 __device__ void solo_block(const IterArgs& a, uint32_t v, SoloLds& L, const StopInputs& p) {
     __shared__ uint64_t s_sum[kWaves];
-    const uint32_t tid = threadIdx.x, k = a.k;
+    const uint32_t tid = threadIdx.x;
     const uint32_t e0 = a.row_off[v];
     const uint32_t ne = p.done ? 0u : a.row_off[v + 1] - e0;
-    bool write = tid == 0;
-    if (a.bc.gid) write = write && k <= a.bc.done_level[a.bc.gid[v]];
+    const bool write = tid == 0 && (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k));
     const uint64_t tv = a.t[v];
     const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
     uint32_t w[kLaneEdges];
@@ -589,7 +592,7 @@ __device__ void solo_block(const IterArgs& a, uint32_t v, SoloLds& L, const Stop
 // kIsoPerBlock vertices without out-edges: h^k = M(t ^ M(C_S)) for every
 // k >= 1, written where the hash buffer does not hold it yet.
 __device__ void iso_block(const IterArgs& a, uint32_t blk, const StopInputs& p) {
-    const uint32_t tid = threadIdx.x, k = a.k;
+    const uint32_t tid = threadIdx.x;
     if (stop_decision(a, p)) return;
     uint32_t v[kIsoPerThread];
     uint64_t tv[kIsoPerThread];
@@ -603,10 +606,7 @@ __device__ void iso_block(const IterArgs& a, uint32_t blk, const StopInputs& p) 
         live[r] = false;
         if (mine[r]) {
             live[r] = !a.alive || a.alive[v[r]];
-            if (a.bc.gid) {
-                const uint32_t gi = a.bc.gid[v[r]];
-                mine[r] = !(a.bc.ext && a.bc.ext[gi]) && k <= a.bc.done_level[gi];
-            }
+            if (a.bc.gid) mine[r] = batch_refines(a.bc, a.bc.gid[v[r]], a.k);
             tv[r] = a.t[v[r]];
         }
     }
@@ -714,7 +714,7 @@ __global__ void __launch_bounds__(kBlock) k_split(SplitArgs a) {
         gi[q] = 0;
         if (probe[q] && a.bc.gid) {
             gi[q] = a.bc.gid[v[q]];
-            probe[q] = !(a.bc.ext && a.bc.ext[gi[q]]) && k <= a.bc.done_level[gi[q]];
+            probe[q] = batch_refines(a.bc, gi[q], k);
         }
         probe[q] = probe[q] && r[q] != v[q] && r[q] != 0xFFFFFFFFu;  // (a dead vertex has no class)
     }
@@ -947,7 +947,7 @@ __global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
     acc[0] = 0;
     acc[1] = 0;
     const uint32_t v = a.hub_v[hi];
-    if (!a.bc.gid || a.k <= a.bc.done_level[a.bc.gid[v]]) a.h_next[v] = mix64(a.t[v] ^ mix64(kCS + all));
+    if (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k)) a.h_next[v] = mix64(a.t[v] ^ mix64(kCS + all));
 }
 
 // ------------------------------------------------------------ batched stop
