@@ -104,8 +104,8 @@ __global__ void __launch_bounds__(kBlock) k_fin_first(const uint32_t* __restrict
 // (cmin is not read any more), and a size of one for the block.
 __global__ void __launch_bounds__(kBlock) k_fin_name(const uint32_t* __restrict__ rep,
                                                      const uint64_t* __restrict__ first,
-                                                     const uint32_t* __restrict__ start, uint32_t* __restrict__ name,
-                                                     uint32_t* __restrict__ sizes) {
+                                                     const uint32_t* __restrict__ start, uint32_t nb,
+                                                     uint32_t* __restrict__ name, uint32_t* __restrict__ sizes) {
     const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kIdsPerBlock;
     const uint64_t* word = first + static_cast<uint64_t>(blockIdx.x) * kIdsWords;
     const uint32_t lane = lane_id();
@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(kBlock) k_fin_name(const uint32_t* __restrict_
         const uint64_t w = word[g];
         const uint32_t before = static_cast<uint32_t>(__shfl(static_cast<int>(excl), static_cast<int>(g), 64));
         if ((w >> lane) & 1) {
-            const uint32_t id = id0 + before + static_cast<uint32_t>(__popcll(w & ((1ull << lane) - 1)));
+            const uint32_t id = block_slot(id0 + before + static_cast<uint32_t>(__popcll(w & ((1ull << lane) - 1))), nb);
             name[rep[base + r * kBlock + threadIdx.x]] = id;
             sizes[id] = 1;
         }
@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(kBlock) k_fin_name(const uint32_t* __restrict_
 __global__ void __launch_bounds__(kBlock) k_fin_ids(const uint8_t* __restrict__ alive, uint32_t n,
                                                     const uint32_t* __restrict__ rep,
                                                     const uint32_t* __restrict__ name,
-                                                    const uint64_t* __restrict__ first,
+                                                    const uint64_t* __restrict__ first, uint32_t nb,
                                                     uint32_t* __restrict__ block_ids, uint32_t* __restrict__ sizes) {
     __shared__ uint32_t s_key[kIdsSlots];
     __shared__ uint32_t s_cnt[kIdsSlots];
@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(kBlock) k_fin_ids(const uint8_t* __restrict__ 
         const uint64_t v = base + r * kBlock + threadIdx.x;
         bid[r] = 0xFFFFFFFFu;
         if (v < n && (!alive || alive[v])) {
-            bid[r] = name[rep[v]];
+            bid[r] = block_slot(name[rep[v]], nb);
             if (!((word[r * kWaves + (threadIdx.x >> 6)] >> lane) & 1)) more |= 1u << r;
         }
     }
@@ -411,8 +411,8 @@ void number_blocks(const Staged& g, const uint32_t* rep, uint32_t nb, uint32_t* 
         k_fin_min<true><<<gv, kBlock, 0, s>>>(rep, g.alive, n, name);
     k_fin_first<<<gb, kBlock, 0, s>>>(rep, g.alive, n, name, first, count);
     scan_exclusive(count, count, gb, seen, arena, s);
-    k_fin_name<<<gb, kBlock, 0, s>>>(rep, first, count, name, sizes);
-    k_fin_ids<<<gb, kBlock, 0, s>>>(g.alive, n, rep, name, first, ids, sizes);
+    k_fin_name<<<gb, kBlock, 0, s>>>(rep, first, count, nb, name, sizes);
+    k_fin_ids<<<gb, kBlock, 0, s>>>(g.alive, n, rep, name, first, nb, ids, sizes);
     hip_check(hipGetLastError(), "finalize launch");
 }
 

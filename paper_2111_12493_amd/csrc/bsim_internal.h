@@ -507,6 +507,13 @@ uint32_t query_hub_table_slots(int device, bool device_max = false);
 // whichever holds the result.
 uint64_t* radix_sort(uint64_t* a, uint64_t* b, uint32_t m, int bits, Arena& arena, hipStream_t s, int lo = 0);
 
+// Where finalize keeps what belongs to block id, in arrays sized for the nb
+// blocks that the refinement counted (and one word more): ids past the last
+// one stay inside them.  Numbering that finds more classes than were counted
+// is an internal error, which the host sees once the counts are back; until
+// then nothing may be written by such an id.
+__host__ __device__ constexpr uint32_t block_slot(uint32_t id, uint32_t nb) { return id < nb ? id : nb ? nb - 1 : 0u; }
+
 // Finalize (a8): block ids, block sizes, sorted distinct quotient edges.
 struct FinalOut {
     // preset: the output arrays below are already allocated by the caller
