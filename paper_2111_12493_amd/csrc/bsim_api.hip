@@ -490,15 +490,10 @@ int bsim_result_copy(const bsim_result* r, const char* field, void* dst, uint32_
                              ? hipMemcpyHostToDevice
                              : (dst_mem_kind == BSIM_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice);
     if (hipSetDevice(p->device) != hipSuccess) return BSIM_E_DEVICE;
-    if (kind == hipMemcpyDeviceToDevice && reinterpret_cast<uintptr_t>(dst) % 4 == 0) {
-        try {
-            copy_ranges(&dst, &src, &bytes, 1, p->stream);
-        } catch (const DeviceError& e) {
-            return e.status;
-        }
-    } else if (hipMemcpyAsync(dst, src, bytes, kind, p->stream) != hipSuccess) {
-        return BSIM_E_DEVICE;
-    }
+    // (not a kernel of this library: dst is the caller's pointer, and the
+    // runtime knows whether it names memory of this device, of another, or
+    // none of either; a launch saves nothing here, 15.2 us against 14.5)
+    if (hipMemcpyAsync(dst, src, bytes, kind, p->stream) != hipSuccess) return BSIM_E_DEVICE;
     if (hipStreamSynchronize(p->stream) != hipSuccess) return BSIM_E_DEVICE;
     return BSIM_OK;
 }

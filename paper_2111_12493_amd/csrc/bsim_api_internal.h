@@ -124,8 +124,10 @@ struct DeviceGraph {
 void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
                   const std::shared_ptr<PinnedPool>& pool = nullptr, std::shared_ptr<HostBlock>* block = nullptr);
 
-// Queue up to 8 device-visible copies in one launch where they are small (a
-// copy apiece otherwise); bytes are multiples of 4, addresses 4-byte aligned.
+// Queue up to 8 copies between arrays of the library's own, all visible to the
+// device, in one launch where they are small (a copy apiece otherwise); bytes
+// are multiples of 4, addresses 4-byte aligned.  Never with a caller's pointer:
+// the kernel would fault where the runtime's copy returns an error.
 void copy_ranges(void* const* dst, const void* const* src, const size_t* bytes, int n, hipStream_t s);
 
 // The six result arrays copied from dev[] into one block of host memory;
