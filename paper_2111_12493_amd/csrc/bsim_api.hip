@@ -44,6 +44,8 @@ void* PinnedPool::take(size_t bytes, size_t* cap) {
     // size find each other's blocks
     const size_t want = bytes <= (1u << 20) ? static_cast<size_t>(next_pow2(std::max<size_t>(bytes, 4096)))
                                             : (bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1);
+    std::vector<void*> out;  // kept blocks that make room
+    bool room = true;
     {
         std::lock_guard<std::mutex> lk(mu_);
         size_t best = free_.size();
@@ -59,10 +61,25 @@ void* PinnedPool::take(size_t bytes, size_t* cap) {
             free_.pop_back();
             return p;
         }
+        room = pinned_ - kept_ + want <= kPinnedMost;
+        if (room) {
+            out.reserve(free_.size());
+            while (pinned_ + want > kPinnedMost) {
+                out.push_back(free_.back().first);
+                kept_ -= free_.back().second;
+                pinned_ -= free_.back().second;
+                free_.pop_back();
+            }
+            pinned_ += want;
+        }
     }
+    for (void* p : out) (void)hipHostFree(p);
+    if (!room) return nullptr;
     void* p = nullptr;
     if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
+        std::lock_guard<std::mutex> lk(mu_);
+        pinned_ -= want;
         return nullptr;
     }
     *cap = want;
@@ -72,7 +89,7 @@ void* PinnedPool::take(size_t bytes, size_t* cap) {
 void PinnedPool::give(void* p, size_t cap) {
     {
         std::lock_guard<std::mutex> lk(mu_);
-        if (!closed_ && kept_ + cap <= kPinnedKeep) {
+        if (contexts_ && kept_ + cap <= kPinnedKeep) {
             try {
                 free_.emplace_back(p, cap);
                 kept_ += cap;
@@ -80,23 +97,35 @@ void PinnedPool::give(void* p, size_t cap) {
             } catch (const std::bad_alloc&) {
             }
         }
+        pinned_ -= cap;
     }
     (void)hipHostFree(p);
+}
+
+void PinnedPool::open() {
+    std::lock_guard<std::mutex> lk(mu_);
+    contexts_++;
 }
 
 void PinnedPool::close() {
     std::vector<std::pair<void*, size_t>> all;
     {
         std::lock_guard<std::mutex> lk(mu_);
-        closed_ = true;
+        if (--contexts_) return;
         all.swap(free_);
+        pinned_ -= kept_;
         kept_ = 0;
     }
     for (auto& b : all) (void)hipHostFree(b.first);
 }
 
+void share_host_pool(bsim_ctx* ctx, const bsim_ctx* with) {
+    with->host_pool->open();
+    ctx->host_pool->close();
+    ctx->host_pool = with->host_pool;
+}
+
 HostBlock::HostBlock(const std::shared_ptr<PinnedPool>& from, size_t bytes) {
-    // (pinning gigabytes takes longer than the copy that it speeds up)
     if (from && bytes <= PinnedPool::kPinnedKeep) p = from->take(bytes, &cap);
     if (p) {
         pool = from;
@@ -213,6 +242,13 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
     if (!c) return BSIM_E_NOMEM;
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
+    try {
+        c->host_pool = std::make_shared<PinnedPool>();
+    } catch (const std::bad_alloc&) {
+        bsim_ctx_free(c);
+        return BSIM_E_NOMEM;
+    }
+    c->host_pool->open();
     c->hub_table_slots = query_hub_table_slots(device);
     if (hipHostMalloc(reinterpret_cast<void**>(&c->pinned), sizeof(CtxPinned),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
@@ -245,7 +281,7 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     (void)hipSetDevice(ctx->device);
     ctx_release_work(ctx);
     (void)hipStreamSynchronize(ctx->stream);
-    ctx->host_pool->close();
+    if (ctx->host_pool) ctx->host_pool->close();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
 }

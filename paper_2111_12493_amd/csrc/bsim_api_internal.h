@@ -14,22 +14,33 @@ namespace bsim {
 // Pinned host memory that a context's calls move their arrays through: the
 // host arrays of results, and the uploads of small graphs.  Blocks come back
 // when their result is freed, on any thread, and are kept for later calls up
-// to kPinnedKeep bytes; the context's end gives the kept ones back, and
-// blocks still out then are freed as they come.
+// to kPinnedKeep bytes.  A caller that keeps its results gets fresh blocks
+// until kPinnedMost bytes are pinned, kept ones included, and ordinary memory
+// from there on.  The contexts of a server share one pool; the end of the last
+// context gives the kept blocks back, and blocks still out then are freed as
+// they come.
+//
+// A fresh block costs less than the copy through the runtime's staging buffer
+// that it replaces, also where no block ever comes back: a call that returns
+// 22 KB (2.3, 52, 207 MB) and whose result is kept takes 0.35 ms (0.62, 2.3,
+// 7.4) with pinned blocks and 0.90 (2.6, 17, 68) without.
 class PinnedPool {
   public:
-    static constexpr size_t kPinnedKeep = 512ull << 20;
-    // A block of at least `bytes`; nullptr when there is no pinned memory.
-    // *cap: its size, for give().
+    static constexpr size_t kPinnedKeep = 512ull << 20;   // kept blocks, and the largest block
+    static constexpr size_t kPinnedMost = 1024ull << 20;  // kept blocks and those out
+    // A block of at least `bytes`; nullptr when there is no pinned memory or
+    // no more may be pinned.  *cap: its size, for give().
     void* take(size_t bytes, size_t* cap);
     void give(void* p, size_t cap);
-    void close();
+    void open();   // one more context
+    void close();  // one less
 
   private:
     std::mutex mu_;
     std::vector<std::pair<void*, size_t>> free_;
-    size_t kept_ = 0;
-    bool closed_ = false;
+    size_t kept_ = 0;    // bytes of free_
+    size_t pinned_ = 0;  // bytes of all blocks
+    int contexts_ = 0;
 };
 
 // One block, owned: pinned from the pool, or ordinary memory where that failed.
@@ -64,7 +75,7 @@ struct bsim_ctx {
     bsim::StageHost* stage_host = nullptr;   // what staging copies back
     bsim::FinalHost* final_host = nullptr;   // what finalize copies back
     uint64_t* report_host = nullptr;         // kReportRing words, written by refinement launches
-    std::shared_ptr<bsim::PinnedPool> host_pool = std::make_shared<bsim::PinnedPool>();
+    std::shared_ptr<bsim::PinnedPool> host_pool;
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;
     uint32_t hub_table_slots = 8192;  // LDS slots per hub-bucket block on this device
@@ -118,6 +129,9 @@ struct ResultPriv {
 struct DeviceGraph {
     Staged g;
 };
+
+// Let ctx take its pinned memory from the pool of `with`.
+void share_host_pool(bsim_ctx* ctx, const bsim_ctx* with);
 
 // pool: pinned memory for the upload of a small graph; *block (nullable with
 // pool) keeps it until the upload is done.
