@@ -46,26 +46,25 @@ __global__ void __launch_bounds__(kBlock) k_kept_rows(const uint32_t* __restrict
     f_row_off[v] = e < m ? kpos[e] : *m_kept;
 }
 
-// The source of every edge, from the tile schedule: one wave per tile, solo
-// vertices and hubs by a workgroup each.
-__global__ void __launch_bounds__(kBlock) k_edge_sources(const uint32_t* __restrict__ row_off,
+// The source of every edge, from the tile schedule: one wave per tile, longer
+// rows by workgroups.
+__global__ void __launch_bounds__(kBlock) k_edge_sources(LongRows rows,
                                                          const uint4* __restrict__ tiles,
                                                          const uint32_t* __restrict__ act,
                                                          const uint32_t* __restrict__ act_off, uint32_t n_tiles,
-                                                         const uint32_t* __restrict__ solo_v, uint32_t n_solo,
-                                                         const uint32_t* __restrict__ hub_v, uint32_t n_hubs,
                                                          uint32_t* __restrict__ src) {
     __shared__ struct {
         uint32_t v[kTileMaxVerts];
         alignas(8) uint8_t owner[kTileMaxEdges];
     } sh[kWaves];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < n_hubs + n_solo) {
-        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
-        for (uint32_t e = row_off[v] + tid; e < row_off[v + 1]; e += kBlock) src[e] = v;
+    if (blockIdx.x < rows.blocks()) {
+        uint32_t e0, e1;
+        const uint32_t v = rows.share(blockIdx.x, &e0, &e1);
+        for (uint32_t e = e0 + tid; e < e1; e += kBlock) src[e] = v;
         return;
     }
-    const uint32_t lane = lane_id(), tile = (blockIdx.x - n_hubs - n_solo) * kWaves + (tid >> 6);
+    const uint32_t lane = lane_id(), tile = (blockIdx.x - rows.blocks()) * kWaves + (tid >> 6);
     if (tile >= n_tiles) return;
     auto& S = sh[tid >> 6];
     const uint4 td = tiles[tile];
@@ -202,8 +201,8 @@ void build_view(const Staged& g, uint32_t flags, const std::vector<uint32_t>* la
     out.f_staged = true;
     uint32_t* src = arena.alloc<uint32_t>(static_cast<size_t>(m) + 1);
     if (m)
-        k_edge_sources<<<g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves), kBlock, 0, s>>>(
-            g.row_off, g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo, g.hub_v, g.n_hubs, src);
+        k_edge_sources<<<long_rows(g).blocks() + ceil_div(g.n_tiles, kWaves), kBlock, 0, s>>>(
+            long_rows(g), g.tiles, g.act, g.act_off, g.n_tiles, src);
     uint32_t m_f = m;
     if (labels) {
         // the kept edges

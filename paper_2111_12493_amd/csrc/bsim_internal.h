@@ -409,6 +409,37 @@ struct Staged {
     uint32_t hub_table_slots = 0;
 };
 
+// The rows that no tile holds, for kernels that pass over all edges once: a
+// workgroup per chunk of a hub, then one per solo vertex.  (A workgroup per
+// hub takes as long as the longest row: the 2^22 edges of one vertex took
+// k_seg_fill 21.4 ms, in chunks 70 us.)
+struct LongRows {
+    const uint32_t* row_off;
+    const uint32_t* hc_hub;
+    const uint32_t* hc_e0;
+    const uint32_t* hub_v;
+    const uint32_t* solo_v;
+    uint32_t n_hub_chunks;
+    uint32_t n_solo;
+    __host__ __device__ uint32_t blocks() const { return n_hub_chunks + n_solo; }
+    // Block b's vertex and edges [*e0, *e1).
+    __device__ uint32_t share(uint32_t b, uint32_t* e0, uint32_t* e1) const {
+        if (b >= n_hub_chunks) {
+            const uint32_t v = solo_v[b - n_hub_chunks];
+            *e0 = row_off[v];
+            *e1 = row_off[v + 1];
+            return v;
+        }
+        const uint32_t v = hub_v[hc_hub[b]];
+        *e0 = hc_e0[b];
+        *e1 = *e0 + min(static_cast<uint32_t>(kChunkEdges), row_off[v + 1] - *e0);
+        return v;
+    }
+};
+inline LongRows long_rows(const Staged& g) {
+    return {g.row_off, g.hc_hub, g.hc_e0, g.hub_v, g.solo_v, g.n_hub_chunks, g.n_solo};
+}
+
 // What staging copies back, in pinned memory: the validation status, the
 // counts (hubs, tile vertices, solo vertices, tiles) and the first hubs as
 // (vertex, degree, first edge).  4,096 hubs are 48 KiB, a copy that costs

@@ -565,28 +565,27 @@ struct FillShared {
 };
 
 // Every edge (v, l, w) writes l << bb | block(w) into v's claimed range: one
-// wave per tile, the eight gathers of a lane in flight together; solo
-// vertices and hubs by a workgroup each.
+// wave per tile, the eight gathers of a lane in flight together; longer rows
+// by workgroups.
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_seg_fill(
-    const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt, const LabT* __restrict__ lab,
+    LongRows rows, const uint32_t* __restrict__ tgt, const LabT* __restrict__ lab,
     const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst, const uint32_t* __restrict__ estart,
     const uint32_t* __restrict__ voff, const uint4* __restrict__ tiles, const uint32_t* __restrict__ act,
-    const uint32_t* __restrict__ act_off, uint32_t n_tiles, const uint32_t* __restrict__ solo_v, uint32_t n_solo,
-    const uint32_t* __restrict__ hub_v, uint32_t n_hubs, int bb, uint64_t* __restrict__ vals) {
+    const uint32_t* __restrict__ act_off, uint32_t n_tiles, int bb, uint64_t* __restrict__ vals) {
     __shared__ FillShared sh[kWaves];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < n_hubs + n_solo) {
-        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
-        const uint32_t e0 = row_off[v], e1 = row_off[v + 1];
-        uint64_t* out = vals + estart[bid[v]] + voff[v];
+    if (blockIdx.x < rows.blocks()) {
+        uint32_t e0, e1;
+        const uint32_t v = rows.share(blockIdx.x, &e0, &e1);
+        uint64_t* out = vals + estart[bid[v]] + voff[v] + (e0 - rows.row_off[v]);
         for (uint32_t e = e0 + tid; e < e1; e += kBlock)
             out[e - e0] = (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
         return;
     }
     const uint32_t lane = lane_id();
     const uint32_t wv = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(tid >> 6)));
-    const uint32_t tile = (blockIdx.x - n_hubs - n_solo) * kWaves + wv;
+    const uint32_t tile = (blockIdx.x - rows.blocks()) * kWaves + wv;
     if (tile >= n_tiles) return;
     FillShared& S = sh[wv];
     const uint4 td = tiles[tile];
@@ -800,15 +799,14 @@ void bucketed_summary_edges(const Staged& g, const uint32_t* bid, uint32_t nb, c
     scan_exclusive(ecount, estart, nb, estart + nb, arena, s);
     // 2. values
     uint64_t* vals = arena.alloc<uint64_t>(m);
-    const uint32_t grid = g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves);
+    const LongRows rows = long_rows(g);
+    const uint32_t grid = rows.blocks() + ceil_div(g.n_tiles, kWaves);
     if (g.label_bytes == 2)
-        k_seg_fill<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint16_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tiles, g.act, g.act_off, g.n_tiles,
-                                                     g.solo_v, g.n_solo, g.hub_v, g.n_hubs, bb, vals);
+        k_seg_fill<uint16_t><<<grid, kBlock, 0, s>>>(rows, g.tgt, static_cast<const uint16_t*>(g.lab), bid, dst_ids,
+                                                     estart, voff, g.tiles, g.act, g.act_off, g.n_tiles, bb, vals);
     else
-        k_seg_fill<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt, static_cast<const uint32_t*>(g.lab), bid,
-                                                     dst_ids, estart, voff, g.tiles, g.act, g.act_off, g.n_tiles,
-                                                     g.solo_v, g.n_solo, g.hub_v, g.n_hubs, bb, vals);
+        k_seg_fill<uint32_t><<<grid, kBlock, 0, s>>>(rows, g.tgt, static_cast<const uint32_t*>(g.lab), bid, dst_ids,
+                                                     estart, voff, g.tiles, g.act, g.act_off, g.n_tiles, bb, vals);
     // 3. size classes
     uint32_t* uniq = arena.alloc<uint32_t>(static_cast<size_t>(nb) + 1);
     // at most this many segments hold more than `above` values
