@@ -19,7 +19,7 @@
 //                         512 threads up to 4,096 values, else 1,024): the
 //                         values go to buckets by their highest bits that
 //                         differ, and each counts the ones of its bucket up
-//                         to it; LDS radix sort where a bucket is too long,
+//                         to it; LDS radix sort where that would read more,
 //                         and for the largest class;
 //        more             one global LSD radix sort over all such segments
 //                         on (segment rank, value);
@@ -48,11 +48,16 @@ constexpr uint32_t kSmallMaxSeg = kSmallRange / 2;           // segments of >= 2
 // more of their waves fit a CU; fewer do not fill the chip, and wait less
 // beside the longer ones (2^20 edges: 34 + 40 us for two launches, 28 for one).
 constexpr uint32_t kMidApart = 4096;
-// Longest bucket whose values are ranked by counting; longer ones (nearly equal
-// or repeated values) send the segment to the radix passes.  With 128 the
-// segments of 513 to 4,096 values took 7.8 ms on R-MAT 2^27, with 512 6.6; dropping repeats through a
-// table and counting again in between only added to it.
-constexpr uint32_t kBucketMax = 512;
+// A value counts the ones of its bucket, so a segment costs the squares of its
+// bucket lengths in reads; a radix pass costs each value about kRankReads of
+// them, and there is one per byte in which the values differ.  A limit on the
+// longest bucket instead (512) let segments of 600 values in two buckets of 300
+// through at many times the cost of their two passes.  2^25 edges in segments of
+// 8 (1,024) distinct values, whole call, 600 values a segment: 2.73 (1.66) ms
+// with that limit, 1.67 (1.65) with 24 reads, 1.67 (1.93) with 12 and 1.69
+// (1.65) with 96; 500 values: 2.07 (2.13), 1.15 (1.36), 1.15 (1.37) and 1.16
+// (2.15).  R-MAT graphs take the same with any of these.
+constexpr uint32_t kRankReads = 24;
 constexpr uint32_t kUnpackTile = kBlock * 16;
 constexpr uint32_t kUnpackCache = 4096;    // block offsets a tile keeps in LDS
 
@@ -69,14 +74,6 @@ __device__ __forceinline__ void group_sync() {
         wave_sync();
     else
         __syncthreads();
-}
-
-template <int NT>
-__device__ __forceinline__ bool group_any(bool x) {
-    if constexpr (NT == 64)
-        return __any(x);
-    else
-        return __syncthreads_or(x);
 }
 
 // Exclusive scan over the group; *total gets the sum.  All threads must call
@@ -386,8 +383,8 @@ __global__ void __launch_bounds__(kSmallBlock) k_seg_small(SegArgs a) {
 
 // Places of a segment's keys by counting: to buckets by their highest
 // differing bits, then each key counts the ones of its bucket up to it.  On
-// return S.mark holds a key per taken place, S.buf the keys; false where a
-// bucket is too long (S.buf and S.wc are free again).
+// return S.mark holds a key per taken place, S.buf the keys; false where that
+// reads more than radix passes cost (S.buf and S.wc are free again).
 template <int NT>
 __device__ bool rank_segment(const SegSmem<NT>& S, uint32_t cnt, uint32_t ipt, uint64_t diff,
                              const uint64_t (&key)[SegSmem<NT>::kIpt]) {
@@ -409,13 +406,15 @@ __device__ bool rank_segment(const SegSmem<NT>& S, uint32_t cnt, uint32_t ipt, u
         if (r < ipt && (w * ipt + r) * 64 + lane < cnt) atomicAdd(&S.wc[bucket(key[r])], 1u);
     group_sync<NT>();
     uint4 c[kOwn];
-    uint32_t longest = 0, sum = 0;
+    uint32_t reads = 0, sum = 0;  // (at most kCap^2 reads)
 #pragma unroll
     for (uint32_t i = 0; i < kOwn; i++) {
         c[i] = own[i];
-        longest = max(longest, max(max(c[i].x, c[i].y), max(c[i].z, c[i].w)));
+        reads += c[i].x * c[i].x + c[i].y * c[i].y + c[i].z * c[i].z + c[i].w * c[i].w;
         sum += c[i].x + c[i].y + c[i].z + c[i].w;
     }
+    reads = wave_sum_u32(reads);
+    if (NT > 64 && lane == 0) S.red[8 + w] = reads;  // (the scan uses the first eight)
     uint32_t all = 0;
     uint32_t at = group_excl_scan<NT>(sum, S.red, &all);
 #pragma unroll
@@ -423,9 +422,14 @@ __device__ bool rank_segment(const SegSmem<NT>& S, uint32_t cnt, uint32_t ipt, u
         own[i] = make_uint4(at, at + c[i].x, at + c[i].x + c[i].y, at + c[i].x + c[i].y + c[i].z);
         at += c[i].x + c[i].y + c[i].z + c[i].w;
     }
-    const bool over = group_any<NT>(longest > kBucketMax);
+    if constexpr (NT > 64) {
+        reads = 0;
+        for (uint32_t i = 0; i < NT / 64; i++) reads += S.red[8 + i];
+    }
     group_sync<NT>();
-    if (over) return false;
+    uint32_t passes = 0;
+    for (int b = 0; b < 64; b += 8) passes += (diff >> b & 0xFF) != 0;
+    if (reads > kRankReads * passes * cnt) return false;
     // scattered, a bucket's counter holds its end
 #pragma unroll
     for (uint32_t r = 0; r < kIpt; r++)
