@@ -166,8 +166,9 @@ typedef struct {
     float ms_iter_kernels; /* when the ctx option "time_launches" is N > 0: summed
                               durations of every N-th refinement-kernel launch
                               among those that hashed a level (launches
-                              1..k_done, and k_done+1 with tail_split_ppm 0),
-                              with the class test of that level, else 0 */
+                              1..k_done, and k_done+1 where the stop test
+                              looks two levels back, see "tail_split_ppm"),
+                              with their class tests, else 0 */
     float ms_hub_kernels;  /* the same for the hub-vertex launches */
     uint32_t n_timed_launches; /* launches those sums cover */
     uint32_t n_split_launches; /* refinement launches that ran after the class
@@ -223,8 +224,9 @@ const char* bsim_status_string(int status);
  * share of the out-edges that a level's frontier reads;
  * "tail_split_ppm" (0..1000000, default 100) = above 0, a refinement
  * launch's stop test knows the classes of the level just hashed, so a run
- * hashes no level past its last one; 0 = the test looks one level further
- * back, and level k_done + 1 is hashed and dropped;
+ * hashes no level past its last one (from level 257 on, on graphs of up to
+ * 16,384 workgroups, it looks two levels back); 0 = the test always looks two
+ * levels back, and level k_done + 1 is hashed and dropped;
  * "autotune" (0/1, default 1) = batched calls pick their schedule per size
  * class by timing the candidates on the first call of the class;
  * "batch_small_edges" (N >= 0) = a fixed batched schedule instead: graphs

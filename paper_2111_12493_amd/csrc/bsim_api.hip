@@ -297,8 +297,8 @@ const char* bsim_option_names(void) {
            "recomputed for all vertices; 0 = always, the plain full recomputation; default 10); "
            "frontier_edge_pct (1..100: the same for a frontier's share of the out-edges; default 15); "
            "tail_split_ppm (0..1000000: above 0, the default is 100, a launch's stop test knows the classes of "
-           "the level just hashed, and a run hashes no level past its last; 0 = the test looks one level "
-           "further back and one more level is hashed); "
+           "the level just hashed, and a run of up to 256 levels hashes no level past its last; 0 = the test "
+           "looks one level further back and one more level is hashed); "
            "autotune (0/1: batched calls pick their schedule per size class by timing the candidates on the "
            "first call of the class; 1 = default); "
            "batch_small_edges (N >= 0: a fixed batched schedule, graphs of at most N edges that fit one "

@@ -493,12 +493,14 @@ void alloc_run_buffers(const Staged& g, RunBuffers& rb, Arena& arena, hipStream_
 // Level 0: label salts, type hashes, h^0 = t, the type classes (rep) and n_0.
 void launch_init(const Staged& g, const RunBuffers& rb, bool untyped, hipStream_t s);
 
-// Launch k: stop test of level k - lag, h^k (tiles and hub chunks).
-// stop_only: one workgroup that takes the stop decision and reports it to
-// the host, where a whole grid would only dispatch and exit.
+// Launch k: stop test of level k - lag, and h^k (tiles and hub chunks), the
+// classes of level k-1 (with lag 2, k >= 2), both or neither; neither is one
+// workgroup that takes the stop decision and reports it to the host, where a
+// whole grid would only dispatch and exit.
+enum class IterParts { kHashes, kHashesAndSplit, kSplit, kStopTest };
 void launch_iteration(const Staged& g, const RunBuffers& rb, uint32_t k, uint32_t lag, uint32_t k_max, bool stop,
-                      bool all_levels, uint64_t* report, bool stop_only, hipStream_t s);
-// Workgroups of a full launch k.
+                      bool all_levels, uint64_t* report, IterParts parts, hipStream_t s);
+// Workgroups of the hashes of level k.
 uint32_t iteration_grid(const Staged& g, uint32_t k, bool all_levels);
 
 // The classes of level k from h^k.

@@ -124,13 +124,21 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
     }
 
     LoopResult lr;
-    // Launch k tests level k - lag.  With lag 1 it knows the classes of the
-    // level just hashed, and a run hashes no level past its last; with
-    // tail_split_ppm = 0 the test looks one level further back, so level
-    // k_done + 1 is hashed and dropped.
-    const uint32_t lag = ctx->tail_split_ppm ? 1u : 2u;
-    const uint64_t k_last = static_cast<uint64_t>(p.k_max) + lag;
     const bool all = sink && !sink->levels.empty();
+    // Launch k tests level k - lag_of(k).  With lag 1 the classes of every level
+    // are a launch of their own after its hashes: the next launch knows them,
+    // and a run hashes no level past its last.  With lag 2 (always with
+    // tail_split_ppm = 0) they are tested beside the next level's hashes, in one
+    // launch, and level k_done + 1 is hashed and dropped.  A run past kDeep
+    // levels goes over to that: a level of a small graph costs its launches
+    // (20,000 vertices in 20,000 levels 253 ms with two, 150 with one), and one
+    // more level than 256 hardly shows.  Large grids pay their work, not the
+    // launch.
+    constexpr uint64_t kDeep = 256;
+    constexpr uint32_t kLargeGrid = 16384;
+    const uint32_t full_grid = iteration_grid(g, 3, all);
+    auto lag_of = [&](uint64_t kk) { return !ctx->tail_split_ppm || (kk > kDeep && full_grid <= kLargeGrid) ? 2u : 1u; };
+    const uint64_t k_last = static_cast<uint64_t>(p.k_max) + lag_of(p.k_max + 1ull);
     // The host follows the run through the words that block 0 of every launch
     // writes to pinned memory, and queues at most `ahead` launches past the
     // last one it has seen: enough that the device never waits for the host,
@@ -141,8 +149,7 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
     // (about 2 ns a workgroup), so past kLargeGrid workgroups, where one
     // would cost more than the host's round trip of some 10 us, the stop test
     // runs as a launch of one workgroup and the host waits for its answer.
-    constexpr uint32_t kLargeGrid = 16384;
-    const bool large = iteration_grid(g, 3, all) > kLargeGrid || ctx->chunk_max == 1;
+    const bool large = full_grid > kLargeGrid || ctx->chunk_max == 1;
     const uint32_t ahead = std::min<uint32_t>(ctx->chunk_max, 4);
     uint64_t* const report = ctx->report_host;
     for (uint32_t i = 0; i < kReportRing; i++) report[i] = 0;
@@ -171,7 +178,9 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
         const uint32_t flags = static_cast<uint32_t>(x >> 32);
         if (flags & kReportError)
             throw DeviceError{BSIM_E_DEVICE, "a hub hash bucket could not be split to fit its table"};
-        if (!rb.bc.gid && kk >= lag) lr.blocks_per_iter.push_back(static_cast<uint32_t>(x));
+        const uint32_t lag = lag_of(kk);
+        // (launch kDeep + 1 tests the level that the one before it tested)
+        if (!rb.bc.gid && kk == lr.blocks_per_iter.size() + lag) lr.blocks_per_iter.push_back(static_cast<uint32_t>(x));
         if (flags & kReportDone) {
             done = true;
             lr.k_done = static_cast<uint32_t>(kk - lag);
@@ -207,11 +216,16 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
             rb.bc.hist = nh;
             rb.bc.hist_cap = static_cast<uint32_t>(cap);
         }
+        const uint32_t lag = lag_of(kk);
         if (rb.bc.gid) launch_graph_stop(rb, kk, lag, p.k_max, stop, s);
         const bool hashes = kk <= p.k_max;
-        if (large || !hashes) {
-            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report, true, s);
-            if (!hashes) return;
+        const bool splits = lag == 2 && kk >= 2 && kk - 1 <= p.k_max;  // level kk-1, whose split launch was left out
+        if (!hashes) {
+            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report, splits ? IterParts::kSplit : IterParts::kStopTest, s);
+            return;
+        }
+        if (large) {
+            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report, IterParts::kStopTest, s);
             read_report(kk, true);
             if (done) return;
         }
@@ -228,7 +242,8 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
             }
         }
         mark(0);
-        launch_iteration(g, rb, kk, lag, p.k_max, stop, all, large ? nullptr : report, false, s);
+        launch_iteration(g, rb, kk, lag, p.k_max, stop, all, large ? nullptr : report,
+                         splits ? IterParts::kHashesAndSplit : IterParts::kHashes, s);
         mark(1);
         launch_hubs(g, rb, kk, s);
         mark(2);
@@ -239,7 +254,7 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
                       "previous classes");
             prev_taken = true;
         }
-        launch_split(g, rb, kk, s);
+        if (lag_of(kk + 1ull) == 1) launch_split(g, rb, kk, s);
         mark(3);
         lr.launches++;
         if (lag == 1) lr.split_launches++;
@@ -259,7 +274,7 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
     // launches past the last hashed level return at once
     if (!timers.empty()) hip_check(hipStreamSynchronize(s), "launch timers");
     for (size_t i = 0; 4 * i + 3 < timers.size(); i++) {
-        if (timed_k[i] > lr.k_done + lag - 1) break;
+        if (timed_k[i] > lr.k_done + lag_of(timed_k[i]) - 1) break;
         float t[3] = {0.f, 0.f, 0.f};
         for (int j = 0; j < 3; j++)
             hip_check(hipEventElapsedTime(&t[j], timers[4 * i + j], timers[4 * i + j + 1]), "launch timer");
