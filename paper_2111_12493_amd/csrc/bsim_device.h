@@ -56,37 +56,6 @@ __device__ __forceinline__ uint64_t block_sum_u64(uint64_t x, uint64_t* red) {
     return t;
 }
 
-// Insert hash h into a key-only open-addressing table (0 = empty slot,
-// capacity mask+1 > number of keys).  The hash 0 itself is tracked by a flag.
-// Returns 1 if h was not present before.
-//
-// Many vertices share a hash (e.g. every isolated vertex with the same type
-// set), so a slot is read before it is CASed: within one launch a slot only
-// changes from 0 to a key, so a plain read either sees the final key (no
-// atomic needed) or a possibly stale 0 that the CAS then resolves.  Without
-// this, all vertices of a large block serialize on one address.
-__device__ __forceinline__ uint32_t count_insert(uint64_t* tab, uint32_t mask, uint32_t* zflag,
-                                                 uint64_t h) {
-    if (h == 0) {
-        if (*reinterpret_cast<volatile uint32_t*>(zflag)) return 0u;
-        return atomicExch(zflag, 1u) == 0u ? 1u : 0u;
-    }
-    uint32_t slot = static_cast<uint32_t>(h) & mask;
-    for (;;) {
-        uint64_t cur = tab[slot];
-        if (cur == h) return 0u;
-        if (cur == 0) {
-            unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(tab + slot), 0ull,
-                                               static_cast<unsigned long long>(h));
-            if (old == 0ull) return 1u;
-            if (old == h) return 0u;
-        }
-        slot = (slot + 1) & mask;
-    }
-}
-
-// Insert a nonzero key into an LDS open-addressing region; returns 1 if it
-// was not present.  Same read-before-CAS rule as count_insert.
 // Current value of an LDS table slot other lanes may be writing.  A relaxed
 // atomic load (a volatile one would keep the generic address space and
 // compile to a flat load, which also waits on every global load in flight).
@@ -94,6 +63,10 @@ __device__ __forceinline__ uint64_t lds_peek(uint64_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Insert a nonzero key into an LDS open-addressing region; returns 1 if it
+// was not present.  A slot only changes from 0 to a key while it is in use, so
+// it is read before it is CASed: the read sees the key (no atomic needed), or a
+// 0 that the CAS then resolves.
 __device__ __forceinline__ uint32_t lds_insert(uint64_t* tab, uint32_t slot, uint32_t base,
                                                uint32_t end, uint64_t f) {
     for (;;) {
@@ -106,27 +79,6 @@ __device__ __forceinline__ uint32_t lds_insert(uint64_t* tab, uint32_t slot, uin
             if (old == f) return 0u;
         }
         if (++slot == end) slot = base;
-    }
-}
-
-// Insert a nonzero key into an LDS table of `slots` slots by double hashing:
-// after `slot` (already tried), probe slot + step, slot + 2 step, ... mod
-// slots.  With slots prime and 0 < step < slots the sequence visits every
-// slot, so a table with a free slot always ends the loop: 1 = inserted,
-// 0 = already present.
-__device__ __forceinline__ uint32_t lds_insert_step(uint64_t* tab, uint32_t slot, uint32_t step, uint32_t slots,
-                                                    uint64_t f) {
-    for (;;) {
-        slot += step;
-        if (slot >= slots) slot -= slots;
-        uint64_t cur = lds_peek(&tab[slot]);
-        if (cur == f) return 0u;
-        if (cur == 0) {
-            unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[slot]), 0ull,
-                                               static_cast<unsigned long long>(f));
-            if (old == 0ull) return 1u;
-            if (old == f) return 0u;
-        }
     }
 }
 

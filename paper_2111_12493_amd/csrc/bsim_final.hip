@@ -13,8 +13,10 @@
 //   3. every vertex takes the id under its class's name; the members besides
 //      the smallest are counted per workgroup in LDS first.
 // Summary edges (Sec. 2.6: edges between vertex summaries) are the distinct
-// (block(v), l, block(w)) triples: packed into one 64-bit key per edge,
-// sorted by an LSD radix sort over the used bits, de-duplicated and unpacked.
+// (block(v), l, block(w)) triples.  Graphs with a tile schedule take them from
+// bsim_sedges.hip; a resident state, which keeps its edges as (source, label,
+// target) lists, packs one 64-bit key per edge here, sorts the keys by an LSD
+// radix sort over the used bits, and unpacks the distinct ones.
 #include "bsim_api_internal.h"
 #include "bsim_device.h"
 
@@ -184,47 +186,6 @@ __global__ void __launch_bounds__(kBlock) k_fin_ids(const uint8_t* __restrict__ 
         if (s_cnt[i]) atomicAdd(&sizes[s_key[i]], s_cnt[i]);
 }
 
-// ------------------------------------------------------------ edge keys
-
-struct KeyShared {
-    uint64_t src[kTileMaxVerts];        // block of the tile's vertices, in place
-    alignas(8) uint8_t owner[kTileMaxEdges];
-};
-
-// One wave per tile; solo vertices and hubs by a workgroup each.
-template <typename LabT>
-__global__ void __launch_bounds__(kBlock) k_edge_keys(
-    const uint32_t* __restrict__ row_off, const uint32_t* __restrict__ tgt,
-    const LabT* __restrict__ lab, const uint32_t* __restrict__ bid, const uint32_t* __restrict__ bid_dst,
-    const uint4* __restrict__ tiles, const uint32_t* __restrict__ act, const uint32_t* __restrict__ act_off,
-    uint32_t n_tiles, const uint32_t* __restrict__ solo_v, uint32_t n_solo, const uint32_t* __restrict__ hub_v,
-    uint32_t n_hubs, int lb, int bb, uint64_t* __restrict__ keys) {
-    __shared__ KeyShared sh[kWaves];
-    const uint32_t tid = threadIdx.x;
-    if (blockIdx.x < n_hubs + n_solo) {
-        const uint32_t v = blockIdx.x < n_hubs ? hub_v[blockIdx.x] : solo_v[blockIdx.x - n_hubs];
-        const uint64_t src = static_cast<uint64_t>(bid[v]) << (lb + bb);
-        for (uint32_t e = row_off[v] + tid; e < row_off[v + 1]; e += kBlock)
-            keys[e] = src | (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
-        return;
-    }
-    const uint32_t lane = lane_id(), tile = (blockIdx.x - n_hubs - n_solo) * kWaves + (tid >> 6);
-    if (tile >= n_tiles) return;
-    KeyShared& S = sh[tid >> 6];
-    const uint4 td = tiles[tile];
-    const uint32_t nv = td.y - td.x, ne = td.w - td.z;
-    uint32_t off = 0;
-    if (lane < nv) {
-        S.src[lane] = static_cast<uint64_t>(bid[act[td.x + lane]]) << (lb + bb);
-        off = act_off[td.x + lane] - td.z;
-    }
-    tile_owners(S.owner, lane < nv, off);
-    for (uint32_t j = lane; j < ne; j += 64) {
-        const uint32_t e = td.z + j;
-        keys[e] = S.src[S.owner[j]] | (static_cast<uint64_t>(lab[e]) << bb) | bid_dst[tgt[e]];
-    }
-}
-
 // ------------------------------------------------------------ radix sort
 //
 // LSD radix sort of 64-bit keys, 8 bits per pass.  Each pass: per-block digit
@@ -237,7 +198,7 @@ __global__ void __launch_bounds__(kBlock) k_edge_keys(
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kBlock * kSortItems;
 
-// Edge keys from a COO source array (graphs without a tile schedule).
+// Edge keys from a source per edge (a resident state).
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_edge_keys_coo(const uint32_t* __restrict__ src,
                                                           const uint32_t* __restrict__ tgt,
@@ -489,29 +450,19 @@ void finalize_edges(const Staged& g, const uint32_t* rep, const uint32_t* rep_pr
             throw DeviceError{BSIM_E_DEVICE, "internal: class count mismatch in finalize"};
         return;
     }
-    if (2 * bb + lb > 64)
+    // (labels are below 2^24, so graphs with a tile schedule that the bucketed
+    // path refuses, for more than 46 value bits, are refused here too)
+    if (2 * bb + lb > 64 || !g.src)
         throw DeviceError{BSIM_E_UNSUPPORTED, "summary-edge triple does not fit 64 bits"};
     const uint32_t m = static_cast<uint32_t>(g.m);
     uint64_t* ka = arena.alloc<uint64_t>(m);
     uint64_t* kb = arena.alloc<uint64_t>(m);
-    const uint32_t grid = std::max<uint32_t>(g.n_hubs + g.n_solo + ceil_div(g.n_tiles, kWaves), 1);
-    if (g.src) {
-        if (g.label_bytes == 2)
-            k_edge_keys_coo<uint16_t><<<ceil_div(m, kBlock), kBlock, 0, s>>>(
-                g.src, g.tgt, static_cast<const uint16_t*>(g.lab), out.block_ids, dst_ids, m, lb, bb, ka);
-        else
-            k_edge_keys_coo<uint32_t><<<ceil_div(m, kBlock), kBlock, 0, s>>>(
-                g.src, g.tgt, static_cast<const uint32_t*>(g.lab), out.block_ids, dst_ids, m, lb, bb, ka);
-    } else if (g.label_bytes == 2)
-        k_edge_keys<uint16_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
-                                                      static_cast<const uint16_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo,
-                                                      g.hub_v, g.n_hubs, lb, bb, ka);
+    if (g.label_bytes == 2)
+        k_edge_keys_coo<uint16_t><<<ceil_div(m, kBlock), kBlock, 0, s>>>(
+            g.src, g.tgt, static_cast<const uint16_t*>(g.lab), out.block_ids, dst_ids, m, lb, bb, ka);
     else
-        k_edge_keys<uint32_t><<<grid, kBlock, 0, s>>>(g.row_off, g.tgt,
-                                                      static_cast<const uint32_t*>(g.lab), out.block_ids, dst_ids,
-                                                      g.tiles, g.act, g.act_off, g.n_tiles, g.solo_v, g.n_solo,
-                                                      g.hub_v, g.n_hubs, lb, bb, ka);
+        k_edge_keys_coo<uint32_t><<<ceil_div(m, kBlock), kBlock, 0, s>>>(
+            g.src, g.tgt, static_cast<const uint32_t*>(g.lab), out.block_ids, dst_ids, m, lb, bb, ka);
     hip_check(hipGetLastError(), "edge key launch");
     uint64_t* sorted = radix_sort(ka, kb, m, 2 * bb + lb, arena, s);
     uint32_t* flag = arena.alloc<uint32_t>(m);

@@ -995,13 +995,6 @@ __global__ void __launch_bounds__(kBlock) k_graph_stop(BatchCtl bc, uint32_t k, 
     }
 }
 
-// ------------------------------------------------------------ level classes
-//
-// The classes of stored levels h^0..h^K, level by level (used by the
-// resident state, whose levels change under update batches): level 0 groups
-// alive vertices by t(v); level j >= 1 splits every class by h^j with the
-// same split test as launch j+1 of the refinement loop.
-
 }  // namespace
 
 uint32_t query_hub_table_slots(int device, bool device_max) {

@@ -2,8 +2,8 @@
 // the device prefix sum the library uses.
 //
 // Staging validates the CSR (paper Sec. 3.1 Phase 0 co-locates every vertex
-// with its out-edges; here that is the out-edge CSR itself), computes the
-// label salts, and cuts the vertex range into tiles and hub buckets:
+// with its out-edges; here that is the out-edge CSR itself) and cuts the vertex
+// range into tiles, solo vertices and hub buckets:
 //   * a vertex of 1..kTileMaxEdges out-edges belongs to exactly one tile, a
 //     run of consecutive such vertices packed greedily (within kStageVerts
 //     vertices) up to kTileMaxEdges edges and kTileMaxVerts vertices;
@@ -177,8 +177,9 @@ namespace {
 // vertex, no out-edges), compacts the tile vertices' edge ranges in LDS and
 // packs them into tiles, so a tile never leaves its workgroup's vertices.
 // The first pass counts (hubs, tile vertices, solo vertices, tiles), the scan
-// places the counts, the second pass repeats the work and writes the lists.  Repeating it costs 4 bytes per vertex; carrying flags, positions
-// and three separate scans and compactions between passes cost 72.
+// places the counts, the second pass repeats the work and writes the lists.
+// Repeating it costs 4 bytes per vertex; carrying flags, positions and three
+// separate scans and compactions between passes cost 72.
 //
 // Packing is greedy.  Row ends grow with the vertex, so the vertices that
 // still fit a tile starting at edge a are a prefix (row end - a at most

@@ -1,10 +1,11 @@
 // bsim_summarize.hip -- host driver of one batch summarization.
 //
 // Device round trips per call: one after staging (tile and hub counts), two
-// in finalize (block and edge counts).  The refinement loop has none: the
-// host queues a few launches ahead of what the device reports through pinned
-// memory, so a run of thousands of iterations (long k-chaining) costs only
-// the kernels themselves plus a few early-exit launches.
+// in finalize (block and edge counts).  The refinement loop has none on grids
+// of up to 16,384 workgroups: the host queues a few launches ahead of what the
+// device reports through pinned memory, so a run of thousands of iterations
+// (long k-chaining) costs only the kernels themselves plus a few early-exit
+// launches.  Past that it has one per level, for the stop test's answer.
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
