@@ -7,7 +7,10 @@
 #include <cstring>
 #include <new>
 
+#include <sys/mman.h>
+
 #include "bsim_api_internal.h"
+#include "bsim_resolve.h"  // shared_host_pool
 
 using namespace bsim;
 
@@ -39,13 +42,13 @@ void ctx_note_demand(bsim_ctx* ctx, const Arena& arena) {
     if (ctx->keep_work) ctx->work_want = std::max(ctx->work_want, arena.demand());
 }
 
-void* PinnedPool::take(size_t bytes, size_t* cap) {
-    // powers of two below 1 MiB, whole MiB above, so that calls of about one
-    // size find each other's blocks
-    const size_t want = bytes <= (1u << 20) ? static_cast<size_t>(next_pow2(std::max<size_t>(bytes, 4096)))
-                                            : (bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1);
-    std::vector<void*> out;  // kept blocks that make room
-    bool room = true;
+void* BlockPool::take(size_t bytes, size_t* cap) {
+    // powers of two below 1 MiB, whole 2 MiB pages above (asked for as such:
+    // 512 times fewer faults), so that calls of about one size find each
+    // other's blocks
+    constexpr size_t kHuge = 2u << 20;
+    const size_t want = bytes <= kHuge / 2 ? static_cast<size_t>(next_pow2(std::max<size_t>(bytes, 4096)))
+                                           : (bytes + kHuge - 1) & ~(kHuge - 1);
     {
         std::lock_guard<std::mutex> lk(mu_);
         size_t best = free_.size();
@@ -61,35 +64,18 @@ void* PinnedPool::take(size_t bytes, size_t* cap) {
             free_.pop_back();
             return p;
         }
-        room = pinned_ - kept_ + want <= kPinnedMost;
-        if (room) {
-            out.reserve(free_.size());
-            while (pinned_ + want > kPinnedMost) {
-                out.push_back(free_.back().first);
-                kept_ -= free_.back().second;
-                pinned_ -= free_.back().second;
-                free_.pop_back();
-            }
-            pinned_ += want;
-        }
     }
-    for (void* p : out) (void)hipHostFree(p);
-    if (!room) return nullptr;
-    void* p = nullptr;
-    if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        std::lock_guard<std::mutex> lk(mu_);
-        pinned_ -= want;
-        return nullptr;
-    }
+    void* p = want < kHuge ? malloc(want) : aligned_alloc(kHuge, want);
+    if (!p) throw DeviceError{BSIM_E_NOMEM, "host result allocation failed"};
+    if (want >= kHuge) (void)madvise(p, want, MADV_HUGEPAGE);
     *cap = want;
     return p;
 }
 
-void PinnedPool::give(void* p, size_t cap) {
-    {
+void BlockPool::give(void* p, size_t cap) {
+    if (owner_ == getpid()) {  // (else its lock may have been held at the fork)
         std::lock_guard<std::mutex> lk(mu_);
-        if (contexts_ && kept_ + cap <= kPinnedKeep) {
+        if (contexts_ && kept_ + cap <= kKeep) {
             try {
                 free_.emplace_back(p, cap);
                 kept_ += cap;
@@ -97,49 +83,61 @@ void PinnedPool::give(void* p, size_t cap) {
             } catch (const std::bad_alloc&) {
             }
         }
-        pinned_ -= cap;
     }
-    (void)hipHostFree(p);
+    free(p);
 }
 
-void PinnedPool::open() {
+void BlockPool::open() {
     std::lock_guard<std::mutex> lk(mu_);
     contexts_++;
 }
 
-void PinnedPool::close() {
+void BlockPool::close() {
     std::vector<std::pair<void*, size_t>> all;
     {
         std::lock_guard<std::mutex> lk(mu_);
         if (--contexts_) return;
         all.swap(free_);
-        pinned_ -= kept_;
         kept_ = 0;
     }
-    for (auto& b : all) (void)hipHostFree(b.first);
+    for (auto& b : all) free(b.first);
 }
 
-void share_host_pool(bsim_ctx* ctx, const bsim_ctx* with) {
-    with->host_pool->open();
-    ctx->host_pool->close();
-    ctx->host_pool = with->host_pool;
+void share_blocks(bsim_ctx* ctx, const bsim_ctx* with) {
+    with->blocks->open();
+    ctx->blocks->close();
+    ctx->blocks = with->blocks;
 }
 
-HostBlock::HostBlock(const std::shared_ptr<PinnedPool>& from, size_t bytes) {
-    if (from && bytes <= PinnedPool::kPinnedKeep) p = from->take(bytes, &cap);
-    if (p) {
-        pool = from;
-        return;
+void* HostStaging::get_small() {
+    if (!small && hipHostMalloc(&small, kSmall, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        small = nullptr;
     }
-    p = malloc(bytes ? bytes : 8);
-    if (!p) throw DeviceError{BSIM_E_NOMEM, "host result allocation failed"};
+    return small;
 }
 
-HostBlock::~HostBlock() {
-    if (pool)
-        pool->give(p, cap);
-    else
-        free(p);
+char* HostStaging::get_large() {
+    for (hipEvent_t& e : full)
+        if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            e = nullptr;
+            return nullptr;
+        }
+    void* q = nullptr;
+    if (!large && hipHostMalloc(&q, 2 * kHalf, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (q) large = static_cast<char*>(q);
+    return large;
+}
+
+void HostStaging::release() {
+    if (small) (void)hipHostFree(small);
+    if (large) (void)hipHostFree(large);
+    for (hipEvent_t e : full)
+        if (e) (void)hipEventDestroy(e);
 }
 
 namespace {
@@ -185,26 +183,67 @@ void copy_ranges(void* const* dst, const void* const* src, const size_t* bytes, 
     hip_check(hipGetLastError(), "copy launch");
 }
 
-// Pageable arrays come back through the runtime's staging buffer, with every
-// page of fresh memory touched for the first time on the way: 125 MB of a
-// batched call's results took 33 ms that way; into pinned blocks that later
-// calls use again they take 2.3.
+namespace {
+
+// memcpy on the process's host threads; by itself where they are busy.
+void copy_on_threads(char* dst, const char* src, size_t bytes) {
+    constexpr size_t kShare = 256u << 10;
+    const size_t T = std::min<size_t>(8, bytes / kShare);
+    const std::function<void(size_t)> share = [&](size_t t) {
+        const size_t at = bytes / T * t, end = t + 1 == T ? bytes : bytes / T * (t + 1);
+        memcpy(dst + at, src + at, end - at);
+    };
+    if (T < 2 || !shared_host_pool().try_run(T, share)) memcpy(dst, src, bytes);
+}
+
+}  // namespace
+
 std::shared_ptr<HostBlock> host_arrays(bsim_ctx* ctx, void* const* dev, const size_t* bytes, void** base) {
     size_t at[6], total = 0;
     for (int i = 0; i < 6; i++) {
         at[i] = total;
         total += (bytes[i] + 63) & ~size_t(63);
     }
-    auto block = std::make_shared<HostBlock>(ctx->host_pool, total);
+    auto block = std::make_shared<HostBlock>(ctx->blocks, total);
     for (int i = 0; i < 6; i++) base[i] = static_cast<char*>(block->p) + at[i];
-    if (block->pool) {
-        copy_ranges(base, dev, bytes, 6, ctx->stream);
-    } else {
-        for (int i = 0; i < 6; i++)
-            if (bytes[i])
-                hip_check(hipMemcpyAsync(base[i], dev[i], bytes[i], hipMemcpyDeviceToHost, ctx->stream), "result copy");
+    hipStream_t s = ctx->stream;
+    HostStaging& st = ctx->staging;
+    if (total <= HostStaging::kSmall && st.get_small()) {
+        void* to[6];
+        for (int i = 0; i < 6; i++) to[i] = static_cast<char*>(st.small) + at[i];
+        copy_ranges(to, dev, bytes, 6, s);
+        hip_check(hipStreamSynchronize(s), "result sync");
+        for (int i = 0; i < 6; i++) memcpy(base[i], to[i], bytes[i]);
+        return block;
     }
-    hip_check(hipStreamSynchronize(ctx->stream), "result sync");
+    if (total > HostStaging::kSmall && st.get_large()) {
+        struct Piece {
+            char* to;
+            size_t n;
+        } piece[2] = {};
+        int half = 0;
+        auto empty = [&](int h) {
+            if (!piece[h].n) return;
+            hip_check(hipEventSynchronize(st.full[h]), "result copy");
+            copy_on_threads(piece[h].to, st.large + h * HostStaging::kHalf, piece[h].n);
+            piece[h].n = 0;
+        };
+        for (int i = 0; i < 6; i++)
+            for (size_t o = 0; o < bytes[i]; o += HostStaging::kHalf, half ^= 1) {
+                const size_t n = std::min(HostStaging::kHalf, bytes[i] - o);
+                hip_check(hipMemcpyAsync(st.large + half * HostStaging::kHalf, static_cast<const char*>(dev[i]) + o, n,
+                                         hipMemcpyDeviceToHost, s), "result copy");
+                hip_check(hipEventRecord(st.full[half], s), "result copy");
+                piece[half] = {static_cast<char*>(base[i]) + o, n};
+                empty(half ^ 1);
+            }
+        empty(half);
+        empty(half ^ 1);
+        return block;
+    }
+    for (int i = 0; i < 6; i++)
+        if (bytes[i]) hip_check(hipMemcpyAsync(base[i], dev[i], bytes[i], hipMemcpyDeviceToHost, s), "result copy");
+    hip_check(hipStreamSynchronize(s), "result sync");
     return block;
 }
 
@@ -243,12 +282,12 @@ int bsim_ctx_create(int device, void* hip_stream, bsim_ctx** out) {
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
     try {
-        c->host_pool = std::make_shared<PinnedPool>();
+        c->blocks = std::make_shared<BlockPool>();
     } catch (const std::bad_alloc&) {
         bsim_ctx_free(c);
         return BSIM_E_NOMEM;
     }
-    c->host_pool->open();
+    c->blocks->open();
     c->hub_table_slots = query_hub_table_slots(device);
     if (hipHostMalloc(reinterpret_cast<void**>(&c->pinned), sizeof(CtxPinned),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
@@ -281,7 +320,8 @@ void bsim_ctx_free(bsim_ctx* ctx) {
     (void)hipSetDevice(ctx->device);
     ctx_release_work(ctx);
     (void)hipStreamSynchronize(ctx->stream);
-    if (ctx->host_pool) ctx->host_pool->close();
+    ctx->staging.release();
+    if (ctx->blocks) ctx->blocks->close();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
 }

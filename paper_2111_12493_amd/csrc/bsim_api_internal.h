@@ -1,6 +1,8 @@
 // bsim_api_internal.h -- host-side objects behind the opaque ABI handles.
 #pragma once
 
+#include <unistd.h>
+
 #include <map>
 #include <memory>
 #include <mutex>
@@ -11,25 +13,15 @@
 
 namespace bsim {
 
-// Pinned host memory that a context's calls move their arrays through: the
-// host arrays of results, and the uploads of small graphs.  Blocks come back
-// when their result is freed, on any thread, and are kept for later calls up
-// to kPinnedKeep bytes.  A caller that keeps its results gets fresh blocks
-// until kPinnedMost bytes are pinned, kept ones included, and ordinary memory
-// from there on.  The contexts of a server share one pool; the end of the last
-// context gives the kept blocks back, and blocks still out then are freed as
-// they come.
-//
-// A fresh block costs less than the copy through the runtime's staging buffer
-// that it replaces, also where no block ever comes back: a call that returns
-// 22 KB (2.3, 52, 207 MB) and whose result is kept takes 0.35 ms (0.62, 2.3,
-// 7.4) with pinned blocks and 0.90 (2.6, 17, 68) without.
-class PinnedPool {
+// Host memory of results that were freed, kept for later ones up to kKeep
+// bytes: touching fresh pages takes longer than the copy into them.  Blocks
+// come back on any thread.  The contexts of a server share one pool; the end
+// of the last context frees what is kept, and blocks still out then are freed
+// as they come.
+class BlockPool {
   public:
-    static constexpr size_t kPinnedKeep = 512ull << 20;   // kept blocks, and the largest block
-    static constexpr size_t kPinnedMost = 1024ull << 20;  // kept blocks and those out
-    // A block of at least `bytes`; nullptr when there is no pinned memory or
-    // no more may be pinned.  *cap: its size, for give().
+    static constexpr size_t kKeep = 512ull << 20;
+    // A block of at least `bytes`; *cap: its size, for give().
     void* take(size_t bytes, size_t* cap);
     void give(void* p, size_t cap);
     void open();   // one more context
@@ -38,20 +30,39 @@ class PinnedPool {
   private:
     std::mutex mu_;
     std::vector<std::pair<void*, size_t>> free_;
-    size_t kept_ = 0;    // bytes of free_
-    size_t pinned_ = 0;  // bytes of all blocks
+    size_t kept_ = 0;
     int contexts_ = 0;
+    const pid_t owner_ = getpid();  // (a forked process frees its copies)
 };
 
-// One block, owned: pinned from the pool, or ordinary memory where that failed.
+// The host arrays of a result: ordinary memory, which a caller may hold as long
+// and as much of as it likes, and which a forked process finds where it was.
+// Pinned memory, which the device could write itself, is not inherited.
 struct HostBlock {
-    std::shared_ptr<PinnedPool> pool;  // nullptr: ordinary memory
-    void* p = nullptr;
+    std::shared_ptr<BlockPool> pool;
     size_t cap = 0;
-    HostBlock(const std::shared_ptr<PinnedPool>& from, size_t bytes);
-    ~HostBlock();
+    void* p = nullptr;
+    HostBlock(const std::shared_ptr<BlockPool>& from, size_t bytes) : pool(from), p(from->take(bytes, &cap)) {}
+    ~HostBlock() { pool->give(p, cap); }
     HostBlock(const HostBlock&) = delete;
     HostBlock& operator=(const HostBlock&) = delete;
+};
+
+// Pinned memory of a context that its calls move host arrays through, taken at
+// the first call that needs it: one small block, and a large one as two halves,
+// of which the device fills one while host threads empty the other.  A call
+// that returns 265 MB takes 8.8 ms that way (16.4 with halves of 2 MiB, 11.5
+// with 4, 9.0 with 16), 7.8 where the device wrote the result's own pinned
+// memory, and 64 through the runtime's copies into fresh pageable arrays.
+struct HostStaging {
+    static constexpr size_t kSmall = 1u << 20;
+    static constexpr size_t kHalf = 8u << 20;
+    void* small = nullptr;
+    char* large = nullptr;
+    hipEvent_t full[2] = {nullptr, nullptr};
+    void* get_small();  // nullptr when there is no pinned memory
+    char* get_large();
+    void release();
 };
 
 // What the device and the host tell each other during a call, in one pinned
@@ -75,7 +86,8 @@ struct bsim_ctx {
     bsim::StageHost* stage_host = nullptr;   // what staging copies back
     bsim::FinalHost* final_host = nullptr;   // what finalize copies back
     uint64_t* report_host = nullptr;         // kReportRing words, written by refinement launches
-    std::shared_ptr<bsim::PinnedPool> host_pool;
+    bsim::HostStaging staging;
+    std::shared_ptr<bsim::BlockPool> blocks;
     uint32_t chunk_max = 32;
     uint32_t time_launches = 0;
     uint32_t hub_table_slots = 8192;  // LDS slots per hub-bucket block on this device
@@ -130,13 +142,12 @@ struct DeviceGraph {
     Staged g;
 };
 
-// Let ctx take its pinned memory from the pool of `with`.
-void share_host_pool(bsim_ctx* ctx, const bsim_ctx* with);
+// Let ctx take the memory of its host results from the pool of `with`.
+void share_blocks(bsim_ctx* ctx, const bsim_ctx* with);
 
-// pool: pinned memory for the upload of a small graph; *block (nullable with
-// pool) keeps it until the upload is done.
-void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
-                  const std::shared_ptr<PinnedPool>& pool = nullptr, std::shared_ptr<HostBlock>* block = nullptr);
+// staging: pinned memory for the upload of a small graph (nullable), in use
+// until the stream has run past the upload.
+void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s, HostStaging* staging = nullptr);
 
 // Queue up to 8 copies between arrays of the library's own, all visible to the
 // device, in one launch where they are small (a copy apiece otherwise); bytes

@@ -106,7 +106,7 @@ void bsim_server::worker(uint32_t w) {
                 } else if ((d.status = bsim_ctx_create(device, os.stream, &os.ctx)) == BSIM_OK) {
                     ctx = os.ctx;
                     ctx->keep_work = 0;
-                    share_host_pool(ctx, ctxs[w]);
+                    share_blocks(ctx, ctxs[w]);
                     std::vector<std::pair<std::string, int64_t>> opts;
                     {
                         std::lock_guard<std::mutex> lk(opt_mu);
@@ -165,7 +165,7 @@ int bsim_server_create(int device, uint64_t budget, uint32_t n_workers, bsim_ser
         // the scheduler's memory budget counts a request's temporaries
         // while it runs only: workers keep no buffer between requests
         c->keep_work = 0;
-        if (w) share_host_pool(c, s->ctxs[0]);
+        if (w) share_blocks(c, s->ctxs[0]);
         s->streams.push_back(st);
         s->ctxs.push_back(c);
     }

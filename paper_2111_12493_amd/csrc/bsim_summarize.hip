@@ -42,8 +42,7 @@ void validate_params(const bsim_graph& graph, const bsim_params& p, bool directi
                                               "bsim_summarize without a state only"};
 }
 
-void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
-                  const std::shared_ptr<PinnedPool>& pool, std::shared_ptr<HostBlock>* block) {
+void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s, HostStaging* staging) {
     g.n = in.n_vertices;
     g.m = in.n_edges;
     g.label_bytes = in.label_bytes;
@@ -69,17 +68,14 @@ void upload_graph(const bsim_graph& in, Staged& g, Arena& arena, hipStream_t s,
     }
     // A small graph goes up in one copy from pinned memory: five copies from
     // pageable memory, each through the runtime's staging, took 110 us of a
-    // 1,000-vertex graph's 456.  Past kUploadOne the extra pass over the host's
+    // 1,000-vertex graph's 456.  Past a MiB the extra pass over the host's
     // arrays would cost more than the copies' overhead.
-    constexpr size_t kUploadOne = 1u << 20;
     uint8_t* dev = arena.alloc<uint8_t>(total);
-    std::shared_ptr<HostBlock> up;
-    if (pool && total <= kUploadOne) up = std::make_shared<HostBlock>(pool, total);
-    if (up && up->pool) {
+    uint8_t* up = staging && total <= HostStaging::kSmall ? static_cast<uint8_t*>(staging->get_small()) : nullptr;
+    if (up) {
         for (int i = 0; i < 6; i++)
-            if (bytes[i]) memcpy(static_cast<uint8_t*>(up->p) + at[i], from[i], bytes[i]);
-        hip_check(hipMemcpyAsync(dev, up->p, total, hipMemcpyHostToDevice, s), "upload graph");
-        *block = up;
+            if (bytes[i]) memcpy(up + at[i], from[i], bytes[i]);
+        hip_check(hipMemcpyAsync(dev, up, total, hipMemcpyHostToDevice, s), "upload graph");
     } else {
         for (int i = 0; i < 6; i++)
             if (bytes[i]) hip_check(hipMemcpyAsync(dev + at[i], from[i], bytes[i], hipMemcpyHostToDevice, s), "upload graph");
@@ -369,8 +365,7 @@ bsim_result* summarize_graph(bsim_ctx* ctx, const bsim_graph& graph, const bsim_
     } guard{ev};
     hip_check(hipEventRecord(ev[0], s), "event");
     Staged g;
-    std::shared_ptr<HostBlock> upload;  // until the call's end
-    upload_graph(graph, g, arena, s, ctx->host_pool, &upload);
+    upload_graph(graph, g, arena, s, &ctx->staging);
     g.hub_table_slots = ctx->hub_table_slots;
     stage_graph(g, ctx->stage_host, arena, s);
     // direction / label parameterizations: refine the view h, take the
