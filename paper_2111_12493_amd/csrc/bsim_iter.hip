@@ -389,7 +389,8 @@ __device__ __forceinline__ void wave_tile(const IterArgs& a, uint32_t tile, Wave
 #pragma unroll
     for (int q = 0; q < kLaneEdges; q++) f[q] = static_cast<uint32_t>(q) < cnt ? a.h_prev[w[q]] : 0;
     const uint64_t tv = mine ? a.t[v] : 0;
-    const bool write = mine && (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k));
+    bool write = mine;
+    if (mine && a.bc.gid) write = batch_refines(a.bc, a.bc.gid[v], a.k);
     const LaneOwners own = lane_owners(reinterpret_cast<uint8_t*>(L.slot), mine, off);
     if (stop_decision(a, p)) return;
     uint32_t todo = 0;
@@ -531,7 +532,8 @@ __device__ void solo_block(const IterArgs& a, uint32_t v, SoloLds& L, const Stop
     const uint32_t tid = threadIdx.x;
     const uint32_t e0 = a.row_off[v];
     const uint32_t ne = p.done ? 0u : a.row_off[v + 1] - e0;
-    const bool write = tid == 0 && (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k));
+    bool write = tid == 0;
+    if (a.bc.gid) write = write && batch_refines(a.bc, a.bc.gid[v], a.k);
     const uint64_t tv = a.t[v];
     const LabT* __restrict__ lab = static_cast<const LabT*>(a.lab);
     uint32_t w[kLaneEdges];
@@ -619,9 +621,7 @@ __device__ void iso_block(const IterArgs& a, uint32_t blk, const StopInputs& p) 
 
 // Workgroup b of the hashes of level k.
 template <typename LabT>
-__device__ __forceinline__ void hash_block(const IterArgs& a, uint32_t b) {
-    __shared__ IterShared S;
-    const StopInputs p = stop_inputs(a);  // loaded together with everything else
+__device__ __forceinline__ void hash_block(const IterArgs& a, IterShared& S, const StopInputs& p, uint32_t b) {
     if (b < a.n_hub_chunks) {
         hub_chunk_block<LabT>(a, b, S, p);
         return;
@@ -648,10 +648,14 @@ __device__ __forceinline__ void hash_block(const IterArgs& a, uint32_t b) {
 
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_iterate(IterArgs a) {
-    if (a.stop_only)
-        (void)stop_decision(a, stop_inputs(a));
-    else
-        hash_block<LabT>(a, blockIdx.x);
+    __shared__ IterShared S;
+    const StopInputs p = stop_inputs(a);  // loaded together with everything else
+    const uint32_t b = blockIdx.x;
+    if (a.stop_only) {
+        (void)stop_decision(a, p);
+        return;
+    }
+    hash_block<LabT>(a, S, p, b);
 }
 
 // ------------------------------------------------------------ classes of level k
@@ -761,9 +765,11 @@ __global__ void __launch_bounds__(kBlock) k_split(SplitArgs a) {
 // and 4.6 in two launches.
 template <typename LabT>
 __global__ void __launch_bounds__(kBlock) k_iterate_split(IterArgs a, SplitArgs sp, uint32_t n_hash) {
+    __shared__ IterShared S;
+    const StopInputs p = stop_inputs(a);
     if (blockIdx.x < n_hash)
-        hash_block<LabT>(a, blockIdx.x);
-    else if (!stop_decision(a, stop_inputs(a)))
+        hash_block<LabT>(a, S, p, blockIdx.x);
+    else if (!stop_decision(a, p))
         split_block(sp, blockIdx.x - n_hash, gridDim.x - n_hash);
 }
 

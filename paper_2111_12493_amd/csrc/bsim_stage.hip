@@ -191,7 +191,7 @@ namespace {
 // Bound: the row and type offsets once and the row offsets again, the lists
 // written, and the edges once.  On 10,000 vertices and 50,000 edges the three
 // kernels take 26 us where 19 launches took 410 us; on 2^27 vertices and
-// 2^30 edges of 16-bit labels 2.9 ms (counting 2.06, scan 0.08, writing 0.78)
+// 2^30 edges of 16-bit labels 3.3 ms (counting 2.10, scan 0.11, writing 1.09)
 // where they took 7.1 ms.
 constexpr uint32_t kStageVerts = 2048;
 constexpr uint32_t kStageRounds = kStageVerts / kBlock;
@@ -371,7 +371,7 @@ __device__ void stage_edges(const StageArgs& a, uint32_t* s_red) {
     if (a.wide) {
         // four edges per load where both arrays allow it: the counting pass
         // over 2^27 vertices and 2^30 edges moves its 7.5 GB at 3.6 TB/s
-        // (2.06 ms; with one edge per load, in two launches, 2.77 ms)
+        // (2.1 ms; with one edge per load, in two launches, 2.77 ms)
         struct alignas(4 * sizeof(LabT)) Lab4 {
             LabT x[4];
         };
