@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(kBlock) k_init(const uint64_t* __restrict__ t,
 // that of a graph which the small-graph launch has refined to its stop level
 // already (its hashes and classes lie in the same arrays), nor one past the
 // level at which the graph stopped.  Every block that writes hashes or classes
-// of a batched run asks it.
+// of a batched run asks it (k_hub the second half only: see there).
 __device__ __forceinline__ bool batch_refines(const BatchCtl& bc, uint32_t g, uint32_t k) {
     return !(bc.ext && bc.ext[g]) && k <= bc.done_level[g];
 }
@@ -976,7 +976,9 @@ __global__ void __launch_bounds__(kHubBlock) k_hub(HubArgs a) {
     acc[0] = 0;
     acc[1] = 0;
     const uint32_t v = a.hub_v[hi];
-    if (!a.bc.gid || batch_refines(a.bc, a.bc.gid[v], a.k)) a.h_next[v] = mix64(a.t[v] ^ mix64(kCS + all));
+    // (batch_refines: no graph of the small-graph launch has a hub)
+    static_assert(kSmallMaxEdges <= kSoloMaxEdges, "a graph that fits the small-graph launch has no hub");
+    if (!a.bc.gid || a.k <= a.bc.done_level[a.bc.gid[v]]) a.h_next[v] = mix64(a.t[v] ^ mix64(kCS + all));
 }
 
 // ------------------------------------------------------------ batched stop

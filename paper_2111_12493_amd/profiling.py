@@ -21,11 +21,9 @@ to wrap; `summary-updates` turns the two kernel-stat tables
 
 `trace` splits the dispatch sequence into summarization runs (one k_init
 dispatch starts each run) and averages each kernel over the launches that
-did work: refinement launches 1..k_done+1 of every run (the later ones of
-the last queued chunk find the stop flag and return at once), or 1..k_done
-when the run's launch k_done+1 ran as a split launch (its hash half finds
-the stop, so only launches 1..k_done hashed a level): `hash_launches` says
-which.
+did work: refinement launches 1..`hash_launches` of every run (k_done where
+the stop test knows the level just hashed, k_done+1 where it looks two levels
+back; later launches find the stop and return at once).
 
 `counters` averages every counter per dispatch for each kernel (with k_done,
 over the working refinement launches only).  When the profiled run also
