@@ -218,7 +218,8 @@ LoopResult run_refinement(bsim_ctx* ctx, const Staged& g, const bsim_params& p, 
         const bool hashes = kk <= p.k_max;
         const bool splits = lag == 2 && kk >= 2 && kk - 1 <= p.k_max;  // level kk-1, whose split launch was left out
         if (!hashes) {
-            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report, splits ? IterParts::kSplit : IterParts::kStopTest, s);
+            launch_iteration(g, rb, kk, lag, p.k_max, stop, all, report,
+                             splits ? IterParts::kSplit : IterParts::kStopTest, s);
             return;
         }
         if (large) {
